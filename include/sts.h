@@ -301,7 +301,7 @@ int sts_version(void);
  * stream is being captured into a graph (the stamped launch is not a capturable node).
  */
 typedef enum {
-  STS_K_SELECT_CLEAR = 0,  /* zero histograms */
+  STS_K_SELECT_CLEAR = 0,  /* zero histograms, or the words that the parts of a row exchange */
   STS_K_SELECT_AGG = 1,    /* aggregation + first-digit histogram */
   STS_K_SELECT_HIST = 2,   /* refinement histograms */
   STS_K_SELECT_ROWPASS = 3,/* many long rows of ready-made scores: one workgroup per row, several passes */
@@ -315,9 +315,9 @@ typedef enum {
   STS_K_SELECT_LOCAL = 11, /* small budgets: aggregation + top-k inside each 8192-token chunk */
   STS_K_SELECT_POOL = 12,  /* small budgets: ranking of the chunks' winners, one workgroup per row */
   STS_K_ATTN_PROBSUM = 13, /* dense second pass over K: attention weights summed over the query block */
-  STS_K_SELECT_FUSED = 14, /* long rows: aggregation, threshold and compaction in one launch */
+  STS_K_SELECT_FUSED = 14, /* long rows: sample, aggregation, threshold and compaction in one launch */
   STS_K_UNION_ROWS = 15,   /* union of per-row index lists + row bits */
-  STS_K_SELECT_BAND = 16,  /* at least a row per compute unit: one workgroup per row, one pass */
+  STS_K_SELECT_BAND = 16,  /* the same with a row for every second compute unit or more (clearing included) */
   STS_K_COUNT_ = 17
 } sts_kernel_kind;
 #define STS_PROF_MAX 4096
@@ -335,14 +335,15 @@ sts_status sts_prof_read(int kernel_kind, int32_t *launches, double *total_ms);
  *    rounding of the output: a workspace sized before the change may be refused afterwards
  *    (STS_EWORKSPACE; never written out of bounds).
  *  - STS_KNOB_SELECT_SPIN_LIMIT (env STS_SELECT_SPIN_LIMIT): polls of another workgroup's
- *    published counts before they are recomputed locally. No effect on results.
+ *    published counts before this one does without them (recounts, or ranks the row by itself). No
+ *    effect on results.
  *  - STS_KNOB_PROBSUM_WGS_PER_CU (env STS_PROBSUM_WGS_PER_CU): workgroups per compute unit of the
  *    pass that writes weights_sum_out. No effect on results.
  *  - STS_KNOB_SELECT_PATH (env STS_SELECT_PATH): 0 the library's rule, 1 histogram pipeline only,
- *    2 pipeline or chunk-local top-k + pool, 3 the one-launch selection for rows of up to 256
- *    parts (the rule stops at 8), 4 one workgroup per row in several passes wherever the shape
+ *    2 pipeline or chunk-local top-k + pool, 3 the sampled selection for rows of up to 256 units
+ *    of 32768 tokens (the rule stops at 8 in calls of fewer than 4M tokens), 4 one workgroup per row in several passes wherever the shape
  *    allows it (Tq = 1, probabilities, token granularity, no agg_out, N a multiple of 4, or of 8
- *    for bf16), 5 one workgroup per row in one pass wherever the shape allows it (token
+ *    for bf16), 5 the sampled selection with one workgroup per row wherever the shape allows it (token
  *    granularity, N a multiple of 4 up to 524288). It changes sts_select_workspace_bytes, never
  *    the results.
  *  - STS_KNOB_SELECT_ROW_THREADS (env STS_SELECT_ROW_THREADS): 256 or 1024, the workgroup size of

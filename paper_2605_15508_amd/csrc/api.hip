@@ -319,21 +319,35 @@ struct SelectPlan {
   bool rowpass;        // many long rows of ready-made scores: one workgroup per row, no workspace
   int rowpass_threads;
   int nchunks, page, srcN, pool_pitch, pool_chunk, pool_nchunks;
-  int part_tokens, parts;
+  int part_tokens, parts, smp_tokens, smp_parts;
   size_t agg_bytes, blk_bytes, hist_bytes, state_bytes, chunk_bytes;
   size_t pool_key_bytes;
-  size_t pub_bytes, pflag_bytes;
+  size_t pub_bytes;
   size_t pipeline_total() const { return agg_bytes + blk_bytes + hist_bytes + state_bytes + chunk_bytes; }
   size_t pool_total() const { return pool ? 2 * pool_key_bytes : 0; }
-  size_t fused_total() const { return pub_bytes + pflag_bytes; }
+  size_t fused_total() const { return pub_bytes; }
   // a pool-shaped call falls back to the pipeline when its pointers are not 16-byte aligned,
   // so the workspace covers both
   size_t total() const {
-    if (rowpass || band) return 0;
-    if (fused) return fused_total();
+    if (rowpass) return 0;
+    if (fused || band) return fused_total();
     return pipeline_total() > pool_total() ? pipeline_total() : pool_total();
   }
 };
+
+// How the sampled selection cuts its rows: as many workgroups as there are CUs, in equal shares of at
+// least 8192 tokens (below that the fixed part of a workgroup's work exceeds its share of the pass)
+// and at most 32 per row (the exchange grows with the square).
+void plan_sampled(const sts_select_params *p, size_t rows, SelectPlan &pl) {
+  int64_t q = cu_count() / (int64_t)(rows ? rows : 1);
+  if (q > ((int64_t)p->N + 8191) / 8192) q = ((int64_t)p->N + 8191) / 8192;
+  if (q > 32) q = 32;
+  const int64_t least = ((int64_t)p->N + SMP_MAX_TOKENS - 1) / SMP_MAX_TOKENS;
+  if (q < least) q = least;
+  if (q < 1) q = 1;
+  pl.smp_tokens = (int)((((int64_t)p->N + q - 1) / q + 255) / 256 * 256);
+  pl.smp_parts = (int)(((int64_t)p->N + pl.smp_tokens - 1) / pl.smp_tokens);
+}
 
 sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
   if (!p) return STS_EINVAL;
@@ -359,22 +373,20 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
   pl.rowpass = false;
   pl.band = false;
   pl.rowpass_threads = 0;
-  pl.part_tokens = pl.parts = 0;
-  pl.pub_bytes = pl.pflag_bytes = 0;
+  pl.part_tokens = pl.parts = pl.smp_tokens = pl.smp_parts = 0;
+  pl.pub_bytes = 0;
   // test / tuning knob: 0 the library's rule, 1 histogram pipeline only, 2 pipeline or pool,
-  // 3 the one-launch selection wherever its shape limits allow, 4 one workgroup per row in
-  // several passes wherever its shape limits allow, 5 one workgroup per row in one pass likewise
+  // 3 the sampled selection wherever its shape limits allow, 4 one workgroup per row in
+  // several passes wherever its shape limits allow, 5 the sampled selection with one workgroup per row likewise
   const double path_knob = knob(STS_KNOB_SELECT_PATH);
   const int path = path_knob == path_knob ? (int)path_knob : 0;
   // Enough rows to give at least every second CU one, and rows that do not fit one workgroup's
-  // LDS: one workgroup per row, which samples the row, keeps the band of keys around the
-  // threshold in LDS during a single pass and never talks to another workgroup
-  // (select_band_kernel); nothing to clear, no workspace. The band of a full-length row with the
-  // call's largest budget has to fit (rows for which it does not, decided in the kernel, are
-  // ranked by plain passes there). Measured against the paths below, 128K-token rows, 10%: 256
-  // rows of 8 fp32 scores per token 220 against 289 us, bf16 140 against 203, 512 rows of 16 bf16
-  // scores 448 against 613, 256 rows of one fp32 score 67 against 147 (pipeline, in place), 128
-  // rows of 5 scores 93 against 111; 64 rows: 83 against 58, hence the limit.
+  // LDS: the sampled selection with one workgroup per row (two when that still fits the chip, as
+  // for 128 rows on 256 CUs). The band of a full-length row with the call's largest budget has to
+  // fit (rows for which it does not, decided in the kernel, are ranked by plain passes there).
+  // Measured, 128K-token rows, 10%: 128 rows of one fp32 score per token 45 us (two workgroups per
+  // row; one workgroup per row took 57), 128 rows of eight bf16 scaled logits of 50000 tokens 52
+  // (70 with one workgroup per row).
   // One bf16 score per token and many rows per CU (a mask per query row of prefill) is the one
   // shape that plain passes by small workgroups serve better (select_rowpass_kernel; 4096 rows of
   // 128K: 754 against 962 us; one workgroup per row out of parts that exchange: 2.1 ms).
@@ -405,6 +417,10 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
       pl.nchunks = 0;
       pl.pool_chunk = pl.pool_nchunks = 0;
       pl.agg_bytes = pl.blk_bytes = pl.hist_bytes = pl.state_bytes = pl.chunk_bytes = 0;
+      if (take_band) {
+        plan_sampled(p, path == 5 ? (size_t)cus : rows, pl);
+        if (pl.smp_parts > 1) pl.pub_bytes = align256(rows * (size_t)pl.smp_parts * SMP_WORDS * sizeof(unsigned long long));
+      }
       return STS_OK;
     }
   }
@@ -438,20 +454,17 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
       }
     }
   }
-  // Long rows at token granularity: one launch in which every workgroup keeps a part of a row in
-  // LDS (select_fused_kernel). Parts are as large as LDS allows (32768 tokens) when that still
-  // gives a workgroup per CU, else smaller, down to 8192, to spread short calls over the chip.
-  // (One exception under the library's own rule: a ready-made fp32 aggregate, Tq = 1, that the
-  // pipeline ranks where it lies, in a call with more workgroups than CUs. There the pipeline's
-  // passes over the caller's tensor beat several rounds of workgroups that wait for each other:
-  // 70B-shaped layer, 256 rows of 128K: 153 against 182 us.)
-  const bool in_place = p->Tq == 1 && p->kind == STS_SCORES_PROBS && !p->scores_bf16 && !p->agg_out;
-  const bool many_rounds = (int64_t)rows * (((int64_t)p->N + SEL_SMALL_N - 1) / SEL_SMALL_N) > cu_count();
-  if (pl.page == 1 && p->N > SEL_FUSED_N && path != 1 && path != 2 && !(path == 0 && in_place && many_rounds)) {
-    const int max_parts = path == 3 ? 256 : SEL_FUSED_MAX_PARTS;
+  // Long rows at token granularity: the sampled selection (select_sampled.hip), one pass over the
+  // scores, any budget. Rows of more than 256K tokens (eight units of 32768) take it in calls of 4M
+  // tokens or more: 16 rows of 1M tokens, 2%: 84 us against 126 for the pipeline; budgets small enough
+  // for the pool keep it (256 tokens: 89 against 92). Smaller calls of such rows keep the paths above
+  // and below, which are bound by launches and latencies there.
+  if (pl.page == 1 && p->N > SEL_FUSED_N && path != 1 && path != 2) {
+    const bool large = (int64_t)rows * p->N >= (int64_t)1 << 22 && !pl.pool;
+    const int max_parts = path == 3 || large ? 256 : SEL_FUSED_MAX_PARTS;
     int P = SEL_SMALL_N;
     while (P > SEL_FUSED_N && (int64_t)rows * (((int64_t)p->N + P - 1) / P) < cu_count() &&
-           ((int64_t)p->N + P / 2 - 1) / (P / 2) <= max_parts)
+           ((int64_t)p->N + P / 2 - 1) / (P / 2) <= SEL_FUSED_MAX_PARTS)
       P >>= 1;
     const int64_t parts = ((int64_t)p->N + P - 1) / P;
     if (parts <= max_parts) {
@@ -459,8 +472,11 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
       pl.pool = false;
       pl.part_tokens = P;
       pl.parts = (int)parts;
-      pl.pub_bytes = align256(rows * 3 * (size_t)parts * 1024 * sizeof(unsigned long long));
-      pl.pflag_bytes = 0;
+      plan_sampled(p, rows, pl);
+      pl.pub_bytes = align256(rows * (size_t)pl.smp_parts * SMP_WORDS * sizeof(unsigned long long));
+      // (at least what the row cut into parts of part_tokens takes at 24 KB each)
+      const size_t least = rows * 3 * (size_t)pl.parts * 1024 * sizeof(unsigned long long);
+      if (pl.pub_bytes < least) pl.pub_bytes = least;
     }
   }
   pl.agg_bytes = p->agg_out ? 0 : align256(rows * (size_t)p->N * sizeof(float));
@@ -532,7 +548,13 @@ static sts_status enqueue_select(const sts_select_params *p, void *stream) {
   if (p->B == 0) return STS_OK;
   if (p->N > 0 && !p->scores) return STS_EINVAL;
   if (p->kind == STS_SCORES_LOGITS_LSE && !p->lse) return STS_EINVAL;
-  const size_t need = pl.total();
+  size_t need = pl.total();
+  if (pl.band && need > 0 && (!p->workspace || p->workspace_bytes < need)) {
+    // one workgroup per row needs no scratch memory: such calls are served without any
+    pl.smp_parts = 1;
+    pl.smp_tokens = (p->N + 255) / 256 * 256;
+    need = 0;
+  }
   if (need > 0) {
     if (!p->workspace || p->workspace_bytes < need) return STS_EWORKSPACE;
     if (reinterpret_cast<uintptr_t>(p->workspace) % 256 != 0) return STS_EWORKSPACE;
@@ -577,8 +599,8 @@ static sts_status enqueue_select(const sts_select_params *p, void *stream) {
     const double v = knob(STS_KNOB_SELECT_SPIN_LIMIT);
     const bool set = v == v;   // not NaN
     a.spin_limit = !set ? 256 : (v < 0 ? 0 : (v > 65536 ? 65536 : (int)v));
-    // the parts of the one-launch selection wait for ALL parts of their row, and recomputing a
-    // missing part's histogram means re-reading its scores: a far longer patience by default
+    // the parts of the sampled selection wait for ALL parts of their row, and doing without them
+    // means ranking the row by plain passes over its scores: a far longer patience by default
     a.fused_spin_limit = !set ? 20000 : a.spin_limit;
   }
   // inverse of the head map: the target heads fed by each draft head, in head order
@@ -599,6 +621,9 @@ static sts_status enqueue_select(const sts_select_params *p, void *stream) {
     a.agg = p->agg_out;   // optional output only
     a.src = nullptr;
     a.hist = a.state = a.chunk_cnt = nullptr;
+    a.pub = p->workspace;
+    a.smp_tokens = pl.smp_tokens;
+    a.smp_parts = pl.smp_parts;
     rc = run_kernel(STS_K_SELECT_BAND, s, [&] { return launch_select_band(a, s); });
     return rc == hipSuccess ? STS_OK : STS_EHIP;
   }
@@ -611,14 +636,15 @@ static sts_status enqueue_select(const sts_select_params *p, void *stream) {
     return rc == hipSuccess ? STS_OK : STS_EHIP;
   }
   if (pl.fused) {
-    unsigned char *fw = static_cast<unsigned char *>(p->workspace);
-    a.pub = reinterpret_cast<unsigned long long *>(fw);
+    a.pub = p->workspace;
+    a.smp_tokens = pl.smp_tokens;
+    a.smp_parts = pl.smp_parts;
     a.part_tokens = pl.part_tokens;
     a.parts = pl.parts;
     a.agg = p->agg_out;   // optional output only: the keys never leave LDS
     a.src = nullptr;
     a.hist = a.state = a.chunk_cnt = nullptr;   // the pipeline's scratch does not exist on this path
-    if (pl.parts > 1) {
+    if (pl.parts > 1 || pl.smp_parts > 1) {
       rc = run_kernel(STS_K_SELECT_CLEAR, s, [&] { return launch_select_clear_pub(a, s); });
       if (rc != hipSuccess) return STS_EHIP;
     }

@@ -33,7 +33,7 @@ inline void sts_launch(void (*kernel)(P...), dim3 grid, dim3 block, unsigned shm
   void *ptrs[sizeof...(P)];
   sts_arg_pointers(vals, ptrs, std::index_sequence_for<P...>{});
   const hipError_t rc =
-      g_sts_launch_events.start
+      g_sts_launch_events.start || g_sts_launch_events.stop
           ? hipExtLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, ptrs, shmem, stream,
                                g_sts_launch_events.start, g_sts_launch_events.stop, 0)
           : hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, ptrs, shmem, stream);
@@ -114,15 +114,16 @@ constexpr int SEL_THREADS = 256;
 constexpr int SEL_SMALL_N = 32768;      // LDS capacity of the one-workgroup-per-row selection (tokens)
 constexpr int SEL_FLAG_PITCH = 32;      // words between the published counts of two chunks: one 128-byte line each
 constexpr int SEL_FUSED_N = 8192;
-constexpr int SEL_FUSED_MAX_PARTS = 8;   // parts per row of the one-launch selection: every part reads every other
-                                         // part's histograms, which grows with the square (256K tokens; a test knob
-                                         // allows up to 256)
+constexpr int SEL_FUSED_MAX_PARTS = 8;   // units of 32768 tokens up to which small calls take the sampled selection
+                                         // (256K tokens; large calls and a test knob: up to 256)
+constexpr int SMP_MAX_TOKENS = 524288;  // sampled selection: tokens per workgroup (a bit each in LDS)
+constexpr int SMP_WORDS = 1096;         // 64-bit words a part exchanges with the other parts of its row
 constexpr int SEL_POOL_MAX = 16384;     // chunk-local winners per row that the pool kernel ranks out of LDS       // rows up to this many tokens always take it
 
-// One workgroup per row, one pass (select_band_kernel): what the strided sample of a row of nb
-// ranked tokens with budget c looks like, and whether the band it is expected to give fits the
-// workgroup's store. The kernel decides per row with this; the host asks the same question for
-// a full-length row when it chooses the path.
+// What a strided sample of a row of nb ranked tokens with budget c looks like, and whether the band of
+// keys around the threshold that it is expected to give fits one workgroup's store. The host asks this
+// for a full-length row when it chooses the path of calls with many rows (budgets next to the row's
+// length and, beyond 256K tokens, large ones go elsewhere); the kernel samples for itself.
 constexpr int BAND_CAP = 8192;          // band entries (key and token) a workgroup holds; it samples up to twice as many keys
 constexpr int BAND_MAX_N = 524288;      // tokens per row: one bit each in LDS
 constexpr int BAND_Z = 5;               // half-width of the band in standard deviations of the sample count
@@ -181,10 +182,11 @@ struct SelectArgs {
   uint64_t clear_words;       // words to zero from `hist` on: histograms, state and chunk flags
   int32_t hist_cpw;           // consecutive chunks per workgroup of the refinement histograms (1, 2 or 4)
   int32_t spin_limit;         // polls of an unpublished earlier chunk before it is recounted locally
-  unsigned long long *pub;    // fused selection: [rows][3][parts][1024] words the parts publish (top bit: written;
-                              // two bin counts in the halves), zero before the launch
-  int32_t part_tokens, parts; // fused selection: tokens per part (8192..32768) and parts per row
-  int32_t fused_spin_limit;   // polls of another part's flag before its histogram is recomputed locally
+  int32_t part_tokens, parts; // long rows: the row in units of 8192, 16384 or 32768 tokens (what the choice of path goes by)
+  void *pub;                  // sampled selection: [rows][smp_parts][SMP_WORDS] 64-bit words that the parts of a row
+                              // exchange (top bit: written), zero before the launch
+  int32_t smp_tokens, smp_parts;   // tokens per workgroup (a multiple of 256), workgroups per row
+  int32_t fused_spin_limit;   // polls of another part's words before the row is ranked by plain passes instead
   int32_t rowpass_threads;    // one workgroup per row (select_rowpass_kernel): 256 or 1024 threads
   int32_t agg_is_input;       // `agg` is the caller's score tensor itself (one fp32 probability row per head): never stored to
   int32_t B, Hd, Tq, N, Hq, k, kind, reduce, nchunks;   // k: row pitch of indices = largest budget

@@ -1,0 +1,753 @@
+// Sampled selection (gfx950): rows longer than one workgroup's LDS holds, read ONCE.
+//
+// A row is cut into as many parts as give every CU a workgroup (one part when there are rows enough);
+// one 1024-thread workgroup per part:
+//  1. Sample. Runs of 128 bytes of the row's scores (the whole row's, not only the part's), one in
+//     every S, are aggregated in the usual fp32 order and counted into 2048 bins that divide the
+//     sample's own key range. From them come two keys L < U between which the row's threshold lies
+//     unless the sample is 5 standard deviations off; the deviation is the sample's own, the spread
+//     of the counts of large keys over its runs, so rows whose heavy tokens sit next to each other
+//     get the wider band that they need. Every part of a row samples the same tokens and finds the
+//     same L and U. The part's first loads are on their way meanwhile.
+//  2. The pass over the part, eight loads in flight per thread all the time. A token whose key is >= U
+//     is certainly kept: a bit in LDS. One in [L, U), a few per cent of the row, goes to the
+//     band list in LDS with its key. Nothing else is remembered.
+//  3. The threshold. The parts exchange a histogram of their bands (512 bins over [L, U)) and their
+//     counts, then the keys of the one bin that holds the threshold, 64 at most (where that bin holds
+//     more, another histogram narrows it first). That gives every part the exact threshold key T, the
+//     number r of tokens equal to T that are kept, and the number of kept tokens in earlier parts.
+//  4. Band tokens above T get their bit, of those equal to T the r lowest do, and the list is the bits
+//     read in order.
+//
+// Exchange protocol: the words are zeroed by a small kernel launched before this one. Every 64-bit word
+// carries its own top bit as "written" (a device-scope store of 8 aligned bytes: the word arrives
+// whole), so one memory round trip per exchange is all the parts wait for each other, without
+// fences. The wait is bounded: a workgroup that runs out of polls ranks the row by plain passes over
+// the scores and writes its own part of the list from that (rank_by_passes), so every workgroup exits
+// whatever the others do; a row's parts have neighbouring workgroup ids and start together.
+//
+// The result never depends on the sample: if the counts show that the threshold lies outside [L, U),
+// or a band list overflowed, every part goes by plain passes likewise. A band that is a single key (one
+// value repeated: zeros, a constant row) needs no list: a second bitmap holds it.
+//
+// What bounds it (64 rows of 128K tokens, 5 fp32 scores each, 4 parts per row, lengths between half and all
+// of it, 133 MB): the sample and the pass together 27 us (133 MB and 21 MB of samples, mostly from the
+// last-level cache: the rate of the memory), then latency: 7 us for the histogram exchange, 3.5 us for the
+// keys, 3.5 us for bits and list; kernel 45-48 us. Histograms of all keys at three digit levels, with the
+// part's keys in LDS, took 50: the same 27 us, then 20 us for three levels and 5 us for the list. 16 rows of 1M
+// tokens (335 MB, 16 parts per row): 80 us against 122 for five kernels that stored the aggregate and read it
+// three times. Rows of one score per token are bound by vector instructions instead (about 60 per 256 tokens
+// and wave), those of scaled logits by the exponentials.
+#include "select_util.h"
+
+namespace {
+
+constexpr int SMP_THREADS = 1024;
+constexpr int SMP_WAVES = SMP_THREADS / 64;
+constexpr int SMP_GROUP = 256;            // tokens per wave step: four per lane
+constexpr int SMP_HIST = 512;             // bins of an exchanged histogram, two per word
+constexpr int SMP_ROUNDS = 4;             // histograms: 9 bits of a 32-bit key each
+constexpr int SMP_CAND = 64;              // keys of the threshold's bin that are exchanged one by one
+constexpr int SMP_G_WORD = SMP_ROUNDS * SMP_HIST / 2, SMP_CAND_WORD = SMP_G_WORD + 8;
+static_assert(SMP_CAND_WORD + SMP_CAND == SMP_WORDS, "layout of a part's exchange words");
+constexpr unsigned long long SMP_VALID = 1ull << 63, SMP_OVER = 1ull << 62;
+
+// Which runs of a row of nb ranked tokens are sampled: one in every S, at a scattered place of its
+// period (a fixed stride of 4 KB and more lands on a few memory channels only: the sample's loads
+// took 6.5 and, at 1M tokens, 12 us more). About 4096 keys (8192 for rows beyond 256K tokens): at a
+// tenth of the row kept the band is then about 5% of a 128K row.
+struct SamplePlan {
+  int S, runs;
+  __device__ __forceinline__ int start(int i, int run) const {       // first token of sampled run i
+    return (i * S + (int)((((uint32_t)i * 0x9e3779b1u) >> 16) & (uint32_t)(S - 1))) * run;
+  }
+};
+__device__ __forceinline__ SamplePlan sample_plan(int nb, int run) {
+  SamplePlan p;
+  const int row_runs = (nb + run - 1) / run, target = nb > 262144 ? 8192 : 4096;
+  p.S = 1;
+  while (((row_runs + p.S - 1) / p.S) * run > target) p.S <<= 1;
+  p.runs = row_runs / p.S;                             // (at least one: S is at most half the runs here)
+  return p;
+}
+
+// One quad of one score row as loaded.
+template <bool BF16>
+using RawQuad = typename ScoreLoad<f32x4, BF16>::raw;
+
+// the band that the sample gives: keys L .. L + last, whether there is an upper edge, and how far the sample's keys
+// reach (without an upper edge the band is the top of the row: its histogram is laid out for the sample's
+// keys, and what lies above them goes to the last bin)
+struct Band {
+  uint32_t L, last, span;
+  bool haveU;
+};
+
+// Ranks the sampled quads (up to QT per thread, `acc` their aggregated scores). h: SEL_BINS words, zeroed.
+template <int QT>
+__device__ __forceinline__ Band sample_band(const SamplePlan &sp, int run, int nb, uint32_t c, const int (&pos)[QT],
+                                            const f32x4 (&acc)[QT], uint32_t *h, uint32_t *tmp, uint32_t *red, uint32_t *found) {
+  constexpr int T = SMP_THREADS;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int rq = run >> 2, nsq = sp.runs * rq;
+  auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+  uint32_t key[QT][4];
+  bool ok[QT][4];
+  uint32_t kmin = 0xffffffffu, kmax = 0u;
+#pragma unroll
+  for (int x = 0; x < QT; ++x)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      key[x][e] = key_of(acc[x][e]);
+      ok[x][e] = tid + x * T < nsq && pos[x] + e < nb;
+      if (ok[x][e]) {
+        kmin = min(kmin, key[x][e]);
+        kmax = max(kmax, key[x][e]);
+      }
+    }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, off, 64));
+    kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off, 64));
+  }
+  if (lane == 0) {
+    red[2 * wave] = kmin;
+    red[2 * wave + 1] = kmax;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < T / 64; ++w) {
+    kmin = min(kmin, red[2 * w]);
+    kmax = max(kmax, red[2 * w + 1]);
+  }
+  // Bins of 2^shift keys over the window base .. base + range, which is the sample's own key range at first.
+  // Rows with values far from the rest (exact zeros, negative scores) make those bins coarse and the band
+  // with them far wider than the margin; the window is then narrowed to the band until it is not, at
+  // the last to a single key.
+  uint32_t base = uniform(kmin), range = uniform(kmax - kmin), over = 0;     // over: sampled keys above the window
+  uint32_t ns = 0, cs = 0;
+  const uint32_t highest = uniform(kmax);
+  Band b = {0u, 0xffffffffu, 0u, false};
+#pragma unroll 1
+  for (;;) {
+    const int shift = max(0, 32 - __clz((int)range) - 11);                   // range >> shift < 2048
+#pragma unroll
+    for (int x = 0; x < QT; ++x)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (ok[x][e] && key[x][e] - base <= range) atomicAdd(&h[(key[x][e] - base) >> shift], 1u);
+    __syncthreads();
+    // thread t owns bins 2t and 2t + 1; `above` keys of the sample lie in higher bins than its own
+    const uint32_t h0 = h[2 * tid], h1 = h[2 * tid + 1];
+    uint32_t in_window;
+    const uint32_t excl = block_excl_scan<T>(h0 + h1, tmp, in_window);
+    const uint32_t above = over + in_window - excl - (h0 + h1);
+    in_window = uniform(in_window);
+    // the bin of the rank-th largest, and how many keys lie from that bin (with) or above it (without)
+    auto locate = [&](uint32_t rank, int slot, bool with) {
+      if (above < rank && above + h1 >= rank) {
+        found[2 * slot] = 2 * tid + 1;
+        found[2 * slot + 1] = above + (with ? h1 : 0u);
+      } else if (above + h1 < rank && above + h1 + h0 >= rank) {
+        found[2 * slot] = 2 * tid;
+        found[2 * slot + 1] = above + h1 + (with ? h0 : 0u);
+      }
+    };
+    if (ns == 0u) {                                    // the first window is the whole sample
+      ns = in_window;
+      cs = max(1u, min(ns, (uint32_t)((uint64_t)c * ns / (uint32_t)nb)));    // expected rank of the threshold
+    }
+    uint32_t margin = 0;                               // (S == 1: the sample is the row)
+    if (sp.S > 1) {
+      locate(cs, 0, false);
+      __syncthreads();
+      const uint32_t centre = base + (found[0] << shift);
+      // Keys from the centre on, per run; their spread over the runs is what the rank estimate's is made of
+      // (differences of neighbouring runs, as for any systematic sample: a row that changes slowly, or has one
+      // long stretch of heavy tokens, is sampled far more exactly than the runs' plain variance says).
+      uint32_t sq = 0;
+#pragma unroll
+      for (int x = 0; x < QT; ++x) {
+        uint32_t n = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) n += (ok[x][e] && key[x][e] >= centre) ? 1u : 0u;
+        for (int off = 1; off < rq; off <<= 1) n += (uint32_t)__shfl_xor((int)n, off, 64);
+        const int d = (int)n - __shfl_down((int)n, rq, 64);
+        sq += (lane & (rq - 1)) == 0 && lane + rq < 64 && tid + x * T + rq < nsq ? (uint32_t)(d * d) : 0u;
+      }
+      const uint32_t sum_sq = block_sum1<T>(sq, red);
+      const float pairs = (float)(64 - rq) / 64.f;     // share of the neighbouring pairs that lie in one wave
+      margin = uniform((uint32_t)(5.f * sqrtf(fmaxf(0.5f * (float)sum_sq / pairs, (float)cs))) + 4u);
+    }
+    // an edge that lies outside the window stays what it was
+    const bool haveL = cs + margin <= over + in_window, haveU = cs > margin + over;
+    if (haveL) locate(cs + margin, 1, true);
+    if (haveU) locate(cs - margin, 2, false);
+    __syncthreads();
+    const uint32_t lo_bin = uniform(haveL ? found[2] : 0u), hi_bin = uniform(haveU ? found[4] : range >> shift);
+    const uint32_t upto = uniform(haveL ? found[3] : over + in_window), beyond = uniform(haveU ? found[5] : over);
+    uint32_t top = base + range;                       // last key of the next window
+    const uint32_t last_key = b.L + b.last;
+    if (haveL) b.L = base + (lo_bin << shift);
+    if (haveU) {
+      const uint64_t u = (uint64_t)base + ((uint64_t)(hi_bin + 1u) << shift);
+      if (u <= 0xffffffffull) {
+        b.haveU = true;
+        top = min(top, (uint32_t)u - 1u);
+        b.last = (uint32_t)u - 1u - b.L;
+      } else {
+        b.last = 0xffffffffu - b.L;
+      }
+    } else {
+      b.last = last_key - b.L;
+    }
+    b.span = b.haveU ? b.last : max(highest, b.L) - b.L;
+    if (shift == 0 || hi_bin - lo_bin >= 64u || upto - beyond <= 4u * margin + 64u) return b;
+    base = haveL ? b.L : base;
+    range = top - base;
+    over = beyond;
+    for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
+    __syncthreads();
+  }
+}
+
+// TOK: tokens a workgroup can hold bits of; CAP: entries of its band list.
+template <bool BF16, int TOK, int CAP>
+__global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const SelectArgs A) {
+  constexpr int T = SMP_THREADS, W = SMP_WAVES;
+  typedef ScoreLoad<f32x4, BF16> SL;
+  __shared__ uint32_t bits[TOK / 32];                  // kept tokens of the part
+  // the band list (key, token of the part); a band of one key: the bits of its tokens; at last the staged tokens
+  __shared__ u32x2 list[CAP];
+  static_assert(2 * CAP >= TOK / 32, "the bits of a one-key band share the list's memory");
+  uint32_t *const store = reinterpret_cast<uint32_t *>(list);
+  __shared__ uint32_t h[SEL_BINS];
+  __shared__ uint32_t hb[SMP_HIST];                    // the earlier parts' share of an exchanged histogram
+  __shared__ uint32_t tmp[T / 64 + 2];
+  __shared__ uint32_t red[2 * T / 64];
+  __shared__ uint32_t found[6];
+  __shared__ uint32_t ticket;                          // next group of the pass
+  __shared__ uint32_t ctr[8];                          // 0 band entries, 1 certain tokens, 2.. see below
+  __shared__ u32x2 cand[SMP_CAND];                     // key; token of the part (own) or 1 << 31 | part
+  const int row = blockIdx.y, part = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int bt = row / A.Hd, j = row % A.Hd;
+  const int nb = __builtin_amdgcn_readfirstlane(row_len(A, bt));       // (a loaded value: said to be uniform, like others below)
+  const uint32_t c = (uint32_t)min(A.kh[j], nb);
+  const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
+  if (part == 0) write_tail<T>(A, bt, j, c);
+  float *out = A.agg ? A.agg + (size_t)row * A.N : nullptr;
+  const bool ranked = c > 0 && t0 != t1;
+  const int P = A.smp_tokens, n0 = part * P;
+  const int m = ranked ? max(0, min(n0 + P, nb) - n0) : 0;             // ranked tokens of this part
+  const int span = out ? min(n0 + P, A.N) - n0 : m;                    // tokens it reads
+  if (span <= 0) return;                                               // (a part without ranked tokens is not waited for)
+  const int ng = (span + SMP_GROUP - 1) / SMP_GROUP;
+  const AggRow R = agg_row(A, row);
+  const int Tq = R.Tq;
+  for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
+  if (tid < 8) ctr[tid] = 0u;
+  if (tid == 0) ticket = 2 * W;
+  const float lse_of = R.logits && lane < Tq ? R.L[lane] : 0.f;        // row i's normaliser in lane i (Tq <= 64)
+  __syncthreads();
+  // ---- the sample's loads, then the first eight of the part's own
+  constexpr int QT = 2;
+  const int run = BF16 ? 64 : 32, rq = run >> 2;       // tokens and quads of a 128-byte run
+  const SamplePlan sp = sample_plan(max(nb, 1), run);
+  const int nsq = sp.runs * rq;
+  int pos[QT];
+  f32x4 sacc[QT];
+#pragma unroll
+  for (int x = 0; x < QT; ++x) {
+    const int s = min(tid + x * T, nsq - 1);           // sampled quad s: quad s % rq of run s / rq
+    pos[x] = sp.start(s / rq, run) + (s % rq) * 4;
+  }
+  // The part's loads: a group of 256 tokens at a time, whichever is next when the wave has room (a fixed
+  // share per wave left the oldest waves idle for the last third of the pass), and the Tq rows of it; eight in
+  // flight. The address is a scalar base and a 32-bit lane offset: no vector arithmetic but the clamp at the
+  // row's end.
+  RawQuad<BF16> raw[8];
+  int grp[8];                                          // group of each slot (wave-uniform), >= ng: none
+  int ld_g = wave, ld_i = 0;                           // next load: group and row (wave-uniform)
+  uint32_t next_g = (uint32_t)(wave + W);              // in lane 0: the group after that, asked for one group ahead
+  const int lane4 = 4 * lane;
+  auto issue = [&](RawQuad<BF16> &r, int &slot) {
+    slot = ld_g;
+    // (a last group of fewer than four tokens starts past the last whole quad: read that quad, see classify)
+    const int start = min(n0 + min(ld_g, ng - 1) * SMP_GROUP, R.N - 4);
+    const unsigned char *base = static_cast<const unsigned char *>(R.P) + ((size_t)ld_i * R.N + start) * (BF16 ? 2 : 4);
+    const uint32_t off = (uint32_t)min(lane4, R.N - 4 - start) * (BF16 ? 2u : 4u);
+    r = SL::load_at(base + off);
+    if (++ld_i == Tq) {
+      ld_i = 0;
+      ld_g = __builtin_amdgcn_readfirstlane((int)next_g);
+      if (lane == 0) next_g = atomicAdd(&ticket, 1u);
+    }
+  };
+  if (m > 0) {
+    if (nsq <= T) {                                    // one sampled quad per thread
+      const int p1[1] = {pos[0]};
+      f32x4 a1[1];
+      agg_quads_any<1, 8>(R, p1, false, a1);
+      sacc[0] = sacc[1] = a1[0];
+    } else {
+#pragma unroll 1
+      for (int x = 0; x < QT; ++x) {
+        const int p1[1] = {x == 0 ? pos[0] : pos[1]};
+        f32x4 a1[1];
+        agg_quads_any<1, 8>(R, p1, false, a1);
+        if (x == 0) sacc[0] = a1[0];
+        sacc[1] = a1[0];
+      }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < 8; ++u) issue(raw[u], grp[u]);
+  Band band = {0u, 0u, 0u, false};
+  if (m > 0) band = sample_band<QT>(sp, run, nb, c, pos, sacc, h, tmp, red, found);   // (uniform; its barriers publish ctr)
+  else __syncthreads();
+  const bool single = band.haveU && band.last == 0u;
+
+  // ---- the pass
+  // INT_MIN marks what is no token of the row: it stays below every edge
+  const int sL = max(ordered_of_key(band.L), (int)0x80000001);
+  const int sU = band.haveU ? ordered_of_key(band.L + band.last + 1u) : 0x7fffffff;
+  const bool plain = sL > 0;       // scores below the band, negative ones included, compare right as bit patterns
+  uint32_t certain = 0;            // wave-uniform
+  auto classify = [&](int g, f32x4 acc) {
+    const int n = n0 + g * SMP_GROUP + lane4;
+    if (n0 + (g + 1) * SMP_GROUP > R.N) {              // the row's end: the quad was read where it still fits
+      const int d = n - min(n, R.N - 4);
+      const f32x4 y = acc;
+      acc[0] = d == 0 ? y[0] : d == 1 ? y[1] : d == 2 ? y[2] : y[3];
+      acc[1] = d == 0 ? y[1] : d == 1 ? y[2] : y[3];
+      acc[2] = d == 0 ? y[2] : y[3];
+    }
+    if (out && n < R.N) {
+      f32x4 o = acc;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = n + e < nb ? o[e] : 0.f;      // the stored aggregate is 0 past the valid length
+      if (n + 4 <= R.N) *reinterpret_cast<f32x4_any *>(out + n) = o;
+      else
+        for (int e = 0; n + e < R.N; ++e) out[n + e] = o[e];
+    }
+    if (g * SMP_GROUP >= m) return;                    // wave-uniform
+    int v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float f = acc[e];
+      v[e] = __builtin_bit_cast(int, f);
+    }
+    if (!plain) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = ordered(v[e]);
+    }
+    if ((g + 1) * SMP_GROUP > m) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = n + e < nb ? v[e] : (int)0x80000000;
+    }
+    uint32_t nib = 0, held = 0;
+    bool in_band[4];
+    uint64_t bd[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool sure = v[e] >= sU;
+      in_band[e] = !sure && v[e] >= sL;
+      nib |= sure ? 1u << e : 0u;
+      certain += (uint32_t)__builtin_popcountll(ballot64(sure));
+      bd[e] = ballot64(in_band[e]);
+      held += (uint32_t)__builtin_popcountll(bd[e]);
+    }
+    // the nibbles of eight neighbouring quads make one bitmap word, stored whole by the first lane of
+    // the eight: three shifts by 1, 2, 4 lanes inside a row of 16 lanes, OR-ed
+    auto word = [&](uint32_t b, uint32_t *to) {
+      int w = (int)(b << (4 * (lane & 7)));
+      w |= __builtin_amdgcn_update_dpp(0, w, 0x101, 0xf, 0xf, true);   // row_shl:1
+      w |= __builtin_amdgcn_update_dpp(0, w, 0x102, 0xf, 0xf, true);   // row_shl:2
+      w |= __builtin_amdgcn_update_dpp(0, w, 0x104, 0xf, 0xf, true);   // row_shl:4
+      if ((lane & 7) == 0) to[g * 8 + (lane >> 3)] = (uint32_t)w;
+    };
+    word(nib, bits);
+    uint32_t at = 0;
+    if (lane == 0) at = atomicAdd(&ctr[0], held);
+    if (single) {
+      uint32_t b = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) b |= in_band[e] ? 1u << e : 0u;
+      word(b, store);
+      return;
+    }
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+    if (at + held > (uint32_t)CAP) return;             // does not fit: the count says so, the row goes by plain passes
+    const uint32_t tok = (uint32_t)(g * SMP_GROUP + lane4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (in_band[e]) list[lanes_before(bd[e], at)] = u32x2{key_of_ordered(v[e]), tok + e};
+      at += (uint32_t)__builtin_popcountll(bd[e]);
+    }
+  };
+  {
+    int i = 0;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    while (grp[0] < ng) {                              // (groups come in order: behind a slot without one there is none)
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        f32x4 p = SL::widen(raw[u]);
+        const int g = grp[u];
+        issue(raw[u], grp[u]);
+        if (R.logits) {
+          const float l = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lse_of), i));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) p[e] = prob_of(p[e], l);
+        }
+        if (i == 0) {
+          acc = p;
+        } else if (R.use_max) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] = fmaxf(acc[e], p[e]);
+        } else {
+          acc = acc + p;
+        }
+        if (++i == Tq) {
+          i = 0;
+          if (g < ng) classify(g, acc);
+        }
+      }
+    }
+  }
+  if (m == 0) return;
+  if (lane == 0) atomicAdd(&ctr[1], certain);
+  __syncthreads();
+  const uint32_t own_M = ctr[0], own_G = ctr[1];
+  const uint32_t listed = single ? 0u : min(own_M, (uint32_t)CAP);
+
+  // ---- the threshold
+  const int Qv = (nb + P - 1) / P;                     // parts that hold ranked tokens
+  unsigned long long *pub = Qv > 1 ? static_cast<unsigned long long *>(A.pub) + (size_t)row * A.smp_parts * SMP_WORDS : nullptr;
+  auto plain_passes = [&]() { rank_by_passes<T, 1>(A, R, bt, nb, c, t0, t1, h, tmp, n0, min(n0 + P, nb)); };
+  uint32_t lo = band.L, last = band.last;              // keys in question: lo .. lo + last
+  int shift = max(0, 32 - __clz((int)band.span) - 9);
+  uint32_t krem = 0, G = 0, pre = 0, pre_gt = 0, pre_in = 0, in_bin = 0;
+#pragma unroll 1
+  for (int round = 0;; ++round) {
+    for (int i = tid; i < SMP_HIST; i += T) h[i] = 0u;
+    __syncthreads();
+    if (single) {
+      if (tid == 0) h[0] = own_M;
+    } else {
+      for (uint32_t i = tid; i < listed; i += T) {
+        const uint32_t k = list[i][0];
+        if (k - lo <= last) atomicAdd(&h[min((k - lo) >> shift, (uint32_t)SMP_HIST - 1u)], 1u);
+      }
+    }
+    __syncthreads();
+    uint32_t s_M = own_M, over = own_M > (uint32_t)CAP && !single ? 1u : 0u;
+    if (Qv > 1) {
+      // threads 0..255: two bins each; in the first round thread 256 sends the part's counts
+      const bool sends = tid < SMP_HIST / 2 || (tid == SMP_HIST / 2 && round == 0);
+      const int word = tid < SMP_HIST / 2 ? round * (SMP_HIST / 2) + tid : SMP_G_WORD;
+      uint32_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;
+      bool complete = true;
+      if (sends) {
+        const uint32_t o0 = tid < SMP_HIST / 2 ? h[2 * tid] : own_G, o1 = tid < SMP_HIST / 2 ? h[2 * tid + 1] : own_M;
+        __hip_atomic_store(&pub[(size_t)part * SMP_WORDS + word],
+                           SMP_VALID | (tid < SMP_HIST / 2 || !over ? 0ull : SMP_OVER) | o0 | ((unsigned long long)o1 << 32),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        complete = false;
+        for (int spin = 0; !complete && spin <= A.fused_spin_limit; ++spin) {
+          if (spin) __builtin_amdgcn_s_sleep(2);
+          a0 = o0; a1 = o1; b0 = b1 = 0;
+          complete = true;
+          // eight unconditional loads at a time (this part's own word contributes nothing)
+#pragma unroll 1
+          for (int q0 = 0; q0 < Qv; q0 += 8) {
+            unsigned long long w[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+              w[u] = __hip_atomic_load(&pub[(size_t)min(q0 + u, Qv - 1) * SMP_WORDS + word], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+              const int q = q0 + u;
+              const bool use = q != part && q < Qv;
+              if (use && !(w[u] & SMP_VALID)) complete = false;
+              if (use && (w[u] & SMP_OVER)) over = 1u;
+              const uint32_t w0 = use ? (uint32_t)w[u] & 0xffffffu : 0u, w1 = use ? (uint32_t)(w[u] >> 32) & 0xffffffu : 0u;
+              a0 += w0;
+              a1 += w1;
+              b0 += q < part ? w0 : 0u;
+              b1 += q < part ? w1 : 0u;
+            }
+          }
+        }
+      }
+      if (!complete) ctr[2] = 1u;
+      __syncthreads();                                 // every thread has read its bins of h
+      if (tid < SMP_HIST / 2) {
+        h[2 * tid] = a0;
+        h[2 * tid + 1] = a1;
+        hb[2 * tid] = b0;
+        hb[2 * tid + 1] = b1;
+      } else if (sends) {
+        ctr[3] = a0;                                   // certain tokens of the row
+        ctr[4] = a1;                                   // band tokens of the row
+        ctr[5] = b0;                                   // certain tokens of the earlier parts
+        ctr[6] = over;
+      }
+      __syncthreads();
+      if (ctr[2]) {
+        plain_passes();
+        return;
+      }
+      if (round == 0) {
+        G = ctr[3];
+        s_M = ctr[4];
+        pre = ctr[5];
+        over = ctr[6];
+      }
+    } else if (round == 0) {
+      G = own_G;
+    }
+    if (round == 0) {
+      if (over || G >= c || G + s_M < c) {             // the same in every part of the row
+        plain_passes();
+        return;
+      }
+      krem = c - G;
+    }
+    // every wave finds the bin by itself: lane l owns bins 8 l .. 8 l + 7
+    uint32_t x[8], y[8], sx = 0, sy = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      x[i] = h[8 * lane + i];
+      y[i] = Qv > 1 ? hb[8 * lane + i] : 0u;
+      sx += x[i];
+      sy += y[i];
+    }
+    const uint32_t incl = wave_incl_scan(sx);
+    uint32_t above = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63) - incl;   // keys in bins of higher lanes
+    const uint64_t has = ballot64(above < krem && above + sx >= krem);
+    const int owner = has ? __builtin_ctzll(has) : 0;
+    uint32_t bin = 0, left = krem, held = 0, gt = lane > owner ? sy : 0u, at = 0;
+    if (lane == owner) {
+#pragma unroll
+      for (int i = 7; i >= 0; --i) {
+        if (above < krem && above + x[i] >= krem) {
+          bin = 8 * lane + i;
+          left = krem - above;
+          held = x[i];
+          at = y[i];
+        } else if (above < krem) {
+          gt += y[i];                                  // a bin above the threshold's
+        }
+        above += x[i];
+      }
+    }
+    bin = (uint32_t)__builtin_amdgcn_readlane((int)bin, owner);
+    krem = (uint32_t)__builtin_amdgcn_readlane((int)left, owner);
+    in_bin = (uint32_t)__builtin_amdgcn_readlane((int)held, owner);
+    pre_in = (uint32_t)__builtin_amdgcn_readlane((int)at, owner);
+    pre_gt += wave_sum(gt);
+    lo += bin << shift;
+    last = bin == (uint32_t)SMP_HIST - 1u ? last - (bin << shift) : (1u << shift) - 1u;   // the last bin has no upper end
+    if (last == 0u || in_bin <= (uint32_t)SMP_CAND) break;
+    if (round + 1 == SMP_ROUNDS) {                     // the same in every part of the row
+      plain_passes();
+      return;
+    }
+    shift = max(0, 32 - __clz((int)last) - 9);
+    __syncthreads();                                   // every wave has read the histogram
+  }
+  uint32_t Tk = lo, r = krem, E = in_bin, pre_eq = pre_in;
+  if (last != 0u) {
+    // few keys share the threshold's bin: they are exchanged one by one and ranked against each other
+    for (uint32_t i = tid; i < listed; i += T) {
+      const u32x2 x = list[i];
+      if (x[0] - lo <= last) {
+        const uint32_t s = atomicAdd(&ctr[7], 1u);
+        if (s < (uint32_t)SMP_CAND) cand[s] = x;
+      }
+    }
+    __syncthreads();
+    const uint32_t own = min(ctr[7], (uint32_t)SMP_CAND);
+    if (Qv > 1) {
+      if (tid < SMP_CAND)
+        __hip_atomic_store(&pub[(size_t)part * SMP_WORDS + SMP_CAND_WORD + tid],
+                           SMP_VALID | ((unsigned long long)own << 32) | ((uint32_t)tid < own ? cand[tid][0] : 0u), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      bool complete = true;
+      for (int q = tid / SMP_CAND; q < Qv; q += T / SMP_CAND) {
+        if (q == part) continue;
+        unsigned long long w = 0;
+        for (int spin = 0; !(w & SMP_VALID) && spin <= A.fused_spin_limit; ++spin) {
+          if (spin) __builtin_amdgcn_s_sleep(2);
+          w = __hip_atomic_load(&pub[(size_t)q * SMP_WORDS + SMP_CAND_WORD + tid % SMP_CAND], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (!(w & SMP_VALID)) complete = false;
+        else if ((uint32_t)(tid % SMP_CAND) < ((uint32_t)(w >> 32) & 127u)) {
+          const uint32_t s = atomicAdd(&ctr[7], 1u);
+          if (s < (uint32_t)SMP_CAND) cand[s] = u32x2{(uint32_t)w, 0x80000000u | (uint32_t)q};
+        }
+      }
+      if (!complete) ctr[2] = 1u;
+      __syncthreads();
+      if (ctr[2]) {
+        plain_passes();
+        return;
+      }
+    }
+    // every wave by itself: lane i ranks candidate i
+    const uint32_t n = min(in_bin, (uint32_t)SMP_CAND);
+    const u32x2 mine = cand[min((uint32_t)lane, n - 1u)];
+    uint32_t g = 0, e = 0;
+    for (uint32_t q = 0; q < n; ++q) {
+      const uint32_t k = cand[q][0];
+      g += k > mine[0] ? 1u : 0u;
+      e += k == mine[0] ? 1u : 0u;
+    }
+    const int win = __builtin_ctzll(ballot64((uint32_t)lane < n && g < krem && g + e >= krem) | (1ull << 63));
+    Tk = (uint32_t)__builtin_amdgcn_readlane((int)mine[0], win);
+    r = krem - (uint32_t)__builtin_amdgcn_readlane((int)g, win);
+    E = (uint32_t)__builtin_amdgcn_readlane((int)e, win);
+    const bool early = (uint32_t)lane < n && (mine[1] >> 31) && (int)(mine[1] & 0x7fffffffu) < part;
+    pre_gt += (uint32_t)__builtin_popcountll(ballot64(early && mine[0] > Tk));
+    pre_eq = (uint32_t)__builtin_popcountll(ballot64(early && mine[0] == Tk));
+  }
+  pre += pre_gt + min(pre_eq, r);                      // kept tokens of the earlier parts
+
+  // ---- the part's kept tokens: bits of the band's. Of the tokens equal to T the first `quota` of this part
+  // are kept: all of them, unless the row has more than r.
+  const uint32_t quota = r > pre_eq ? r - pre_eq : 0u;
+  uint32_t own_eq = 0;
+  if (single) {
+    own_eq = own_M;
+  } else {
+    uint32_t n = 0;
+    for (uint32_t i = tid; i < listed; i += T) {
+      const u32x2 x = list[i];
+      if (x[0] > Tk || (x[0] == Tk && r >= E)) atomicOr(&bits[x[1] >> 5], 1u << (x[1] & 31u));
+      n += x[0] == Tk ? 1u : 0u;
+    }
+    if (r < E) own_eq = block_sum1<T>(n, red);         // (uniform)
+  }
+  if (single || (r < E && quota > 0u)) {
+    if (single) {
+      // the equal tokens are a bitmap: the first `quota` of its bits, by words in order
+      const int words = ((m + SMP_GROUP - 1) / SMP_GROUP) * 8, per = (words + T - 1) / T;
+      const int w0 = min(tid * per, words), w1 = min(w0 + per, words);
+      uint32_t n = 0, total;
+      for (int w = w0; w < w1; ++w) n += (uint32_t)__builtin_popcount(store[w]);
+      uint32_t before = block_excl_scan<T>(n, tmp, total);
+      for (int w = w0; w < w1; ++w)
+        for (uint32_t rest = store[w]; rest && before < quota; rest &= rest - 1u, ++before) bits[w] |= rest & (0u - rest);
+    } else {
+      // the lowest tokens of the list's equal ones: their reversed ids are ranked like keys, 11 + 9 bits
+      static_assert(TOK <= 1 << 20, "token ids of a part");
+      constexpr uint32_t REV = (1u << 20) - 1u;
+      uint32_t cut = 0;
+      if (own_eq > quota) {
+        uint32_t da, ra, db, rb;
+        for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
+        __syncthreads();
+        for (uint32_t i = tid; i < listed; i += T)
+          if (list[i][0] == Tk) atomicAdd(&h[(REV - list[i][1]) >> 9], 1u);
+        __syncthreads();
+        find_digit<SEL_BINS, T>(h, quota, tmp, da, ra);
+        for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
+        __syncthreads();
+        for (uint32_t i = tid; i < listed; i += T)
+          if (list[i][0] == Tk && ((REV - list[i][1]) >> 9) == da) atomicAdd(&h[(REV - list[i][1]) & 511u], 1u);
+        __syncthreads();
+        find_digit<SEL_BINS, T>(h, ra, tmp, db, rb);
+        cut = (da << 9) | db;
+      }
+      for (uint32_t i = tid; i < listed; i += T)
+        if (list[i][0] == Tk && REV - list[i][1] >= cut) atomicOr(&bits[list[i][1] >> 5], 1u << (list[i][1] & 31u));
+    }
+  }
+  __syncthreads();
+
+  // ---- the list: set bits in token order. A thread owns a run of words, one block scan gives its first place; the
+  // tokens are staged in LDS (the band list is done with) and copied out coalesced, once per target head.
+  const int words = (m + 31) >> 5, per = (words + T - 1) / T;
+  const int w0 = min(tid * per, words), w1 = min(w0 + per, words);
+  uint32_t mine = 0, total;
+  for (int w = w0; w < w1; ++w) mine += (uint32_t)__builtin_popcount(bits[w]);
+  const uint32_t first = block_excl_scan<T>(mine, tmp, total);
+  total = pre < c ? min(total, c - pre) : 0u;          // unchanged for a consistent state; keeps a bad one in bounds
+  int32_t *staged = reinterpret_cast<int32_t *>(store);
+#pragma unroll 1
+  for (uint32_t base = 0; base < total; base += 2 * CAP) {
+    uint32_t p = first;
+    if (p < base + 2 * CAP && p + mine > base)
+      for (int w = w0; w < w1; ++w)
+        for (uint32_t rest = bits[w]; rest; rest &= rest - 1u, ++p)
+          if (p - base < 2u * CAP) staged[p - base] = n0 + 32 * w + __builtin_ctz(rest);
+    __syncthreads();
+    const uint32_t cnt = min(total - base, 2u * CAP);
+    for (int ti = t0; ti < t1; ++ti) {
+      int32_t *dst = A.indices + ((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + pre + base;
+      for (uint32_t i = tid; i < cnt; i += T) dst[i] = staged[i];
+    }
+    __syncthreads();
+  }
+}
+
+__global__ void __launch_bounds__(SEL_THREADS) select_clear16_kernel(u32x4 *p, size_t n) {
+  const size_t i = (size_t)blockIdx.x * SEL_THREADS + threadIdx.x;
+  if (i < n) p[i] = u32x4{0u, 0u, 0u, 0u};
+}
+
+}  // namespace
+
+static void clear_words(const SelectArgs &a, hipStream_t s) {
+  const size_t n16 = (size_t)a.B * a.Hd * (size_t)a.smp_parts * SMP_WORDS / 2;
+  STS_LAUNCH(select_clear16_kernel, dim3((unsigned)((n16 + SEL_THREADS - 1) / SEL_THREADS)), dim3(SEL_THREADS), 0, s,
+             static_cast<u32x4 *>(a.pub), n16);
+}
+
+static bool launch_sampled(const SelectArgs &a, hipStream_t s) {
+  if (a.N < 4 || a.smp_tokens % SMP_GROUP != 0 || (int64_t)a.smp_tokens * a.smp_parts < a.N || a.smp_tokens > SMP_MAX_TOKENS)
+    return false;
+  const dim3 grid(a.smp_parts, a.B * a.Hd), block(SMP_THREADS);
+  if (a.smp_tokens <= 65536) {
+    if (a.scores_bf16) STS_LAUNCH((select_sampled_kernel<true, 65536, 16384>), grid, block, 0, s, a);
+    else STS_LAUNCH((select_sampled_kernel<false, 65536, 16384>), grid, block, 0, s, a);
+  } else {
+    if (a.scores_bf16) STS_LAUNCH((select_sampled_kernel<true, SMP_MAX_TOKENS, 8192>), grid, block, 0, s, a);
+    else STS_LAUNCH((select_sampled_kernel<false, SMP_MAX_TOKENS, 8192>), grid, block, 0, s, a);
+  }
+  return true;
+}
+
+// zeroes the words that the parts of a row exchange, 16 bytes per thread
+hipError_t launch_select_clear_pub(const SelectArgs &a, hipStream_t s) {
+  if ((size_t)a.B * a.Hd == 0 || a.smp_parts == 0) return hipSuccess;
+  clear_words(a, s);
+  return sts_take_launch_status();
+}
+
+hipError_t launch_select_fused(const SelectArgs &a, hipStream_t s) {
+  if ((size_t)a.B * a.Hd == 0 || a.smp_parts == 0) return hipSuccess;
+  if (!launch_sampled(a, s)) return hipErrorInvalidValue;
+  return sts_take_launch_status();
+}
+
+bool select_band_ok(const SelectArgs &a) {
+  return a.page == 1 && a.N > 0 && a.N <= BAND_MAX_N && (a.N % 4) == 0 && (reinterpret_cast<uintptr_t>(a.scores) % 16) == 0 &&
+         (a.agg == nullptr || (reinterpret_cast<uintptr_t>(a.agg) % 16) == 0);
+}
+
+// rows enough for every second CU at least: one workgroup per row, or a few with the words between them cleared first
+hipError_t launch_select_band(const SelectArgs &a, hipStream_t s) {
+  if ((size_t)a.B * a.Hd == 0) return hipSuccess;
+  if (!select_band_ok(a)) return hipErrorInvalidValue;
+  const StsLaunchEvents ev = g_sts_launch_events;      // the timing aid's pair of events spans both launches
+  if (a.smp_parts > 1) {
+    g_sts_launch_events = StsLaunchEvents{ev.start, nullptr};
+    clear_words(a, s);
+    g_sts_launch_events = StsLaunchEvents{nullptr, ev.stop};
+  }
+  const bool ok = launch_sampled(a, s);
+  g_sts_launch_events = ev;
+  return ok ? sts_take_launch_status() : hipErrorInvalidValue;
+}

@@ -1,0 +1,415 @@
+// Device code shared by the selection kernels: the order-preserving keys, the aggregation of a row's
+// scores, block-wide scans and digit searches, and the plain several-pass ranking of a row.
+// Internal; included by the selection's translation units only.
+#pragma once
+
+#include "common.h"
+
+namespace {
+
+
+__device__ __forceinline__ uint32_t key_of_bits(uint32_t u) {
+  if (u == 0x80000000u) u = 0u;                       // -0 == +0
+  // ascending with the float order: negative values have all bits flipped, the others the sign bit set
+  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+}
+__device__ __forceinline__ uint32_t key_of(float x) { return key_of_bits(__builtin_bit_cast(uint32_t, x)); }
+
+// exp(s - lse) through the hardware base-2 exponential (about 1 ulp; the product with log2(e)
+// adds a relative error below 1e-6 for |s - lse| < 40, far inside the stage-wise tolerance)
+__device__ __forceinline__ float prob_of(float s, float lse) {
+  return __builtin_amdgcn_exp2f((s - lse) * 1.44269504088896340736f);
+}
+
+__device__ __forceinline__ int row_len(const SelectArgs &A, int bt) {
+  int nb = A.seq_lens ? A.seq_lens[bt] : A.N;
+  return min(max(nb, 0), A.N);
+}
+
+// number of ranked units (tokens, or blocks of `page` tokens) in the row of batch bt
+__device__ __forceinline__ int src_len(const SelectArgs &A, int bt) {
+  return (row_len(A, bt) + A.page - 1) / A.page;
+}
+
+// Inclusive prefix sum over the 64 lanes of a wave with data-parallel-primitive moves (no LDS
+// round trips): shifts by 1, 2, 4, 8 inside each row of 16 lanes (a lane whose source lies
+// outside its row adds 0), then lane 15 of row 0 / 2 is added to row 1 / 3, then lane 31 to
+// rows 2 and 3.
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+  int x = (int)v;
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return (uint32_t)x;
+}
+
+// signed image of a score's order: positive scores are their own bit pattern
+__device__ __forceinline__ int ordered(int v) {
+  v = v == (int)0x80000000 ? 0 : v;                    // -0 == +0
+  return v ^ ((v >> 31) & 0x7fffffff);
+}
+__device__ __forceinline__ uint32_t key_of_ordered(int s) { return (uint32_t)s ^ 0x80000000u; }
+__device__ __forceinline__ int ordered_of_key(uint32_t k) { return (int)(k ^ 0x80000000u); }
+
+__device__ __forceinline__ uint64_t ballot64(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+__device__ __forceinline__ uint32_t lanes_before(uint64_t mask, uint32_t base) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, base));
+}
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), 63); }
+
+// exclusive prefix sum of one value per thread over a THREADS-thread block; also returns the
+// total. lds_wave_tot needs THREADS/64 words.
+template <int THREADS = SEL_THREADS>
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *lds_wave_tot, uint32_t &total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t incl = wave_incl_scan(v);
+  if (lane == 63) lds_wave_tot[wave] = incl;
+  __syncthreads();
+  uint32_t base = 0, tot = 0;
+#pragma unroll
+  for (int w = 0; w < THREADS / 64; ++w) {
+    const uint32_t t = lds_wave_tot[w];
+    if (w < wave) base += t;
+    tot += t;
+  }
+  __syncthreads();
+  total = tot;
+  return base + incl - v;
+}
+
+// Walk a digit histogram from the top: the digit holding the krem-th largest key of the
+// candidates, and how many keys of that digit are still wanted. Requires 1 <= krem <= total.
+// lds_tmp needs THREADS/64 + 2 words; the result lands in its last two.
+template <int NBINS, int THREADS = SEL_THREADS>
+__device__ __forceinline__ void find_digit(const uint32_t *hist, uint32_t krem, uint32_t *lds_tmp,
+                                           uint32_t &digit, uint32_t &krem_next) {
+  constexpr int PER = NBINS / THREADS;
+  constexpr int RES = THREADS / 64;
+  uint32_t loc[PER], sum = 0;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    loc[i] = hist[threadIdx.x * PER + i];
+    sum += loc[i];
+  }
+  uint32_t total;
+  const uint32_t excl = block_excl_scan<THREADS>(sum, lds_tmp, total);
+  uint32_t above = total - excl - sum;   // keys in bins owned by higher threads
+#pragma unroll
+  for (int i = PER - 1; i >= 0; --i) {
+    if (above < krem && above + loc[i] >= krem) {
+      lds_tmp[RES] = threadIdx.x * PER + i;
+      lds_tmp[RES + 1] = krem - above;
+    }
+    above += loc[i];
+  }
+  __syncthreads();
+  digit = lds_tmp[RES];
+  krem_next = lds_tmp[RES + 1];
+  __syncthreads();
+}
+
+// ------------------------------------------------------------------- aggregation of a row
+// The Tq score rows of one (batch, draft head), reduced per token strictly in row order.
+struct AggRow {
+  const void *P;    // [Tq][N] fp32, or bf16 bit patterns
+  const float *L;   // [Tq] natural-log normalisers (scaled-logit input) or nullptr
+  int Tq, N;
+  bool bf16, logits, use_max;
+};
+
+__device__ __forceinline__ AggRow agg_row(const SelectArgs &A, int row) {
+  AggRow R;
+  const size_t off = (size_t)row * A.Tq * A.N;
+  R.bf16 = A.scores_bf16 != 0;
+  R.P = R.bf16 ? static_cast<const void *>(static_cast<const uint16_t *>(A.scores) + off)
+               : static_cast<const void *>(static_cast<const float *>(A.scores) + off);
+  R.L = A.lse ? A.lse + (size_t)row * A.Tq : nullptr;
+  R.Tq = A.Tq;
+  R.N = A.N;
+  R.logits = A.kind == STS_SCORES_LOGITS_LSE;
+  R.use_max = A.reduce == STS_REDUCE_MAX;
+  return R;
+}
+
+// One score (V = float) or four consecutive ones (V = f32x4) of row i, as stored: the raw load, and
+// its exact widening to fp32. Nontemporal: every score is read exactly once. Four scores need no
+// more than their element's alignment (rows of N % 4 != 0 scores start anywhere): the vector types
+// below say so, and this chip's global loads of 8 and 16 bytes take any address.
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+template <class V, bool BF16>
+struct ScoreLoad;
+template <>
+struct ScoreLoad<float, false> {
+  typedef float raw;
+  static __device__ __forceinline__ raw load(const AggRow &R, int i, int n) {
+    return __builtin_nontemporal_load(static_cast<const float *>(R.P) + (size_t)i * R.N + n);
+  }
+  static __device__ __forceinline__ float widen(raw x) { return x; }
+};
+template <>
+struct ScoreLoad<f32x4, false> {
+  typedef f32x4 raw;
+  static __device__ __forceinline__ raw load(const AggRow &R, int i, int n) {
+    return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any *>(static_cast<const float *>(R.P) + (size_t)i * R.N + n));
+  }
+  static __device__ __forceinline__ raw load_at(const unsigned char *p) { return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any *>(p)); }
+  static __device__ __forceinline__ f32x4 widen(raw x) { return x; }
+};
+template <>
+struct ScoreLoad<float, true> {
+  typedef uint16_t raw;
+  static __device__ __forceinline__ raw load(const AggRow &R, int i, int n) {
+    return __builtin_nontemporal_load(static_cast<const uint16_t *>(R.P) + (size_t)i * R.N + n);
+  }
+  static __device__ __forceinline__ float widen(raw x) { return __builtin_bit_cast(float, (uint32_t)x << 16); }
+};
+template <>
+struct ScoreLoad<f32x4, true> {
+  typedef u32x2 raw;   // four bf16 values
+  static __device__ __forceinline__ raw load(const AggRow &R, int i, int n) {
+    return __builtin_nontemporal_load(reinterpret_cast<const u32x2_any *>(static_cast<const uint16_t *>(R.P) + (size_t)i * R.N + n));
+  }
+  static __device__ __forceinline__ raw load_at(const unsigned char *p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x2_any *>(p)); }
+  static __device__ __forceinline__ f32x4 widen(raw x) {
+    return f32x4{__builtin_bit_cast(float, x[0] << 16), __builtin_bit_cast(float, x[0] & 0xffff0000u),
+                 __builtin_bit_cast(float, x[1] << 16), __builtin_bit_cast(float, x[1] & 0xffff0000u)};
+  }
+};
+
+// NROWS consecutive score rows, from row i on, of the token(s) at each of the NPOS positions n[]:
+// all loads first (their latencies overlap), then the reduction strictly in row order. FIRST: row
+// i is row 0 and initialises the accumulators.
+template <int NROWS, bool FIRST, bool BF16, int NPOS, class V>
+__device__ __forceinline__ void agg_rows(const AggRow &R, int i, const int (&n)[NPOS], V (&acc)[NPOS]) {
+  typedef ScoreLoad<V, BF16> SL;
+  typename SL::raw raw[NPOS][NROWS];
+#pragma unroll
+  for (int x = 0; x < NPOS; ++x)
+#pragma unroll
+    for (int u = 0; u < NROWS; ++u) raw[x][u] = SL::load(R, i + u, n[x]);
+#pragma unroll
+  for (int x = 0; x < NPOS; ++x)
+#pragma unroll
+    for (int u = 0; u < NROWS; ++u) {
+      V p = SL::widen(raw[x][u]);
+      if (R.logits) {
+        const float l = R.L[i + u];
+        if constexpr (sizeof(V) == sizeof(float)) {
+          p = prob_of(p, l);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) p[e] = prob_of(p[e], l);
+        }
+      }
+      if (FIRST && u == 0) {
+        acc[x] = p;
+      } else if (R.use_max) {
+        if constexpr (sizeof(V) == sizeof(float)) {
+          acc[x] = fmaxf(acc[x], p);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[x][e] = fmaxf(acc[x][e], p[e]);
+        }
+      } else {
+        acc[x] = acc[x] + p;
+      }
+    }
+}
+
+template <bool FIRST, bool BF16, int NPOS, class V>
+__device__ __forceinline__ void agg_group(const AggRow &R, int i, int rows, const int (&n)[NPOS], V (&acc)[NPOS]) {
+  switch (rows) {   // uniform: a scalar branch; every case is straight-line code
+    case 1: agg_rows<1, FIRST, BF16>(R, i, n, acc); break;
+    case 2: agg_rows<2, FIRST, BF16>(R, i, n, acc); break;
+    case 3: agg_rows<3, FIRST, BF16>(R, i, n, acc); break;
+    case 4: agg_rows<4, FIRST, BF16>(R, i, n, acc); break;
+    case 5: agg_rows<5, FIRST, BF16>(R, i, n, acc); break;
+    case 6: agg_rows<6, FIRST, BF16>(R, i, n, acc); break;
+    case 7: agg_rows<7, FIRST, BF16>(R, i, n, acc); break;
+    default: agg_rows<8, FIRST, BF16>(R, i, n, acc); break;
+  }
+}
+
+// aggregated score(s) at NPOS positions at once: rows in groups of up to 8 loads per position in
+// flight
+template <class V, int NPOS>
+__device__ __forceinline__ void agg_multi(const AggRow &R, const int (&n)[NPOS], V (&acc)[NPOS]) {
+  if (R.bf16) {
+    agg_group<true, true>(R, 0, min(R.Tq, 8), n, acc);
+    for (int i = 8; i < R.Tq; i += 8) agg_group<false, true>(R, i, min(R.Tq - i, 8), n, acc);
+  } else {
+    agg_group<true, false>(R, 0, min(R.Tq, 8), n, acc);
+    for (int i = 8; i < R.Tq; i += 8) agg_group<false, false>(R, i, min(R.Tq - i, 8), n, acc);
+  }
+}
+
+// the same for a caller that knows Tq <= MAXG (MAXG <= 8): only those cases are compiled, so many
+// positions in flight do not cost the registers of eight rows each
+template <bool BF16, int MAXG, int NPOS, class V>
+__device__ __forceinline__ void agg_group_lim(const AggRow &R, int rows, const int (&n)[NPOS], V (&acc)[NPOS]) {
+  if constexpr (MAXG <= 1) {
+    agg_rows<1, true, BF16>(R, 0, n, acc);
+  } else {
+    if (rows >= MAXG) agg_rows<MAXG, true, BF16>(R, 0, n, acc);
+    else agg_group_lim<BF16, MAXG - 1>(R, rows, n, acc);
+  }
+}
+template <class V, int NPOS, int MAXG>
+__device__ __forceinline__ void agg_multi_lim(const AggRow &R, const int (&n)[NPOS], V (&acc)[NPOS]) {
+  if constexpr (MAXG >= 8) {
+    agg_multi<V, NPOS>(R, n, acc);
+  } else {
+    if (R.bf16) agg_group_lim<true, MAXG>(R, R.Tq, n, acc);
+    else agg_group_lim<false, MAXG>(R, R.Tq, n, acc);
+  }
+}
+
+template <class V>
+__device__ __forceinline__ V agg_at(const AggRow &R, int n) {
+  const int pos[1] = {n};
+  V acc[1];
+  agg_multi<V, 1>(R, pos, acc);
+  return acc[0];
+}
+
+__device__ __forceinline__ f32x4 agg_quad(const AggRow &R, int n) { return agg_at<f32x4>(R, n); }
+
+// The quads at n[] of a row whose length need not be a multiple of 4 (R.N >= 4): a quad that would
+// run past the row's end is read where it still fits and shifted; elements past the end (all of a
+// quad's that starts there) come out as some score of the row and are the caller's to ignore.
+// inside (wave-uniform): every quad of the wave lies inside the row.
+template <int NPOS, int MAXG>
+__device__ __forceinline__ void agg_quads_any(const AggRow &R, const int (&n)[NPOS], bool inside, f32x4 (&acc)[NPOS]) {
+  int m[NPOS];
+#pragma unroll
+  for (int x = 0; x < NPOS; ++x) m[x] = min(n[x], R.N - 4);
+  agg_multi_lim<f32x4, NPOS, MAXG>(R, m, acc);
+  if (!inside) {
+#pragma unroll
+    for (int x = 0; x < NPOS; ++x) {
+      const int d = n[x] - m[x];
+      const f32x4 y = acc[x];
+      acc[x][0] = d == 0 ? y[0] : d == 1 ? y[1] : d == 2 ? y[2] : y[3];
+      acc[x][1] = d == 0 ? y[1] : d == 1 ? y[2] : y[3];
+      acc[x][2] = d == 0 ? y[2] : y[3];
+    }
+  }
+}
+__device__ __forceinline__ float agg_one(const AggRow &R, int n) { return agg_at<float>(R, n); }
+
+// tail padding (-1 from position c on) and counts for every target head of draft head j
+template <int THREADS>
+__device__ __forceinline__ void write_tail(const SelectArgs &A, int bt, int j, uint32_t c) {
+  for (int ti = A.targets.off[j]; ti < A.targets.off[j + 1]; ++ti) {
+    const int tgt = A.targets.tgt[ti];
+    int32_t *dst = A.indices + ((size_t)bt * A.Hq + tgt) * A.k;
+    for (uint32_t p = c + threadIdx.x; p < (uint32_t)A.k; p += THREADS) dst[p] = -1;
+    if (A.counts && threadIdx.x == 0) A.counts[(size_t)bt * A.Hq + tgt] = (int32_t)c;
+  }
+}
+
+// bin of `key` at `level` under the prefix fixed so far, or -1 when the key is no candidate
+__device__ __forceinline__ int fused_bin(uint32_t key, int level, uint32_t d0, uint32_t pre01) {
+  if (level == 0) return (int)(key >> (32 - SEL_BITS0));
+  if (level == 1) return (key >> (SEL_BITS1 + SEL_BITS2)) == d0 ? (int)((key >> SEL_BITS2) & ((1u << SEL_BITS1) - 1)) : -1;
+  return (key >> SEL_BITS2) == pre01 ? (int)(key & ((1u << SEL_BITS2) - 1)) : -1;
+}
+
+// sum over the block of one value per thread; red needs THREADS / 64 words
+template <int THREADS>
+__device__ __forceinline__ uint32_t block_sum1(uint32_t a, uint32_t *red) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) a += (uint32_t)__shfl_xor((int)a, off, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+  __syncthreads();
+  uint32_t s = 0;
+#pragma unroll
+  for (int w = 0; w < THREADS / 64; ++w) s += red[w];
+  __syncthreads();
+  return s;
+}
+
+// The plain way for one workgroup to rank a row it cannot hold: a pass over the scores per digit
+// level (the Tq rows are aggregated again each time, in the same order, so the keys repeat bit
+// for bit), then a pass that compacts in token order. h: SEL_BINS words, tmp: THREADS/64 + 2.
+template <int THREADS, int NPOS = 2>
+__device__ __forceinline__ void rank_by_passes(const SelectArgs &A, const AggRow &R, int bt, int nb, uint32_t c,
+                                               int t0, int t1, uint32_t *h, uint32_t *tmp, int from = 0, int to = 0x7fffffff) {
+  const int tid = threadIdx.x;
+  const int nq = (nb + 3) >> 2;           // quads that hold ranked tokens
+  uint32_t d0 = 0, pre01 = 0, krem = c, d2 = 0;
+#pragma unroll 1
+  for (int level = 0; level < 3; ++level) {
+    for (int i = tid; i < SEL_BINS; i += THREADS) h[i] = 0u;
+    __syncthreads();
+#pragma unroll 1
+    for (int q0 = tid; q0 < nq; q0 += THREADS * NPOS) {
+      int pos[NPOS];
+      f32x4 acc[NPOS];
+#pragma unroll
+      for (int x = 0; x < NPOS; ++x) pos[x] = 4 * min(q0 + x * THREADS, nq - 1);
+      agg_quads_any<NPOS, 8>(R, pos, false, acc);
+#pragma unroll
+      for (int x = 0; x < NPOS; ++x)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int n = 4 * (q0 + x * THREADS) + e;
+          const int bin = fused_bin(key_of(acc[x][e]), level, d0, pre01);
+          if (n < nb && bin >= 0) atomicAdd(&h[bin], 1u);
+        }
+    }
+    __syncthreads();
+    uint32_t digit, knext;
+    find_digit<SEL_BINS, THREADS>(h, krem, tmp, digit, knext);
+    if (level == 0) d0 = digit;
+    else if (level == 1) pre01 = (d0 << SEL_BITS1) | digit;
+    else d2 = digit;
+    krem = knext;
+  }
+  const uint32_t r = krem, Tk = (pre01 << SEL_BITS2) | d2;
+  // ordered compaction: per step, thread tid owns the NPOS consecutive quads from (step + tid * NPOS)
+  uint32_t gbase = 0, qbase = 0;
+#pragma unroll 1
+  for (int step = 0; step < nq; step += THREADS * NPOS) {
+    const int qlo = step + tid * NPOS;
+    int pos[NPOS];
+    f32x4 acc[NPOS];
+#pragma unroll
+    for (int x = 0; x < NPOS; ++x) pos[x] = 4 * min(qlo + x, nq - 1);
+    agg_quads_any<NPOS, 8>(R, pos, false, acc);
+    uint32_t gt_mask = 0, eq_mask = 0;
+#pragma unroll
+    for (int x = 0; x < NPOS; ++x)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t key = key_of(acc[x][e]);
+        const bool in = 4 * (qlo + x) + e < nb;
+        gt_mask |= (in && key > Tk) ? 1u << (4 * x + e) : 0u;
+        eq_mask |= (in && key == Tk) ? 1u << (4 * x + e) : 0u;
+      }
+    uint32_t total;
+    const uint32_t excl = block_excl_scan<THREADS>(__builtin_popcount(gt_mask) | (__builtin_popcount(eq_mask) << 16), tmp, total);
+    uint32_t g = gbase + (excl & 0xffffu), q = qbase + (excl >> 16);
+    for (uint32_t rest = gt_mask | eq_mask; rest; rest &= rest - 1) {
+      const int i = __builtin_ctz(rest);
+      const bool is_gt = (gt_mask >> i) & 1u;
+      if (is_gt || q < r) {
+        const uint32_t p = g + min(q, r);
+        const int n = 4 * qlo + i;
+        if (p < c && n >= from && n < to)
+          for (int ti = t0; ti < t1; ++ti) A.indices[((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + p] = n;
+      }
+      g += is_gt ? 1u : 0u;
+      q += is_gt ? 0u : 1u;
+    }
+    gbase += total & 0xffffu;
+    qbase += total >> 16;
+    if (gbase + min(qbase, r) >= c || 4 * (step + THREADS * NPOS) >= to) break;   // the list is complete (uniform)
+  }
+}
+
+}  // namespace

@@ -1,0 +1,91 @@
+"""The sampled selection (csrc/select_sampled.hip) where it can go wrong: row lengths that are no multiple
+of a quad, a group or a part, scores at any alignment, rows whose sample misleads or whose band is
+one key, and rows cut into more than eight parts. Bit for bit against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_15508_amd as sts
+from gpu_util import stored_agg
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def make(what, B, Hd, Tq, N, seed):
+    g = torch.Generator().manual_seed(seed)
+    s = torch.softmax(torch.randn(B, Hd, Tq, N, generator=g) * 2, dim=-1)
+    if what == "zeros":                       # the threshold is one value that most tokens share
+        return s * (torch.rand(B, Hd, 1, N, generator=g) < 0.05)
+    if what == "constant":
+        return torch.full((B, Hd, Tq, N), 0.25)
+    if what == "levels":                      # two neighbouring levels can fill the band: ranked by plain passes
+        return torch.randint(0, 5, (B, Hd, 1, N), generator=g).float().expand(B, Hd, Tq, N).contiguous() / 8
+    if what == "signed":                      # negative scores, -0 and +0
+        s = torch.randn(B, Hd, Tq, N, generator=g)
+        s[..., ::7] = 0.0
+        s[..., 3::14] = -0.0
+        return s
+    if what == "stretch":                     # all heavy tokens next to each other
+        s[..., N // 3:N // 3 + N // 8] += 1e-3
+        return s
+    if what == "passages":                    # heavy passages of 200 tokens
+        m = (torch.rand(B, Hd, 1, N // 200 + 1, generator=g) < 0.1).float().repeat_interleave(200, -1)[..., :N]
+        return s * (1 + 20 * m)
+    if what == "inf":                         # infinite scores are kept before all others
+        s[..., N // 2::1000] = float("inf")
+        return s
+    return s
+
+
+@pytest.mark.parametrize("B,Hd,Tq,N,k,bf16,what", [
+    (2, 3, 5, 8193, 819, False, "softmax"),          # one token past the shortest row; two parts
+    (2, 3, 5, 33001, 3301, False, "softmax"),
+    (1, 2, 1, 65537, 6554, True, "softmax"),         # bf16 rows at any even address, ties at the threshold
+    (1, 2, 9, 100003, 700, False, "softmax"),        # more score rows than are in flight
+    (2, 2, 3, 8447, 8447, False, "softmax"),         # everything kept, a group that ends one token short
+    (2, 2, 2, 40961, 1, False, "softmax"),
+    (2, 2, 2, 40002, 9000, False, "zeros"),
+    (2, 2, 2, 40002, 9000, True, "constant"),
+    (2, 2, 2, 40002, 9000, False, "levels"),
+    (2, 2, 1, 40002, 30000, False, "signed"),        # the threshold among the negative scores
+    (2, 2, 3, 70001, 7000, False, "stretch"),
+    (2, 2, 3, 70001, 7000, False, "passages"),
+    (2, 2, 2, 40002, 100, False, "inf"),
+    (1, 16, 1, 262147, 9000, True, "softmax"),       # more than eight parts per row
+    (3, 48, 1, 33000, 1500, False, "softmax"),       # one part per row: 144 rows
+    (1, 128, 2, 16500, 800, True, "softmax"),        # two parts per row, a row for every second CU
+])
+def test_sampled_selection(B, Hd, Tq, N, k, bf16, what):
+    scores = make(what, B, Hd, Tq, N, N + k)
+    scores = scores.to(torch.bfloat16) if bf16 else scores
+    off = 1 if N % 2 else 0                          # an odd row length also starts at an odd element
+    flat = torch.zeros(scores.numel() + 8, dtype=scores.dtype, device=DEV)
+    sd = flat[off:off + scores.numel()].view(B, Hd, Tq, N)
+    sd.copy_(scores)
+    hm = [t // 2 for t in range(Hd)] + [Hd - 1]      # pairs share a draft head, the upper half but one is unread
+    kh = [max(1, k - 5 * j) for j in range(Hd)]
+    lens = torch.tensor([N, N - 13, N // 3][:B], dtype=torch.int32)
+    idx, cnt, agg = sts.sts_select(sd, hm, k, seq_lens=lens.to(DEV), k_head=kh, want_agg=True)
+    idx2, cnt2, _ = sts.sts_select(sd, hm, k, seq_lens=lens.to(DEV), k_head=kh)
+    torch.cuda.synchronize()
+    o_idx, o_cnt, o_agg = oracle.select_indices(scores.float().numpy(), np.asarray(hm, np.int32), k, k_head=kh, seq_lens=lens.numpy())
+    np.testing.assert_array_equal(cnt.cpu().numpy(), o_cnt)
+    np.testing.assert_array_equal(idx.cpu().numpy(), o_idx)
+    np.testing.assert_array_equal(agg.cpu().numpy().view(np.uint32), stored_agg(o_agg, lens).view(np.uint32))
+    assert torch.equal(idx2, idx) and torch.equal(cnt2, cnt)
+
+
+def test_sampled_selection_without_the_other_parts():
+    """A poll limit of 0: workgroups that do not find the other parts' words rank the row themselves."""
+    scores = make("softmax", 1, 4, 2, 50001, 3)
+    sts.set_knob("select_spin_limit", 0)
+    try:
+        idx, cnt, _ = sts.sts_select(scores.to(DEV), [0, 1, 2, 3], 5000)
+        torch.cuda.synchronize()
+    finally:
+        sts.set_knob("select_spin_limit", None)
+    o_idx, o_cnt, _ = oracle.select_indices(scores.numpy(), np.arange(4, dtype=np.int32), 5000)
+    np.testing.assert_array_equal(idx.cpu().numpy(), o_idx)
+    np.testing.assert_array_equal(cnt.cpu().numpy(), o_cnt)
