@@ -10,7 +10,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsts.so")
-SOURCES = ["api.hip", "attn.hip", "select.hip", "select_sampled.hip", "headmap.hip", "scratch.hip", "union.hip"]
+SOURCES = ["api.hip", "attn.hip", "select.hip", "select_sampled.hip", "select_row.hip", "headmap.hip", "scratch.hip", "union.hip"]
 HEADERS = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "select_util.h"), os.path.join(HERE, "..", "include", "sts.h")]
 
 # -packed-fp32-ops is switched off on purpose: packed fp32 instructions are not to be
@@ -20,9 +20,10 @@ COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-
           "-Rpass-analysis=kernel-resource-usage"]   # registers, spills and scratch of every kernel, kept beside the objects
 RESOURCES = os.path.join(HERE, "_build", "kernel_resources.txt")
 # selection must reproduce a fixed fp32 addition order bit for bit: no contraction there
-PER_FILE = {"select.hip": ["-ffp-contract=off"], "select_sampled.hip": ["-ffp-contract=off",
-                                # its single-lane LDS counters need none of the wave-wide reduction code that the pass adds
-                                "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]}
+# (the single-lane LDS counters of the selection kernels need none of the wave-wide reduction code that the
+# atomic optimizer adds)
+_SELECT = ["-ffp-contract=off", "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]
+PER_FILE = {"select.hip": ["-ffp-contract=off"], "select_sampled.hip": _SELECT, "select_row.hip": _SELECT}
 
 
 def _hipcc() -> str:

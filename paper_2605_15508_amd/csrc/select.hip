@@ -21,7 +21,8 @@
 //             chunk's own top-k (same tie rule) goes to a pool, in token order. Every token of
 //             the row's top-k is in the top-k of its chunk.
 //      pool   one workgroup per row ranks the pooled candidates out of LDS and writes the list.
-//  * short rows -- one workgroup per row does everything out of LDS (select_small_kernel).
+//  * short lists of block scores -- one workgroup per row ranks them out of LDS (select_small_kernel);
+//    short rows of scores are ranked in registers (select_row.hip).
 // Keys are the usual order-preserving map of fp32 to uint32 (with -0 folded onto +0), so the
 // whole selection is integer arithmetic: the index sets are exact, ties go to the lower token.
 // Histograms use LDS atomics per workgroup and integer global atomics to merge (order-free).
@@ -583,14 +584,12 @@ __device__ __forceinline__ void lds_compact(const uint32_t *keys, int m, uint32_
   else lds_compact_run<THREADS, MAXPER>(keys, m, T, r, c, tmp, emit);
 }
 
-// ------------------------------------------------- whole selection in one workgroup per row
-// For rows of up to SEL_SMALL_N tokens the keys of a row fit in LDS (128 KB of the 160 KB), so
-// one 1024-thread workgroup per (batch, draft head) does everything in a single launch:
-// aggregate (same fp32 order), three digit histograms over the LDS-resident keys, ordered
-// compaction and the copies to the target heads. No global histograms, nothing to clear.
+// ------------------------------------------------- keys of a row in LDS, ranked by one workgroup
 // FROM_SRC: the scores to rank are already there (A.src, row pitch A.srcN: the block sums of
-// block-granular selection) and only have to be loaded.
-template <bool VEC4, bool FROM_SRC>
+// block-granular selection) and are loaded, up to SEL_SMALL_N of them (128 KB of the 160 KB of LDS), then
+// three digit histograms over the LDS-resident keys, ordered compaction and the copies to the target
+// heads in a single launch. Otherwise: rows of fewer than four tokens, which are aggregated here.
+template <bool FROM_SRC>
 __global__ void __launch_bounds__(SMALL_THREADS) select_small_kernel(const SelectArgs A) {
   __shared__ uint32_t keys[SEL_SMALL_N + SEL_SMALL_N / 32];
   __shared__ uint32_t h[SEL_BINS];
@@ -615,19 +614,6 @@ __global__ void __launch_bounds__(SMALL_THREADS) select_small_kernel(const Selec
       const uint32_t key = key_of(src[n]);
       keys[small_slot(n)] = key;
       atomicAdd(&h[key >> (32 - SEL_BITS0)], 1u);
-    }
-  } else if (VEC4) {
-    for (int n = tid * 4; n < A.N; n += SMALL_THREADS * 4) {
-      const f32x4 acc = agg_quad(R, n);
-      f32x4 o = acc;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t key = key_of(acc[e]);
-        keys[small_slot(n + e)] = key;
-        if (n + e < nb) atomicAdd(&h[key >> (32 - SEL_BITS0)], 1u);
-        else o[e] = 0.f;
-      }
-      if (want_agg) *reinterpret_cast<f32x4 *>(out + n) = o;
     }
   } else {
     for (int n = tid; n < A.N; n += SMALL_THREADS) {
@@ -1106,20 +1092,15 @@ static inline bool src_vec_ok(const SelectArgs &a) {   // ranking passes: rows o
 
 hipError_t launch_select_small(const SelectArgs &a, hipStream_t s) {
   if ((size_t)a.B * a.Hd == 0) return hipSuccess;
-  const dim3 grid(a.B * a.Hd), block(SMALL_THREADS);
-  const bool v = (a.N % 4) == 0 && (reinterpret_cast<uintptr_t>(a.scores) % 16) == 0 &&
-                 (a.agg == nullptr || (reinterpret_cast<uintptr_t>(a.agg) % 16) == 0);
-  if (v)
-    STS_LAUNCH((select_small_kernel<true, false>), grid, block, 0, s, a);
-  else
-    STS_LAUNCH((select_small_kernel<false, false>), grid, block, 0, s, a);
+  if (a.N >= 4) return launch_select_row(a, s);        // rows that hold a quad
+  STS_LAUNCH(select_small_kernel<false>, dim3(a.B * a.Hd), dim3(SMALL_THREADS), 0, s, a);
   return sts_take_launch_status();
 }
 
 // ranks the rows of a.src (up to SEL_SMALL_N entries each) out of LDS
 hipError_t launch_select_rank(const SelectArgs &a, hipStream_t s) {
   if ((size_t)a.B * a.Hd == 0) return hipSuccess;
-  STS_LAUNCH((select_small_kernel<false, true>), dim3(a.B * a.Hd), dim3(SMALL_THREADS), 0, s, a);
+  STS_LAUNCH(select_small_kernel<true>, dim3(a.B * a.Hd), dim3(SMALL_THREADS), 0, s, a);
   return sts_take_launch_status();
 }
 
