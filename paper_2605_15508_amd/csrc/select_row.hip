@@ -77,9 +77,9 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
       any |= v[i][e];
     }
   };
-  if constexpr (IT <= 2) {
+  if constexpr (T == 1024) {
     // few quads: their score rows are in flight together
-#pragma unroll
+#pragma clang loop unroll(full)
     for (int i = 0; i < IT; ++i) {
       const int n[1] = {4 * (i * T + tid)};
       f32x4 acc[1];
@@ -382,19 +382,24 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
 
 }  // namespace
 
-// Rows of 4 to 32768 tokens. Calls with a row for every CU or fewer get 1024 threads per row (latency), others as few
-// as hold the row in 64 registers per thread (several workgroups per CU).
+// Rows of 4 to 32768 tokens. Calls of up to 512 rows get 1024 threads per row (latency: 256 rows of 16384 tokens 25 us
+// with 256 threads per row), others as few as hold the row in 64 registers per thread (several workgroups per CU: 4096
+// such rows 128 us; one workgroup per CU took 290).
 hipError_t launch_select_row(const SelectArgs &a, hipStream_t s) {
   const int64_t rows = (int64_t)a.B * a.Hd;
   if (rows == 0) return hipSuccess;
   if (a.N < 4 || a.N > SEL_SMALL_N) return hipErrorInvalidValue;
   const dim3 grid((unsigned)rows);
-  if (a.N <= 4096) {
-    if (rows <= 512) STS_LAUNCH((select_row_kernel<1024, 1, false>), grid, dim3(1024), 0, s, a);
-    else STS_LAUNCH((select_row_kernel<256, 4, false>), grid, dim3(256), 0, s, a);
+  if (rows <= 512) {
+    const dim3 block(1024);
+    if (a.N <= 4096) STS_LAUNCH((select_row_kernel<1024, 1, false>), grid, block, 0, s, a);
+    else if (a.N <= 8192) STS_LAUNCH((select_row_kernel<1024, 2, false>), grid, block, 0, s, a);
+    else if (a.N <= 16384) STS_LAUNCH((select_row_kernel<1024, 4, true>), grid, block, 0, s, a);
+    else STS_LAUNCH((select_row_kernel<1024, 8, true>), grid, block, 0, s, a);
+  } else if (a.N <= 4096) {
+    STS_LAUNCH((select_row_kernel<256, 4, false>), grid, dim3(256), 0, s, a);
   } else if (a.N <= 8192) {
-    if (rows <= 512) STS_LAUNCH((select_row_kernel<1024, 2, false>), grid, dim3(1024), 0, s, a);
-    else STS_LAUNCH((select_row_kernel<256, 8, true>), grid, dim3(256), 0, s, a);
+    STS_LAUNCH((select_row_kernel<256, 8, true>), grid, dim3(256), 0, s, a);
   } else if (a.N <= 16384) {
     STS_LAUNCH((select_row_kernel<256, 16, true>), grid, dim3(256), 0, s, a);
   } else {

@@ -709,9 +709,13 @@ static bool launch_sampled(const SelectArgs &a, hipStream_t s) {
   if (a.N < 4 || a.smp_tokens % SMP_GROUP != 0 || (int64_t)a.smp_tokens * a.smp_parts < a.N || a.smp_tokens > SMP_MAX_TOKENS)
     return false;
   const dim3 grid(a.smp_parts, a.B * a.Hd), block(SMP_THREADS);
+  // The band's list and a bit per token share the LDS: the fewer tokens, the more room for the list.
   if (a.smp_tokens <= 65536) {
     if (a.scores_bf16) STS_LAUNCH((select_sampled_kernel<true, 65536, 16384>), grid, block, 0, s, a);
     else STS_LAUNCH((select_sampled_kernel<false, 65536, 16384>), grid, block, 0, s, a);
+  } else if (a.smp_tokens <= SMP_PART_TOKENS) {
+    if (a.scores_bf16) STS_LAUNCH((select_sampled_kernel<true, SMP_PART_TOKENS, 15360>), grid, block, 0, s, a);
+    else STS_LAUNCH((select_sampled_kernel<false, SMP_PART_TOKENS, 15360>), grid, block, 0, s, a);
   } else {
     if (a.scores_bf16) STS_LAUNCH((select_sampled_kernel<true, SMP_MAX_TOKENS, 8192>), grid, block, 0, s, a);
     else STS_LAUNCH((select_sampled_kernel<false, SMP_MAX_TOKENS, 8192>), grid, block, 0, s, a);
