@@ -55,18 +55,19 @@ constexpr unsigned long long SMP_VALID = 1ull << 63, SMP_OVER = 1ull << 62;
 // Which runs of a row of nb ranked tokens are sampled: one in every S, at a scattered place of its
 // period (a fixed stride of 4 KB and more lands on a few memory channels only: the sample's loads
 // took 6.5 and, at 1M tokens, 12 us more). About 4096 keys: at a tenth of the row kept the band is then
-// about 5% of a 128K row. 8192 for rows beyond 256K tokens and where a workgroup holds more than 64K
-// tokens of its row: with 4096 the band of half of such a part overflowed its list (256 rows of 128K
-// tokens 277 us against 138 before this kernel).
+// about 5% of a 128K row. 8192 for rows beyond 256K tokens, and where a workgroup holds more than 64K
+// tokens and an eighth of the row or more is kept: with 4096 the band of half of such a part overflowed
+// its list (256 rows of 128K tokens 277 us, with 8192 83). Smaller budgets have room enough and save the
+// larger sample's 2 to 4 us.
 struct SamplePlan {
   int S, runs;
   __device__ __forceinline__ int start(int i, int run) const {       // first token of sampled run i
     return (i * S + (int)((((uint32_t)i * 0x9e3779b1u) >> 16) & (uint32_t)(S - 1))) * run;
   }
 };
-__device__ __forceinline__ SamplePlan sample_plan(int nb, int run, int part) {
+__device__ __forceinline__ SamplePlan sample_plan(int nb, int run, bool wide) {
   SamplePlan p;
-  const int row_runs = (nb + run - 1) / run, target = nb > 262144 || part > 65536 ? 8192 : 4096;
+  const int row_runs = (nb + run - 1) / run, target = nb > 262144 || wide ? 8192 : 4096;
   p.S = 1;
   while (((row_runs + p.S - 1) / p.S) * run > target) p.S <<= 1;
   p.runs = row_runs / p.S;                             // (at least one: S is at most half the runs here)
@@ -255,7 +256,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   // ---- the sample's loads, then the first eight of the part's own
   constexpr int QT = 2;
   const int run = BF16 ? 64 : 32, rq = run >> 2;       // tokens and quads of a 128-byte run
-  const SamplePlan sp = sample_plan(max(nb, 1), run, A.smp_tokens);
+  const SamplePlan sp = sample_plan(max(nb, 1), run, A.smp_tokens > 65536 && 8 * (int64_t)c >= nb);
   const int nsq = sp.runs * rq;
   int pos[QT];
   f32x4 sacc[QT];

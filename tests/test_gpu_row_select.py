@@ -22,10 +22,12 @@ DEV = "cuda:0"
     (9, 64, 2, 4090, 300, False, "softmax"),         # many rows: 256 threads, four quads each
     (9, 64, 1, 8189, 512, False, "softmax"),         # ... eight quads, a sixteenth of the keys sampled
     (9, 64, 1, 6000, 5000, True, "softmax"),         # ... a budget whose band cannot fit: all keys counted
-    (4, 64, 1, 16384, 512, False, "softmax"),        # sixteen quads
+    (4, 64, 1, 16384, 512, False, "softmax"),        # 256 rows: 1024 threads, four quads each
+    (9, 64, 1, 16384, 512, False, "softmax"),        # more rows: 256 threads, sixteen quads
+    (9, 64, 1, 30001, 900, True, "softmax"),         # ... 512 threads
     (4, 64, 1, 12345, 512, False, "zeros"),          # the sample's band is one value that most tokens share
     (4, 64, 2, 16001, 800, True, "passages"),
-    (4, 64, 1, 32768, 1000, False, "stretch"),       # 512 threads
+    (4, 64, 1, 32768, 1000, False, "stretch"),       # 1024 threads, eight quads
     (4, 64, 3, 20002, 300, False, "levels"),
 ])
 def test_rows_in_registers(B, Hd, Tq, N, k, bf16, what):

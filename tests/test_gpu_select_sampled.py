@@ -56,6 +56,8 @@ def make(what, B, Hd, Tq, N, seed):
     (1, 16, 1, 262147, 9000, True, "softmax"),       # more than eight parts per row
     (3, 48, 1, 33000, 1500, False, "softmax"),       # one part per row: 144 rows
     (1, 128, 2, 16500, 800, True, "softmax"),        # two parts per row, a row for every second CU
+    (1, 130, 1, 131072, 65536, True, "softmax"),     # one part of more than 64K tokens: the larger sample
+    (1, 130, 1, 100004, 9000, False, "softmax"),     # ... and a small budget there
 ])
 def test_sampled_selection(B, Hd, Tq, N, k, bf16, what):
     scores = make(what, B, Hd, Tq, N, N + k)
