@@ -230,7 +230,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   __shared__ uint32_t red[2 * T / 64];
   __shared__ uint32_t found[6];
   __shared__ uint32_t ticket;                          // next group of the pass
-  __shared__ uint32_t ctr[8];                          // 0 band entries, 1 certain tokens, 2.. see below
+  __shared__ uint32_t ctr[9];                          // 0 band entries, 1 certain tokens, 2.. see below
   __shared__ u32x2 cand[SMP_CAND];                     // key; token of the part (own) or 1 << 31 | part
   const int row = blockIdx.y, part = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -249,7 +249,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   const AggRow R = agg_row(A, row);
   const int Tq = R.Tq;
   for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
-  if (tid < 8) ctr[tid] = 0u;
+  if (tid < 9) ctr[tid] = 0u;
   if (tid == 0) ticket = 2 * W;
   const float lse_of = R.logits && lane < Tq ? R.L[lane] : 0.f;        // row i's normaliser in lane i (Tq <= 64)
   __syncthreads();
@@ -571,6 +571,8 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
       }
     }
     __syncthreads();
+    // The other parts' keys follow the own ones under a counter of their own (ctr[8]): ctr[7] and the own entries,
+    // which one wave publishes while the others already poll, stay as they are from the barrier on.
     const uint32_t own = min(ctr[7], (uint32_t)SMP_CAND);
     if (Qv > 1) {
       if (tid < SMP_CAND)
@@ -587,7 +589,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
         }
         if (!(w & SMP_VALID)) complete = false;
         else if ((uint32_t)(tid % SMP_CAND) < ((uint32_t)(w >> 32) & 127u)) {
-          const uint32_t s = atomicAdd(&ctr[7], 1u);
+          const uint32_t s = own + atomicAdd(&ctr[8], 1u);
           if (s < (uint32_t)SMP_CAND) cand[s] = u32x2{(uint32_t)w, 0x80000000u | (uint32_t)q};
         }
       }

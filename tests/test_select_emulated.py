@@ -1,0 +1,89 @@
+"""The selection's kernels compiled for the CPU (tests/emulated: a workgroup is a thread, its work-items are
+fibers) under schedules that a GPU run does not take on demand: the order of the waves between two barriers is
+random, and one wave of one part can be held back until nothing else in its workgroup can go on. Index lists
+and counts against the CPU oracle, bit for bit. No GPU is involved."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2605_15508_amd import binding
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2605_15508_amd", "csrc")
+HERE = os.path.join(ROOT, "tests", "emulated")
+SOURCES = ["api.hip", "select.hip", "select_sampled.hip", "select_row.hip", "headmap.hip", "union.hip"]
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    clang = shutil.which("clang++") or "/opt/rocm/llvm/bin/clang++"
+    if not os.path.exists(clang):
+        pytest.skip("clang++ not available")          # (the sources use its vector types)
+    tmp = tmp_path_factory.mktemp("emulated")
+    flags = ["-std=c++17", "-O1", "-fPIC", "-w", "-ffp-contract=off", "-I", HERE, "-I", CSRC]
+    jobs = [(s, ["-x", "c++", "-include", os.path.join(HERE, "launch.h"), os.path.join(CSRC, s)]) for s in SOURCES]
+    jobs.append(("emulator.cpp", [os.path.join(HERE, "emulator.cpp")]))
+    procs = [(s, subprocess.Popen([clang, *flags, "-c", *a, "-o", str(tmp / (s + ".o"))], stderr=subprocess.PIPE, text=True))
+             for s, a in jobs]
+    for s, p in procs:
+        err = p.communicate()[1]
+        assert p.returncode == 0, f"{s}: {err[-3000:]}"
+    so = str(tmp / "libemulated.so")
+    subprocess.run([clang, "-shared", "-o", so, *[str(tmp / (s + ".o")) for s, _ in jobs], "-lpthread"], check=True)
+    lib = ctypes.CDLL(so)
+    lib.sts_select_workspace_bytes.restype = ctypes.c_size_t
+    lib.sts_set_knob.argtypes = [ctypes.c_int, ctypes.c_double]
+    return lib
+
+
+def select(lib, scores, hm, k, k_head=None, lens=None):
+    B, Hd, Tq, N = scores.shape
+    hm = np.asarray(hm, np.int32)
+    kh = None if k_head is None else np.asarray(k_head, np.int32)
+    lens = None if lens is None else np.asarray(lens, np.int32)
+    idx, cnt = np.full((B, len(hm), k), -7, np.int32), np.full((B, len(hm)), -7, np.int32)
+    at = lambda a: None if a is None else a.ctypes.data
+    p = binding.SelectParams(B=B, Hd=Hd, Tq=Tq, N=N, Hq=len(hm), k=k, scores=scores.data_ptr(), head_map=at(hm), seq_lens=at(lens),
+                             indices=at(idx), counts=at(cnt), k_head=at(kh), scores_bf16=int(scores.dtype == torch.bfloat16))
+    need = lib.sts_select_workspace_bytes(ctypes.byref(p))
+    ws = np.full(need + 256, 0xA5, np.uint8)
+    p.workspace, p.workspace_bytes = ws.ctypes.data + -ws.ctypes.data % 256, need
+    assert lib.sts_select(ctypes.byref(p), None) == 0
+    return idx, cnt
+
+
+def check(lib, scores, hm, k, **kw):
+    idx, cnt = select(lib, scores, hm, k, **kw)
+    lens = kw.get("lens")
+    o_idx, o_cnt, _ = oracle.select_indices(scores.float().numpy(), np.asarray(hm, np.int32), k, k_head=kw.get("k_head"),
+                                            seq_lens=None if lens is None else np.asarray(lens, np.int32))
+    np.testing.assert_array_equal(cnt, o_cnt)
+    np.testing.assert_array_equal(idx, o_idx)
+
+
+def softmax(B, Hd, Tq, N, seed):
+    g = torch.Generator().manual_seed(seed)
+    return torch.softmax(torch.randn(B, Hd, Tq, N, generator=g) * 2, dim=-1)
+
+
+# (seed, part and wave held back; -1: none)
+SCHEDULES = [(1, -1, -1), (2, -1, -1), (3, 0, 0), (4, 1, 0), (5, 1, 1), (6, 0, 15)]
+
+
+@pytest.mark.parametrize("schedule", SCHEDULES)
+@pytest.mark.parametrize("B,Hd,Tq,N,k", [
+    (1, 2, 2, 20000, 2000),          # three parts
+    (2, 1, 1, 33001, 3301),          # five
+    (1, 1, 1, 70000, 300),           # nine; a small budget
+])
+def test_parts_that_exchange_the_keys_around_the_threshold(lib, B, Hd, Tq, N, k, schedule):
+    """The keys that share the threshold's bin travel between the parts one by one: what a part publishes is its own
+    keys only, however late the wave that publishes them comes."""
+    lib.emu_schedule(*schedule)
+    check(lib, softmax(B, Hd, Tq, N, N + k), list(range(Hd)) + [0], k, lens=[N, N - 777][:B])
