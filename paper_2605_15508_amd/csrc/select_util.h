@@ -341,6 +341,7 @@ __device__ __forceinline__ void rank_by_passes(const SelectArgs &A, const AggRow
                                                int t0, int t1, uint32_t *h, uint32_t *tmp, int from = 0, int to = 0x7fffffff) {
   const int tid = threadIdx.x;
   const int nq = (nb + 3) >> 2;           // quads that hold ranked tokens
+  __syncthreads();                        // the caller's waves have read what they need of h and tmp
   uint32_t d0 = 0, pre01 = 0, krem = c, d2 = 0;
 #pragma unroll 1
   for (int level = 0; level < 3; ++level) {

@@ -8,6 +8,7 @@ import torch
 import oracle
 import paper_2605_15508_amd as sts
 from gpu_util import stored_agg
+from test_select_emulated import between_samples
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -91,3 +92,22 @@ def test_sampled_selection_without_the_other_parts():
     o_idx, o_cnt, _ = oracle.select_indices(scores.numpy(), np.arange(4, dtype=np.int32), 5000)
     np.testing.assert_array_equal(idx.cpu().numpy(), o_idx)
     np.testing.assert_array_equal(cnt.cpu().numpy(), o_cnt)
+
+
+@pytest.mark.parametrize("N,k,path", [(40002, 50, 0), (131072, 50, 0), (131072, 50, 5)])      # several parts; one part per row
+def test_equal_scores_above_all_that_the_sample_saw(N, k, path):
+    """More equal scores than are ranked one by one, far above the rest, where no sampled run lies."""
+    s = make("softmax", 1, 2, 1, N, N) * 1e-20
+    at, _ = between_samples(N)
+    s[..., at:at + 250] = 3.0
+    s[..., at + 250:at + 290] = torch.linspace(1.0, 2.0, 40)
+    sts.set_knob("select_path", path)
+    try:
+        for budget in (k, 270):
+            idx, cnt, _ = sts.sts_select(s.to(DEV), [0, 1, 1], budget)
+            torch.cuda.synchronize()
+            o_idx, o_cnt, _ = oracle.select_indices(s.numpy(), np.asarray([0, 1, 1], np.int32), budget)
+            np.testing.assert_array_equal(idx.cpu().numpy(), o_idx)
+            np.testing.assert_array_equal(cnt.cpu().numpy(), o_cnt)
+    finally:
+        sts.set_knob("select_path", None)

@@ -87,3 +87,34 @@ def test_parts_that_exchange_the_keys_around_the_threshold(lib, B, Hd, Tq, N, k,
     keys only, however late the wave that publishes them comes."""
     lib.emu_schedule(*schedule)
     check(lib, softmax(B, Hd, Tq, N, N + k), list(range(Hd)) + [0], k, lens=[N, N - 777][:B])
+
+
+def between_samples(N, run=32, at_least=300):
+    """A stretch of a row of N tokens that no sampled run touches (one run in S, at a scattered place of its
+    period, about 4096 keys, 8192 beyond 256K tokens)."""
+    row_runs, target, S = -(-N // run), 8192 if N > 262144 else 4096, 1
+    while -(-row_runs // S) * run > target:
+        S *= 2
+    starts = [(i * S + ((i * 0x9e3779b1 & 0xffffffff) >> 16 & (S - 1))) * run for i in range(row_runs // S)]
+    gaps = [(b - a - run, a + run) for a, b in zip(starts, starts[1:])]
+    size, at = max(gaps)
+    assert size >= at_least
+    return at, size
+
+
+@pytest.mark.parametrize("late_wave", [-1, 0, 5, 15])
+@pytest.mark.parametrize("N,k,path", [(40002, 50, 0), (131072, 50, 0), (131072, 50, 5)])      # several parts; one part per row
+def test_equal_scores_above_all_that_the_sample_saw(lib, N, k, path, late_wave):
+    """A few hundred equal scores far above the rest where no sampled run lies: the band has no upper edge, and the
+    threshold is found by narrowing its last, open bin down to the one key."""
+    s = softmax(1, 1, 1, N, N) * 1e-20
+    at, _ = between_samples(N)
+    s[..., at:at + 250] = 3.0
+    s[..., at + 250:at + 290] = torch.linspace(1.0, 2.0, 40)
+    lib.sts_set_knob(3, float(path))
+    lib.emu_schedule(2, 0 if path == 5 else at // 8192, late_wave)       # in the part that holds the stretch
+    try:
+        check(lib, s, [0, 0], k)
+        check(lib, s, [0], 270)
+    finally:
+        lib.sts_set_knob(3, float("nan"))
