@@ -326,7 +326,6 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
   // of their own (the list's memory is free)
   const int sT = ordered_of_key(Tk);
   const bool all_eq = r >= E;
-  const int sK = all_eq ? sT : sT + 1;                 // kept from here on (sT is no INT_MAX where ties are open but for NaNs)
   __syncthreads();
   static_assert(sizeof(store) >= sizeof(bits), "the equal tokens' bits");
 #pragma clang loop unroll(full)
@@ -338,13 +337,13 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
       w |= __builtin_amdgcn_update_dpp(0, w, 0x104, 0xf, 0xf, true);   // row_shl:4
       if ((lane & 7) == 0) to[(i * T + tid) >> 3] = (uint32_t)w;
     };
-    uint32_t kept = 0, eq = 0;
+    uint32_t above = 0, eq = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      kept |= v[i][e] >= sK ? 1u << e : 0u;
+      above |= v[i][e] > sT ? 1u << e : 0u;
       eq |= v[i][e] == sT ? 1u << e : 0u;
     }
-    word(kept, bits);
+    word(all_eq ? above | eq : above, bits);
     if (!all_eq) word(eq, store);
   }
   __syncthreads();

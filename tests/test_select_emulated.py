@@ -118,3 +118,23 @@ def test_equal_scores_above_all_that_the_sample_saw(lib, N, k, path, late_wave):
         check(lib, s, [0], 270)
     finally:
         lib.sts_set_knob(3, float("nan"))
+
+
+@pytest.mark.parametrize("B,Hd,N,k", [
+    (1, 1, 4000, 700), (1, 1, 8190, 700),            # 1024 threads per row: one quad each, two
+    (1, 256, 8193, 40), (3, 200, 4001, 40),          # many rows: 1024 threads and four quads, 256 threads
+    (1, 1, 20000, 700),                              # the sampled selection
+])
+def test_more_equal_nans_than_are_kept(lib, B, Hd, N, k):
+    """NaNs are ordered above +inf by their bits: the highest of them, 0x7fffffff, has no key above it."""
+    lib.emu_schedule(1, -1, -1)
+    bits = torch.rand(B, Hd, 1, N, generator=torch.Generator().manual_seed(N)).view(torch.int32)
+    bits[..., 3::2] = 0x7fffffff
+    bits[..., 1::10] = 0x7fc00000
+    s = bits.view(torch.float32)
+    for budget in (k, N - N // 3):                   # ... and all of them kept
+        idx, cnt = select(lib, s, [0, Hd - 1], budget)
+        for t, j in ((0, 0), (1, Hd - 1)):           # (no negative values: the keys are ordered like the bits)
+            want = np.sort(np.argsort(-bits[0, j, 0].numpy().astype(np.int64), kind="stable")[:budget])
+            np.testing.assert_array_equal(idx[0, t], want)
+        assert (cnt == budget).all()
