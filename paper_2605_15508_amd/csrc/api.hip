@@ -553,16 +553,15 @@ static sts_status enqueue_select(const sts_select_params *p, void *stream) {
   if (p->N > 0 && !p->scores) return STS_EINVAL;
   if (p->kind == STS_SCORES_LOGITS_LSE && !p->lse) return STS_EINVAL;
   size_t need = pl.total();
-  if (pl.band && need > 0 && (!p->workspace || p->workspace_bytes < need)) {
-    // one workgroup per row needs no scratch memory: such calls are served without any
+  const bool ws_usable = p->workspace && p->workspace_bytes >= need && reinterpret_cast<uintptr_t>(p->workspace) % 256 == 0;
+  if (pl.band && need > 0 && !ws_usable) {
+    // one workgroup per row needs no scratch memory: such calls are served without any, also where there is some that
+    // is too small or not aligned
     pl.smp_parts = 1;
     pl.smp_tokens = (p->N + 255) / 256 * 256;
     need = 0;
   }
-  if (need > 0) {
-    if (!p->workspace || p->workspace_bytes < need) return STS_EWORKSPACE;
-    if (reinterpret_cast<uintptr_t>(p->workspace) % 256 != 0) return STS_EWORKSPACE;
-  }
+  if (need > 0 && !ws_usable) return STS_EWORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
 
   SelectArgs a;

@@ -42,7 +42,7 @@ def lib(tmp_path_factory):
     return lib
 
 
-def select(lib, scores, hm, k, k_head=None, lens=None):
+def select(lib, scores, hm, k, k_head=None, lens=None, ws_offset=0, ws_bytes=None, status=0):
     B, Hd, Tq, N = scores.shape
     hm = np.asarray(hm, np.int32)
     kh = None if k_head is None else np.asarray(k_head, np.int32)
@@ -52,9 +52,10 @@ def select(lib, scores, hm, k, k_head=None, lens=None):
     p = binding.SelectParams(B=B, Hd=Hd, Tq=Tq, N=N, Hq=len(hm), k=k, scores=scores.data_ptr(), head_map=at(hm), seq_lens=at(lens),
                              indices=at(idx), counts=at(cnt), k_head=at(kh), scores_bf16=int(scores.dtype == torch.bfloat16))
     need = lib.sts_select_workspace_bytes(ctypes.byref(p))
-    ws = np.full(need + 256, 0xA5, np.uint8)
-    p.workspace, p.workspace_bytes = ws.ctypes.data + -ws.ctypes.data % 256, need
-    assert lib.sts_select(ctypes.byref(p), None) == 0
+    ws = np.full(need + 512, 0xA5, np.uint8)
+    p.workspace = ws.ctypes.data + -ws.ctypes.data % 256 + ws_offset if ws_bytes != 0 else None
+    p.workspace_bytes = need if ws_bytes is None else ws_bytes
+    assert lib.sts_select(ctypes.byref(p), None) == status
     return idx, cnt
 
 
@@ -138,3 +139,13 @@ def test_more_equal_nans_than_are_kept(lib, B, Hd, N, k):
             want = np.sort(np.argsort(-bits[0, j, 0].numpy().astype(np.int64), kind="stable")[:budget])
             np.testing.assert_array_equal(idx[0, t], want)
         assert (cnt == budget).all()
+
+
+@pytest.mark.parametrize("ws_offset,ws_bytes", [(0, None), (64, None), (0, 256), (0, 0)])
+def test_many_rows_are_served_without_a_usable_workspace(lib, ws_offset, ws_bytes):
+    """A row for every second compute unit: one workgroup per row needs no scratch memory, so one that is missing, too
+    small or not aligned is no reason to refuse the call; fewer rows need theirs."""
+    lib.emu_schedule(1, -1, -1)
+    check(lib, softmax(2, 64, 1, 8200, 5), [0, 63, 17], 500, lens=[8200, 8197], ws_offset=ws_offset, ws_bytes=ws_bytes)
+    few = softmax(1, 2, 1, 20000, 5)
+    select(lib, few, [0, 1], 500, ws_offset=ws_offset, ws_bytes=ws_bytes, status=0 if (ws_offset, ws_bytes) == (0, None) else -3)
