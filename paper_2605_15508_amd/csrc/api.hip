@@ -821,7 +821,7 @@ sts_status sts_head_map(const sts_headmap_params *p, void *stream) {
   if (e != hipSuccess) return STS_EHIP;
   if (have_rows) {
     e = run_kernel(STS_K_HEADMAP, s, [&] {
-      return launch_headmap_overlap(idx_d, idx_t, p->S, p->R, p->Hd, p->Ht, p->k, c, ov, s);
+      return launch_headmap_overlap(idx_d, idx_t, p->S, p->R, p->Hd, p->Ht, p->N, p->k, c, ov, s);
     });
     if (e != hipSuccess) return STS_EHIP;
   }

@@ -192,7 +192,7 @@ void sleep() { leave(SLEEPING); }
 // Workgroups start in the order of their ids, a few at a time, each on a thread of its own: the parts of a row
 // run side by side, and every workgroup's LDS (thread-local statics) is its own.
 void launch(void (*body)(void *), void *arg, dim3 grid, dim3 block) {
-  const unsigned total = grid.x * grid.y, at_once = grid.x > 8 ? grid.x : 8 / grid.x * grid.x;
+  const unsigned total = grid.x * grid.y * grid.z, at_once = grid.x > 8 ? grid.x : 8 / grid.x * grid.x;
   for (unsigned first = 0; first < total; first += at_once) {
     std::vector<std::thread> threads;
     for (unsigned b = first; b < total && b < first + at_once; ++b)
@@ -202,7 +202,7 @@ void launch(void (*body)(void *), void *arg, dim3 grid, dim3 block) {
         g.arg = arg;
         const size_t bytes = block.x * STACK;
         g.stacks = static_cast<char *>(mmap(nullptr, bytes, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0));
-        run_group(&g, block, dim3(b % grid.x, b / grid.x, 0));
+        run_group(&g, block, dim3(b % grid.x, b / grid.x % grid.y, b / grid.x / grid.y));
         munmap(g.stacks, bytes);
       });
     for (std::thread &t : threads) t.join();

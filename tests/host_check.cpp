@@ -139,7 +139,7 @@ hipError_t launch_union_rows(const UnionArgs &a, hipStream_t) {
   return hipSuccess;
 }
 hipError_t launch_headmap_clear(unsigned long long *, int, hipStream_t) { ++g_launches; return hipSuccess; }
-hipError_t launch_headmap_overlap(const int32_t *, const int32_t *, int, int, int, int, int, int, unsigned long long *, hipStream_t) { ++g_launches; return hipSuccess; }
+hipError_t launch_headmap_overlap(const int32_t *, const int32_t *, int, int, int, int, int, int, int, unsigned long long *, hipStream_t) { ++g_launches; return hipSuccess; }
 hipError_t launch_headmap_argmax(const unsigned long long *, int, int, int32_t *, hipStream_t) { ++g_launches; return hipSuccess; }
 
 // The sampling plan of the one-pass selection (shared by host and kernel): the sample fits the

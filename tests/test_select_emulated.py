@@ -38,6 +38,7 @@ def lib(tmp_path_factory):
     subprocess.run([clang, "-shared", "-o", so, *[str(tmp / (s + ".o")) for s, _ in jobs], "-lpthread"], check=True)
     lib = ctypes.CDLL(so)
     lib.sts_select_workspace_bytes.restype = ctypes.c_size_t
+    lib.sts_headmap_workspace_bytes.restype = ctypes.c_size_t
     lib.sts_set_knob.argtypes = [ctypes.c_int, ctypes.c_double]
     return lib
 
@@ -149,3 +150,26 @@ def test_many_rows_are_served_without_a_usable_workspace(lib, ws_offset, ws_byte
     check(lib, softmax(2, 64, 1, 8200, 5), [0, 63, 17], 500, lens=[8200, 8197], ws_offset=ws_offset, ws_bytes=ws_bytes)
     few = softmax(1, 2, 1, 20000, 5)
     select(lib, few, [0, 1], 500, ws_offset=ws_offset, ws_bytes=ws_bytes, status=0 if (ws_offset, ws_bytes) == (0, None) else -3)
+
+
+@pytest.mark.parametrize("S,Hd,Ht,R,N,k", [
+    (1, 4, 3, 1, 70001, 9000),       # few row pairs: 2048 tokens and several waves on a list
+    (2, 33, 17, 1, 40000, 333),      # two groups of draft heads, chunks of 32768
+    (1, 1, 1, 3, 9, 20),             # fewer tokens than asked for
+    (1, 2, 20, 1, 33000, 33000),     # every token
+])
+def test_overlap_counts_of_chunks(lib, S, Hd, Ht, R, N, k):
+    lib.emu_schedule(1, -1, -1)
+    rng = np.random.default_rng(N + k)
+    a_d = rng.random((S, Hd, R, N), dtype=np.float32)
+    a_t = rng.random((S, Ht, R, N), dtype=np.float32)
+    mp, ov = np.full(Ht, -7, np.int32), np.full((Ht, Hd), -7, np.int64)
+    p = binding.HeadmapParams(S=S, R=R, Hd=Hd, Ht=Ht, N=N, k=k, a_d=a_d.ctypes.data, a_t=a_t.ctypes.data, map=mp.ctypes.data,
+                              overlap=ov.ctypes.data)
+    need = lib.sts_headmap_workspace_bytes(ctypes.byref(p))
+    ws = np.full(need + 256, 0xA5, np.uint8)
+    p.workspace, p.workspace_bytes = ws.ctypes.data + -ws.ctypes.data % 256, need
+    assert lib.sts_head_map(ctypes.byref(p), None) == 0
+    o_mp, o_ov = oracle.head_mapping(a_d, a_t, k)
+    np.testing.assert_array_equal(ov, o_ov)
+    np.testing.assert_array_equal(mp, o_mp)
