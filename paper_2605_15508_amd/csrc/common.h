@@ -118,7 +118,7 @@ constexpr int SEL_FUSED_MAX_PARTS = 8;   // units of 32768 tokens up to which sm
                                          // (256K tokens; large calls and a test knob: up to 256)
 constexpr int SMP_MAX_TOKENS = 524288;  // sampled selection: most tokens per workgroup (a bit each in LDS)
 constexpr int SMP_PART_TOKENS = 131072; // ... and where the call has a workspace to exchange counts in
-constexpr int SMP_WORDS = 1096;         // 64-bit words a part exchanges with the other parts of its row
+constexpr int SMP_WORDS = 1352;         // 64-bit words a part exchanges with the other parts of its row
 constexpr int SEL_POOL_MAX = 16384;     // chunk-local winners per row that the pool kernel ranks out of LDS       // rows up to this many tokens always take it
 
 // What a strided sample of a row of nb ranked tokens with budget c looks like, and whether the band of
