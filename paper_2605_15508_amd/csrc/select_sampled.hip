@@ -27,8 +27,11 @@
 // whatever the others do; a row's parts have neighbouring workgroup ids and start together.
 //
 // The result never depends on the sample: if the counts show that the threshold lies outside [L, U),
-// or a band list overflowed, every part goes by plain passes likewise. A band that is a single key (one
-// value repeated: zeros, a constant row) needs no list: a second bitmap holds it.
+// or a band list overflowed, every part goes by plain passes likewise. Values that repeat do not make it
+// overflow: only two can hold more of the sample than the margins, the lowest key of the band and its
+// highest (any other lies between the two ranks), and where the sample says that one does (zeros, levels, a
+// saturated score), a bitmap holds its tokens and not the list. 16 rows of 1M tokens, a budget at the edge of the
+// zeros: 118 us, 3870 by plain passes; 64 rows of 128K: 74, 520; a constant row with a small budget 58, 435.
 //
 // What bounds it (64 rows of 128K tokens, 5 fp32 scores each, 4 parts per row, lengths between half and all
 // of it, 133 MB): the sample and the pass together 27 us (133 MB and 21 MB of samples, mostly from the
@@ -84,9 +87,11 @@ using RawQuad = typename ScoreLoad<f32x4, BF16>::raw;
 // the band that the sample gives: keys L .. L + last, whether there is an upper edge, and how far the sample's keys
 // reach (without an upper edge the band is the top of the row: its histogram is laid out for the sample's
 // keys, and what lies above them goes to the last bin)
+// heavyL, heavyU: the band's lowest or highest key is a single value that much of the row shares (zeros, a saturated score,
+// one of a few levels); its tokens go to a bitmap of their own and not to the list.
 struct Band {
   uint32_t L, last, span;
-  bool haveU;
+  bool haveU, heavyL, heavyU;
 };
 
 // Ranks the sampled quads (up to QT per thread, `acc` their aggregated scores). h: SEL_BINS words, zeroed.
@@ -99,73 +104,122 @@ __device__ __forceinline__ Band sample_band(const SamplePlan &sp, int run, int n
   auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
   uint32_t key[QT][4];
   bool ok[QT][4];
-  uint32_t kmin = 0xffffffffu, kmax = 0u;
 #pragma unroll
   for (int x = 0; x < QT; ++x)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       key[x][e] = key_of(acc[x][e]);
       ok[x][e] = tid + x * T < nsq && pos[x] + e < nb;
-      if (ok[x][e]) {
-        kmin = min(kmin, key[x][e]);
-        kmax = max(kmax, key[x][e]);
-      }
     }
+  // lowest and highest of the sampled keys in from .. to (there is one); a barrier has to come before red is written again
+  auto range_of = [&](uint32_t from, uint32_t to, uint32_t &lowest, uint32_t &highest) {
+    uint32_t mn = 0xffffffffu, mx = 0u;
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, off, 64));
-    kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off, 64));
-  }
-  if (lane == 0) {
-    red[2 * wave] = kmin;
-    red[2 * wave + 1] = kmax;
-  }
-  __syncthreads();
+    for (int x = 0; x < QT; ++x)
 #pragma unroll
-  for (int w = 0; w < T / 64; ++w) {
-    kmin = min(kmin, red[2 * w]);
-    kmax = max(kmax, red[2 * w + 1]);
-  }
-  // Bins of 2^shift keys over the window base .. base + range, which is the sample's own key range at first.
-  // Rows with values far from the rest (exact zeros, negative scores) make those bins coarse and the band
-  // with them far wider than the margin; the window is then narrowed to the band until it is not, at
-  // the last to a single key.
-  uint32_t base = uniform(kmin), range = uniform(kmax - kmin), over = 0;     // over: sampled keys above the window
-  uint32_t ns = 0, cs = 0;
-  const uint32_t highest = uniform(kmax);
-  Band b = {0u, 0xffffffffu, 0u, false};
-#pragma unroll 1
-  for (;;) {
-    const int shift = max(0, 32 - __clz((int)range) - 11);                   // range >> shift < 2048
+      for (int e = 0; e < 4; ++e)
+        if (ok[x][e] && key[x][e] - from <= to - from) {
+          mn = min(mn, key[x][e]);
+          mx = max(mx, key[x][e]);
+        }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      mn = min(mn, (uint32_t)__shfl_xor((int)mn, off, 64));
+      mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
+    }
+    if (lane == 0) {
+      red[2 * wave] = mn;
+      red[2 * wave + 1] = mx;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < T / 64; ++w) {
+      mn = min(mn, red[2 * w]);
+      mx = max(mx, red[2 * w + 1]);
+    }
+    lowest = uniform(mn);
+    highest = uniform(mx);
+  };
+  // counts the sampled keys base .. base + range into bins of 2^shift keys (h is zeroed before if `again`); `above`
+  // keys of the sample, `over` of them above the window, lie in higher bins than the thread's own two
+  uint32_t h0, h1, above;
+  auto count = [&](bool again, uint32_t base, uint32_t range, int shift, uint32_t over) {
+    if (again) {
+      for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
+      __syncthreads();
+    }
 #pragma unroll
     for (int x = 0; x < QT; ++x)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         if (ok[x][e] && key[x][e] - base <= range) atomicAdd(&h[(key[x][e] - base) >> shift], 1u);
     __syncthreads();
-    // thread t owns bins 2t and 2t + 1; `above` keys of the sample lie in higher bins than its own
-    const uint32_t h0 = h[2 * tid], h1 = h[2 * tid + 1];
+    // thread t owns bins 2t and 2t + 1
+    h0 = h[2 * tid];
+    h1 = h[2 * tid + 1];
     uint32_t in_window;
     const uint32_t excl = block_excl_scan<T>(h0 + h1, tmp, in_window);
-    const uint32_t above = over + in_window - excl - (h0 + h1);
-    in_window = uniform(in_window);
-    // the bin of the rank-th largest, and how many keys lie from that bin (with) or above it (without)
-    auto locate = [&](uint32_t rank, int slot, bool with) {
-      if (above < rank && above + h1 >= rank) {
-        found[2 * slot] = 2 * tid + 1;
-        found[2 * slot + 1] = above + (with ? h1 : 0u);
-      } else if (above + h1 < rank && above + h1 + h0 >= rank) {
-        found[2 * slot] = 2 * tid;
-        found[2 * slot + 1] = above + h1 + (with ? h0 : 0u);
-      }
-    };
+    above = over + in_window - excl - (h0 + h1);
+    return uniform(in_window);
+  };
+  // the bin of the rank-th largest: found[3 * slot ..] = the bin, keys above it, keys in it
+  auto locate = [&](uint32_t rank, int slot) {
+    if (above < rank && above + h1 >= rank) {
+      found[3 * slot] = 2 * tid + 1;
+      found[3 * slot + 1] = above;
+      found[3 * slot + 2] = h1;
+    } else if (above + h1 < rank && above + h1 + h0 >= rank) {
+      found[3 * slot] = 2 * tid;
+      found[3 * slot + 1] = above + h1;
+      found[3 * slot + 2] = h0;
+    }
+  };
+  // An edge of the band: the rank-th largest sampled key, known to lie among the keys lo .. hi, of which the sample
+  // holds cnt, with `above` sampled keys above hi. Values far from the rest and values that repeat leave many
+  // tokens there: as long as that is so, the keys are counted again, within the range that they really have.
+  struct Edge {
+    uint32_t rank, lo, hi, cnt, above;
+    bool heavy;
+  };
+  auto refine = [&](Edge &g, uint32_t most) {
+#pragma unroll 1
+    while (g.cnt > most) {
+      __syncthreads();
+      range_of(g.lo, g.hi, g.lo, g.hi);
+      g.heavy = g.lo == g.hi;
+      if (g.heavy) return;
+      const int shift = max(0, 32 - __clz((int)(g.hi - g.lo)) - 11);
+      (void)count(true, g.lo, g.hi - g.lo, shift, g.above);
+      locate(g.rank, 0);
+      __syncthreads();
+      g.lo += uniform(found[0]) << shift;
+      g.hi = g.lo + min(g.hi - g.lo, (1u << shift) - 1u);
+      g.above = uniform(found[1]);
+      g.cnt = uniform(found[2]);
+    }
+  };
+  // Bins of 2^shift keys over the window base .. base + range, which is the sample's own key range at first.
+  // Rows with values far from the rest (exact zeros, negative scores) make those bins coarse and the band
+  // with them far wider than the margin; the window is then narrowed to the band until it is not, at
+  // the last to a single key.
+  uint32_t base, highest;
+  range_of(0u, 0xffffffffu, base, highest);
+  uint32_t range = highest - base, over = 0;           // over: sampled keys above the window
+  uint32_t ns = 0, cs = 0, margin = 0;
+  bool haveL = false, haveU = false;                   // (an edge outside the sample, or where the last key is all there is)
+  Edge edge[2] = {{0u, 0u, 0u, 0u, 0u, false}, {0u, 0xffffffffu, 0xffffffffu, 0u, 0u, false}};
+  Edge &lower = edge[0], &upper = edge[1];
+#pragma unroll 1
+  for (bool again = false;; again = true) {
+    const int shift = max(0, 32 - __clz((int)range) - 11);                   // range >> shift < 2048
+    const uint32_t in_window = count(again, base, range, shift, over);
     if (ns == 0u) {                                    // the first window is the whole sample
       ns = in_window;
       cs = max(1u, min(ns, (uint32_t)((uint64_t)c * ns / (uint32_t)nb)));    // expected rank of the threshold
     }
-    uint32_t margin = 0;                               // (S == 1: the sample is the row)
+    margin = 0;                                        // (S == 1: the sample is the row)
     if (sp.S > 1) {
-      locate(cs, 0, false);
+      locate(cs, 0);
       __syncthreads();
       const uint32_t centre = base + (found[0] << shift);
       // Keys from the centre on, per run; their spread over the runs is what the rank estimate's is made of
@@ -186,35 +240,45 @@ __device__ __forceinline__ Band sample_band(const SamplePlan &sp, int run, int n
       margin = uniform((uint32_t)(5.f * sqrtf(fmaxf(0.5f * (float)sum_sq / pairs, (float)cs))) + 4u);
     }
     // an edge that lies outside the window stays what it was
-    const bool haveL = cs + margin <= over + in_window, haveU = cs > margin + over;
-    if (haveL) locate(cs + margin, 1, true);
-    if (haveU) locate(cs - margin, 2, false);
+    const bool inL = cs + margin <= over + in_window, inU = cs > margin + over;
+    if (inL) locate(cs + margin, 1);
+    if (inU) locate(cs - margin, 2);
     __syncthreads();
-    const uint32_t lo_bin = uniform(haveL ? found[2] : 0u), hi_bin = uniform(haveU ? found[4] : range >> shift);
-    const uint32_t upto = uniform(haveL ? found[3] : over + in_window), beyond = uniform(haveU ? found[5] : over);
-    uint32_t top = base + range;                       // last key of the next window
-    const uint32_t last_key = b.L + b.last;
-    if (haveL) b.L = base + (lo_bin << shift);
-    if (haveU) {
-      const uint64_t u = (uint64_t)base + ((uint64_t)(hi_bin + 1u) << shift);
-      if (u <= 0xffffffffull) {
-        b.haveU = true;
-        top = min(top, (uint32_t)u - 1u);
-        b.last = (uint32_t)u - 1u - b.L;
-      } else {
-        b.last = 0xffffffffu - b.L;
-      }
-    } else {
-      b.last = last_key - b.L;
+    const uint32_t lo_bin = uniform(inL ? found[3] : 0u), hi_bin = uniform(inU ? found[6] : range >> shift);
+    if (inL) {
+      haveL = true;
+      lower = {cs + margin, base + (lo_bin << shift), 0u, uniform(found[5]), uniform(found[4]), false};
+      lower.hi = lower.lo + min(base + range - lower.lo, (1u << shift) - 1u);
     }
-    b.span = b.haveU ? b.last : max(highest, b.L) - b.L;
-    if (shift == 0 || hi_bin - lo_bin >= 64u || upto - beyond <= 4u * margin + 64u) return b;
-    base = haveL ? b.L : base;
+    if (inU) {
+      haveU = true;
+      upper = {cs - margin, base + (hi_bin << shift), 0u, uniform(found[8]), uniform(found[7]), false};
+      upper.hi = upper.lo + min(base + range - upper.lo, (1u << shift) - 1u);
+    }
+    const uint32_t upto = inL ? lower.above + lower.cnt : over + in_window, beyond = inU ? upper.above : over;
+    if (shift == 0 || hi_bin - lo_bin >= 64u || upto - beyond <= 4u * margin + 64u) break;
+    const uint32_t top = inU ? upper.hi : base + range;
+    base = inL ? lower.lo : base;
     range = top - base;
     over = beyond;
-    for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
-    __syncthreads();
+    if (lo_bin == hi_bin) {
+      range_of(base, top, base, range);
+      range -= base;
+      if (range == 0u) break;                          // one value: both edges lie in it
+    }
   }
+  // (S == 1: the sample is the row, and the list holds all of that)
+  if (sp.S > 1 && (haveL ? lower.above + lower.cnt : ns) - (haveU ? upper.above : 0u) > 4u * margin + 64u) {
+    if (haveL) refine(lower, margin + 16u);
+    if (haveU) refine(upper, margin + 16u);
+  }
+  Band b = {haveL ? lower.lo : 0u, 0u, 0u, false, false, false};
+  b.haveU = haveU && upper.hi != 0xffffffffu;
+  b.last = (b.haveU ? upper.hi : 0xffffffffu) - b.L;
+  b.heavyL = lower.heavy;
+  b.heavyU = upper.heavy && b.haveU && b.last != 0u;
+  b.span = b.haveU ? b.last : max(highest, b.L) - b.L;
+  return b;
 }
 
 // TOK: tokens a workgroup can hold bits of; CAP: entries of its band list.
@@ -223,18 +287,22 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   constexpr int T = SMP_THREADS, W = SMP_WAVES;
   typedef ScoreLoad<f32x4, BF16> SL;
   __shared__ uint32_t bits[TOK / 32];                  // kept tokens of the part
-  // the band list (key, token of the part); a band of one key: the bits of its tokens; at last the staged tokens
+  // the band list (key, token of the part) and behind it, where there are heavy keys, the bits of their tokens (memory
+  // for both heavy keys, or in the largest form for one of them); at last the staged tokens
   __shared__ u32x2 list[CAP];
-  static_assert(2 * CAP >= TOK / 32, "the bits of a one-key band share the list's memory");
+  constexpr int MAP = TOK / 64;                        // list entries that a bitmap takes the place of
+  constexpr bool TWO_MAPS = 2 * MAP < CAP;
+  static_assert(MAP <= CAP, "the bits of a heavy key share the list's memory");
   uint32_t *const store = reinterpret_cast<uint32_t *>(list);
+  uint32_t *const mapL = store + 2 * (CAP - MAP), *const mapU = TWO_MAPS ? mapL - 2 * MAP : mapL;
   __shared__ uint32_t h[SEL_BINS];
   __shared__ uint32_t hb[SMP_HIST];                    // the earlier parts' share of an exchanged histogram
   __shared__ uint32_t tmp[T / 64 + 2];
   __shared__ uint32_t red[2 * T / 64];
-  __shared__ uint32_t found[6];
+  __shared__ uint32_t found[9];
   __shared__ uint32_t ticket;                          // next group of the pass
-  __shared__ uint32_t ctr[9];                          // 0 band entries, 1 certain tokens, 2.. see below
-  __shared__ u32x2 cand[SMP_CAND];                     // key; token of the part (own) or 1 << 31 | part
+  __shared__ uint32_t ctr[11];                         // 0 list entries, 1 certain tokens, 9, 10 tokens of the heavy keys, 2.. see below
+  __shared__ u32x2 cand[SMP_CAND];                     // key; 0 (own) or 1 << 31 | part
   const int row = blockIdx.y, part = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int bt = row / A.Hd, j = row % A.Hd;
@@ -252,7 +320,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   const AggRow R = agg_row(A, row);
   const int Tq = R.Tq;
   for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
-  if (tid < 9) ctr[tid] = 0u;
+  if (tid < 11) ctr[tid] = 0u;
   if (tid == 0) ticket = 2 * W;
   const float lse_of = R.logits && lane < Tq ? R.L[lane] : 0.f;        // row i's normaliser in lane i (Tq <= 64)
   __syncthreads();
@@ -309,15 +377,17 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   }
 #pragma unroll
   for (int u = 0; u < 8; ++u) issue(raw[u], grp[u]);
-  Band band = {0u, 0u, 0u, false};
+  Band band = {0u, 0u, 0u, false, false, false};
   if (m > 0) band = sample_band<QT>(sp, run, nb, c, pos, sacc, h, tmp, red, found);   // (uniform; its barriers publish ctr)
   else __syncthreads();
-  const bool single = band.haveU && band.last == 0u;
+  const bool heavyL = band.heavyL, heavyU = band.heavyU && (TWO_MAPS || !heavyL), heavy = heavyL || heavyU;
+  const uint32_t cap = (uint32_t)(CAP - (heavyL ? MAP : 0) - (heavyU ? MAP : 0));
 
   // ---- the pass
   // INT_MIN marks what is no token of the row: it stays below every edge
   const int sL = max(ordered_of_key(band.L), (int)0x80000001);
   const int sU = band.haveU ? ordered_of_key(band.L + band.last + 1u) : 0x7fffffff;
+  const int sLast = ordered_of_key(band.L + band.last);
   const bool plain = sL > 0;       // scores below the band, negative ones included, compare right as bit patterns
   uint32_t certain = 0;            // wave-uniform
   auto classify = [&](int g, f32x4 acc) {
@@ -361,8 +431,6 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
       in_band[e] = !sure && v[e] >= sL;
       nib |= sure ? 1u << e : 0u;
       certain += (uint32_t)__builtin_popcountll(ballot64(sure));
-      bd[e] = ballot64(in_band[e]);
-      held += (uint32_t)__builtin_popcountll(bd[e]);
     }
     // the nibbles of eight neighbouring quads make one bitmap word, stored whole by the first lane of
     // the eight: three shifts by 1, 2, 4 lanes inside a row of 16 lanes, OR-ed
@@ -374,17 +442,27 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
       if ((lane & 7) == 0) to[g * 8 + (lane >> 3)] = (uint32_t)w;
     };
     word(nib, bits);
+    if (heavy) {
+      uint32_t nibL = 0, nibU = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool l = heavyL && v[e] == sL, u = heavyU && v[e] == sLast;
+        nibL |= l ? 1u << e : 0u;
+        nibU |= u ? 1u << e : 0u;
+        in_band[e] = in_band[e] && !l && !u;
+      }
+      if (heavyL) word(nibL, mapL);
+      if (heavyU) word(nibU, mapU);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      bd[e] = ballot64(in_band[e]);
+      held += (uint32_t)__builtin_popcountll(bd[e]);
+    }
     uint32_t at = 0;
     if (lane == 0) at = atomicAdd(&ctr[0], held);
-    if (single) {
-      uint32_t b = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) b |= in_band[e] ? 1u << e : 0u;
-      word(b, store);
-      return;
-    }
     at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-    if (at + held > (uint32_t)CAP) return;             // does not fit: the count says so, the row goes by plain passes
+    if (at + held > cap) return;                       // does not fit: the count says so, the row goes by plain passes
     const uint32_t tok = (uint32_t)(g * SMP_GROUP + lane4);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -424,8 +502,25 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   if (m == 0) return;
   if (lane == 0) atomicAdd(&ctr[1], certain);
   __syncthreads();
-  const uint32_t own_M = ctr[0], own_G = ctr[1];
-  const uint32_t listed = single ? 0u : min(own_M, (uint32_t)CAP);
+  const int words = (m + 31) >> 5, per = (words + T - 1) / T;
+  const int w0 = min(tid * per, words), w1 = min(w0 + per, words);     // a thread's run of the bitmaps' words
+  if (heavy) {
+    uint32_t ofL = 0, ofU = 0;
+    for (int w = w0; w < w1; ++w) {
+      if (heavyL) ofL += (uint32_t)__builtin_popcount(mapL[w]);
+      if (heavyU) ofU += (uint32_t)__builtin_popcount(mapU[w]);
+    }
+    ofL = wave_sum(ofL);
+    ofU = wave_sum(ofU);
+    if (lane == 0) {
+      atomicAdd(&ctr[9], ofL);
+      atomicAdd(&ctr[10], ofU);
+    }
+    __syncthreads();
+  }
+  const uint32_t own_G = ctr[1], own_L = ctr[9], own_U = ctr[10], own_M = ctr[0] + own_L + own_U;
+  const bool fits = ctr[0] <= cap;
+  const uint32_t listed = min(ctr[0], cap);
 
   // ---- the threshold
   const int Qv = (nb + P - 1) / P;                     // parts that hold ranked tokens
@@ -438,16 +533,14 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   for (int round = 0;; ++round) {
     for (int i = tid; i < SMP_HIST; i += T) h[i] = 0u;
     __syncthreads();
-    if (single) {
-      if (tid == 0) h[0] = own_M;
-    } else {
-      for (uint32_t i = tid; i < listed; i += T) {
-        const uint32_t k = list[i][0];
-        if (k - lo <= last) atomicAdd(&h[min((k - lo) >> shift, (uint32_t)SMP_HIST - 1u)], 1u);
-      }
-    }
+    auto in_question = [&](uint32_t k, uint32_t n) {
+      if (k - lo <= last) atomicAdd(&h[min((k - lo) >> shift, (uint32_t)SMP_HIST - 1u)], n);
+    };
+    for (uint32_t i = tid; i < listed; i += T) in_question(list[i][0], 1u);
+    if (tid == 0 && heavyL) in_question(band.L, own_L);
+    if (tid == 0 && heavyU) in_question(band.L + band.last, own_U);
     __syncthreads();
-    uint32_t s_M = own_M, over = own_M > (uint32_t)CAP && !single ? 1u : 0u;
+    uint32_t s_M = own_M, over = fits ? 0u : 1u;
     if (Qv > 1) {
       // threads 0..255: two bins each; in the first round thread 256 sends the part's counts
       const bool sends = tid < SMP_HIST / 2 || (tid == SMP_HIST / 2 && round == 0);
@@ -562,13 +655,15 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   uint32_t Tk = lo, r = krem, E = in_bin, pre_eq = pre_in;
   if (last != 0u) {
     // few keys share the threshold's bin: they are exchanged one by one and ranked against each other
-    for (uint32_t i = tid; i < listed; i += T) {
-      const u32x2 x = list[i];
-      if (x[0] - lo <= last) {
+    auto add = [&](uint32_t k) {
+      if (k - lo <= last) {
         const uint32_t s = atomicAdd(&ctr[7], 1u);
-        if (s < (uint32_t)SMP_CAND) cand[s] = x;
+        if (s < (uint32_t)SMP_CAND) cand[s] = u32x2{k, 0u};
       }
-    }
+    };
+    for (uint32_t i = tid; i < listed; i += T) add(list[i][0]);
+    if (heavyL && (uint32_t)tid < min(own_L, (uint32_t)SMP_CAND)) add(band.L);
+    if (heavyU && (uint32_t)tid < min(own_U, (uint32_t)SMP_CAND)) add(band.L + band.last);
     __syncthreads();
     // The other parts' keys follow the own ones under a counter of their own (ctr[8]): ctr[7] and the own entries,
     // which one wave publishes while the others already poll, stay as they are from the barrier on.
@@ -621,59 +716,59 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   // ---- the part's kept tokens: bits of the band's. Of the tokens equal to T the first `quota` of this part
   // are kept: all of them, unless the row has more than r.
   const uint32_t quota = r > pre_eq ? r - pre_eq : 0u;
-  uint32_t own_eq = 0;
-  if (single) {
-    own_eq = own_M;
-  } else {
-    uint32_t n = 0;
-    for (uint32_t i = tid; i < listed; i += T) {
-      const u32x2 x = list[i];
-      if (x[0] > Tk || (x[0] == Tk && r >= E)) atomicOr(&bits[x[1] >> 5], 1u << (x[1] & 31u));
-      n += x[0] == Tk ? 1u : 0u;
-    }
-    if (r < E) own_eq = block_sum1<T>(n, red);         // (uniform)
+  const bool all_eq = r >= E, of_map = (heavyL && Tk == band.L) || (heavyU && Tk == band.L + band.last);
+  uint32_t n_eq = 0;
+  for (uint32_t i = tid; i < listed; i += T) {
+    const u32x2 x = list[i];
+    if (x[0] > Tk || (x[0] == Tk && all_eq)) atomicOr(&bits[x[1] >> 5], 1u << (x[1] & 31u));
+    n_eq += x[0] == Tk ? 1u : 0u;
   }
-  if (single || (r < E && quota > 0u)) {
-    if (single) {
-      // the equal tokens are a bitmap: the first `quota` of its bits, by words in order
-      const int words = ((m + SMP_GROUP - 1) / SMP_GROUP) * 8, per = (words + T - 1) / T;
-      const int w0 = min(tid * per, words), w1 = min(w0 + per, words);
-      uint32_t n = 0, total;
-      for (int w = w0; w < w1; ++w) n += (uint32_t)__builtin_popcount(store[w]);
-      uint32_t before = block_excl_scan<T>(n, tmp, total);
-      for (int w = w0; w < w1; ++w)
-        for (uint32_t rest = store[w]; rest && before < quota; rest &= rest - 1u, ++before) bits[w] |= rest & (0u - rest);
-    } else {
-      // the lowest tokens of the list's equal ones: their reversed ids are ranked like keys, 11 + 9 bits
-      static_assert(TOK <= 1 << 20, "token ids of a part");
-      constexpr uint32_t REV = (1u << 20) - 1u;
-      uint32_t cut = 0;
-      if (own_eq > quota) {
-        uint32_t da, ra, db, rb;
-        for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
-        __syncthreads();
-        for (uint32_t i = tid; i < listed; i += T)
-          if (list[i][0] == Tk) atomicAdd(&h[(REV - list[i][1]) >> 9], 1u);
-        __syncthreads();
-        find_digit<SEL_BINS, T>(h, quota, tmp, da, ra);
-        for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
-        __syncthreads();
-        for (uint32_t i = tid; i < listed; i += T)
-          if (list[i][0] == Tk && ((REV - list[i][1]) >> 9) == da) atomicAdd(&h[(REV - list[i][1]) & 511u], 1u);
-        __syncthreads();
-        find_digit<SEL_BINS, T>(h, ra, tmp, db, rb);
-        cut = (da << 9) | db;
-      }
+  if (!all_eq && !of_map && quota > 0u) {
+    // the lowest tokens of the list's equal ones: their reversed ids are ranked like keys, 11 + 9 bits
+    static_assert(TOK <= 1 << 20, "token ids of a part");
+    constexpr uint32_t REV = (1u << 20) - 1u;
+    const uint32_t own_eq = block_sum1<T>(n_eq, red);
+    uint32_t cut = 0;
+    if (own_eq > quota) {
+      uint32_t da, ra, db, rb;
+      for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
+      __syncthreads();
       for (uint32_t i = tid; i < listed; i += T)
-        if (list[i][0] == Tk && REV - list[i][1] >= cut) atomicOr(&bits[list[i][1] >> 5], 1u << (list[i][1] & 31u));
+        if (list[i][0] == Tk) atomicAdd(&h[(REV - list[i][1]) >> 9], 1u);
+      __syncthreads();
+      find_digit<SEL_BINS, T>(h, quota, tmp, da, ra);
+      for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
+      __syncthreads();
+      for (uint32_t i = tid; i < listed; i += T)
+        if (list[i][0] == Tk && ((REV - list[i][1]) >> 9) == da) atomicAdd(&h[(REV - list[i][1]) & 511u], 1u);
+      __syncthreads();
+      find_digit<SEL_BINS, T>(h, ra, tmp, db, rb);
+      cut = (da << 9) | db;
     }
+    for (uint32_t i = tid; i < listed; i += T)
+      if (list[i][0] == Tk && REV - list[i][1] >= cut) atomicOr(&bits[list[i][1] >> 5], 1u << (list[i][1] & 31u));
   }
   __syncthreads();
+  if (heavy) {
+    auto take = [&](uint32_t k, uint32_t n, const uint32_t *map) {
+      if (k < Tk || (k == Tk && quota == 0u)) return;
+      if (k > Tk || all_eq || n <= quota) {
+        for (int w = w0; w < w1; ++w) bits[w] |= map[w];
+      } else {                                         // the first `quota` of the bits, by words in order
+        uint32_t n_own = 0, total;
+        for (int w = w0; w < w1; ++w) n_own += (uint32_t)__builtin_popcount(map[w]);
+        uint32_t before = block_excl_scan<T>(n_own, tmp, total);
+        for (int w = w0; w < w1; ++w)
+          for (uint32_t rest = map[w]; rest && before < quota; rest &= rest - 1u, ++before) bits[w] |= rest & (0u - rest);
+      }
+    };
+    if (heavyL) take(band.L, own_L, mapL);
+    if (heavyU) take(band.L + band.last, own_U, mapU);
+    __syncthreads();
+  }
 
   // ---- the list: set bits in token order. A thread owns a run of words, one block scan gives its first place; the
   // tokens are staged in LDS (the band list is done with) and copied out coalesced, once per target head.
-  const int words = (m + 31) >> 5, per = (words + T - 1) / T;
-  const int w0 = min(tid * per, words), w1 = min(w0 + per, words);
   uint32_t mine = 0, total;
   for (int w = w0; w < w1; ++w) mine += (uint32_t)__builtin_popcount(bits[w]);
   const uint32_t first = block_excl_scan<T>(mine, tmp, total);

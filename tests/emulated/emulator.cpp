@@ -13,11 +13,13 @@
 namespace emu {
 
 thread_local Lane *lane = nullptr;
+thread_local uint64_t loaded = 0;
 
 namespace {
 constexpr size_t STACK = 64 * 1024;
 int g_slow_wave = -1, g_slow_part = -1, g_cus = 256;
 unsigned g_seed = 1;
+uint64_t g_loaded = 0;
 
 enum State { READY, IN_WAVE_OP, AT_BARRIER, SLEEPING, ENDED };
 struct Fiber : Lane {
@@ -204,6 +206,7 @@ void launch(void (*body)(void *), void *arg, dim3 grid, dim3 block) {
         g.stacks = static_cast<char *>(mmap(nullptr, bytes, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0));
         run_group(&g, block, dim3(b % grid.x, b / grid.x % grid.y, b / grid.x / grid.y));
         munmap(g.stacks, bytes);
+        __atomic_fetch_add(&g_loaded, loaded, __ATOMIC_SEQ_CST);
       });
     for (std::thread &t : threads) t.join();
   }
@@ -219,6 +222,9 @@ extern "C" void emu_schedule(int seed, int slow_part, int slow_wave) {
   emu::g_slow_part = slow_part;
   emu::g_slow_wave = slow_wave;
 }
+
+// bytes of scores loaded since the last call
+extern "C" uint64_t emu_loaded() { return __atomic_exchange_n(&emu::g_loaded, 0, __ATOMIC_SEQ_CST); }
 
 sts_status sts_static_scratch(void **) { return STS_EUNSUPPORTED; }
 hipError_t launch_attn_split(const AttnArgs &, int, int, bool, hipStream_t) { return hipErrorInvalidValue; }

@@ -39,6 +39,7 @@ def lib(tmp_path_factory):
     lib = ctypes.CDLL(so)
     lib.sts_select_workspace_bytes.restype = ctypes.c_size_t
     lib.sts_headmap_workspace_bytes.restype = ctypes.c_size_t
+    lib.emu_loaded.restype = ctypes.c_uint64
     lib.sts_set_knob.argtypes = [ctypes.c_int, ctypes.c_double]
     return lib
 
@@ -173,3 +174,48 @@ def test_overlap_counts_of_chunks(lib, S, Hd, Ht, R, N, k):
     o_mp, o_ov = oracle.head_mapping(a_d, a_t, k)
     np.testing.assert_array_equal(ov, o_ov)
     np.testing.assert_array_equal(mp, o_mp)
+
+
+def repeated(what, N, k, seed):
+    """Rows in which one or two values, next to the threshold, are shared by much of the row."""
+    g = torch.Generator().manual_seed(seed)
+    s = softmax(1, 1, 1, N, seed)
+    few = torch.rand(1, 1, 1, N, generator=g) < k / N
+    if what == "zeros":                               # about as many scores as are kept, zeros otherwise
+        return s * few
+    if what == "window":                              # ... in one stretch
+        s[..., :N - k] = 0
+        return s
+    if what == "two":                                 # two values, the threshold at the edge between them
+        return torch.where(few, 0.5, 0.25)
+    if what == "between":                             # ... and a few hundred values between the two
+        return torch.where(torch.rand(1, 1, 1, N, generator=g) < 0.01, 0.3 + s, torch.where(few, 0.5, 0.25))
+    if what == "top":                                 # saturated scores, more than are kept of them or not quite
+        s[torch.rand(1, 1, 1, N, generator=g) < k / N] = float("inf")
+        return s
+    if what == "negative":                            # zeros of both signs above negative scores
+        s = torch.where(few, -0.0, 0.0)
+        return torch.where(torch.rand(1, 1, 1, N, generator=g) < 0.5, s, -torch.rand(1, 1, 1, N, generator=g))
+    return torch.full((1, 1, 1, N), 0.25)
+
+
+@pytest.mark.parametrize("what,k", [("zeros", 13000), ("window", 13000), ("two", 13000), ("between", 13000), ("top", 4000), ("top", 40000),
+                                    ("negative", 66000), ("constant", 100), ("constant", 13000)])
+def test_values_that_repeat_next_to_the_threshold(lib, what, k):
+    """One part per row: the scores are read once (with the sample and what the waves ask for past the end 1.36 times),
+    whatever values repeat and however often. Several parts: the same lists."""
+    N = 131072
+    lib.emu_schedule(1, -1, -1)
+    for bf16 in (False, True):
+        s = repeated(what, N, k, k)
+        s = s.to(torch.bfloat16) if bf16 else s
+        lib.sts_set_knob(3, 5.0)
+        lib.emu_loaded()
+        try:
+            for budget in (k, k - k // 50, k + k // 50):
+                check(lib, s, [0], budget, lens=[N - 13])
+                assert lib.emu_loaded() <= 1.5 * N * s.element_size()
+        finally:
+            lib.sts_set_knob(3, float("nan"))
+        check(lib, s, [0, 0], k)
+        check(lib, s[..., :40001].contiguous(), [0], k // 4, lens=[39999])
