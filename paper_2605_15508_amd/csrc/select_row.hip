@@ -78,14 +78,25 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
     }
   };
   if constexpr (T == 1024) {
-    // few quads: their score rows are in flight together
+    // Few quads: their score rows are in flight together. Up to four by code for each number of rows (256 rows of 16384
+    // tokens 16.9 us, 18.7 with branches between the rows), eight with branches: that kernel was 305 KB (256 rows of 30000
+    // tokens, 5 scores: 39.8 us, 48.7 with the caches flushed; now 40.5 and 44.6).
+    auto quads = [&](auto bf16) {
 #pragma clang loop unroll(full)
-    for (int i = 0; i < IT; ++i) {
-      const int n[1] = {4 * (i * T + tid)};
-      f32x4 acc[1];
-      agg_quads_any<1, 8>(R, n, 4 * (i + 1) * T <= R.N, acc);
-      take(i, acc[0]);
-    }
+      for (int i = 0; i < IT; ++i) {
+        const int n = 4 * (i * T + tid);
+        const bool inside = 4 * (i + 1) * T <= R.N;
+        if constexpr (IT == 8) {
+          take(i, agg_quad_any<decltype(bf16)::value>(R, n, inside));
+        } else {
+          const int at = min(n, R.N - 4);
+          const f32x4 y = agg_quad(R, at);
+          take(i, inside ? y : shifted_quad(y, n - at));
+        }
+      }
+    };
+    if (IT < 8 || R.bf16) quads(std::true_type{});     // (the type matters for the form with branches only)
+    else quads(std::false_type{});
   } else {
     // many quads: one score row at a time, all quads of it in flight together (same order of additions per token)
     f32x4 acc[IT];

@@ -359,20 +359,11 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
     }
   };
   if (m > 0) {
-    if (nsq <= T) {                                    // one sampled quad per thread
-      const int p1[1] = {pos[0]};
-      f32x4 a1[1];
-      agg_quads_any<1, 8>(R, p1, false, a1);
-      sacc[0] = sacc[1] = a1[0];
-    } else {
 #pragma unroll 1
-      for (int x = 0; x < QT; ++x) {
-        const int p1[1] = {x == 0 ? pos[0] : pos[1]};
-        f32x4 a1[1];
-        agg_quads_any<1, 8>(R, p1, false, a1);
-        if (x == 0) sacc[0] = a1[0];
-        sacc[1] = a1[0];
-      }
+    for (int x = 0; x < (nsq <= T ? 1 : QT); ++x) {    // (one sampled quad per thread, or two)
+      const f32x4 a = agg_quad_any<BF16>(R, x == 0 ? pos[0] : pos[1], false);
+      if (x == 0) sacc[0] = a;
+      sacc[1] = a;
     }
   }
 #pragma unroll
@@ -525,7 +516,8 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   // ---- the threshold
   const int Qv = (nb + P - 1) / P;                     // parts that hold ranked tokens
   unsigned long long *pub = Qv > 1 ? static_cast<unsigned long long *>(A.pub) + (size_t)row * A.smp_parts * SMP_WORDS : nullptr;
-  auto plain_passes = [&]() { rank_by_passes<T, 1>(A, R, bt, nb, c, t0, t1, h, tmp, n0, min(n0 + P, nb)); };
+  // false: the row has to be ranked by plain passes
+  auto rank = [&]() -> bool {
   uint32_t lo = band.L, last = band.last;              // keys in question: lo .. lo + last
   int shift = max(0, 32 - __clz((int)band.span) - 9);
   uint32_t krem = 0, G = 0, pre = 0, pre_gt = 0, pre_in = 0, in_bin = 0;
@@ -594,8 +586,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
       }
       __syncthreads();
       if (ctr[2]) {
-        plain_passes();
-        return;
+        return false;
       }
       if (round == 0) {
         G = ctr[3];
@@ -608,8 +599,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
     }
     if (round == 0) {
       if (over || G >= c || G + s_M < c) {             // the same in every part of the row
-        plain_passes();
-        return;
+        return false;
       }
       krem = c - G;
     }
@@ -690,8 +680,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
       if (!complete) ctr[2] = 1u;
       __syncthreads();
       if (ctr[2]) {
-        plain_passes();
-        return;
+        return false;
       }
     }
     // every wave by itself: lane i ranks candidate i
@@ -789,6 +778,9 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
     }
     __syncthreads();
   }
+  return true;
+  };
+  if (!rank()) rank_by_passes<BF16, T>(A, R, bt, nb, c, t0, t1, h, tmp, n0, min(n0 + P, nb));
 }
 
 __global__ void __launch_bounds__(SEL_THREADS) select_clear16_kernel(u32x4 *p, size_t n) {

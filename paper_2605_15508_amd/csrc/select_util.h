@@ -247,27 +247,6 @@ __device__ __forceinline__ void agg_multi(const AggRow &R, const int (&n)[NPOS],
   }
 }
 
-// the same for a caller that knows Tq <= MAXG (MAXG <= 8): only those cases are compiled, so many
-// positions in flight do not cost the registers of eight rows each
-template <bool BF16, int MAXG, int NPOS, class V>
-__device__ __forceinline__ void agg_group_lim(const AggRow &R, int rows, const int (&n)[NPOS], V (&acc)[NPOS]) {
-  if constexpr (MAXG <= 1) {
-    agg_rows<1, true, BF16>(R, 0, n, acc);
-  } else {
-    if (rows >= MAXG) agg_rows<MAXG, true, BF16>(R, 0, n, acc);
-    else agg_group_lim<BF16, MAXG - 1>(R, rows, n, acc);
-  }
-}
-template <class V, int NPOS, int MAXG>
-__device__ __forceinline__ void agg_multi_lim(const AggRow &R, const int (&n)[NPOS], V (&acc)[NPOS]) {
-  if constexpr (MAXG >= 8) {
-    agg_multi<V, NPOS>(R, n, acc);
-  } else {
-    if (R.bf16) agg_group_lim<true, MAXG>(R, R.Tq, n, acc);
-    else agg_group_lim<false, MAXG>(R, R.Tq, n, acc);
-  }
-}
-
 template <class V>
 __device__ __forceinline__ V agg_at(const AggRow &R, int n) {
   const int pos[1] = {n};
@@ -278,26 +257,58 @@ __device__ __forceinline__ V agg_at(const AggRow &R, int n) {
 
 __device__ __forceinline__ f32x4 agg_quad(const AggRow &R, int n) { return agg_at<f32x4>(R, n); }
 
-// The quads at n[] of a row whose length need not be a multiple of 4 (R.N >= 4): a quad that would
+// a quad that was read d tokens before its place
+__device__ __forceinline__ f32x4 shifted_quad(f32x4 y, int d) {
+  return f32x4{d == 0 ? y[0] : d == 1 ? y[1] : d == 2 ? y[2] : y[3], d == 0 ? y[1] : d == 1 ? y[2] : y[3], d == 0 ? y[2] : y[3], y[3]};
+}
+
+// The quad at n of a row whose length need not be a multiple of 4 (R.N >= 4): a quad that would
 // run past the row's end is read where it still fits and shifted; elements past the end (all of a
 // quad's that starts there) come out as some score of the row and are the caller's to ignore.
-// inside (wave-uniform): every quad of the wave lies inside the row.
-template <int NPOS, int MAXG>
-__device__ __forceinline__ void agg_quads_any(const AggRow &R, const int (&n)[NPOS], bool inside, f32x4 (&acc)[NPOS]) {
-  int m[NPOS];
+// inside (wave-uniform): every quad of the wave lies inside the row. Up to eight rows are in flight; the rows are
+// told apart by scalar branches and not by a copy of the code for every number of rows: the sampled selection, which
+// calls this at three places, is 61 KB of instructions with it and was 400 (the instruction cache holds 64): 64 rows of
+// 128K tokens 51.1 -> 50.2 us and, with the caches flushed, 58.4 -> 57.1, 16 rows of 33001 28.8 -> 27.5 and 38.1 -> 35.7.
+template <bool BF16>
+__device__ __forceinline__ f32x4 agg_quad_any(const AggRow &R, int n, bool inside) {
+  typedef ScoreLoad<f32x4, BF16> SL;
+  const int m = min(n, R.N - 4);
+  f32x4 acc;
+  auto rows = [&](auto logits, auto use_max) {
+#pragma unroll 1
+    for (int i = 0; i < R.Tq; i += 8) {
+      typename SL::raw raw[8];
 #pragma unroll
-  for (int x = 0; x < NPOS; ++x) m[x] = min(n[x], R.N - 4);
-  agg_multi_lim<f32x4, NPOS, MAXG>(R, m, acc);
-  if (!inside) {
+      for (int u = 0; u < 8; ++u)
+        if (i + u < R.Tq) raw[u] = SL::load(R, i + u, m);
 #pragma unroll
-    for (int x = 0; x < NPOS; ++x) {
-      const int d = n[x] - m[x];
-      const f32x4 y = acc[x];
-      acc[x][0] = d == 0 ? y[0] : d == 1 ? y[1] : d == 2 ? y[2] : y[3];
-      acc[x][1] = d == 0 ? y[1] : d == 1 ? y[2] : y[3];
-      acc[x][2] = d == 0 ? y[2] : y[3];
+      for (int u = 0; u < 8; ++u)
+        if (i + u < R.Tq) {
+          f32x4 p = SL::widen(raw[u]);
+          if constexpr (decltype(logits)::value) {
+            const float l = R.L[i + u];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[e] = prob_of(p[e], l);
+          }
+          if (u == 0 && i == 0) {
+            acc = p;
+          } else if constexpr (decltype(use_max)::value) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = fmaxf(acc[e], p[e]);
+          } else {
+            acc = acc + p;
+          }
+        }
     }
+  };
+  if (R.logits) {
+    if (R.use_max) rows(std::true_type{}, std::true_type{});
+    else rows(std::true_type{}, std::false_type{});
+  } else {
+    if (R.use_max) rows(std::false_type{}, std::true_type{});
+    else rows(std::false_type{}, std::false_type{});
   }
+  return inside ? acc : shifted_quad(acc, n - m);
 }
 __device__ __forceinline__ float agg_one(const AggRow &R, int n) { return agg_at<float>(R, n); }
 
@@ -336,7 +347,7 @@ __device__ __forceinline__ uint32_t block_sum1(uint32_t a, uint32_t *red) {
 // The plain way for one workgroup to rank a row it cannot hold: a pass over the scores per digit
 // level (the Tq rows are aggregated again each time, in the same order, so the keys repeat bit
 // for bit), then a pass that compacts in token order. h: SEL_BINS words, tmp: THREADS/64 + 2.
-template <int THREADS, int NPOS = 2>
+template <bool BF16, int THREADS>
 __device__ __forceinline__ void rank_by_passes(const SelectArgs &A, const AggRow &R, int bt, int nb, uint32_t c,
                                                int t0, int t1, uint32_t *h, uint32_t *tmp, int from = 0, int to = 0x7fffffff) {
   const int tid = threadIdx.x;
@@ -348,20 +359,13 @@ __device__ __forceinline__ void rank_by_passes(const SelectArgs &A, const AggRow
     for (int i = tid; i < SEL_BINS; i += THREADS) h[i] = 0u;
     __syncthreads();
 #pragma unroll 1
-    for (int q0 = tid; q0 < nq; q0 += THREADS * NPOS) {
-      int pos[NPOS];
-      f32x4 acc[NPOS];
+    for (int q = tid; q < nq; q += THREADS) {
+      const f32x4 acc = agg_quad_any<BF16>(R, 4 * q, false);
 #pragma unroll
-      for (int x = 0; x < NPOS; ++x) pos[x] = 4 * min(q0 + x * THREADS, nq - 1);
-      agg_quads_any<NPOS, 8>(R, pos, false, acc);
-#pragma unroll
-      for (int x = 0; x < NPOS; ++x)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int n = 4 * (q0 + x * THREADS) + e;
-          const int bin = fused_bin(key_of(acc[x][e]), level, d0, pre01);
-          if (n < nb && bin >= 0) atomicAdd(&h[bin], 1u);
-        }
+      for (int e = 0; e < 4; ++e) {
+        const int bin = fused_bin(key_of(acc[e]), level, d0, pre01);
+        if (4 * q + e < nb && bin >= 0) atomicAdd(&h[bin], 1u);
+      }
     }
     __syncthreads();
     uint32_t digit, knext;
@@ -372,26 +376,20 @@ __device__ __forceinline__ void rank_by_passes(const SelectArgs &A, const AggRow
     krem = knext;
   }
   const uint32_t r = krem, Tk = (pre01 << SEL_BITS2) | d2;
-  // ordered compaction: per step, thread tid owns the NPOS consecutive quads from (step + tid * NPOS)
+  // ordered compaction: per step, thread tid owns quad step + tid
   uint32_t gbase = 0, qbase = 0;
 #pragma unroll 1
-  for (int step = 0; step < nq; step += THREADS * NPOS) {
-    const int qlo = step + tid * NPOS;
-    int pos[NPOS];
-    f32x4 acc[NPOS];
-#pragma unroll
-    for (int x = 0; x < NPOS; ++x) pos[x] = 4 * min(qlo + x, nq - 1);
-    agg_quads_any<NPOS, 8>(R, pos, false, acc);
+  for (int step = 0; step < nq; step += THREADS) {
+    const int qlo = step + tid;
+    const f32x4 acc = agg_quad_any<BF16>(R, 4 * min(qlo, nq - 1), false);
     uint32_t gt_mask = 0, eq_mask = 0;
 #pragma unroll
-    for (int x = 0; x < NPOS; ++x)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t key = key_of(acc[x][e]);
-        const bool in = 4 * (qlo + x) + e < nb;
-        gt_mask |= (in && key > Tk) ? 1u << (4 * x + e) : 0u;
-        eq_mask |= (in && key == Tk) ? 1u << (4 * x + e) : 0u;
-      }
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t key = key_of(acc[e]);
+      const bool in = 4 * qlo + e < nb;
+      gt_mask |= (in && key > Tk) ? 1u << e : 0u;
+      eq_mask |= (in && key == Tk) ? 1u << e : 0u;
+    }
     uint32_t total;
     const uint32_t excl = block_excl_scan<THREADS>(__builtin_popcount(gt_mask) | (__builtin_popcount(eq_mask) << 16), tmp, total);
     uint32_t g = gbase + (excl & 0xffffu), q = qbase + (excl >> 16);
@@ -409,7 +407,7 @@ __device__ __forceinline__ void rank_by_passes(const SelectArgs &A, const AggRow
     }
     gbase += total & 0xffffu;
     qbase += total >> 16;
-    if (gbase + min(qbase, r) >= c || 4 * (step + THREADS * NPOS) >= to) break;   // the list is complete (uniform)
+    if (gbase + min(qbase, r) >= c || 4 * (step + THREADS) >= to) break;   // the list is complete (uniform)
   }
 }
 
