@@ -27,8 +27,11 @@
 // whatever the others do; a row's parts have neighbouring workgroup ids and start together.
 //
 // The result never depends on the sample: if the counts show that the threshold lies outside [L, U),
-// or a band list overflowed, every part goes by plain passes likewise. Values that repeat do not make it
-// overflow: only two can hold more of the sample than the margins, the lowest key of the band and its
+// every part goes by plain passes likewise. Where a part's list has no room for its band (heavy tokens next to each
+// other, all in that part), what does not fit is only counted, and the part reads its own tokens once more when the
+// threshold's bin is known: 16 rows of 1M tokens, the last 5% of them heavy 113 us, the first eighth after a third
+// 114, against 1955 and 1692 by plain passes of every part. Values that repeat do not make the list overflow:
+// only two can hold more of the sample than the margins, the lowest key of the band and its
 // highest (any other lies between the two ranks), and where the sample says that one does (zeros, levels, a
 // saturated score), a bitmap holds its tokens and not the list. 16 rows of 1M tokens, a budget at the edge of the
 // zeros: 118 us, 3870 by plain passes; 64 rows of 128K: 74, 520; a constant row with a small budget 58, 435.
@@ -56,7 +59,7 @@ constexpr int SMP_ROUNDS = 5;
 constexpr int SMP_CAND = 64;              // keys of the threshold's bin that are exchanged one by one
 constexpr int SMP_G_WORD = SMP_ROUNDS * SMP_HIST / 2, SMP_CAND_WORD = SMP_G_WORD + 8;
 static_assert(SMP_CAND_WORD + SMP_CAND == SMP_WORDS, "layout of a part's exchange words");
-constexpr unsigned long long SMP_VALID = 1ull << 63, SMP_OVER = 1ull << 62;
+constexpr unsigned long long SMP_VALID = 1ull << 63;
 
 // Which runs of a row of nb ranked tokens are sampled: one in every S, at a scattered place of its
 // period (a fixed stride of 4 KB and more lands on a few memory channels only: the sample's loads
@@ -272,7 +275,7 @@ __device__ __forceinline__ Band sample_band(const SamplePlan &sp, int run, int n
     if (haveL) refine(lower, margin + 16u);
     if (haveU) refine(upper, margin + 16u);
   }
-  Band b = {haveL ? lower.lo : 0u, 0u, 0u, false, false, false};
+  Band b = {max(haveL ? lower.lo : 0u, 1u), 0u, 0u, false, false, false};   // (0 marks what is no token)
   b.haveU = haveU && upper.hi != 0xffffffffu;
   b.last = (b.haveU ? upper.hi : 0xffffffffu) - b.L;
   b.heavyL = lower.heavy;
@@ -296,12 +299,13 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   uint32_t *const store = reinterpret_cast<uint32_t *>(list);
   uint32_t *const mapL = store + 2 * (CAP - MAP), *const mapU = TWO_MAPS ? mapL - 2 * MAP : mapL;
   __shared__ uint32_t h[SEL_BINS];
-  __shared__ uint32_t hb[SMP_HIST];                    // the earlier parts' share of an exchanged histogram
+  __shared__ uint32_t hb[SMP_HIST];                    // the earlier parts' share of an exchanged histogram; first the band
+                                                       // tokens that the list has no room for, by bins
   __shared__ uint32_t tmp[T / 64 + 2];
   __shared__ uint32_t red[2 * T / 64];
   __shared__ uint32_t found[9];
   __shared__ uint32_t ticket;                          // next group of the pass
-  __shared__ uint32_t ctr[11];                         // 0 list entries, 1 certain tokens, 9, 10 tokens of the heavy keys, 2.. see below
+  __shared__ uint32_t ctr[12];                         // 0 list entries, 1 certain tokens, 9, 10 tokens of the heavy keys, 2.. see below
   __shared__ u32x2 cand[SMP_CAND];                     // key; 0 (own) or 1 << 31 | part
   const int row = blockIdx.y, part = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -320,7 +324,8 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   const AggRow R = agg_row(A, row);
   const int Tq = R.Tq;
   for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
-  if (tid < 11) ctr[tid] = 0u;
+  if (tid < SMP_HIST) hb[tid] = 0u;
+  if (tid < 12) ctr[tid] = 0u;
   if (tid == 0) ticket = 2 * W;
   const float lse_of = R.logits && lane < Tq ? R.L[lane] : 0.f;        // row i's normaliser in lane i (Tq <= 64)
   __syncthreads();
@@ -371,16 +376,18 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   Band band = {0u, 0u, 0u, false, false, false};
   if (m > 0) band = sample_band<QT>(sp, run, nb, c, pos, sacc, h, tmp, red, found);   // (uniform; its barriers publish ctr)
   else __syncthreads();
-  const bool heavyL = band.heavyL, heavyU = band.heavyU && (TWO_MAPS || !heavyL), heavy = heavyL || heavyU;
+  const bool heavyL = band.heavyL, heavyU = band.heavyU && (TWO_MAPS || !heavyL);
   const uint32_t cap = (uint32_t)(CAP - (heavyL ? MAP : 0) - (heavyU ? MAP : 0));
 
   // ---- the pass
   // INT_MIN marks what is no token of the row: it stays below every edge
-  const int sL = max(ordered_of_key(band.L), (int)0x80000001);
+  const int sL = ordered_of_key(band.L);
   const int sU = band.haveU ? ordered_of_key(band.L + band.last + 1u) : 0x7fffffff;
-  const int sLast = ordered_of_key(band.L + band.last);
+  const int sHL = heavyL ? sL : (int)0x80000000, sHU = heavyU ? ordered_of_key(band.L + band.last) : (int)0x80000000;
+  const bool heavy = heavyL || heavyU;
   const bool plain = sL > 0;       // scores below the band, negative ones included, compare right as bit patterns
   uint32_t certain = 0;            // wave-uniform
+  int shift = max(0, 32 - __clz((int)band.span) - 9);  // bins of the first histogram
   auto classify = [&](int g, f32x4 acc) {
     const int n = n0 + g * SMP_GROUP + lane4;
     if (n0 + (g + 1) * SMP_GROUP > R.N) {              // the row's end: the quad was read where it still fits
@@ -413,16 +420,6 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = n + e < nb ? v[e] : (int)0x80000000;
     }
-    uint32_t nib = 0, held = 0;
-    bool in_band[4];
-    uint64_t bd[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const bool sure = v[e] >= sU;
-      in_band[e] = !sure && v[e] >= sL;
-      nib |= sure ? 1u << e : 0u;
-      certain += (uint32_t)__builtin_popcountll(ballot64(sure));
-    }
     // the nibbles of eight neighbouring quads make one bitmap word, stored whole by the first lane of
     // the eight: three shifts by 1, 2, 4 lanes inside a row of 16 lanes, OR-ed
     auto word = [&](uint32_t b, uint32_t *to) {
@@ -432,34 +429,55 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
       w |= __builtin_amdgcn_update_dpp(0, w, 0x104, 0xf, 0xf, true);   // row_shl:4
       if ((lane & 7) == 0) to[g * 8 + (lane >> 3)] = (uint32_t)w;
     };
-    word(nib, bits);
-    if (heavy) {
-      uint32_t nibL = 0, nibU = 0;
+    auto place = [&](auto with_heavy) {
+      uint32_t nib = 0, held = 0;
+      bool in_band[4];
+      uint64_t bd[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const bool l = heavyL && v[e] == sL, u = heavyU && v[e] == sLast;
-        nibL |= l ? 1u << e : 0u;
-        nibU |= u ? 1u << e : 0u;
-        in_band[e] = in_band[e] && !l && !u;
+        const bool sure = v[e] >= sU;
+        in_band[e] = !sure && v[e] >= sL;
+        nib |= sure ? 1u << e : 0u;
+        certain += (uint32_t)__builtin_popcountll(ballot64(sure));
       }
-      if (heavyL) word(nibL, mapL);
-      if (heavyU) word(nibU, mapU);
-    }
+      word(nib, bits);
+      if constexpr (decltype(with_heavy)::value) {
+        uint32_t nibL = 0, nibU = 0;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      bd[e] = ballot64(in_band[e]);
-      held += (uint32_t)__builtin_popcountll(bd[e]);
-    }
-    uint32_t at = 0;
-    if (lane == 0) at = atomicAdd(&ctr[0], held);
-    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-    if (at + held > cap) return;                       // does not fit: the count says so, the row goes by plain passes
-    const uint32_t tok = (uint32_t)(g * SMP_GROUP + lane4);
+        for (int e = 0; e < 4; ++e) {
+          const bool l = in_band[e] && v[e] == sHL, u = in_band[e] && v[e] == sHU;
+          nibL |= l ? 1u << e : 0u;
+          nibU |= u ? 1u << e : 0u;
+          in_band[e] = in_band[e] && !l && !u;
+        }
+        if (sHL != (int)0x80000000) word(nibL, mapL);
+        if (sHU != (int)0x80000000) word(nibU, mapU);
+      }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (in_band[e]) list[lanes_before(bd[e], at)] = u32x2{key_of_ordered(v[e]), tok + e};
-      at += (uint32_t)__builtin_popcountll(bd[e]);
-    }
+      for (int e = 0; e < 4; ++e) {
+        bd[e] = ballot64(in_band[e]);
+        held += (uint32_t)__builtin_popcountll(bd[e]);
+      }
+      uint32_t at = 0;
+      if (lane == 0) at = atomicAdd(&ctr[0], held);
+      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+      if (at + held > cap) {                           // does not fit: counted only
+        if (lane == 0 && at < cap) ctr[11] = at;       // (entries from here on are not written)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (in_band[e]) atomicAdd(&hb[min((key_of_ordered(v[e]) - key_of_ordered(sL)) >> shift, (uint32_t)SMP_HIST - 1u)], 1u);
+      } else {
+        const uint32_t tok = (uint32_t)(g * SMP_GROUP + lane4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (in_band[e]) list[lanes_before(bd[e], at)] = u32x2{key_of_ordered(v[e]), tok + e};
+          at += (uint32_t)__builtin_popcountll(bd[e]);
+        }
+      }
+    };
+    // (apart, not a branch inside: the ordinary way has no instruction for heavy keys)
+    if (heavy) place(std::true_type{});
+    else place(std::false_type{});
   };
   {
     int i = 0;
@@ -493,6 +511,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   if (m == 0) return;
   if (lane == 0) atomicAdd(&ctr[1], certain);
   __syncthreads();
+  const uint32_t first_key = key_of_ordered(sL), last_key = first_key + band.last;   // of the band
   const int words = (m + 31) >> 5, per = (words + T - 1) / T;
   const int w0 = min(tid * per, words), w1 = min(w0 + per, words);     // a thread's run of the bitmaps' words
   if (heavy) {
@@ -509,30 +528,72 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
     }
     __syncthreads();
   }
-  const uint32_t own_G = ctr[1], own_L = ctr[9], own_U = ctr[10], own_M = ctr[0] + own_L + own_U;
-  const bool fits = ctr[0] <= cap;
-  const uint32_t listed = min(ctr[0], cap);
+  const uint32_t own_G = ctr[1], own_M = ctr[0] + ctr[9] + ctr[10];
+  // the heavy keys whose tokens mapL and mapU mark, and how many those are; the entries of the list
+  uint32_t keyL = first_key, keyU = last_key, own_L = ctr[9], own_U = ctr[10];
+  bool hasL = heavyL, hasU = heavyU, fits = ctr[0] <= cap;
+  uint32_t listed = fits ? ctr[0] : ctr[11] ? ctr[11] : cap;
 
   // ---- the threshold
   const int Qv = (nb + P - 1) / P;                     // parts that hold ranked tokens
   unsigned long long *pub = Qv > 1 ? static_cast<unsigned long long *>(A.pub) + (size_t)row * A.smp_parts * SMP_WORDS : nullptr;
-  // false: the row has to be ranked by plain passes
+  // false: the row has to be ranked by plain passes (the threshold is not in the band, or another part's words are late)
   auto rank = [&]() -> bool {
-  uint32_t lo = band.L, last = band.last;              // keys in question: lo .. lo + last
-  int shift = max(0, 32 - __clz((int)band.span) - 9);
+  uint32_t lo = first_key, last = last_key - first_key;              // keys in question: lo .. lo + last
   uint32_t krem = 0, G = 0, pre = 0, pre_gt = 0, pre_in = 0, in_bin = 0;
 #pragma unroll 1
   for (int round = 0;; ++round) {
-    for (int i = tid; i < SMP_HIST; i += T) h[i] = 0u;
-    __syncthreads();
+    for (int i = tid; i < SMP_HIST; i += T) h[i] = round == 0 ? hb[i] : 0u;
     auto in_question = [&](uint32_t k, uint32_t n) {
       if (k - lo <= last) atomicAdd(&h[min((k - lo) >> shift, (uint32_t)SMP_HIST - 1u)], n);
     };
-    for (uint32_t i = tid; i < listed; i += T) in_question(list[i][0], 1u);
-    if (tid == 0 && heavyL) in_question(band.L, own_L);
-    if (tid == 0 && heavyU) in_question(band.L + band.last, own_U);
+    if (round > 0 && !fits) {
+      // The band did not fit this part's list (heavy tokens next to each other, all in one part): its tokens are read again,
+      // and what is left of the keys in question is listed, or, where one key is left, marked. While that is too much as
+      // well, the tokens are only counted.
+      const bool collect = last == 0u || in_bin <= (uint32_t)CAP;
+      if (collect && last == 0u)
+        for (int w = w0; w < w1; ++w) mapL[w] = 0u;
+      if (tid == 0) ctr[0] = 0u;
+      __syncthreads();
+#pragma unroll 1
+      for (int q = tid; 4 * q < m; q += T) {
+        const f32x4 a = agg_quad_any<BF16>(R, n0 + 4 * q, false);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t k = key_of(a[e]), n = 4 * q + e;
+          if ((int)n >= m) continue;
+          if (!collect) {
+            in_question(k, 1u);
+          } else if (k - lo <= last) {
+            const uint32_t at = atomicAdd(&ctr[0], 1u);
+            if (last == 0u) atomicOr(&mapL[n >> 5], 1u << (n & 31u));
+            else if (at < (uint32_t)CAP) list[at] = u32x2{k, n};
+          } else if (k > lo && k <= last_key) {
+            atomicOr(&bits[n >> 5], 1u << (n & 31u));
+          }
+        }
+      }
+      if (collect) {
+        __syncthreads();
+        fits = true;
+        hasL = last == 0u;
+        hasU = false;
+        keyL = lo;
+        own_L = ctr[0];
+        listed = hasL ? 0u : min(own_L, (uint32_t)CAP);
+      }
+    } else {
+      __syncthreads();
+    }
+    if (round > 0 && (last == 0u || in_bin <= (uint32_t)SMP_CAND)) break;
+    if (fits || round == 0) {
+      for (uint32_t i = tid; i < listed; i += T) in_question(list[i][0], 1u);
+      if (tid == 0 && hasL) in_question(keyL, own_L);
+      if (tid == 0 && hasU) in_question(keyU, own_U);
+    }
     __syncthreads();
-    uint32_t s_M = own_M, over = fits ? 0u : 1u;
+    uint32_t s_M = own_M;
     if (Qv > 1) {
       // threads 0..255: two bins each; in the first round thread 256 sends the part's counts
       const bool sends = tid < SMP_HIST / 2 || (tid == SMP_HIST / 2 && round == 0);
@@ -542,8 +603,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
       if (sends) {
         const uint32_t o0 = tid < SMP_HIST / 2 ? h[2 * tid] : own_G, o1 = tid < SMP_HIST / 2 ? h[2 * tid + 1] : own_M;
         __hip_atomic_store(&pub[(size_t)part * SMP_WORDS + word],
-                           SMP_VALID | (tid < SMP_HIST / 2 || !over ? 0ull : SMP_OVER) | o0 | ((unsigned long long)o1 << 32),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                           SMP_VALID | o0 | ((unsigned long long)o1 << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         complete = false;
         for (int spin = 0; !complete && spin <= A.fused_spin_limit; ++spin) {
           if (spin) __builtin_amdgcn_s_sleep(2);
@@ -561,7 +621,6 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
               const int q = q0 + u;
               const bool use = q != part && q < Qv;
               if (use && !(w[u] & SMP_VALID)) complete = false;
-              if (use && (w[u] & SMP_OVER)) over = 1u;
               const uint32_t w0 = use ? (uint32_t)w[u] & 0xffffffu : 0u, w1 = use ? (uint32_t)(w[u] >> 32) & 0xffffffu : 0u;
               a0 += w0;
               a1 += w1;
@@ -582,25 +641,19 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
         ctr[3] = a0;                                   // certain tokens of the row
         ctr[4] = a1;                                   // band tokens of the row
         ctr[5] = b0;                                   // certain tokens of the earlier parts
-        ctr[6] = over;
       }
       __syncthreads();
-      if (ctr[2]) {
-        return false;
-      }
+      if (ctr[2]) return false;
       if (round == 0) {
         G = ctr[3];
         s_M = ctr[4];
         pre = ctr[5];
-        over = ctr[6];
       }
     } else if (round == 0) {
       G = own_G;
     }
     if (round == 0) {
-      if (over || G >= c || G + s_M < c) {             // the same in every part of the row
-        return false;
-      }
+      if (G >= c || G + s_M < c) return false;         // the same in every part of the row
       krem = c - G;
     }
     // every wave finds the bin by itself: lane l owns bins 8 l .. 8 l + 7
@@ -638,7 +691,8 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
     pre_gt += wave_sum(gt);
     lo += bin << shift;
     last = bin == (uint32_t)SMP_HIST - 1u ? last - (bin << shift) : (1u << shift) - 1u;   // the last bin has no upper end
-    if (last == 0u || in_bin <= (uint32_t)SMP_CAND) break;             // at the latest in round SMP_ROUNDS - 1
+    // one key or few are left at the latest after round SMP_ROUNDS - 1
+    if (fits && (last == 0u || in_bin <= (uint32_t)SMP_CAND)) break;
     shift = max(0, 32 - __clz((int)last) - 9);
     __syncthreads();                                   // every wave has read the histogram
   }
@@ -652,8 +706,8 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
       }
     };
     for (uint32_t i = tid; i < listed; i += T) add(list[i][0]);
-    if (heavyL && (uint32_t)tid < min(own_L, (uint32_t)SMP_CAND)) add(band.L);
-    if (heavyU && (uint32_t)tid < min(own_U, (uint32_t)SMP_CAND)) add(band.L + band.last);
+    if (hasL && (uint32_t)tid < min(own_L, (uint32_t)SMP_CAND)) add(keyL);
+    if (hasU && (uint32_t)tid < min(own_U, (uint32_t)SMP_CAND)) add(keyU);
     __syncthreads();
     // The other parts' keys follow the own ones under a counter of their own (ctr[8]): ctr[7] and the own entries,
     // which one wave publishes while the others already poll, stay as they are from the barrier on.
@@ -679,9 +733,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
       }
       if (!complete) ctr[2] = 1u;
       __syncthreads();
-      if (ctr[2]) {
-        return false;
-      }
+      if (ctr[2]) return false;
     }
     // every wave by itself: lane i ranks candidate i
     const uint32_t n = min(in_bin, (uint32_t)SMP_CAND);
@@ -705,7 +757,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   // ---- the part's kept tokens: bits of the band's. Of the tokens equal to T the first `quota` of this part
   // are kept: all of them, unless the row has more than r.
   const uint32_t quota = r > pre_eq ? r - pre_eq : 0u;
-  const bool all_eq = r >= E, of_map = (heavyL && Tk == band.L) || (heavyU && Tk == band.L + band.last);
+  const bool all_eq = r >= E, of_map = (hasL && Tk == keyL) || (hasU && Tk == keyU);
   uint32_t n_eq = 0;
   for (uint32_t i = tid; i < listed; i += T) {
     const u32x2 x = list[i];
@@ -738,7 +790,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
       if (list[i][0] == Tk && REV - list[i][1] >= cut) atomicOr(&bits[list[i][1] >> 5], 1u << (list[i][1] & 31u));
   }
   __syncthreads();
-  if (heavy) {
+  if (hasL || hasU) {
     auto take = [&](uint32_t k, uint32_t n, const uint32_t *map) {
       if (k < Tk || (k == Tk && quota == 0u)) return;
       if (k > Tk || all_eq || n <= quota) {
@@ -751,8 +803,8 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
           for (uint32_t rest = map[w]; rest && before < quota; rest &= rest - 1u, ++before) bits[w] |= rest & (0u - rest);
       }
     };
-    if (heavyL) take(band.L, own_L, mapL);
-    if (heavyU) take(band.L + band.last, own_U, mapU);
+    if (hasL) take(keyL, own_L, mapL);
+    if (hasU) take(keyU, own_U, mapU);
     __syncthreads();
   }
 

@@ -219,3 +219,23 @@ def test_values_that_repeat_next_to_the_threshold(lib, what, k):
             lib.sts_set_knob(3, float("nan"))
         check(lib, s, [0, 0], k)
         check(lib, s[..., :40001].contiguous(), [0], k // 4, lens=[39999])
+
+
+@pytest.mark.parametrize("levels,one_part", [(0, False), (5, False), (0, True), (5, True)])
+def test_bands_that_lie_in_one_part(lib, levels, one_part):
+    """All tokens around the threshold next to each other, more than a part's list holds: that part reads its own
+    tokens again, once, or, where the excess is one value, once per histogram; the others are done."""
+    N, k = 524288, 60000
+    g = torch.Generator().manual_seed(levels)
+    s = torch.rand(1, 1, 1, N, generator=g) * 1e-3
+    heavy = torch.rand(100000, generator=g) if not levels else torch.randint(1, levels + 1, (100000,), generator=g) / levels
+    s[..., 140000:240000] = 1.0 + heavy
+    lib.emu_schedule(1, 1, 3)
+    lib.sts_set_knob(3, 5.0)
+    lib.emu_loaded()
+    try:
+        check(lib, s, [0], k, lens=[N - 5], ws_bytes=0 if one_part else None)
+    finally:
+        lib.sts_set_knob(3, float("nan"))
+    read = lib.emu_loaded() / (4 * N)
+    assert read < (2.5 if one_part else 1.8) + (3.0 if one_part else 1.0) * (levels > 0), read
