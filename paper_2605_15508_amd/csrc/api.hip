@@ -314,12 +314,12 @@ sts_status run_attn(const sts_attn_params *p, int sparse, hipStream_t s, void *w
 struct SelectPlan {
   bool small;          // one workgroup per row, keys in LDS, a single launch
   bool pool;           // shape allows chunk-local top-k + one ranking workgroup per row
-  bool fused;          // long rows: parts of a row in LDS, one launch (plus the flag clear)
-  bool band;           // at least a row per CU: one workgroup per row, one pass, no workspace
+  bool fused;          // long rows: the sampled selection, one launch (plus the clearing of the exchanged words)
+  bool band;           // the same for a row for every second CU or more: can do without a workspace
   bool rowpass;        // many long rows of ready-made scores: one workgroup per row, no workspace
   int rowpass_threads;
   int nchunks, page, srcN, pool_pitch, pool_chunk, pool_nchunks;
-  int part_tokens, parts, smp_tokens, smp_parts;
+  int smp_tokens, smp_parts;
   size_t agg_bytes, blk_bytes, hist_bytes, state_bytes, chunk_bytes;
   size_t pool_key_bytes;
   size_t pub_bytes;
@@ -335,22 +335,44 @@ struct SelectPlan {
   }
 };
 
+int largest_budget(const sts_select_params *p) {
+  if (!p->k_head) return p->k;
+  int k = 1;
+  for (int j = 0; j < p->Hd; ++j) k = p->k_head[j] > k ? p->k_head[j] : k;
+  return k;
+}
+
+// does the list of a workgroup with `tokens` tokens, one of q parts of the row, have room for its share of the band?
+bool smp_list_fits(const sts_select_params *p, int k, int64_t tokens, int64_t q) {
+  const int64_t band = smp_expected_band(p->N, k < p->N ? k : p->N, (int)tokens);
+  for (int f = 0; f < SMP_FORMS; ++f)
+    if (tokens <= SMP_TOKENS[f]) return band >= 0 && band <= q * SMP_LIST[f];
+  return false;
+}
+
 // How the sampled selection cuts its rows: as many workgroups as there are CUs, in equal shares of at
 // least 8192 tokens (below that the fixed part of a workgroup's work exceeds its share of the pass)
 // and at most 32 per row (the exchange grows with the square).
+// Parts of more than 128K tokens only where the list, the shorter the more tokens there are, has room for the band (else
+// it is read again), and for one or two parts per row or a grid that fits the chip. One part per row against parts of
+// at most 128K: 256 rows of 524288 tokens, one score each, 0.5% kept 130 us, 213; 256 rows of 200000, four scores, 10% kept
+// 144, 182; 512 rows of 200000, one bf16 score, 10% 160, 249; two parts: 128 rows of 524288, one score, 4% 88, 118; but
+// three for 10%: 144, 127.
+// Calls with a row for every second CU or more take one part for short rows: no words to clear and to exchange. 128 rows of
+// 12000 tokens, one score: 20.9 us, 26.3 in two parts; 26000, five scores: 31.5, 32.8; 26000, eight bf16 scores: 36.0, 33.1.
 void plan_sampled(const sts_select_params *p, size_t rows, SelectPlan &pl) {
-  int64_t q = cu_count() / (int64_t)(rows ? rows : 1);
+  const int k = largest_budget(p);
+  const int64_t cus = cu_count(), r = rows ? (int64_t)rows : 1;
+  int64_t q = cus / r;
   if (q > ((int64_t)p->N + 8191) / 8192) q = ((int64_t)p->N + 8191) / 8192;
   if (q > 32) q = 32;
-  // At most 128K tokens per part: a tenth of such a row leaves a band of 6700 tokens and up to a half more where
-  // bins are coarse. The list of a workgroup with more tokens has room for 8192, too few for that: 128 rows of
-  // 512K tokens took 232 us before this kernel and take 87 us in one part, 116 us in four, but 256 rows of 128K
-  // tokens with the short list 239 us against 54.
-  const int64_t least = ((int64_t)p->N + SMP_PART_TOKENS - 1) / SMP_PART_TOKENS;
-  if (q < least) q = least;
-  if (q < 1) q = 1;
-  pl.smp_tokens = (int)((((int64_t)p->N + q - 1) / q + 255) / 256 * 256);
+  if (q < 1 || (2 * r >= cus && p->N <= 32768 && (int64_t)p->N * p->Tq <= 131072)) q = 1;
+  auto tokens = [&] { return (((int64_t)p->N + q - 1) / q + 255) / 256 * 256; };
+  auto fits = [&] { return tokens() <= SMP_MAX_TOKENS && (q <= 2 || r * q <= cus) && smp_list_fits(p, k, tokens(), q); };
+  while (tokens() > 131072 && !fits()) ++q;
+  pl.smp_tokens = (int)tokens();
   pl.smp_parts = (int)(((int64_t)p->N + pl.smp_tokens - 1) / pl.smp_tokens);
+  pl.pub_bytes = pl.smp_parts > 1 ? align256(rows * (size_t)pl.smp_parts * SMP_WORDS * sizeof(unsigned long long)) : 0;
 }
 
 sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
@@ -377,7 +399,7 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
   pl.rowpass = false;
   pl.band = false;
   pl.rowpass_threads = 0;
-  pl.part_tokens = pl.parts = pl.smp_tokens = pl.smp_parts = 0;
+  pl.smp_tokens = pl.smp_parts = 0;
   pl.pub_bytes = 0;
   // test / tuning knob: 0 the library's rule, 1 histogram pipeline only, 2 pipeline or pool,
   // 3 the sampled selection wherever its shape limits allow, 4 one workgroup per row in
@@ -385,9 +407,9 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
   const double path_knob = knob(STS_KNOB_SELECT_PATH);
   const int path = path_knob == path_knob ? (int)path_knob : 0;
   // Enough rows to give at least every second CU one, and rows that do not fit one workgroup's
-  // LDS: the sampled selection with one workgroup per row (two when that still fits the chip, as
-  // for 128 rows on 256 CUs). The band of a full-length row with the call's largest budget has to
-  // fit (rows for which it does not, decided in the kernel, are ranked by plain passes there).
+  // LDS: the sampled selection, which here can do without a workspace, in one workgroup per row (with one it
+  // may take more, see plan_sampled). Budgets next to the row's length, and rows of more than 512K tokens, go by the
+  // rules further down and need theirs.
   // Measured, 128K-token rows, 10%: 128 rows of one fp32 score per token 45 us (two workgroups per
   // row; one workgroup per row took 57), 128 rows of eight bf16 scaled logits of 50000 tokens 52
   // (70 with one workgroup per row).
@@ -395,23 +417,17 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
   // shape that plain passes by small workgroups serve better (select_rowpass_kernel; 4096 rows of
   // 128K: 754 against 962 us; one workgroup per row out of parts that exchange: 2.1 ms).
   {
-    int kmax = p->k;
-    if (p->k_head) {
-      kmax = 1;
-      for (int j = 0; j < p->Hd; ++j) kmax = p->k_head[j] > kmax ? p->k_head[j] : kmax;
-    }
     const bool aligned = reinterpret_cast<uintptr_t>(p->scores) % 16 == 0;
-    const bool band_ok = pl.page == 1 && p->N > 0 && p->N <= BAND_MAX_N && (p->N % 4) == 0 && aligned &&
-                         (!p->agg_out || reinterpret_cast<uintptr_t>(p->agg_out) % 16 == 0);
-    const bool fits = band_ok && (p->N <= BAND_CAP ||
-                                  band_plan(p->N, (uint32_t)(kmax < p->N ? kmax : p->N), p->scores_bf16 ? 64 : 32).fits);
+    const bool band_ok = pl.page == 1 && p->N >= 4 && p->N <= SMP_MAX_TOKENS;
+    const int kmax = largest_budget(p);
+    const bool has_edge = band_ok && smp_expected_band(p->N, kmax < p->N ? kmax : p->N, p->N) >= 0;
     const bool rowpass_ok = pl.page == 1 && p->Tq == 1 && p->kind == STS_SCORES_PROBS && !p->agg_out && p->N > 0 &&
                             (p->N % (p->scores_bf16 ? 8 : 4)) == 0 && aligned;
     const int64_t cus = cu_count();
     const bool long_rows = !pl.small && p->N > SEL_FUSED_N;
     const bool take_rowpass = path == 4 ? rowpass_ok
                                         : path == 0 && rowpass_ok && long_rows && p->scores_bf16 && (int64_t)rows >= 4 * cus;
-    const bool take_band = path == 5 ? band_ok : path == 0 && !take_rowpass && fits && long_rows && 2 * (int64_t)rows >= cus;
+    const bool take_band = path == 5 ? band_ok && p->N % 4 == 0 && aligned : path == 0 && !take_rowpass && has_edge && long_rows && 2 * (int64_t)rows >= cus;
     if (take_rowpass || take_band) {
       pl.small = false;
       pl.band = take_band;
@@ -422,8 +438,12 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
       pl.pool_chunk = pl.pool_nchunks = 0;
       pl.agg_bytes = pl.blk_bytes = pl.hist_bytes = pl.state_bytes = pl.chunk_bytes = 0;
       if (take_band) {
-        plan_sampled(p, path == 5 ? (size_t)cus : rows, pl);
-        if (pl.smp_parts > 1) pl.pub_bytes = align256(rows * (size_t)pl.smp_parts * SMP_WORDS * sizeof(unsigned long long));
+        plan_sampled(p, rows, pl);
+        if (path == 5) {                               // (the knob's meaning: one workgroup per row)
+          pl.smp_tokens = (p->N + 255) / 256 * 256;
+          pl.smp_parts = 1;
+          pl.pub_bytes = 0;
+        }
       }
       return STS_OK;
     }
@@ -465,22 +485,10 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
   // and below, which are bound by launches and latencies there.
   if (pl.page == 1 && p->N > SEL_FUSED_N && path != 1 && path != 2) {
     const bool large = (int64_t)rows * p->N >= (int64_t)1 << 22 && !pl.pool;
-    const int max_parts = path == 3 || large ? 256 : SEL_FUSED_MAX_PARTS;
-    int P = SEL_SMALL_N;
-    while (P > SEL_FUSED_N && (int64_t)rows * (((int64_t)p->N + P - 1) / P) < cu_count() &&
-           ((int64_t)p->N + P / 2 - 1) / (P / 2) <= SEL_FUSED_MAX_PARTS)
-      P >>= 1;
-    const int64_t parts = ((int64_t)p->N + P - 1) / P;
-    if (parts <= max_parts) {
+    if (((int64_t)p->N + 32767) / 32768 <= (path == 3 || large ? 256 : SEL_FUSED_MAX_PARTS)) {
       pl.fused = true;
       pl.pool = false;
-      pl.part_tokens = P;
-      pl.parts = (int)parts;
       plan_sampled(p, rows, pl);
-      pl.pub_bytes = align256(rows * (size_t)pl.smp_parts * SMP_WORDS * sizeof(unsigned long long));
-      // (at least what the row cut into parts of part_tokens takes at 24 KB each)
-      const size_t least = rows * 3 * (size_t)pl.parts * 1024 * sizeof(unsigned long long);
-      if (pl.pub_bytes < least) pl.pub_bytes = least;
     }
   }
   pl.agg_bytes = p->agg_out ? 0 : align256(rows * (size_t)p->N * sizeof(float));
@@ -642,12 +650,10 @@ static sts_status enqueue_select(const sts_select_params *p, void *stream) {
     a.pub = p->workspace;
     a.smp_tokens = pl.smp_tokens;
     a.smp_parts = pl.smp_parts;
-    a.part_tokens = pl.part_tokens;
-    a.parts = pl.parts;
     a.agg = p->agg_out;   // optional output only: the keys never leave LDS
     a.src = nullptr;
     a.hist = a.state = a.chunk_cnt = nullptr;   // the pipeline's scratch does not exist on this path
-    if (pl.parts > 1 || pl.smp_parts > 1) {
+    if (pl.smp_parts > 1) {
       rc = run_kernel(STS_K_SELECT_CLEAR, s, [&] { return launch_select_clear_pub(a, s); });
       if (rc != hipSuccess) return STS_EHIP;
     }

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
+#include <math.h>
 #include <stdint.h>
 
 #include <tuple>
@@ -116,42 +117,26 @@ constexpr int SEL_FLAG_PITCH = 32;      // words between the published counts of
 constexpr int SEL_FUSED_N = 8192;
 constexpr int SEL_FUSED_MAX_PARTS = 8;   // units of 32768 tokens up to which small calls take the sampled selection
                                          // (256K tokens; large calls and a test knob: up to 256)
-constexpr int SMP_MAX_TOKENS = 524288;  // sampled selection: most tokens per workgroup (a bit each in LDS)
-constexpr int SMP_PART_TOKENS = 131072; // ... and where the call has a workspace to exchange counts in
+// The forms of the sampled selection: most tokens per workgroup (a bit each in LDS) and entries of its band list.
+// The bits and the list share the LDS.
+constexpr int SMP_FORMS = 4;
+constexpr int SMP_TOKENS[SMP_FORMS] = {65536, 131072, 262144, 524288}, SMP_LIST[SMP_FORMS] = {16384, 15360, 13312, 8192};
+constexpr int SMP_MAX_TOKENS = SMP_TOKENS[SMP_FORMS - 1];
+// how many keys of a row of nb tokens with budget c are sampled where a workgroup holds part_tokens: see sample_plan
+__host__ __device__ inline int smp_sample(int64_t nb, int64_t c, int part_tokens) {
+  return nb > 262144 || part_tokens > 131072 || (part_tokens > 65536 && 8 * c >= nb) ? 8192 : 4096;
+}
 constexpr int SMP_WORDS = 1352;         // 64-bit words a part exchanges with the other parts of its row
 constexpr int SEL_POOL_MAX = 16384;     // chunk-local winners per row that the pool kernel ranks out of LDS       // rows up to this many tokens always take it
 
-// What a strided sample of a row of nb ranked tokens with budget c looks like, and whether the band of
-// keys around the threshold that it is expected to give fits one workgroup's store. The host asks this
-// for a full-length row when it chooses the path of calls with many rows (budgets next to the row's
-// length and, beyond 256K tokens, large ones go elsewhere); the kernel samples for itself.
-constexpr int BAND_CAP = 8192;          // band entries (key and token) a workgroup holds; it samples up to twice as many keys
-constexpr int BAND_MAX_N = 524288;      // tokens per row: one bit each in LDS
-constexpr int BAND_Z = 5;               // half-width of the band in standard deviations of the sample count
-struct BandPlan {
-  int S;                // one run of `run` tokens is sampled in every S runs
-  int runs, ns;         // sampled runs and tokens (the last run may be cut by the row's end)
-  long long s_hi, s_lo; // sample ranks that give the band's upper and lower edge (s_hi < 1: no upper edge)
-  bool fits;
-};
-__host__ __device__ inline BandPlan band_plan(int nb, uint32_t c, int run) {
-  BandPlan p;
-  const int row_runs = (nb + run - 1) / run;
-  p.S = 16;
-  while (((row_runs + p.S - 1) / p.S) * run > 2 * BAND_CAP) p.S <<= 1;
-  p.runs = (row_runs + p.S - 1) / p.S;              // sampled run i starts at token i * S * run
-  const int last = nb - (p.runs - 1) * p.S * run;
-  p.ns = (p.runs - 1) * run + (last < run ? last : run);
-  const uint32_t cs = c / (uint32_t)p.S;
-  uint32_t sq = (uint32_t)sqrtf((float)cs);
-  while ((uint64_t)sq * sq > cs) --sq;
-  while ((uint64_t)(sq + 1) * (sq + 1) <= cs) ++sq;
-  ++sq;                                   // > sqrt(cs): one standard deviation of the sample count, rounded up
-  p.s_hi = (long long)cs - (long long)BAND_Z * sq - 2;
-  p.s_lo = (long long)cs + (long long)BAND_Z * sq + 3;
-  const long long expect = (long long)p.S * (p.s_lo - (p.s_hi >= 1 ? p.s_hi : 0));
-  p.fits = nb > 0 && p.s_lo <= p.ns && expect <= BAND_CAP - BAND_CAP / 8;
-  return p;
+// Tokens in the band of keys around the threshold that such a sample is expected to give: 5 standard deviations of
+// the sample's count on either side, and half as much again where bins are coarse. < 0: no lower edge (the budget is next
+// to the row's length).
+inline int64_t smp_expected_band(int64_t nb, int64_t c, int part_tokens) {
+  const double ns = nb < smp_sample(nb, c, part_tokens) ? (double)nb : (double)smp_sample(nb, c, part_tokens);
+  const double cs = (double)c * ns / (double)nb, margin = 5.0 * sqrt(cs) + 4.0;
+  if (cs + margin > ns) return -1;
+  return (int64_t)(1.5 * (margin + (cs < margin ? cs : margin)) * (double)nb / ns);
 }
 
 struct SelectTargets {
@@ -183,7 +168,6 @@ struct SelectArgs {
   uint64_t clear_words;       // words to zero from `hist` on: histograms, state and chunk flags
   int32_t hist_cpw;           // consecutive chunks per workgroup of the refinement histograms (1, 2 or 4)
   int32_t spin_limit;         // polls of an unpublished earlier chunk before it is recounted locally
-  int32_t part_tokens, parts; // long rows: the row in units of 8192, 16384 or 32768 tokens (what the choice of path goes by)
   void *pub;                  // sampled selection: [rows][smp_parts][SMP_WORDS] 64-bit words that the parts of a row
                               // exchange (top bit: written), zero before the launch
   int32_t smp_tokens, smp_parts;   // tokens per workgroup (a multiple of 256), workgroups per row
@@ -225,7 +209,6 @@ bool select_aggblock_ok(const SelectArgs &a);
 hipError_t launch_select_aggblock(const SelectArgs &a, hipStream_t s);
 hipError_t launch_select_fused(const SelectArgs &a, hipStream_t s);
 hipError_t launch_select_clear_pub(const SelectArgs &a, hipStream_t s);
-bool select_band_ok(const SelectArgs &a);
 hipError_t launch_select_band(const SelectArgs &a, hipStream_t s);
 bool select_rowpass_ok(const SelectArgs &a);
 hipError_t launch_select_rowpass(const SelectArgs &a, hipStream_t s);

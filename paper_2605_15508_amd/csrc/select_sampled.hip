@@ -64,9 +64,9 @@ constexpr unsigned long long SMP_VALID = 1ull << 63;
 // Which runs of a row of nb ranked tokens are sampled: one in every S, at a scattered place of its
 // period (a fixed stride of 4 KB and more lands on a few memory channels only: the sample's loads
 // took 6.5 and, at 1M tokens, 12 us more). About 4096 keys: at a tenth of the row kept the band is then
-// about 5% of a 128K row. 8192 for rows beyond 256K tokens, and where a workgroup holds more than 64K
-// tokens and an eighth of the row or more is kept: with 4096 the band of half of such a part overflowed
-// its list (256 rows of 128K tokens 277 us, with 8192 83). Smaller budgets have room enough and save the
+// about 5% of a 128K row. 8192 for rows beyond 256K tokens, for workgroups with more than 128K tokens, and where a
+// workgroup holds more than 64K tokens and an eighth of the row or more is kept: with 4096 the band of half of such a
+// part overflowed its list (256 rows of 128K tokens 277 us, with 8192 83). Smaller budgets have room enough and save the
 // larger sample's 2 to 4 us.
 struct SamplePlan {
   int S, runs;
@@ -74,9 +74,9 @@ struct SamplePlan {
     return (i * S + (int)((((uint32_t)i * 0x9e3779b1u) >> 16) & (uint32_t)(S - 1))) * run;
   }
 };
-__device__ __forceinline__ SamplePlan sample_plan(int nb, int run, bool wide) {
+__device__ __forceinline__ SamplePlan sample_plan(int nb, int run, int target) {
   SamplePlan p;
-  const int row_runs = (nb + run - 1) / run, target = nb > 262144 || wide ? 8192 : 4096;
+  const int row_runs = (nb + run - 1) / run;
   p.S = 1;
   while (((row_runs + p.S - 1) / p.S) * run > target) p.S <<= 1;
   p.runs = row_runs / p.S;                             // (at least one: S is at most half the runs here)
@@ -332,7 +332,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   // ---- the sample's loads, then the first eight of the part's own
   constexpr int QT = 2;
   const int run = BF16 ? 64 : 32, rq = run >> 2;       // tokens and quads of a 128-byte run
-  const SamplePlan sp = sample_plan(max(nb, 1), run, A.smp_tokens > 65536 && 8 * (int64_t)c >= nb);
+  const SamplePlan sp = sample_plan(max(nb, 1), run, smp_sample(nb, c, A.smp_tokens));
   const int nsq = sp.runs * rq;
   int pos[QT];
   f32x4 sacc[QT];
@@ -852,17 +852,16 @@ static bool launch_sampled(const SelectArgs &a, hipStream_t s) {
   if (a.N < 4 || a.smp_tokens % SMP_GROUP != 0 || (int64_t)a.smp_tokens * a.smp_parts < a.N || a.smp_tokens > SMP_MAX_TOKENS)
     return false;
   const dim3 grid(a.smp_parts, a.B * a.Hd), block(SMP_THREADS);
-  // The band's list and a bit per token share the LDS: the fewer tokens, the more room for the list.
-  if (a.smp_tokens <= 65536) {
-    if (a.scores_bf16) STS_LAUNCH((select_sampled_kernel<true, 65536, 16384>), grid, block, 0, s, a);
-    else STS_LAUNCH((select_sampled_kernel<false, 65536, 16384>), grid, block, 0, s, a);
-  } else if (a.smp_tokens <= SMP_PART_TOKENS) {
-    if (a.scores_bf16) STS_LAUNCH((select_sampled_kernel<true, SMP_PART_TOKENS, 15360>), grid, block, 0, s, a);
-    else STS_LAUNCH((select_sampled_kernel<false, SMP_PART_TOKENS, 15360>), grid, block, 0, s, a);
-  } else {
-    if (a.scores_bf16) STS_LAUNCH((select_sampled_kernel<true, SMP_MAX_TOKENS, 8192>), grid, block, 0, s, a);
-    else STS_LAUNCH((select_sampled_kernel<false, SMP_MAX_TOKENS, 8192>), grid, block, 0, s, a);
-  }
+  auto form = [&](auto f) {
+    constexpr int F = decltype(f)::value;
+    if (a.scores_bf16) STS_LAUNCH((select_sampled_kernel<true, SMP_TOKENS[F], SMP_LIST[F]>), grid, block, 0, s, a);
+    else STS_LAUNCH((select_sampled_kernel<false, SMP_TOKENS[F], SMP_LIST[F]>), grid, block, 0, s, a);
+  };
+  static_assert(SMP_FORMS == 4, "the forms below");
+  if (a.smp_tokens <= SMP_TOKENS[0]) form(std::integral_constant<int, 0>{});
+  else if (a.smp_tokens <= SMP_TOKENS[1]) form(std::integral_constant<int, 1>{});
+  else if (a.smp_tokens <= SMP_TOKENS[2]) form(std::integral_constant<int, 2>{});
+  else form(std::integral_constant<int, 3>{});
   return true;
 }
 
@@ -879,15 +878,9 @@ hipError_t launch_select_fused(const SelectArgs &a, hipStream_t s) {
   return sts_take_launch_status();
 }
 
-bool select_band_ok(const SelectArgs &a) {
-  return a.page == 1 && a.N > 0 && a.N <= BAND_MAX_N && (a.N % 4) == 0 && (reinterpret_cast<uintptr_t>(a.scores) % 16) == 0 &&
-         (a.agg == nullptr || (reinterpret_cast<uintptr_t>(a.agg) % 16) == 0);
-}
-
 // rows enough for every second CU at least: one workgroup per row, or a few with the words between them cleared first
 hipError_t launch_select_band(const SelectArgs &a, hipStream_t s) {
   if ((size_t)a.B * a.Hd == 0) return hipSuccess;
-  if (!select_band_ok(a)) return hipErrorInvalidValue;
   const StsLaunchEvents ev = g_sts_launch_events;      // the timing aid's pair of events spans both launches
   if (a.smp_parts > 1) {
     g_sts_launch_events = StsLaunchEvents{ev.start, nullptr};

@@ -96,27 +96,25 @@ hipError_t launch_select_small(const SelectArgs &a, hipStream_t) { check_select(
 hipError_t launch_select_rank(const SelectArgs &a, hipStream_t) { check_select(a, "rank"); return hipSuccess; }
 bool select_aggblock_ok(const SelectArgs &a) { return a.page >= 4 && a.page <= 256 && (a.page & (a.page - 1)) == 0 && a.N % a.page == 0; }
 hipError_t launch_select_aggblock(const SelectArgs &a, hipStream_t) { check_select(a, "aggblock"); return hipSuccess; }
-static void check_fused(const SelectArgs &a, const char *what) {
+static void check_sampled(const SelectArgs &a, const char *what) {
   check_select(a, what);
-  in_ws(a.pub, what);
-  const int P = a.part_tokens;
-  if (P != 8192 && P != 16384 && P != 32768) fail("fused: part size");
-  if (a.parts != (a.N + P - 1) / P || a.parts < 1 || a.parts > 256) fail("fused: parts");
-  if (a.page != 1 || a.N <= SEL_FUSED_N || !a.pub) fail("fused: shape");
-  if (a.fused_spin_limit < 0) fail("fused: spin limit");
-  in_ws(reinterpret_cast<const unsigned char *>(a.pub) + (size_t)a.B * a.Hd * 3 * a.parts * 8192, "fused: end");
+  if (a.page != 1 || a.N < 4) fail("sampled: shape");
+  if (a.smp_tokens % 256 != 0 || a.smp_tokens > SMP_MAX_TOKENS || a.smp_parts < 1) fail("sampled: part size");
+  if ((int64_t)a.smp_tokens * a.smp_parts < a.N || (int64_t)a.smp_tokens * (a.smp_parts - 1) >= a.N) fail("sampled: parts");
+  if (a.fused_spin_limit < 0) fail("sampled: spin limit");
+  if (a.smp_parts > 1) {
+    if (!a.pub) fail("sampled: no words to exchange");
+    in_ws(a.pub, what);
+    in_ws(reinterpret_cast<const unsigned char *>(a.pub) + (size_t)a.B * a.Hd * a.smp_parts * SMP_WORDS * 8, "sampled: end");
+  }
 }
-hipError_t launch_select_fused(const SelectArgs &a, hipStream_t) { check_fused(a, "fused"); return hipSuccess; }
-hipError_t launch_select_clear_pub(const SelectArgs &a, hipStream_t) { check_fused(a, "clear published words"); return hipSuccess; }
-bool select_band_ok(const SelectArgs &a) {
-  return a.page == 1 && a.N > 0 && a.N <= BAND_MAX_N && (a.N % 4) == 0 && (reinterpret_cast<uintptr_t>(a.scores) % 16) == 0 &&
-         (a.agg == nullptr || (reinterpret_cast<uintptr_t>(a.agg) % 16) == 0);
-}
-hipError_t launch_select_band(const SelectArgs &a, hipStream_t) {
-  check_select(a, "band");
-  if (!select_band_ok(a)) fail("band: shape");
+hipError_t launch_select_fused(const SelectArgs &a, hipStream_t) { check_sampled(a, "fused"); return hipSuccess; }
+hipError_t launch_select_clear_pub(const SelectArgs &a, hipStream_t) {
+  check_sampled(a, "clear published words");
+  if (a.smp_parts < 2) fail("sampled: cleared for nothing");
   return hipSuccess;
 }
+hipError_t launch_select_band(const SelectArgs &a, hipStream_t) { check_sampled(a, "band"); return hipSuccess; }
 bool select_rowpass_ok(const SelectArgs &a) {
   return a.Tq == 1 && a.kind == STS_SCORES_PROBS && a.page == 1 && a.agg == nullptr && a.N > 0 &&
          (a.N % (a.scores_bf16 ? 8 : 4)) == 0 && (reinterpret_cast<uintptr_t>(a.scores) % 16) == 0;
@@ -142,30 +140,29 @@ hipError_t launch_headmap_clear(unsigned long long *, int, hipStream_t) { ++g_la
 hipError_t launch_headmap_overlap(const int32_t *, const int32_t *, int, int, int, int, int, int, int, unsigned long long *, hipStream_t) { ++g_launches; return hipSuccess; }
 hipError_t launch_headmap_argmax(const unsigned long long *, int, int, int32_t *, hipStream_t) { ++g_launches; return hipSuccess; }
 
-// The sampling plan of the one-pass selection (shared by host and kernel): the sample fits the
-// workgroup's store, covers the row from its first token to within one period of its end, and a
-// plan that claims to fit leaves the band room with margin.
-static void check_band_plans() {
-  for (int run : {32, 64})
-    for (int nb : {8193, 8200, 20000, 40000, 65536, 131072, 131072 - 13, 262144, 262208, 524288})
-      for (uint32_t c : {1u, 100u, 512u, 3000u, 13108u, 26215u, 65536u, 131072u, 524288u}) {
-        if (c > (uint32_t)nb) continue;
-        const BandPlan p = band_plan(nb, c, run);
-        if (p.S < 16 || (p.S & (p.S - 1)) != 0) fail("band plan: sampling period");
-        if (p.ns < 1 || p.ns > 2 * BAND_CAP || p.ns > nb) fail("band plan: sample size");
-        if ((long long)(p.runs - 1) * p.S * run >= nb) fail("band plan: a sampled run starts past the row");
-        if ((long long)p.runs * p.S * run < nb) fail("band plan: the row's end is not within one period of the last run");
-        if (p.s_lo <= p.s_hi) fail("band plan: empty band");
-        if (p.fits && (p.s_lo > p.ns || (long long)p.S * (p.s_lo - (p.s_hi >= 1 ? p.s_hi : 0)) > BAND_CAP)) fail("band plan: fit");
+// The band that the sampled selection is expected to give, by which the host cuts rows: it grows with the budget and
+// stays within the row (and half as much again), and a budget next to the row's length has no lower edge.
+static void check_expected_bands() {
+  for (int64_t nb : {8193, 20000, 65536, 131072, 131072 - 13, 262144, 262208, 524288})
+    for (int tokens : SMP_TOKENS) {
+      int64_t last = 0;
+      for (int64_t c = 1; c <= nb / 2; c = c * 3 / 2 + 1) {
+        const int64_t band = smp_expected_band(nb, c, tokens);
+        if (band < 1 || 2 * band > 3 * nb) fail("expected band: size");
+        if (band < last && 8 * c < nb) fail("expected band: shrinks with the budget");
+        last = band;
       }
-  // the headline budgets fit at 128K tokens; nearly everything kept does not
-  if (!band_plan(131072, 13108, 32).fits || !band_plan(131072, 26215, 64).fits) fail("band plan: 10% / 20% of 128K must fit");
-  if (band_plan(131072, 131000, 32).fits) fail("band plan: a budget next to the row length cannot fit");
+      if (smp_expected_band(nb, nb - 1, tokens) >= 0) fail("expected band: a budget next to the row length");
+    }
+  // the headline budgets fit one workgroup's list at 128K tokens
+  if (smp_expected_band(131072, 13108, 131072) > SMP_LIST[1] || smp_expected_band(131072, 26215, 131072) > SMP_LIST[1]) fail("expected band: 10% / 20% of 128K must fit");
+  for (int f = 0; f < SMP_FORMS; ++f)            // bits, list, histogram, a part's share of one, and the small words
+    if (SMP_TOKENS[f] / 8 + SMP_LIST[f] * 8 + SEL_BINS * 4 + 2048 + 2048 > 160 * 1024) fail("sampled: LDS");
 }
 
 int main() {
   long calls = 0, accepted = 0;
-  check_band_plans();
+  check_expected_bands();
   // made-up, 256-byte aligned "device" addresses: never dereferenced (the launchers are stubs)
   unsigned char *const fake = reinterpret_cast<unsigned char *>(uintptr_t(1) << 40);
   unsigned char *const ws = reinterpret_cast<unsigned char *>(uintptr_t(2) << 40);

@@ -21,7 +21,7 @@ def make(what, B, Hd, Tq, N, seed):
         return s * (torch.rand(B, Hd, 1, N, generator=g) < 0.05)
     if what == "constant":
         return torch.full((B, Hd, Tq, N), 0.25)
-    if what == "levels":                      # two neighbouring levels can fill the band: ranked by plain passes
+    if what == "levels":                      # two neighbouring levels can fill the band: bitmaps hold them
         return torch.randint(0, 5, (B, Hd, 1, N), generator=g).float().expand(B, Hd, Tq, N).contiguous() / 8
     if what == "signed":                      # negative scores, -0 and +0
         s = torch.randn(B, Hd, Tq, N, generator=g)
@@ -34,6 +34,11 @@ def make(what, B, Hd, Tq, N, seed):
     if what == "passages":                    # heavy passages of 200 tokens
         m = (torch.rand(B, Hd, 1, N // 200 + 1, generator=g) < 0.1).float().repeat_interleave(200, -1)[..., :N]
         return s * (1 + 20 * m)
+    if what == "recent":                      # the last tokens are heavy
+        s[..., -N // 20:] *= 50
+        return s
+    if what == "edge":
+        return s * (torch.rand(B, Hd, 1, N, generator=g) < 0.1)
     if what == "inf":                         # infinite scores are kept before all others
         s[..., N // 2::1000] = float("inf")
         return s
@@ -59,6 +64,10 @@ def make(what, B, Hd, Tq, N, seed):
     (1, 128, 2, 16500, 800, True, "softmax"),        # two parts per row, a row for every second CU
     (1, 130, 1, 131072, 65536, True, "softmax"),     # one part of more than 64K tokens: the larger sample
     (1, 130, 1, 100004, 9000, False, "softmax"),     # ... and a small budget there
+    (1, 130, 1, 200001, 9000, True, "softmax"),      # one part of more than 128K tokens
+    (1, 130, 1, 300003, 3000, False, "recent"),      # ... of more than 256K
+    (1, 64, 1, 262144, 45000, False, "stretch"),     # a band that lies in one of four parts and overflows its list
+    (1, 2, 2, 70001, 7000, False, "edge"),           # zeros from about the budget on
 ])
 def test_sampled_selection(B, Hd, Tq, N, k, bf16, what):
     scores = make(what, B, Hd, Tq, N, N + k)
