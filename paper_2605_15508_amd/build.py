@@ -14,7 +14,7 @@ SOURCES = ["api.hip", "attn.hip", "select.hip", "select_sampled.hip", "select_ro
 HEADERS = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "select_util.h"), os.path.join(HERE, "..", "include", "sts.h")]
 
 # -packed-fp32-ops is switched off on purpose: packed fp32 instructions are not to be
-# generated for the test machines.
+# generated for this hardware.
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-Rpass-analysis=kernel-resource-usage"]   # registers, spills and scratch of every kernel, kept beside the objects

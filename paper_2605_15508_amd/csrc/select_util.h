@@ -64,7 +64,7 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return (uint32_t)__bu
 // total. lds_wave_tot needs THREADS/64 words.
 template <int THREADS = SEL_THREADS>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *lds_wave_tot, uint32_t &total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);   // (a scalar register)
   const uint32_t incl = wave_incl_scan(v);
   if (lane == 63) lds_wave_tot[wave] = incl;
   __syncthreads();

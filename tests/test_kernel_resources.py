@@ -43,3 +43,15 @@ def test_selection_kernels_fit_the_occupancy_they_are_planned_for(resources):
             assert v["VGPRs"] <= 96 and v["ScratchSize"] == 0, demangle(k)        # five workgroups per CU or more
         if "select_write_kernel" in k:
             assert v["VGPRs"] <= 128 and v["ScratchSize"] == 0, demangle(k)       # four workgroups per CU
+
+
+def test_the_sampled_and_the_row_selection_fit_their_registers(resources):
+    sampled = {k: v for k, v in resources.items() if "select_sampled_kernel" in k}
+    row = {k: v for k, v in resources.items() if "select_row_kernel" in k}
+    assert len(sampled) == 8 and len(row) == 8
+    for k, v in {**sampled, **row}.items():
+        assert v["VGPRs"] <= 128, demangle(k)                                         # 16 waves per compute unit
+        # (512 threads hold 64 keys each in 128 registers: one loop-invariant word is spilled and reloaded three times)
+        assert v["ScratchSize"] <= (8 if "ILi512ELi16E" in k else 0), demangle(k)
+    for v in sampled.values():
+        assert v["LDS Size"] <= 160 * 1024
