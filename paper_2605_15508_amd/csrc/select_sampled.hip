@@ -36,14 +36,15 @@
 // saturated score), a bitmap holds its tokens and not the list. 16 rows of 1M tokens, a budget at the edge of the
 // zeros: 118 us, 3870 by plain passes; 64 rows of 128K: 74, 520; a constant row with a small budget 58, 435.
 //
-// What bounds it (64 rows of 128K tokens, 5 fp32 scores each, 4 parts per row, lengths between half and all
-// of it, 133 MB): the sample and the pass together 27 us (133 MB and 21 MB of samples, mostly from the
-// last-level cache: the rate of the memory), then latency: 7 us for the histogram exchange, 3.5 us for the
-// keys, 3.5 us for bits and list; kernel 45-48 us. Histograms of all keys at three digit levels, with the
-// part's keys in LDS, took 50: the same 27 us, then 20 us for three levels and 5 us for the list. 16 rows of 1M
-// tokens (335 MB, 16 parts per row): 80 us against 122 for five kernels that stored the aggregate and read it
+// What bounds it (64 rows of 128K tokens, 5 fp32 scores each, 4 parts per row, 168 MB): the sample and the pass
+// together 29 us (168 MB and 21 MB of samples, mostly from the last-level cache: the rate of the memory), then latency:
+// 5 us for the histogram exchange, 3.5 us for the keys, 3 us for bits and list; kernel 43-45 us on scores that the
+// last-level cache holds, 50 on new ones. Histograms of all keys at three digit levels, with the
+// part's keys in LDS, took 54: the same 29 us, then 20 us for three levels and 5 us for the list. 16 rows of 1M
+// tokens (335 MB, 16 parts per row): 78 us against 122 for five kernels that stored the aggregate and read it
 // three times. Rows of one score per token are bound by vector instructions instead (about 60 per 256 tokens
-// and wave), those of scaled logits by the exponentials.
+// and wave), those of scaled logits by the exponentials. A few short rows are bound by the ranking of the sample
+// (7 us of 25 in the kernel for 16 rows of 32768 tokens, which took 1.4 us less with the histograms).
 #include "select_util.h"
 
 namespace {
@@ -539,298 +540,298 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   unsigned long long *pub = Qv > 1 ? static_cast<unsigned long long *>(A.pub) + (size_t)row * A.smp_parts * SMP_WORDS : nullptr;
   // false: the row has to be ranked by plain passes (the threshold is not in the band, or another part's words are late)
   auto rank = [&]() -> bool {
-  uint32_t lo = first_key, last = last_key - first_key;              // keys in question: lo .. lo + last
-  uint32_t krem = 0, G = 0, pre = 0, pre_gt = 0, pre_in = 0, in_bin = 0;
+    uint32_t lo = first_key, last = last_key - first_key;              // keys in question: lo .. lo + last
+    uint32_t krem = 0, G = 0, pre = 0, pre_gt = 0, pre_in = 0, in_bin = 0;
 #pragma unroll 1
-  for (int round = 0;; ++round) {
-    for (int i = tid; i < SMP_HIST; i += T) h[i] = round == 0 ? hb[i] : 0u;
-    auto in_question = [&](uint32_t k, uint32_t n) {
-      if (k - lo <= last) atomicAdd(&h[min((k - lo) >> shift, (uint32_t)SMP_HIST - 1u)], n);
-    };
-    if (round > 0 && !fits) {
-      // The band did not fit this part's list (heavy tokens next to each other, all in one part): its tokens are read again,
-      // and what is left of the keys in question is listed, or, where one key is left, marked. While that is too much as
-      // well, the tokens are only counted.
-      const bool collect = last == 0u || in_bin <= (uint32_t)CAP;
-      if (collect && last == 0u)
-        for (int w = w0; w < w1; ++w) mapL[w] = 0u;
-      if (tid == 0) ctr[0] = 0u;
-      __syncthreads();
-#pragma unroll 1
-      for (int q = tid; 4 * q < m; q += T) {
-        const f32x4 a = agg_quad_any<BF16>(R, n0 + 4 * q, false);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t k = key_of(a[e]), n = 4 * q + e;
-          if ((int)n >= m) continue;
-          if (!collect) {
-            in_question(k, 1u);
-          } else if (k - lo <= last) {
-            const uint32_t at = atomicAdd(&ctr[0], 1u);
-            if (last == 0u) atomicOr(&mapL[n >> 5], 1u << (n & 31u));
-            else if (at < (uint32_t)CAP) list[at] = u32x2{k, n};
-          } else if (k > lo && k <= last_key) {
-            atomicOr(&bits[n >> 5], 1u << (n & 31u));
-          }
-        }
-      }
-      if (collect) {
+    for (int round = 0;; ++round) {
+      for (int i = tid; i < SMP_HIST; i += T) h[i] = round == 0 ? hb[i] : 0u;
+      auto in_question = [&](uint32_t k, uint32_t n) {
+        if (k - lo <= last) atomicAdd(&h[min((k - lo) >> shift, (uint32_t)SMP_HIST - 1u)], n);
+      };
+      if (round > 0 && !fits) {
+        // The band did not fit this part's list (heavy tokens next to each other, all in one part): its tokens are read again,
+        // and what is left of the keys in question is listed, or, where one key is left, marked. While that is too much as
+        // well, the tokens are only counted.
+        const bool collect = last == 0u || in_bin <= (uint32_t)CAP;
+        if (collect && last == 0u)
+          for (int w = w0; w < w1; ++w) mapL[w] = 0u;
+        if (tid == 0) ctr[0] = 0u;
         __syncthreads();
-        fits = true;
-        hasL = last == 0u;
-        hasU = false;
-        keyL = lo;
-        own_L = ctr[0];
-        listed = hasL ? 0u : min(own_L, (uint32_t)CAP);
-      }
-    } else {
-      __syncthreads();
-    }
-    if (round > 0 && (last == 0u || in_bin <= (uint32_t)SMP_CAND)) break;
-    if (fits || round == 0) {
-      for (uint32_t i = tid; i < listed; i += T) in_question(list[i][0], 1u);
-      if (tid == 0 && hasL) in_question(keyL, own_L);
-      if (tid == 0 && hasU) in_question(keyU, own_U);
-    }
-    __syncthreads();
-    uint32_t s_M = own_M;
-    if (Qv > 1) {
-      // threads 0..255: two bins each; in the first round thread 256 sends the part's counts
-      const bool sends = tid < SMP_HIST / 2 || (tid == SMP_HIST / 2 && round == 0);
-      const int word = tid < SMP_HIST / 2 ? round * (SMP_HIST / 2) + tid : SMP_G_WORD;
-      uint32_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;
-      bool complete = true;
-      if (sends) {
-        const uint32_t o0 = tid < SMP_HIST / 2 ? h[2 * tid] : own_G, o1 = tid < SMP_HIST / 2 ? h[2 * tid + 1] : own_M;
-        __hip_atomic_store(&pub[(size_t)part * SMP_WORDS + word],
-                           SMP_VALID | o0 | ((unsigned long long)o1 << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        complete = false;
-        for (int spin = 0; !complete && spin <= A.fused_spin_limit; ++spin) {
-          if (spin) __builtin_amdgcn_s_sleep(2);
-          a0 = o0; a1 = o1; b0 = b1 = 0;
-          complete = true;
-          // eight unconditional loads at a time (this part's own word contributes nothing)
 #pragma unroll 1
-          for (int q0 = 0; q0 < Qv; q0 += 8) {
-            unsigned long long w[8];
+        for (int q = tid; 4 * q < m; q += T) {
+          const f32x4 a = agg_quad_any<BF16>(R, n0 + 4 * q, false);
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-              w[u] = __hip_atomic_load(&pub[(size_t)min(q0 + u, Qv - 1) * SMP_WORDS + word], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              const int q = q0 + u;
-              const bool use = q != part && q < Qv;
-              if (use && !(w[u] & SMP_VALID)) complete = false;
-              const uint32_t w0 = use ? (uint32_t)w[u] & 0xffffffu : 0u, w1 = use ? (uint32_t)(w[u] >> 32) & 0xffffffu : 0u;
-              a0 += w0;
-              a1 += w1;
-              b0 += q < part ? w0 : 0u;
-              b1 += q < part ? w1 : 0u;
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t k = key_of(a[e]), n = 4 * q + e;
+            if ((int)n >= m) continue;
+            if (!collect) {
+              in_question(k, 1u);
+            } else if (k - lo <= last) {
+              const uint32_t at = atomicAdd(&ctr[0], 1u);
+              if (last == 0u) atomicOr(&mapL[n >> 5], 1u << (n & 31u));
+              else if (at < (uint32_t)CAP) list[at] = u32x2{k, n};
+            } else if (k > lo && k <= last_key) {
+              atomicOr(&bits[n >> 5], 1u << (n & 31u));
             }
           }
         }
-      }
-      if (!complete) ctr[2] = 1u;
-      __syncthreads();                                 // every thread has read its bins of h
-      if (tid < SMP_HIST / 2) {
-        h[2 * tid] = a0;
-        h[2 * tid + 1] = a1;
-        hb[2 * tid] = b0;
-        hb[2 * tid + 1] = b1;
-      } else if (sends) {
-        ctr[3] = a0;                                   // certain tokens of the row
-        ctr[4] = a1;                                   // band tokens of the row
-        ctr[5] = b0;                                   // certain tokens of the earlier parts
-      }
-      __syncthreads();
-      if (ctr[2]) return false;
-      if (round == 0) {
-        G = ctr[3];
-        s_M = ctr[4];
-        pre = ctr[5];
-      }
-    } else if (round == 0) {
-      G = own_G;
-    }
-    if (round == 0) {
-      if (G >= c || G + s_M < c) return false;         // the same in every part of the row
-      krem = c - G;
-    }
-    // every wave finds the bin by itself: lane l owns bins 8 l .. 8 l + 7
-    uint32_t x[8], y[8], sx = 0, sy = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      x[i] = h[8 * lane + i];
-      y[i] = Qv > 1 ? hb[8 * lane + i] : 0u;
-      sx += x[i];
-      sy += y[i];
-    }
-    const uint32_t incl = wave_incl_scan(sx);
-    uint32_t above = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63) - incl;   // keys in bins of higher lanes
-    const uint64_t has = ballot64(above < krem && above + sx >= krem);
-    const int owner = has ? __builtin_ctzll(has) : 0;
-    uint32_t bin = 0, left = krem, held = 0, gt = lane > owner ? sy : 0u, at = 0;
-    if (lane == owner) {
-#pragma unroll
-      for (int i = 7; i >= 0; --i) {
-        if (above < krem && above + x[i] >= krem) {
-          bin = 8 * lane + i;
-          left = krem - above;
-          held = x[i];
-          at = y[i];
-        } else if (above < krem) {
-          gt += y[i];                                  // a bin above the threshold's
+        if (collect) {
+          __syncthreads();
+          fits = true;
+          hasL = last == 0u;
+          hasU = false;
+          keyL = lo;
+          own_L = ctr[0];
+          listed = hasL ? 0u : min(own_L, (uint32_t)CAP);
         }
-        above += x[i];
+      } else {
+        __syncthreads();
       }
-    }
-    bin = (uint32_t)__builtin_amdgcn_readlane((int)bin, owner);
-    krem = (uint32_t)__builtin_amdgcn_readlane((int)left, owner);
-    in_bin = (uint32_t)__builtin_amdgcn_readlane((int)held, owner);
-    pre_in = (uint32_t)__builtin_amdgcn_readlane((int)at, owner);
-    pre_gt += wave_sum(gt);
-    lo += bin << shift;
-    last = bin == (uint32_t)SMP_HIST - 1u ? last - (bin << shift) : (1u << shift) - 1u;   // the last bin has no upper end
-    // one key or few are left at the latest after round SMP_ROUNDS - 1
-    if (fits && (last == 0u || in_bin <= (uint32_t)SMP_CAND)) break;
-    shift = max(0, 32 - __clz((int)last) - 9);
-    __syncthreads();                                   // every wave has read the histogram
-  }
-  uint32_t Tk = lo, r = krem, E = in_bin, pre_eq = pre_in;
-  if (last != 0u) {
-    // few keys share the threshold's bin: they are exchanged one by one and ranked against each other
-    auto add = [&](uint32_t k) {
-      if (k - lo <= last) {
-        const uint32_t s = atomicAdd(&ctr[7], 1u);
-        if (s < (uint32_t)SMP_CAND) cand[s] = u32x2{k, 0u};
+      if (round > 0 && (last == 0u || in_bin <= (uint32_t)SMP_CAND)) break;
+      if (fits || round == 0) {
+        for (uint32_t i = tid; i < listed; i += T) in_question(list[i][0], 1u);
+        if (tid == 0 && hasL) in_question(keyL, own_L);
+        if (tid == 0 && hasU) in_question(keyU, own_U);
       }
-    };
-    for (uint32_t i = tid; i < listed; i += T) add(list[i][0]);
-    if (hasL && (uint32_t)tid < min(own_L, (uint32_t)SMP_CAND)) add(keyL);
-    if (hasU && (uint32_t)tid < min(own_U, (uint32_t)SMP_CAND)) add(keyU);
-    __syncthreads();
-    // The other parts' keys follow the own ones under a counter of their own (ctr[8]): ctr[7] and the own entries,
-    // which one wave publishes while the others already poll, stay as they are from the barrier on.
-    const uint32_t own = min(ctr[7], (uint32_t)SMP_CAND);
-    if (Qv > 1) {
-      if (tid < SMP_CAND)
-        __hip_atomic_store(&pub[(size_t)part * SMP_WORDS + SMP_CAND_WORD + tid],
-                           SMP_VALID | ((unsigned long long)own << 32) | ((uint32_t)tid < own ? cand[tid][0] : 0u), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-      bool complete = true;
-      for (int q = tid / SMP_CAND; q < Qv; q += T / SMP_CAND) {
-        if (q == part) continue;
-        unsigned long long w = 0;
-        for (int spin = 0; !(w & SMP_VALID) && spin <= A.fused_spin_limit; ++spin) {
-          if (spin) __builtin_amdgcn_s_sleep(2);
-          w = __hip_atomic_load(&pub[(size_t)q * SMP_WORDS + SMP_CAND_WORD + tid % SMP_CAND], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        if (!(w & SMP_VALID)) complete = false;
-        else if ((uint32_t)(tid % SMP_CAND) < ((uint32_t)(w >> 32) & 127u)) {
-          const uint32_t s = own + atomicAdd(&ctr[8], 1u);
-          if (s < (uint32_t)SMP_CAND) cand[s] = u32x2{(uint32_t)w, 0x80000000u | (uint32_t)q};
-        }
-      }
-      if (!complete) ctr[2] = 1u;
       __syncthreads();
-      if (ctr[2]) return false;
-    }
-    // every wave by itself: lane i ranks candidate i
-    const uint32_t n = min(in_bin, (uint32_t)SMP_CAND);
-    const u32x2 mine = cand[min((uint32_t)lane, n - 1u)];
-    uint32_t g = 0, e = 0;
-    for (uint32_t q = 0; q < n; ++q) {
-      const uint32_t k = cand[q][0];
-      g += k > mine[0] ? 1u : 0u;
-      e += k == mine[0] ? 1u : 0u;
-    }
-    const int win = __builtin_ctzll(ballot64((uint32_t)lane < n && g < krem && g + e >= krem) | (1ull << 63));
-    Tk = (uint32_t)__builtin_amdgcn_readlane((int)mine[0], win);
-    r = krem - (uint32_t)__builtin_amdgcn_readlane((int)g, win);
-    E = (uint32_t)__builtin_amdgcn_readlane((int)e, win);
-    const bool early = (uint32_t)lane < n && (mine[1] >> 31) && (int)(mine[1] & 0x7fffffffu) < part;
-    pre_gt += (uint32_t)__builtin_popcountll(ballot64(early && mine[0] > Tk));
-    pre_eq = (uint32_t)__builtin_popcountll(ballot64(early && mine[0] == Tk));
-  }
-  pre += pre_gt + min(pre_eq, r);                      // kept tokens of the earlier parts
-
-  // ---- the part's kept tokens: bits of the band's. Of the tokens equal to T the first `quota` of this part
-  // are kept: all of them, unless the row has more than r.
-  const uint32_t quota = r > pre_eq ? r - pre_eq : 0u;
-  const bool all_eq = r >= E, of_map = (hasL && Tk == keyL) || (hasU && Tk == keyU);
-  uint32_t n_eq = 0;
-  for (uint32_t i = tid; i < listed; i += T) {
-    const u32x2 x = list[i];
-    if (x[0] > Tk || (x[0] == Tk && all_eq)) atomicOr(&bits[x[1] >> 5], 1u << (x[1] & 31u));
-    n_eq += x[0] == Tk ? 1u : 0u;
-  }
-  if (!all_eq && !of_map && quota > 0u) {
-    // the lowest tokens of the list's equal ones: their reversed ids are ranked like keys, 11 + 9 bits
-    static_assert(TOK <= 1 << 20, "token ids of a part");
-    constexpr uint32_t REV = (1u << 20) - 1u;
-    const uint32_t own_eq = block_sum1<T>(n_eq, red);
-    uint32_t cut = 0;
-    if (own_eq > quota) {
-      uint32_t da, ra, db, rb;
-      for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
-      __syncthreads();
-      for (uint32_t i = tid; i < listed; i += T)
-        if (list[i][0] == Tk) atomicAdd(&h[(REV - list[i][1]) >> 9], 1u);
-      __syncthreads();
-      find_digit<SEL_BINS, T>(h, quota, tmp, da, ra);
-      for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
-      __syncthreads();
-      for (uint32_t i = tid; i < listed; i += T)
-        if (list[i][0] == Tk && ((REV - list[i][1]) >> 9) == da) atomicAdd(&h[(REV - list[i][1]) & 511u], 1u);
-      __syncthreads();
-      find_digit<SEL_BINS, T>(h, ra, tmp, db, rb);
-      cut = (da << 9) | db;
-    }
-    for (uint32_t i = tid; i < listed; i += T)
-      if (list[i][0] == Tk && REV - list[i][1] >= cut) atomicOr(&bits[list[i][1] >> 5], 1u << (list[i][1] & 31u));
-  }
-  __syncthreads();
-  if (hasL || hasU) {
-    auto take = [&](uint32_t k, uint32_t n, const uint32_t *map) {
-      if (k < Tk || (k == Tk && quota == 0u)) return;
-      if (k > Tk || all_eq || n <= quota) {
-        for (int w = w0; w < w1; ++w) bits[w] |= map[w];
-      } else {                                         // the first `quota` of the bits, by words in order
-        uint32_t n_own = 0, total;
-        for (int w = w0; w < w1; ++w) n_own += (uint32_t)__builtin_popcount(map[w]);
-        uint32_t before = block_excl_scan<T>(n_own, tmp, total);
-        for (int w = w0; w < w1; ++w)
-          for (uint32_t rest = map[w]; rest && before < quota; rest &= rest - 1u, ++before) bits[w] |= rest & (0u - rest);
-      }
-    };
-    if (hasL) take(keyL, own_L, mapL);
-    if (hasU) take(keyU, own_U, mapU);
-    __syncthreads();
-  }
-
-  // ---- the list: set bits in token order. A thread owns a run of words, one block scan gives its first place; the
-  // tokens are staged in LDS (the band list is done with) and copied out coalesced, once per target head.
-  uint32_t mine = 0, total;
-  for (int w = w0; w < w1; ++w) mine += (uint32_t)__builtin_popcount(bits[w]);
-  const uint32_t first = block_excl_scan<T>(mine, tmp, total);
-  total = pre < c ? min(total, c - pre) : 0u;          // unchanged for a consistent state; keeps a bad one in bounds
-  int32_t *staged = reinterpret_cast<int32_t *>(store);
+      uint32_t s_M = own_M;
+      if (Qv > 1) {
+        // threads 0..255: two bins each; in the first round thread 256 sends the part's counts
+        const bool sends = tid < SMP_HIST / 2 || (tid == SMP_HIST / 2 && round == 0);
+        const int word = tid < SMP_HIST / 2 ? round * (SMP_HIST / 2) + tid : SMP_G_WORD;
+        uint32_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;
+        bool complete = true;
+        if (sends) {
+          const uint32_t o0 = tid < SMP_HIST / 2 ? h[2 * tid] : own_G, o1 = tid < SMP_HIST / 2 ? h[2 * tid + 1] : own_M;
+          __hip_atomic_store(&pub[(size_t)part * SMP_WORDS + word],
+                             SMP_VALID | o0 | ((unsigned long long)o1 << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          complete = false;
+          for (int spin = 0; !complete && spin <= A.fused_spin_limit; ++spin) {
+            if (spin) __builtin_amdgcn_s_sleep(2);
+            a0 = o0; a1 = o1; b0 = b1 = 0;
+            complete = true;
+            // eight unconditional loads at a time (this part's own word contributes nothing)
 #pragma unroll 1
-  for (uint32_t base = 0; base < total; base += 2 * CAP) {
-    uint32_t p = first;
-    if (p < base + 2 * CAP && p + mine > base)
-      for (int w = w0; w < w1; ++w)
-        for (uint32_t rest = bits[w]; rest; rest &= rest - 1u, ++p)
-          if (p - base < 2u * CAP) staged[p - base] = n0 + 32 * w + __builtin_ctz(rest);
-    __syncthreads();
-    const uint32_t cnt = min(total - base, 2u * CAP);
-    for (int ti = t0; ti < t1; ++ti) {
-      int32_t *dst = A.indices + ((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + pre + base;
-      for (uint32_t i = tid; i < cnt; i += T) dst[i] = staged[i];
+            for (int q0 = 0; q0 < Qv; q0 += 8) {
+              unsigned long long w[8];
+#pragma unroll
+              for (int u = 0; u < 8; ++u)
+                w[u] = __hip_atomic_load(&pub[(size_t)min(q0 + u, Qv - 1) * SMP_WORDS + word], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+              for (int u = 0; u < 8; ++u) {
+                const int q = q0 + u;
+                const bool use = q != part && q < Qv;
+                if (use && !(w[u] & SMP_VALID)) complete = false;
+                const uint32_t w0 = use ? (uint32_t)w[u] & 0xffffffu : 0u, w1 = use ? (uint32_t)(w[u] >> 32) & 0xffffffu : 0u;
+                a0 += w0;
+                a1 += w1;
+                b0 += q < part ? w0 : 0u;
+                b1 += q < part ? w1 : 0u;
+              }
+            }
+          }
+        }
+        if (!complete) ctr[2] = 1u;
+        __syncthreads();                                 // every thread has read its bins of h
+        if (tid < SMP_HIST / 2) {
+          h[2 * tid] = a0;
+          h[2 * tid + 1] = a1;
+          hb[2 * tid] = b0;
+          hb[2 * tid + 1] = b1;
+        } else if (sends) {
+          ctr[3] = a0;                                   // certain tokens of the row
+          ctr[4] = a1;                                   // band tokens of the row
+          ctr[5] = b0;                                   // certain tokens of the earlier parts
+        }
+        __syncthreads();
+        if (ctr[2]) return false;
+        if (round == 0) {
+          G = ctr[3];
+          s_M = ctr[4];
+          pre = ctr[5];
+        }
+      } else if (round == 0) {
+        G = own_G;
+      }
+      if (round == 0) {
+        if (G >= c || G + s_M < c) return false;         // the same in every part of the row
+        krem = c - G;
+      }
+      // every wave finds the bin by itself: lane l owns bins 8 l .. 8 l + 7
+      uint32_t x[8], y[8], sx = 0, sy = 0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        x[i] = h[8 * lane + i];
+        y[i] = Qv > 1 ? hb[8 * lane + i] : 0u;
+        sx += x[i];
+        sy += y[i];
+      }
+      const uint32_t incl = wave_incl_scan(sx);
+      uint32_t above = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63) - incl;   // keys in bins of higher lanes
+      const uint64_t has = ballot64(above < krem && above + sx >= krem);
+      const int owner = has ? __builtin_ctzll(has) : 0;
+      uint32_t bin = 0, left = krem, held = 0, gt = lane > owner ? sy : 0u, at = 0;
+      if (lane == owner) {
+#pragma unroll
+        for (int i = 7; i >= 0; --i) {
+          if (above < krem && above + x[i] >= krem) {
+            bin = 8 * lane + i;
+            left = krem - above;
+            held = x[i];
+            at = y[i];
+          } else if (above < krem) {
+            gt += y[i];                                  // a bin above the threshold's
+          }
+          above += x[i];
+        }
+      }
+      bin = (uint32_t)__builtin_amdgcn_readlane((int)bin, owner);
+      krem = (uint32_t)__builtin_amdgcn_readlane((int)left, owner);
+      in_bin = (uint32_t)__builtin_amdgcn_readlane((int)held, owner);
+      pre_in = (uint32_t)__builtin_amdgcn_readlane((int)at, owner);
+      pre_gt += wave_sum(gt);
+      lo += bin << shift;
+      last = bin == (uint32_t)SMP_HIST - 1u ? last - (bin << shift) : (1u << shift) - 1u;   // the last bin has no upper end
+      // one key or few are left at the latest after round SMP_ROUNDS - 1
+      if (fits && (last == 0u || in_bin <= (uint32_t)SMP_CAND)) break;
+      shift = max(0, 32 - __clz((int)last) - 9);
+      __syncthreads();                                   // every wave has read the histogram
+    }
+    uint32_t Tk = lo, r = krem, E = in_bin, pre_eq = pre_in;
+    if (last != 0u) {
+      // few keys share the threshold's bin: they are exchanged one by one and ranked against each other
+      auto add = [&](uint32_t k) {
+        if (k - lo <= last) {
+          const uint32_t s = atomicAdd(&ctr[7], 1u);
+          if (s < (uint32_t)SMP_CAND) cand[s] = u32x2{k, 0u};
+        }
+      };
+      for (uint32_t i = tid; i < listed; i += T) add(list[i][0]);
+      if (hasL && (uint32_t)tid < min(own_L, (uint32_t)SMP_CAND)) add(keyL);
+      if (hasU && (uint32_t)tid < min(own_U, (uint32_t)SMP_CAND)) add(keyU);
+      __syncthreads();
+      // The other parts' keys follow the own ones under a counter of their own (ctr[8]): ctr[7] and the own entries,
+      // which one wave publishes while the others already poll, stay as they are from the barrier on.
+      const uint32_t own = min(ctr[7], (uint32_t)SMP_CAND);
+      if (Qv > 1) {
+        if (tid < SMP_CAND)
+          __hip_atomic_store(&pub[(size_t)part * SMP_WORDS + SMP_CAND_WORD + tid],
+                             SMP_VALID | ((unsigned long long)own << 32) | ((uint32_t)tid < own ? cand[tid][0] : 0u), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+        bool complete = true;
+        for (int q = tid / SMP_CAND; q < Qv; q += T / SMP_CAND) {
+          if (q == part) continue;
+          unsigned long long w = 0;
+          for (int spin = 0; !(w & SMP_VALID) && spin <= A.fused_spin_limit; ++spin) {
+            if (spin) __builtin_amdgcn_s_sleep(2);
+            w = __hip_atomic_load(&pub[(size_t)q * SMP_WORDS + SMP_CAND_WORD + tid % SMP_CAND], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+          if (!(w & SMP_VALID)) complete = false;
+          else if ((uint32_t)(tid % SMP_CAND) < ((uint32_t)(w >> 32) & 127u)) {
+            const uint32_t s = own + atomicAdd(&ctr[8], 1u);
+            if (s < (uint32_t)SMP_CAND) cand[s] = u32x2{(uint32_t)w, 0x80000000u | (uint32_t)q};
+          }
+        }
+        if (!complete) ctr[2] = 1u;
+        __syncthreads();
+        if (ctr[2]) return false;
+      }
+      // every wave by itself: lane i ranks candidate i
+      const uint32_t n = min(in_bin, (uint32_t)SMP_CAND);
+      const u32x2 mine = cand[min((uint32_t)lane, n - 1u)];
+      uint32_t g = 0, e = 0;
+      for (uint32_t q = 0; q < n; ++q) {
+        const uint32_t k = cand[q][0];
+        g += k > mine[0] ? 1u : 0u;
+        e += k == mine[0] ? 1u : 0u;
+      }
+      const int win = __builtin_ctzll(ballot64((uint32_t)lane < n && g < krem && g + e >= krem) | (1ull << 63));
+      Tk = (uint32_t)__builtin_amdgcn_readlane((int)mine[0], win);
+      r = krem - (uint32_t)__builtin_amdgcn_readlane((int)g, win);
+      E = (uint32_t)__builtin_amdgcn_readlane((int)e, win);
+      const bool early = (uint32_t)lane < n && (mine[1] >> 31) && (int)(mine[1] & 0x7fffffffu) < part;
+      pre_gt += (uint32_t)__builtin_popcountll(ballot64(early && mine[0] > Tk));
+      pre_eq = (uint32_t)__builtin_popcountll(ballot64(early && mine[0] == Tk));
+    }
+    pre += pre_gt + min(pre_eq, r);                      // kept tokens of the earlier parts
+
+    // ---- the part's kept tokens: bits of the band's. Of the tokens equal to T the first `quota` of this part
+    // are kept: all of them, unless the row has more than r.
+    const uint32_t quota = r > pre_eq ? r - pre_eq : 0u;
+    const bool all_eq = r >= E, of_map = (hasL && Tk == keyL) || (hasU && Tk == keyU);
+    uint32_t n_eq = 0;
+    for (uint32_t i = tid; i < listed; i += T) {
+      const u32x2 x = list[i];
+      if (x[0] > Tk || (x[0] == Tk && all_eq)) atomicOr(&bits[x[1] >> 5], 1u << (x[1] & 31u));
+      n_eq += x[0] == Tk ? 1u : 0u;
+    }
+    if (!all_eq && !of_map && quota > 0u) {
+      // the lowest tokens of the list's equal ones: their reversed ids are ranked like keys, 11 + 9 bits
+      static_assert(TOK <= 1 << 20, "token ids of a part");
+      constexpr uint32_t REV = (1u << 20) - 1u;
+      const uint32_t own_eq = block_sum1<T>(n_eq, red);
+      uint32_t cut = 0;
+      if (own_eq > quota) {
+        uint32_t da, ra, db, rb;
+        for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
+        __syncthreads();
+        for (uint32_t i = tid; i < listed; i += T)
+          if (list[i][0] == Tk) atomicAdd(&h[(REV - list[i][1]) >> 9], 1u);
+        __syncthreads();
+        find_digit<SEL_BINS, T>(h, quota, tmp, da, ra);
+        for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
+        __syncthreads();
+        for (uint32_t i = tid; i < listed; i += T)
+          if (list[i][0] == Tk && ((REV - list[i][1]) >> 9) == da) atomicAdd(&h[(REV - list[i][1]) & 511u], 1u);
+        __syncthreads();
+        find_digit<SEL_BINS, T>(h, ra, tmp, db, rb);
+        cut = (da << 9) | db;
+      }
+      for (uint32_t i = tid; i < listed; i += T)
+        if (list[i][0] == Tk && REV - list[i][1] >= cut) atomicOr(&bits[list[i][1] >> 5], 1u << (list[i][1] & 31u));
     }
     __syncthreads();
-  }
-  return true;
+    if (hasL || hasU) {
+      auto take = [&](uint32_t k, uint32_t n, const uint32_t *map) {
+        if (k < Tk || (k == Tk && quota == 0u)) return;
+        if (k > Tk || all_eq || n <= quota) {
+          for (int w = w0; w < w1; ++w) bits[w] |= map[w];
+        } else {                                         // the first `quota` of the bits, by words in order
+          uint32_t n_own = 0, total;
+          for (int w = w0; w < w1; ++w) n_own += (uint32_t)__builtin_popcount(map[w]);
+          uint32_t before = block_excl_scan<T>(n_own, tmp, total);
+          for (int w = w0; w < w1; ++w)
+            for (uint32_t rest = map[w]; rest && before < quota; rest &= rest - 1u, ++before) bits[w] |= rest & (0u - rest);
+        }
+      };
+      if (hasL) take(keyL, own_L, mapL);
+      if (hasU) take(keyU, own_U, mapU);
+      __syncthreads();
+    }
+
+    // ---- the list: set bits in token order. A thread owns a run of words, one block scan gives its first place; the
+    // tokens are staged in LDS (the band list is done with) and copied out coalesced, once per target head.
+    uint32_t mine = 0, total;
+    for (int w = w0; w < w1; ++w) mine += (uint32_t)__builtin_popcount(bits[w]);
+    const uint32_t first = block_excl_scan<T>(mine, tmp, total);
+    total = pre < c ? min(total, c - pre) : 0u;          // unchanged for a consistent state; keeps a bad one in bounds
+    int32_t *staged = reinterpret_cast<int32_t *>(store);
+#pragma unroll 1
+    for (uint32_t base = 0; base < total; base += 2 * CAP) {
+      uint32_t p = first;
+      if (p < base + 2 * CAP && p + mine > base)
+        for (int w = w0; w < w1; ++w)
+          for (uint32_t rest = bits[w]; rest; rest &= rest - 1u, ++p)
+            if (p - base < 2u * CAP) staged[p - base] = n0 + 32 * w + __builtin_ctz(rest);
+      __syncthreads();
+      const uint32_t cnt = min(total - base, 2u * CAP);
+      for (int ti = t0; ti < t1; ++ti) {
+        int32_t *dst = A.indices + ((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + pre + base;
+        for (uint32_t i = tid; i < cnt; i += T) dst[i] = staged[i];
+      }
+      __syncthreads();
+    }
+    return true;
   };
   if (!rank()) rank_by_passes<BF16, T>(A, R, bt, nb, c, t0, t1, h, tmp, n0, min(n0 + P, nb));
 }
