@@ -172,7 +172,7 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
   };
   // the bin of the rank-th largest of the keys counted in h, and what is left of the rank in it
   auto find = [&](uint32_t rank, uint32_t &bin, uint32_t &left) {
-    find_digit<SEL_BINS, T>(h, rank, tmp, bin, left);
+    find_digit<SEL_BINS, T, true>(h, rank, tmp, bin, left);
     bin = (uint32_t)__builtin_amdgcn_readfirstlane((int)bin);
     left = (uint32_t)__builtin_amdgcn_readfirstlane((int)left);
   };
@@ -205,7 +205,7 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
       uint32_t sum = 0;
 #pragma unroll
       for (int i = 0; i < PER; ++i) sum += h[tid * PER + i];
-      (void)block_excl_scan<T>(sum, tmp, ns);
+      (void)block_excl_scan<T, true>(sum, tmp, ns);
       ns = (uint32_t)__builtin_amdgcn_readfirstlane((int)ns);
     }
     // 5 standard deviations of the sample count, as if the tokens were independent: a stretch of heavy tokens longer
@@ -364,13 +364,13 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
   if (!all_eq) {
     uint32_t n = 0;
     for (int w = w0; w < w1; ++w) n += (uint32_t)__builtin_popcount(store[w]);
-    uint32_t before = block_excl_scan<T>(n, tmp, total);
+    uint32_t before = block_excl_scan<T, true>(n, tmp, total);
     for (int w = w0; w < w1; ++w)
       for (uint32_t rest = store[w]; rest && before < r; rest &= rest - 1u, ++before) bits[w] |= rest & (0u - rest);
   }
   uint32_t mine = 0;
   for (int w = w0; w < w1; ++w) mine += (uint32_t)__builtin_popcount(bits[w]);
-  const uint32_t first = block_excl_scan<T>(mine, tmp, total);         // (its barriers free `store`)
+  const uint32_t first = block_excl_scan<T, true>(mine, tmp, total);         // (its barriers free `store`)
   total = min(total, c);                               // total == c for a consistent state
   int32_t *staged = reinterpret_cast<int32_t *>(store);
 #pragma unroll 1

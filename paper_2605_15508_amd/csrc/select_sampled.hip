@@ -162,7 +162,7 @@ __device__ __forceinline__ Band sample_band(const SamplePlan &sp, int run, int n
     h0 = h[2 * tid];
     h1 = h[2 * tid + 1];
     uint32_t in_window;
-    const uint32_t excl = block_excl_scan<T>(h0 + h1, tmp, in_window);
+    const uint32_t excl = block_excl_scan<T, true>(h0 + h1, tmp, in_window);
     above = over + in_window - excl - (h0 + h1);
     return uniform(in_window);
   };
@@ -778,13 +778,13 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
         for (uint32_t i = tid; i < listed; i += T)
           if (list[i][0] == Tk) atomicAdd(&h[(REV - list[i][1]) >> 9], 1u);
         __syncthreads();
-        find_digit<SEL_BINS, T>(h, quota, tmp, da, ra);
+        find_digit<SEL_BINS, T, true>(h, quota, tmp, da, ra);
         for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
         __syncthreads();
         for (uint32_t i = tid; i < listed; i += T)
           if (list[i][0] == Tk && ((REV - list[i][1]) >> 9) == da) atomicAdd(&h[(REV - list[i][1]) & 511u], 1u);
         __syncthreads();
-        find_digit<SEL_BINS, T>(h, ra, tmp, db, rb);
+        find_digit<SEL_BINS, T, true>(h, ra, tmp, db, rb);
         cut = (da << 9) | db;
       }
       for (uint32_t i = tid; i < listed; i += T)
@@ -799,7 +799,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
         } else {                                         // the first `quota` of the bits, by words in order
           uint32_t n_own = 0, total;
           for (int w = w0; w < w1; ++w) n_own += (uint32_t)__builtin_popcount(map[w]);
-          uint32_t before = block_excl_scan<T>(n_own, tmp, total);
+          uint32_t before = block_excl_scan<T, true>(n_own, tmp, total);
           for (int w = w0; w < w1; ++w)
             for (uint32_t rest = map[w]; rest && before < quota; rest &= rest - 1u, ++before) bits[w] |= rest & (0u - rest);
         }
@@ -813,7 +813,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
     // tokens are staged in LDS (the band list is done with) and copied out coalesced, once per target head.
     uint32_t mine = 0, total;
     for (int w = w0; w < w1; ++w) mine += (uint32_t)__builtin_popcount(bits[w]);
-    const uint32_t first = block_excl_scan<T>(mine, tmp, total);
+    const uint32_t first = block_excl_scan<T, true>(mine, tmp, total);
     total = pre < c ? min(total, c - pre) : 0u;          // unchanged for a consistent state; keeps a bad one in bounds
     int32_t *staged = reinterpret_cast<int32_t *>(store);
 #pragma unroll 1

@@ -61,10 +61,12 @@ __device__ __forceinline__ uint32_t lanes_before(uint64_t mask, uint32_t base) {
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), 63); }
 
 // exclusive prefix sum of one value per thread over a THREADS-thread block; also returns the
-// total. lds_wave_tot needs THREADS/64 words.
-template <int THREADS = SEL_THREADS>
+// total. lds_wave_tot needs THREADS/64 words. SCALAR: the wave's number in a scalar register, which the kernels that
+// hold a row in registers need (28 bytes of scratch per lane less); the pool kernels are 5% slower with it (16 rows of
+// 1M tokens, 256 kept: 94.1 against 89.8 us).
+template <int THREADS = SEL_THREADS, bool SCALAR = false>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *lds_wave_tot, uint32_t &total) {
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);   // (a scalar register)
+  const int lane = threadIdx.x & 63, wave = SCALAR ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : (int)(threadIdx.x >> 6);
   const uint32_t incl = wave_incl_scan(v);
   if (lane == 63) lds_wave_tot[wave] = incl;
   __syncthreads();
@@ -83,7 +85,7 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *lds_wa
 // Walk a digit histogram from the top: the digit holding the krem-th largest key of the
 // candidates, and how many keys of that digit are still wanted. Requires 1 <= krem <= total.
 // lds_tmp needs THREADS/64 + 2 words; the result lands in its last two.
-template <int NBINS, int THREADS = SEL_THREADS>
+template <int NBINS, int THREADS = SEL_THREADS, bool SCALAR = false>
 __device__ __forceinline__ void find_digit(const uint32_t *hist, uint32_t krem, uint32_t *lds_tmp,
                                            uint32_t &digit, uint32_t &krem_next) {
   constexpr int PER = NBINS / THREADS;
@@ -95,7 +97,7 @@ __device__ __forceinline__ void find_digit(const uint32_t *hist, uint32_t krem, 
     sum += loc[i];
   }
   uint32_t total;
-  const uint32_t excl = block_excl_scan<THREADS>(sum, lds_tmp, total);
+  const uint32_t excl = block_excl_scan<THREADS, SCALAR>(sum, lds_tmp, total);
   uint32_t above = total - excl - sum;   // keys in bins owned by higher threads
 #pragma unroll
   for (int i = PER - 1; i >= 0; --i) {
@@ -267,7 +269,7 @@ __device__ __forceinline__ f32x4 shifted_quad(f32x4 y, int d) {
 // quad's that starts there) come out as some score of the row and are the caller's to ignore.
 // inside (wave-uniform): every quad of the wave lies inside the row. Up to eight rows are in flight; the rows are
 // told apart by scalar branches and not by a copy of the code for every number of rows: the sampled selection, which
-// calls this at three places, is 61 KB of instructions with it and was 400 (the instruction cache holds 64): 64 rows of
+// calls this at four places, is 77 KB of instructions and was 400 (the instruction cache holds 64). At 61 KB: 64 rows of
 // 128K tokens 51.1 -> 50.2 us and, with the caches flushed, 58.4 -> 57.1, 16 rows of 33001 28.8 -> 27.5 and 38.1 -> 35.7.
 template <bool BF16>
 __device__ __forceinline__ f32x4 agg_quad_any(const AggRow &R, int n, bool inside) {
@@ -369,7 +371,7 @@ __device__ __forceinline__ void rank_by_passes(const SelectArgs &A, const AggRow
     }
     __syncthreads();
     uint32_t digit, knext;
-    find_digit<SEL_BINS, THREADS>(h, krem, tmp, digit, knext);
+    find_digit<SEL_BINS, THREADS, true>(h, krem, tmp, digit, knext);
     if (level == 0) d0 = digit;
     else if (level == 1) pre01 = (d0 << SEL_BITS1) | digit;
     else d2 = digit;
@@ -391,7 +393,7 @@ __device__ __forceinline__ void rank_by_passes(const SelectArgs &A, const AggRow
       eq_mask |= (in && key == Tk) ? 1u << e : 0u;
     }
     uint32_t total;
-    const uint32_t excl = block_excl_scan<THREADS>(__builtin_popcount(gt_mask) | (__builtin_popcount(eq_mask) << 16), tmp, total);
+    const uint32_t excl = block_excl_scan<THREADS, true>(__builtin_popcount(gt_mask) | (__builtin_popcount(eq_mask) << 16), tmp, total);
     uint32_t g = gbase + (excl & 0xffffu), q = qbase + (excl >> 16);
     for (uint32_t rest = gt_mask | eq_mask; rest; rest &= rest - 1) {
       const int i = __builtin_ctz(rest);
