@@ -100,7 +100,7 @@ def read_traffic(kernel: str, workload: str, version: int):
 
 
 def cpu_baseline(w, idx, cnt, out_s, page=1, budget_s=25.0, scores=None, lse=None):
-    """Time the CPU oracle (as it stands, untuned) on this box's host cores on a bounded sample
+    """Time the CPU oracle (as it stands, untuned) on this machine's host cores on a bounded sample
     of the same workload, and compare what it computes with what the GPU computed (outside any
     timed region). Returns (cpu_baseline object, parity object)."""
     import numpy as np
