@@ -258,6 +258,7 @@ sts_status run_attn(const sts_attn_params *p, int sparse, hipStream_t s, void *w
   a.direct = (pl.num_splits == 1) ? 1 : 0;
   a.num_units = pl.num_units;
   a.num_splits = pl.num_splits;
+  a.z_rounds = (p->B + STS_GRID_Z - 1) / STS_GRID_Z;
   a.scale = p->scale;
   a.scale_log2 = p->scale * 1.44269504088896340736f;
   a.part_o = static_cast<float *>(ws);

@@ -6,9 +6,9 @@
 //
 // Work decomposition. A unit is the set of query heads of one KV group that share one index
 // row; its nheads*Tq query rows are padded to NQ tiles of 16. The unit's index row is cut
-// into num_splits contiguous pieces; one workgroup of 4 waves owns one (batch, unit, split)
-// and its waves take alternating 32-key tiles. Each wave keeps its own online-softmax state
-// (fp32), the 4 waves are merged through LDS and one partial (max, sum, O) per workgroup goes
+// into num_splits contiguous pieces; one workgroup of 4 waves (8 in one variant) owns one (batch, unit,
+// split) and its waves take alternating 32-key tiles. Each wave keeps its own online-softmax state
+// (fp32), the waves are merged through LDS and one partial (max, sum, O) per workgroup goes
 // to the workspace; a second kernel combines the splits in fixed order.
 //
 // Tile arithmetic, all in the transposed orientation so that nothing but K needs LDS:
@@ -26,6 +26,19 @@
 //     MFMA A layout (the only cross-lane transpose on the path).
 // Loads for tile t+1 are issued before tile t is consumed (registers are the staging
 // buffer), indices one tile further ahead.
+//
+// What bounds it: memory for long lists (4 batches of 128K, 13108 tokens kept: 430 MB in 70.4 us, 6.1 TB/s; 71.7 before
+// the points below), the chain of dependent latencies for short ones, and for query blocks that share one cache the
+// instructions per tile, since their gathers hit the die's L2 (16 blocks of 16 rows over 64K: 375 -> 214 us, 177 of them
+// with all rows in L1). Vector instructions per tile of two query tiles: 516 -> 263. What they and the latencies were
+// spent on, and what stands now (calls of 256 / 410 / 512 / 1024 kept tokens 7.6 / 9.3 / 13.0 / 13.3 -> 5.9 / 6.9 /
+// 11.5 / 11.3 us):
+//   - three divisions, a table lookup and a search for set bits before the first load: a grid of three dimensions, the
+//     arguments asked for at once, entries, length and Q in flight together;
+//   - 64-bit row addresses in every lane: one 32-bit offset per row, made by one lane and passed on through LDS;
+//   - maxima across lanes by LDS permutes: the swaps of rows and halves;
+//   - accumulators rescaled for every tile: only where some row's maximum has grown;
+//   - loop exits that made the compiler wait for all loads in flight in every second tile: see the main loop.
 #include "common.h"
 
 #include <mutex>
@@ -37,8 +50,11 @@ template <int D> struct Chunk;
 template <> struct Chunk<128> { typedef u32x4 type; };
 template <> struct Chunk<64> { typedef u32x2 type; };
 
+// position of the n-th set bit (n < popcount)
 __device__ __forceinline__ int nth_member(uint32_t mask, int n) {
-  // position of the n-th set bit (n < popcount)
+  const int first = __builtin_ctz(mask);
+  const uint32_t run = mask >> first;
+  if ((run & (run + 1)) == 0) return first + n;      // (mask is the same for all lanes; nearly always one run of bits)
   int pos = 0;
 #pragma unroll
   for (int i = 0; i < STS_MAX_GROUP; ++i) {
@@ -49,18 +65,37 @@ __device__ __forceinline__ int nth_member(uint32_t mask, int n) {
   return pos;
 }
 
-__device__ __forceinline__ float xor_max(float x, int lanemask) {
-  return fmaxf(x, __shfl_xor(x, lanemask, 64));
+// maximum over the four lanes 16 apart (the row-of-16 swaps of this chip: no LDS round trip)
+__device__ __forceinline__ float max_over_groups(float x) {
+  const uint32_t w = __builtin_bit_cast(uint32_t, x);
+  const auto p = __builtin_amdgcn_permlane16_swap(w, w, false, false);       // rows 0, 0, 2, 2 and 1, 1, 3, 3
+  const float y = fmaxf(__builtin_bit_cast(float, (uint32_t)p[0]), __builtin_bit_cast(float, (uint32_t)p[1]));
+  const uint32_t v = __builtin_bit_cast(uint32_t, y);
+  const auto q = __builtin_amdgcn_permlane32_swap(v, v, false, false);       // the lower and the upper half
+  return fmaxf(__builtin_bit_cast(float, (uint32_t)q[0]), __builtin_bit_cast(float, (uint32_t)q[1]));
 }
+
+// waves per workgroup, and whether a tile's K and V are loaded into one set of registers instead of two
+constexpr bool one_buffer(int D, int NQ, bool cached) { return cached && D == 128 && NQ == 2; }
+constexpr int wg_waves(int D, int NQ, bool cached) { return one_buffer(D, NQ, cached) ? 2 * STS_WG_WAVES : STS_WG_WAVES; }
 
 // One workgroup per CU (the whole register file for it) for exactly the variants the host plans
 // one workgroup per CU for: four query tiles, and head size 128 when dense or with two query tiles.
+// FAR: rows at 64-bit offsets (a paged cache, or heads of 4 GB and more), else 32-bit ones.
 // ROWMASK: every index entry comes with a 16-bit word, bit i set iff query row i of the block keeps
 // the entry (prefill: an index set per query row, gathered once as their union).
-template <int D, int NQ, bool SPARSE, bool LOGITS, bool PAGED, bool ROWMASK = false>
-__global__ void __launch_bounds__(64 * STS_WG_WAVES, (NQ == 4 || (D == 128 && (!SPARSE || NQ == 2))) ? 1 : 2)
+// CACHED: workgroups that gather from the same K and V (blocks of one prompt; the launcher's rule): see the mapping
+// below. Their loads stay in the caches. With two query tiles at head size 128 they run two waves per SIMD on one set of
+// load buffers: one wave per SIMD leaves it idle for half of the time (365 us against 214, the case above).
+template <int D, int NQ, bool SPARSE, bool LOGITS, bool FAR, bool ROWMASK = false, bool CACHED = false>
+__global__ void __launch_bounds__(64 * wg_waves(D, NQ, CACHED),
+                                  one_buffer(D, NQ, CACHED) ? 2 : (NQ == 4 || (D == 128 && (!SPARSE || NQ == 2))) ? 1 : 2)
 attn_split_kernel(const AttnArgs A) {
   typedef typename Chunk<D>::type chunk_t;
+  typedef typename std::conditional<FAR, uint64_t, uint32_t>::type row_off;
+  constexpr int W = wg_waves(D, NQ, CACHED);
+  constexpr bool ONE = one_buffer(D, NQ, CACHED);
+  constexpr bool GATHER = SPARSE || FAR;   // row offsets go from lane to lane through LDS
   constexpr int NT = D / 16;         // output tiles of the PV product == elements per lane chunk
   constexpr int KK = D / 32;         // contraction steps of the QK product
   constexpr int CHB = D / 8;         // bytes per lane chunk
@@ -68,66 +103,103 @@ attn_split_kernel(const AttnArgs A) {
   constexpr int NSLOT = D / 8;       // 16-byte slots per LDS row
   constexpr int OPITCH = D + 4;      // floats per row of the merge buffer
   constexpr int KTILE_BYTES = STS_TILE_KEYS * ROWB;
-  constexpr int MERGE_BYTES = STS_WG_WAVES * 16 * OPITCH * 4;
-  constexpr int LDS_MAIN = (STS_WG_WAVES * KTILE_BYTES > MERGE_BYTES) ? STS_WG_WAVES * KTILE_BYTES : MERGE_BYTES;
+  constexpr int MERGE_BYTES = W * 16 * OPITCH * 4;
+  constexpr int LDS_MAIN = (W * KTILE_BYTES > MERGE_BYTES) ? W * KTILE_BYTES : MERGE_BYTES;
   __shared__ __attribute__((aligned(16))) unsigned char lds[LDS_MAIN];
-  __shared__ float lds_ml[STS_WG_WAVES][NQ * 16][2];
+  __shared__ float lds_ml[W][NQ * 16][2];
   // With two or more query tiles the Q operands (NQ*KK registers quads per lane) no longer fit
   // beside the accumulators and the load buffers: they live in LDS, already in MFMA B layout
   // (one 16-byte slot per lane and (tile, step)), and are re-read for every key tile.
   constexpr bool QLDS = NQ >= 2;
   __shared__ __attribute__((aligned(16))) u32x4 ldsQ[QLDS ? NQ * (D / 32) * 64 : 1];
+  // row offsets of the tile whose loads go out next, and the row bits of the tiles under way (a ring of four)
+  __shared__ __attribute__((aligned(16))) row_off lds_off[GATHER ? W : 1][STS_TILE_KEYS];
+  __shared__ __attribute__((aligned(8))) uint16_t lds_bits[ROWMASK ? W : 1][4][STS_TILE_KEYS];
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // the wave's number and the list's length are told to be the same for the whole wave: with branches that look divergent,
+  // the loop's head waits for every load in flight
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int a = lane >> 4, b = lane & 15;
 
+  // What the first loads need of the arguments, asked for together: waits for scalar loads cannot tell them apart.
+  uint32_t unit = A.units.unit[blockIdx.y];
+  asm volatile("" ::"s"(A.q), "s"(A.k), "s"(A.v), "s"(A.indices), "s"(A.counts), "s"(A.seq_lens), "s"(A.row_mask), "s"(A.stride_b),
+               "s"(A.stride_h), "s"(A.stride_n), "s"(A.idx_stride_b), "s"(A.cnt_stride_b), "s"(A.Tq), "s"(A.Hq), "s"(A.G), "s"(A.N),
+               "s"(A.kmax), "s"(A.num_splits), "s"(A.page), "s"(A.page_shift), "s"(unit), "s"(A.scale), "s"(A.scale_log2), "s"(A.z_rounds));
   const int S = A.num_splits, U = A.num_units;
-  const int split = blockIdx.x % S;
-  const int u = (blockIdx.x / S) % U;
-  const int bt = blockIdx.x / (S * U);
-  const uint32_t unit = A.units.unit[u];
+  int split = blockIdx.x, u = blockIdx.y, bt = blockIdx.z;      // grid (S, U, B): no divisions before the first load
+  if (CACHED) {
+    // Every batch element reads the same cache: the workgroups of a KV head (units are ordered by it) run on as few
+    // dies as possible, those of one range of the index lists next to each other. The lists ascend, so what one of them
+    // fetches is in that die's L2 when the others come to it. (Workgroup i runs on die i % 8.)
+    const int G = S * U * A.B, j = split + S * (u + U * bt), x = j % STS_XCDS;
+    const int i = x * (G / STS_XCDS) + min(x, G % STS_XCDS) + j / STS_XCDS;
+    bt = i % A.B;
+    split = (i / A.B) % S;
+    u = i / (A.B * S);
+    unit = A.units.unit[u];
+  } else if (A.z_rounds > 1) {                 // more batch elements than a grid's last dimension holds
+    bt += split / S * STS_GRID_Z;
+    split %= S;
+    if (bt >= A.B) return;
+  }
   const int g = unit & 0xff;
   const uint32_t mask = (unit >> 8) & 0xffff;
   const int nheads = (unit >> 24) & 0x1f;
   const int rows_valid = nheads * A.Tq;
-  const int head0 = g * A.G + nth_member(mask, 0);
+  const int head0 = g * A.G + __builtin_ctz(mask);
 
   // Length of this unit's key list in token positions. Sparse index entries stand for blocks
   // of `page` consecutive tokens (page = 1: single tokens), so entry e covers positions
   // e*page .. e*page+page-1 of the expanded list. The split boundaries come from the static
-  // upper bound (kmax*page or N), so the first index load below does not wait for the count;
+  // upper bound (kmax*page or N), so the first index loads below do not wait for the count;
   // a unit with fewer keys simply leaves its last splits empty (the longest unit sets the
   // makespan).
   const int psh = A.page_shift, pmask = A.page - 1;
-  int c;
-  if (SPARSE) {
-    c = A.counts ? A.counts[(size_t)bt * A.cnt_stride_b + head0] : A.kmax;
-    c = min(max(c, 0), A.kmax) << psh;
-  } else {
-    c = A.seq_lens ? A.seq_lens[bt] : A.N;
-    c = min(max(c, 0), A.N);
-  }
   const int len_max = SPARSE ? (A.kmax << psh) : A.N;
   const int tiles_max = (len_max + STS_TILE_KEYS - 1) / STS_TILE_KEYS;
   const int tps = (tiles_max + S - 1) / S;
   const int t_begin = split * tps;
-  const int32_t *idx_row = SPARSE ? A.indices + (size_t)bt * A.idx_stride_b + (size_t)head0 * A.kmax : nullptr;
-  // first tile's index entries, issued before anything depends on the count (kmax >= 1
-  // whenever a sparse grid has tiles to do; the clamp keeps the address inside the row)
-  const uint16_t *mask_row = ROWMASK ? A.row_mask + (size_t)bt * A.idx_stride_b + (size_t)head0 * A.kmax : nullptr;
-  int rows_first = 0, bits_first = 0;
-  if (SPARSE && len_max > 0) {
-    rows_first = idx_row[min(((t_begin + wave) * STS_TILE_KEYS + (lane & 31)) >> psh, A.kmax - 1)];
-    if (ROWMASK) bits_first = mask_row[min(((t_begin + wave) * STS_TILE_KEYS + (lane & 31)) >> psh, A.kmax - 1)];
-  }
-  const int tiles_total = (c + STS_TILE_KEYS - 1) / STS_TILE_KEYS;
-  const int t_end = min(t_begin + tps, tiles_total);
+  // (an empty list's entries are read from Q and never used)
+  const bool some = len_max > 0;
+  const int last = max(len_max, 1) - 1;
+  const size_t list = some ? (size_t)bt * A.idx_stride_b + (size_t)head0 * A.kmax : 0;
+  const int32_t *idx_row = SPARSE ? (some ? A.indices : reinterpret_cast<const int32_t *>(A.q)) + list : nullptr;
+  const uint16_t *mask_row = ROWMASK ? (some ? A.row_mask : A.q) + list : nullptr;
+  // Wave w takes tiles t_begin + w, + W, + 2 W, ...; the kernels that dump the logits take pairs of neighbouring tiles
+  // instead (2w, 2w + 1, then + 2 W), so that one wave writes whole 128-byte lines of the dump.
+  auto tile_of = [&](int v) -> int {
+    return LOGITS ? t_begin + (v >> 1) * (2 * W) + 2 * wave + (v & 1) : t_begin + wave + v * W;
+  };
+  // raw index entry (sparse) or logical block (dense) of slot (lane & 31) of a tile, clamped into the row, and the row
+  // bits of the same entry (ROWMASK only)
+  auto fetch_rows = [&](int t) -> int {
+    const int e = min(t * STS_TILE_KEYS + (lane & 31), last) >> psh;
+    return SPARSE ? idx_row[e] : e;
+  };
+  auto fetch_bits = [&](int t) -> int {
+    return ROWMASK ? (int)mask_row[min(t * STS_TILE_KEYS + (lane & 31), last) >> psh] : 0;
+  };
+  // The first three tiles' entries, the length and Q are asked for together; the length by a vector load, as scalar loads
+  // return in any order and a wait for one is a wait for all.
+  int raw_a = fetch_rows(tile_of(0)), bits_a = fetch_bits(tile_of(0));
+  int lane_zero = 0;
+  asm("" : "+v"(lane_zero));
+  const int32_t *len_src = SPARSE ? A.counts : A.seq_lens;
+  const int n_read = (len_src ? len_src + (SPARSE ? (int64_t)bt * A.cnt_stride_b + head0 : (int64_t)bt) : reinterpret_cast<const int32_t *>(A.q))[lane_zero];
+  int raw_b = fetch_rows(tile_of(1)), bits_b = fetch_bits(tile_of(1));
+  const int raw_c = fetch_rows(tile_of(2)), bits_c = fetch_bits(tile_of(2));
   const int nb_max = (A.N + A.page - 1) >> psh;   // logical blocks of the cache
 
-  // query rows owned by this lane: row nq*16 + b
+  // query rows owned by this lane: row nq*16 + b. The softmax scales by |scale| (1 for a scale of 0): a negative
+  // scale turns the signs of Q, a scale of 0 clears it, which is exact.
+  const uint32_t q_keep = A.scale == 0.f ? 0u : 0xffffffffu, q_flip = A.scale < 0.f ? 0x80008000u : 0u;
+  const float scale_abs = fabsf(A.scale), sl2 = A.scale == 0.f ? 1.f : fabsf(A.scale_log2);
   int q_head[NQ], q_tq[NQ];
   bool q_ok[NQ];
   bf16x8 Q[QLDS ? 1 : NQ][QLDS ? 1 : KK];
+  u32x4 qw[NQ][KK];
+  // all of Q is asked for at once: rows that do not exist read row 0 (a branch around a load would wait for it)
 #pragma unroll
   for (int nq = 0; nq < NQ; ++nq) {
     const int r = nq * 16 + b;
@@ -135,93 +207,100 @@ attn_split_kernel(const AttnArgs A) {
     const int hsel = q_ok[nq] ? r / A.Tq : 0;
     q_tq[nq] = q_ok[nq] ? r - hsel * A.Tq : 0;
     q_head[nq] = g * A.G + nth_member(mask, hsel);
-    const uint16_t *qp = A.q + (((size_t)bt * A.Tq + q_tq[nq]) * A.Hq + q_head[nq]) * D;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      u32x4 w = {0u, 0u, 0u, 0u};
-      if (q_ok[nq]) w = *reinterpret_cast<const u32x4 *>(qp + 8 * (a + 4 * kk));
-      if (QLDS) {
-        if (wave == 0) ldsQ[(nq * KK + kk) * 64 + lane] = w;   // identical for every wave
-      } else {
-        Q[nq][kk] = __builtin_bit_cast(bf16x8, w);
-      }
-    }
   }
-  if (QLDS) __syncthreads();
+  auto load_q = [&] {
+#pragma unroll
+    for (int nq = 0; nq < NQ; ++nq) {
+      const uint16_t *qp = A.q + (((size_t)bt * A.Tq + q_tq[nq]) * A.Hq + q_head[nq]) * D;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) qw[nq][kk] = *reinterpret_cast<const u32x4 *>(qp + 8 * (a + 4 * kk));
+    }
+  };
+  auto take_q = [&] {
+#pragma unroll
+    for (int nq = 0; nq < NQ; ++nq)
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        const u32x4 w = (qw[nq][kk] & (q_ok[nq] ? q_keep : 0u)) ^ q_flip;
+        if (QLDS) {
+          if (wave == 0) ldsQ[(nq * KK + kk) * 64 + lane] = w;   // identical for every wave
+        } else {
+          Q[nq][kk] = __builtin_bit_cast(bf16x8, w);
+        }
+      }
+    if (QLDS) __syncthreads();
+  };
+  int c = 0, t_end = 0;              // the list's length, and the end of this workgroup's tiles
 
   // a paged cache is a pool of pages shared by the batch: the page table supplies the batch part
-  const int64_t head_off = ((PAGED ? 0 : (int64_t)bt * A.stride_b) + (int64_t)g * A.stride_h) * 2 + b * CHB;
-  const unsigned char *kbase = reinterpret_cast<const unsigned char *>(A.k) + head_off;
-  const unsigned char *vbase = reinterpret_cast<const unsigned char *>(A.v) + head_off;
+  const bool paged = FAR && A.block_table != nullptr;
+  const int64_t head_off = ((paged ? 0 : (int64_t)bt * A.stride_b) + (int64_t)g * A.stride_h) * 2;
+  const unsigned char *kuni = reinterpret_cast<const unsigned char *>(A.k) + head_off;
+  const unsigned char *vuni = reinterpret_cast<const unsigned char *>(A.v) + head_off;
   const int64_t row_bytes = A.stride_n * 2;
   const int64_t page_bytes = A.stride_page * 2;
-  const int32_t *table_row = PAGED ? A.block_table + (size_t)bt * A.table_stride : nullptr;
+  const int32_t *table_row = paged ? A.block_table + (size_t)bt * A.table_stride : nullptr;
   unsigned char *ldsK = lds + wave * KTILE_BYTES;
 
   // row slot of load m for this lane: 16*(m/4) + 4a + m%4 (the keys the MFMA output hands
   // to lane group a)
   auto slot_of = [&](int m) { return 16 * (m >> 2) + 4 * a + (m & 3); };
 
-  // Three prefetch stages per tile, each one loop half ahead of the next, so that no stage
+  // Prefetch stages per tile, each one loop half ahead of the next, so that no stage
   // waits on a load that was issued after the K/V loads in flight:
-  //   fetch   : raw index entry (sparse) or logical block (dense) for slot (lane & 31);
+  //   fetch   : raw index entry (sparse) or logical block (dense) for slot (lane & 31), see above;
   //   resolve : validity mask of the tile (one bit per slot) and the row to read: the token
   //             id, or with a page table the physical page (a second, dependent load);
+  //   place   : the byte offset of the slot's row, written to LDS (a lane needs eight of them);
   //   issue   : the 16 K/V row loads of the tile.
-  // All three are branch-free and nothing touches a loaded value before the next stage.
-  const int safe_pos = (LOGITS ? t_begin + 2 * wave : t_begin + wave) * STS_TILE_KEYS;
-  auto fetch_rows = [&](int t) -> int {
-    const int pos = t * STS_TILE_KEYS + (lane & 31);
-    const int p = (t < t_end) ? min(pos, c - 1) : safe_pos;
-    const int e = p >> psh;
-    return SPARSE ? idx_row[e] : e;
-  };
-  // the row bits of the same entry (ROWMASK only)
-  auto fetch_bits = [&](int t) -> int {
-    const int pos = t * STS_TILE_KEYS + (lane & 31);
-    const int p = (t < t_end) ? min(pos, c - 1) : safe_pos;
-    return ROWMASK ? (int)mask_row[p >> psh] : 0;
-  };
-
+  // All are branch-free and nothing touches a loaded value before the next stage.
   auto resolve = [&](int raw, int t, uint32_t &tile_mask) -> int {
     const int pos = t * STS_TILE_KEYS + (lane & 31);
-    const int blk = min(max(raw, 0), nb_max - 1);      // memory safety for arbitrary entries
+    // memory safety for arbitrary entries; past this wave's tiles every slot names the same row
+    const int blk = (t < t_end) ? min(max(raw, 0), nb_max - 1) : 0;
     const int tok = (blk << psh) + (pos & pmask);
     // past the list, past the tile range, or in the unfilled part of the last page
     const bool ok = (t < t_end) && (pos < c) && (tok < A.N);
     tile_mask = (uint32_t)__ballot(ok);
-    if (PAGED) return table_row[min(blk, A.table_stride - 1)];
+    if (FAR && paged) return table_row[min(blk, A.table_stride - 1)];
     return min(tok, A.N - 1);
   };
-  // row bits of this lane's slot, cleared where the slot holds no key
-  auto slot_bits = [&](int bits, uint32_t tile_mask) -> int {
-    return ((tile_mask >> (lane & 31)) & 1u) ? bits : 0;
+  // byte offset of the row, and its row bits (cleared where the slot holds no key); lanes 32 apart write the same words
+  auto place = [&](int x, int bits, uint32_t tile_mask, int v) {
+    if (!GATHER) return;
+    if (FAR && paged)
+      lds_off[wave][lane & 31] = (row_off)((int64_t)min(max(x, 0), A.num_pages - 1) * page_bytes + (int64_t)(lane & pmask) * row_bytes);
+    else
+      lds_off[wave][lane & 31] = (row_off)x * (row_off)row_bytes;
+    if (ROWMASK) lds_bits[wave][v & 3][lane & 31] = (uint16_t)(((tile_mask >> (lane & 31)) & 1u) ? bits : 0);
   };
-
-  auto issue_loads = [&](int x, int t, chunk_t (&Kr)[8], chunk_t (&Vr)[8]) {
+  struct Offsets {
+    row_off o[8];
+  };
+  auto offsets = [&](int t, Offsets &o) {
+    if (GATHER) {
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
-      const int slot = slot_of(m);
-      int64_t off;
-      if (!SPARSE && !PAGED) {
-        // contiguous dense cache: the row is the position itself, no cross-lane traffic
-        const int row = (t < t_end) ? min(t * STS_TILE_KEYS + slot, c - 1) : 0;
-        off = (int64_t)row * row_bytes;
-      } else {
-        int X = __shfl(x, slot, 64);
-        if (PAGED) {
-          X = min(max(X, 0), A.num_pages - 1);
-          off = (int64_t)X * page_bytes + (int64_t)(slot & pmask) * row_bytes;
-        } else {
-          off = (int64_t)X * row_bytes;
-        }
-      }
-      // every K/V row is consumed once per launch: stream it past the caches
-      Kr[m] = __builtin_nontemporal_load(reinterpret_cast<const chunk_t *>(kbase + off));
-      Vr[m] = __builtin_nontemporal_load(reinterpret_cast<const chunk_t *>(vbase + off));
+      for (int m = 0; m < 8; ++m) o.o[m] = lds_off[GATHER ? wave : 0][slot_of(m)] + (row_off)(b * CHB);
     }
   };
-
+  // Rows are streamed past the caches where every one is used once per launch.
+  auto load_rows = [&](const unsigned char *base, int t, const Offsets &o, chunk_t (&r)[8]) {
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const chunk_t *src;
+      if (GATHER) {
+        row_off off = o.o[m];
+        asm("" : "+v"(off));      // (seen here as 32 bits, the offset is an operand of the load)
+        src = reinterpret_cast<const chunk_t *>(base + off);
+      } else {
+        // contiguous dense cache: the row is the position itself, no cross-lane traffic
+        const int row = (t < t_end) ? min(t * STS_TILE_KEYS + slot_of(m), c - 1) : 0;
+        src = reinterpret_cast<const chunk_t *>(base + ((int64_t)row * row_bytes + b * CHB));
+      }
+      if (CACHED) r[m] = *src;
+      else r[m] = __builtin_nontemporal_load(src);
+    }
+  };
   float m_run[NQ], l_run[NQ];
   f32x4 acc[NQ][NT];
 #pragma unroll
@@ -259,10 +338,8 @@ attn_split_kernel(const AttnArgs A) {
     }
   };
 
-  auto consume = [&](int t, const chunk_t (&Kr)[8], const chunk_t (&Vr)[8], const uint32_t tile_mask, const bool second,
-                     const int tile_bits) {
-    const int pos0 = t * STS_TILE_KEYS;
-    // ---- K: registers -> swizzled LDS tile (row = slot, 16-byte slot index XOR row)
+  // ---- K: registers -> swizzled LDS tile (row = slot, 16-byte slot index XOR row)
+  auto store_k = [&](const chunk_t (&Kr)[8]) {
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
       const int row = slot_of(m);
@@ -273,6 +350,16 @@ attn_split_kernel(const AttnArgs A) {
         const int sl = (b >> 1) ^ (row & (NSLOT - 1));
         *reinterpret_cast<chunk_t *>(ldsK + row * ROWB + sl * 16 + (b & 1) * 8) = Kr[m];
       }
+    }
+  };
+
+  // tile t, v-th of this wave (K in LDS, V in registers)
+  auto consume = [&](int t, int v, const chunk_t (&Vr)[8], const uint32_t tile_mask, const bool second) {
+    const int pos0 = t * STS_TILE_KEYS;
+    uint64_t key_bits[2];           // ROWMASK: the row bits of this lane's 8 keys, 16 each
+    if constexpr (ROWMASK) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) key_bits[ks] = *reinterpret_cast<const uint64_t *>(&lds_bits[wave][v & 3][16 * ks + 4 * a]);
     }
     // ---- S^T = K Q^T
     f32x4 St[NQ][2];
@@ -302,7 +389,7 @@ attn_split_kernel(const AttnArgs A) {
         for (int nq = 0; nq < NQ; ++nq)
 #pragma unroll
           for (int ks = 0; ks < 2; ++ks) {
-            const f32x4 sc = St[nq][ks] * A.scale;
+            const f32x4 sc = St[nq][ks] * scale_abs;
             const bf16x2 lo = __builtin_convertvector(f32x2{sc[0], sc[1]}, bf16x2);   // round to nearest even
             const bf16x2 hi = __builtin_convertvector(f32x2{sc[2], sc[3]}, bf16x2);
             w[nq][ks] = u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
@@ -328,7 +415,7 @@ attn_split_kernel(const AttnArgs A) {
 #pragma unroll
           for (int ks = 0; ks < 2; ++ks) {
             const int p = pos0 + 16 * ks + 4 * a;
-            const f32x4 sc = St[nq][ks] * A.scale;
+            const f32x4 sc = St[nq][ks] * scale_abs;
             if (p + 3 < c && (A.N & 3) == 0) {
               *reinterpret_cast<f32x4 *>(lp + p) = sc;
             } else {
@@ -340,47 +427,68 @@ attn_split_kernel(const AttnArgs A) {
         }
       }
     }
+    // slots that hold no key (the last tile of a list, and blocks that the cache's end cuts) score -inf
+    if (!ROWMASK && tile_mask != 0xffffffffu) {
+#pragma unroll
+      for (int nq = 0; nq < NQ; ++nq)
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (!((tile_mask >> (16 * ks + 4 * a + r)) & 1u)) St[nq][ks][r] = -INFINITY;
+    }
     // ---- online softmax (log2 domain) and P^T as bf16 B operands, then O^T += V^T P^T.
     // With four query tiles at head size 128 the two steps are done for two tiles at a time (the
     // V operands are permuted twice): all four P tiles next to both K/V buffers do not fit the
     // 256 registers that ordinary instructions can address.
     constexpr int NQH = (NQ == 4 && D == 128) ? 2 : NQ;   // query tiles per round
-    int key_bits[8];                // ROWMASK: the row bits of this lane's 8 keys
-    if constexpr (ROWMASK) {
-#pragma unroll
-      for (int m = 0; m < 8; ++m) key_bits[m] = __shfl(tile_bits, slot_of(m), 64);
-    }
 #pragma unroll
     for (int q0 = 0; q0 < NQ; q0 += NQH) {
       bf16x8 Pb[NQH];
+      float mt[NQH];
+      bool grown = false;
 #pragma unroll
       for (int nq = q0; nq < q0 + NQH; ++nq) {
         float s[8];
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const bool ok = ROWMASK ? ((key_bits[4 * ks + r] >> q_tq[nq]) & 1) != 0
-                                    : ((tile_mask >> (16 * ks + 4 * a + r)) & 1u) != 0;
-            s[4 * ks + r] = ok ? St[nq][ks][r] * A.scale_log2 : -INFINITY;
+        for (int i = 0; i < 8; ++i) {
+          s[i] = St[nq][i >> 2][i & 3];
+          if constexpr (ROWMASK) {                 // all ones if this row keeps the key
+            const uint32_t w = (uint32_t)(key_bits[i >> 2] >> (32 * ((i >> 1) & 1)));
+            const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)w, q_tq[nq] + 16 * (i & 1), 1);
+            s[i] = __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, s[i]) & keep) | (0xff800000u & ~keep));
+            St[nq][i >> 2][i & 3] = s[i];
           }
-        float mt = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
-        mt = xor_max(mt, 16);
-        mt = xor_max(mt, 32);
-        const float m_new = fmaxf(m_run[nq], mt);          // finite: every consumed tile has a valid key ...
-        // ... except with row bits: a row may keep none of a tile's keys, nor of any tile so far
-        const float m_ref = (ROWMASK && m_new == -INFINITY) ? 0.f : m_new;
-        const float alpha = __builtin_amdgcn_exp2f(m_run[nq] - m_ref);
+        }
+        mt[nq - q0] = sl2 * max_over_groups(fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])),
+                                                  fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7]))));
+        grown |= mt[nq - q0] > m_run[nq];
+      }
+      // Most tiles of a long list raise no row's maximum and rescale nothing. (A maximum that may lag by a factor of 256
+      // skips nearly all, but was no faster, and the largest weight is then no longer 1, which bf16 holds exactly: the
+      // outputs were 2% further from 64 bits.)
+      if (__builtin_amdgcn_ballot_w64(grown)) {
+#pragma unroll
+        for (int nq = q0; nq < q0 + NQH; ++nq) {
+          const float m_new = fmaxf(m_run[nq], mt[nq - q0]);   // finite: every consumed tile has a valid key ...
+          // ... except with row bits: a row may keep none of a tile's keys, nor of any tile so far
+          const float alpha = (ROWMASK && m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(m_run[nq] - m_new);
+          l_run[nq] *= alpha;
+          m_run[nq] = m_new;
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) acc[nq][nt] *= alpha;
+        }
+      }
+#pragma unroll
+      for (int nq = q0; nq < q0 + NQH; ++nq) {
+        const float m_ref = (ROWMASK && m_run[nq] == -INFINITY) ? 0.f : m_run[nq];
         float p[8], psum = 0.f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          p[i] = __builtin_amdgcn_exp2f(s[i] - m_ref);
+          p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(St[nq][i >> 2][i & 3], sl2, -m_ref));
           psum += p[i];
         }
-        l_run[nq] = l_run[nq] * alpha + psum;
-        m_run[nq] = m_new;
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[nq][nt] *= alpha;
+        l_run[nq] += psum;
         u32x4 pw;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -404,70 +512,115 @@ attn_split_kernel(const AttnArgs A) {
     }
   };
 
-  // ---- main loop over this wave's tiles. Wave w takes tiles t_begin + w, + 4, + 8, ...; the
-  // kernels that dump the logits take pairs of neighbouring tiles instead (2w, 2w + 1, then + 8),
-  // so that one wave writes whole 128-byte lines of the dump.
-  constexpr int W = STS_WG_WAVES;
-  auto tile_of = [&](int v) -> int {
-    return LOGITS ? t_begin + (v >> 1) * (2 * W) + 2 * wave + (v & 1) : t_begin + wave + v * W;
-  };
-  if (tile_of(0) < t_end) {   // wave-uniform; a wave without tiles touches no memory
-    chunk_t K0[8], V0[8], K1[8], V1[8];
-    uint32_t m0, m1, mk_next, mk_new;
-    int b0 = 0, b1 = 0, bk_next = 0, bk_new = 0;   // ROWMASK: the tiles' row bits, staged like the masks
-    int v = 0;
-    // prologue: tile v in flight, tile v+1 resolved, tile v+2 fetched
-    // The first tile's K/V loads go out as soon as its own index entries are there: the entries of
-    // the second tile are asked for before them (so that waiting for those entries later does not
-    // wait for the K/V rows, which return in order), but not waited for.
-    int raw_a = SPARSE ? rows_first : fetch_rows(tile_of(0));
-    int rbits_a = ROWMASK ? bits_first : 0;
-    int raw_b = fetch_rows(tile_of(1));
-    int rbits_b = fetch_bits(tile_of(1));
-    int x_a = resolve(raw_a, tile_of(0), m0);
-    if (ROWMASK) b0 = slot_bits(rbits_a, m0);
-    if (SPARSE) __builtin_amdgcn_sched_barrier(0);
-    issue_loads(x_a, tile_of(0), K0, V0);
-    if (SPARSE) __builtin_amdgcn_sched_barrier(0);
-    raw_a = fetch_rows(tile_of(2));
-    rbits_a = fetch_bits(tile_of(2));
-    int x_b = resolve(raw_b, tile_of(1), mk_next);
-    if (ROWMASK) bk_next = slot_bits(rbits_b, mk_next);
-    if (SPARSE) __builtin_amdgcn_sched_barrier(0);
-    for (;;) {
-      raw_b = fetch_rows(tile_of(v + 3));
-      rbits_b = fetch_bits(tile_of(v + 3));
-      x_a = resolve(raw_a, tile_of(v + 2), mk_new);
-      if (ROWMASK) bk_new = slot_bits(rbits_a, mk_new);
-      if (SPARSE) __builtin_amdgcn_sched_barrier(0);   // index traffic stays ahead of the K/V loads
-      issue_loads(x_b, tile_of(v + 1), K1, V1);
-      m1 = mk_next;
-      b1 = bk_next;
-      if (SPARSE) __builtin_amdgcn_sched_barrier(0);   // loads are in flight before the tile is consumed
-      consume(tile_of(v), K0, V0, m0, false, b0);      // even step: first tile of a pair
-      mk_next = mk_new;
-      bk_next = bk_new;
-      ++v;
-      if (tile_of(v) >= t_end) break;
-      raw_a = fetch_rows(tile_of(v + 3));
-      rbits_a = fetch_bits(tile_of(v + 3));
-      x_b = resolve(raw_b, tile_of(v + 2), mk_new);
-      if (ROWMASK) bk_new = slot_bits(rbits_b, mk_new);
-      if (SPARSE) __builtin_amdgcn_sched_barrier(0);
-      issue_loads(x_a, tile_of(v + 1), K0, V0);
-      m0 = mk_next;
-      b0 = bk_next;
-      if (SPARSE) __builtin_amdgcn_sched_barrier(0);
-      consume(tile_of(v), K1, V1, m1, true, b1);       // odd step: second tile of the pair
-      mk_next = mk_new;
-      bk_next = bk_new;
-      ++v;
-      if (tile_of(v) >= t_end) break;
+  // ---- main loop over this wave's tiles
+  auto pin = [] { if (SPARSE || (NQ == 4 && D == 128)) __builtin_amdgcn_sched_barrier(0); };
+  // (decided by the arguments alone, so that nothing above waits for the length; a wave without tiles reads one row)
+  if (some) {
+    load_q();
+    pin();
+    const int n_max = SPARSE ? A.kmax : A.N;
+    c = __builtin_amdgcn_readfirstlane(len_src ? min(max(n_read, 0), n_max) : n_max) << (SPARSE ? psh : 0);
+    t_end = min(t_begin + tps, (c + STS_TILE_KEYS - 1) / STS_TILE_KEYS);
+    // Tiles of this wave. The loop below has one exit, after a pair of tiles, and the odd last tile has code of its own:
+    // with an exit between the two halves the compiler cannot tell at the loop's head which loads are in flight and
+    // waits for all of them in every second tile.
+    int nv;
+    {
+      const int d = t_end - t_begin - (LOGITS ? 2 * wave : wave), step = LOGITS ? 2 * W : W;
+      const int q = d > 0 ? (d - 1) / step : 0;
+      nv = d <= 0 ? 0 : LOGITS ? 2 * q + min(2, d - q * step) : q + 1;
     }
-    if (LOGITS && stash_pos >= 0) store_bf16_tile(stash, stash_pos);   // a range that ends on a first tile
+    uint32_t m0, m1, m_next, m_new;
+    int v = 0;
+    int x_a = resolve(raw_a, tile_of(0), m0);
+    place(x_a, bits_a, m0, 0);
+    Offsets o;
+    offsets(tile_of(0), o);
+    pin();
+    if constexpr (ONE) {
+      // One set of registers: K of the next tile is asked for when this one's has gone to LDS, V when this one's has been
+      // used; the second wave of the SIMD works meanwhile.
+      chunk_t K[8], V[8];
+      load_rows(kuni, tile_of(0), o, K);
+      pin();
+      load_rows(vuni, tile_of(0), o, V);
+      pin();
+      take_q();
+      int x = resolve(raw_b, tile_of(1), m1);
+      place(x, bits_b, m1, 1);
+      raw_a = raw_c;
+      bits_a = bits_c;
+      pin();
+      for (; v < nv; ++v) {
+        offsets(tile_of(v + 1), o);
+        raw_b = fetch_rows(tile_of(v + 3));
+        bits_b = fetch_bits(tile_of(v + 3));
+        x = resolve(raw_a, tile_of(v + 2), m_new);
+        place(x, bits_a, m_new, v + 2);
+        store_k(K);
+        pin();
+        load_rows(kuni, tile_of(v + 1), o, K);
+        pin();
+        consume(tile_of(v), v, V, m0, false);
+        pin();
+        load_rows(vuni, tile_of(v + 1), o, V);
+        pin();
+        m0 = m1;
+        m1 = m_new;
+        raw_a = raw_b;
+        bits_a = bits_b;
+      }
+    } else {
+      chunk_t K0[8], V0[8], K1[8], V1[8];
+      // prologue: tile v in flight, tile v+1 resolved, tile v+2 fetched
+      load_rows(kuni, tile_of(0), o, K0);
+      load_rows(vuni, tile_of(0), o, V0);
+      pin();
+      take_q();
+      int x_b = resolve(raw_b, tile_of(1), m_next);
+      place(x_b, bits_b, m_next, 1);
+      raw_a = raw_c;
+      bits_a = bits_c;
+      pin();
+      for (; v + 2 <= nv; v += 2) {
+        offsets(tile_of(v + 1), o);
+        raw_b = fetch_rows(tile_of(v + 3));
+        bits_b = fetch_bits(tile_of(v + 3));
+        x_a = resolve(raw_a, tile_of(v + 2), m_new);
+        if (!FAR) place(x_a, bits_a, m_new, v + 2);
+        pin();   // index traffic stays ahead of the K/V loads
+        load_rows(kuni, tile_of(v + 1), o, K1);
+        load_rows(vuni, tile_of(v + 1), o, V1);
+        m1 = m_next;
+        pin();   // loads are in flight before the tile is consumed
+        store_k(K0);
+        consume(tile_of(v), v, V0, m0, false);      // even step: first tile of a pair
+        if (FAR) place(x_a, bits_a, m_new, v + 2);  // (a page table entry has come by now)
+        m_next = m_new;
+        offsets(tile_of(v + 2), o);
+        raw_a = fetch_rows(tile_of(v + 4));
+        bits_a = fetch_bits(tile_of(v + 4));
+        x_b = resolve(raw_b, tile_of(v + 3), m_new);
+        if (!FAR) place(x_b, bits_b, m_new, v + 3);
+        pin();
+        load_rows(kuni, tile_of(v + 2), o, K0);
+        load_rows(vuni, tile_of(v + 2), o, V0);
+        m0 = m_next;
+        pin();
+        store_k(K1);
+        consume(tile_of(v + 1), v + 1, V1, m1, true);       // odd step: second tile of the pair
+        if (FAR) place(x_b, bits_b, m_new, v + 3);
+        m_next = m_new;
+      }
+      if (v < nv) {
+        store_k(K0);
+        consume(tile_of(v), v, V0, m0, false);
+      }
+      if (LOGITS && stash_pos >= 0) store_bf16_tile(stash, stash_pos);   // a range that ends on a first tile
+    }
   }
 
-  // ---- merge the 4 waves, write one partial per workgroup
+  // ---- merge the waves, write one partial per workgroup
 #pragma unroll
   for (int nq = 0; nq < NQ; ++nq) {
     float l = l_run[nq];
@@ -488,7 +641,7 @@ attn_split_kernel(const AttnArgs A) {
   for (int nq = 0; nq < NQ; ++nq) {
     float mstar = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < STS_WG_WAVES; ++w) mstar = fmaxf(mstar, lds_ml[w][nq * 16 + b][0]);
+    for (int w = 0; w < W; ++w) mstar = fmaxf(mstar, lds_ml[w][nq * 16 + b][0]);
     const float f = (m_run[nq] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_run[nq] - mstar);
     float *orow = Om + (wave * 16 + b) * OPITCH;
 #pragma unroll
@@ -503,7 +656,7 @@ attn_split_kernel(const AttnArgs A) {
       }
     }
     __syncthreads();
-    {
+    if (W == 4 || threadIdx.x < 256) {
       // 256 threads: row = tid / 16, D/16 consecutive floats each
       const int row = threadIdx.x >> 4, seg = threadIdx.x & 15;
       constexpr int SEGF = D / 16;
@@ -511,7 +664,7 @@ attn_split_kernel(const AttnArgs A) {
 #pragma unroll
       for (int e = 0; e < SEGF; ++e) sum[e] = 0.f;
 #pragma unroll
-      for (int w = 0; w < STS_WG_WAVES; ++w) {
+      for (int w = 0; w < W; ++w) {
         const float *src = Om + (w * 16 + row) * OPITCH + seg * SEGF;
 #pragma unroll
         for (int e = 0; e < SEGF; e += 4) {
@@ -526,10 +679,10 @@ attn_split_kernel(const AttnArgs A) {
         if (r < rows_valid) {
           float ms = -INFINITY;
 #pragma unroll
-          for (int w = 0; w < STS_WG_WAVES; ++w) ms = fmaxf(ms, lds_ml[w][r][0]);
+          for (int w = 0; w < W; ++w) ms = fmaxf(ms, lds_ml[w][r][0]);
           float L = 0.f;
 #pragma unroll
-          for (int w = 0; w < STS_WG_WAVES; ++w) {
+          for (int w = 0; w < W; ++w) {
             const float mw = lds_ml[w][r][0];
             L += (mw == -INFINITY) ? 0.f : lds_ml[w][r][1] * __builtin_amdgcn_exp2f(mw - ms);
           }
@@ -597,10 +750,10 @@ attn_split_kernel(const AttnArgs A) {
         const int r = nq * 16 + threadIdx.x;
         float ms = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < STS_WG_WAVES; ++w) ms = fmaxf(ms, lds_ml[w][r][0]);
+        for (int w = 0; w < W; ++w) ms = fmaxf(ms, lds_ml[w][r][0]);
         float L = 0.f;
 #pragma unroll
-        for (int w = 0; w < STS_WG_WAVES; ++w) {
+        for (int w = 0; w < W; ++w) {
           const float mw = lds_ml[w][r][0];
           L += (mw == -INFINITY) ? 0.f : lds_ml[w][r][1] * __builtin_amdgcn_exp2f(mw - ms);
         }
@@ -754,28 +907,38 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const AttnArgs A, con
   }
 }
 
-template <int D, int NQ, bool PAGED>
+template <int D, int NQ, bool FAR>
 hipError_t launch_split_dnp(const AttnArgs &a, bool sparse, hipStream_t s) {
-  const dim3 grid((unsigned)((size_t)a.B * a.num_units * a.num_splits)), block(64 * STS_WG_WAVES);
-  if (sparse && a.row_mask) {
-    if constexpr (!PAGED) STS_LAUNCH((attn_split_kernel<D, NQ, true, false, false, true>), grid, block, 0, s, a);
-    else return hipErrorInvalidValue;           // (the host refuses row bits on a paged cache)
+  const unsigned z = a.B < STS_GRID_Z ? a.B : STS_GRID_Z;
+  const dim3 grid((unsigned)(a.num_splits * a.z_rounds), a.num_units, z), block(64 * STS_WG_WAVES);
+  // Batch elements that share one cache (stride 0): 16 blocks of 16 rows over 64K, 6554 kept per row: 375 -> 214 us;
+  // 8 blocks over 32K, 3277 kept: 55 -> 25. Where each has its own, rows are used once and streamed.
+  const bool shared = !FAR && a.stride_b == 0 && a.B > 1 && a.B <= STS_GRID_Z;
+  if (sparse && shared) {
+    if constexpr (!FAR) {
+      const dim3 wide(64 * wg_waves(D, NQ, true));
+      if (a.row_mask) STS_LAUNCH((attn_split_kernel<D, NQ, true, false, false, true, true>), grid, wide, 0, s, a);
+      else STS_LAUNCH((attn_split_kernel<D, NQ, true, false, false, false, true>), grid, wide, 0, s, a);
+    }
+  } else if (sparse && a.row_mask) {
+    STS_LAUNCH((attn_split_kernel<D, NQ, true, false, FAR, true>), grid, block, 0, s, a);
   } else if (sparse)
-    STS_LAUNCH((attn_split_kernel<D, NQ, true, false, PAGED>), grid, block, 0, s, a);
+    STS_LAUNCH((attn_split_kernel<D, NQ, true, false, FAR>), grid, block, 0, s, a);
   else if (a.logits_out) {
     // the dump at head size 128 is planned with at most two query tiles per unit (its four-tile
     // form does not fit the register file)
     if constexpr (D == 128 && NQ == 4) return hipErrorInvalidValue;
-    else STS_LAUNCH((attn_split_kernel<D, NQ, false, true, PAGED>), grid, block, 0, s, a);
+    else STS_LAUNCH((attn_split_kernel<D, NQ, false, true, FAR>), grid, block, 0, s, a);
   } else
-    STS_LAUNCH((attn_split_kernel<D, NQ, false, false, PAGED>), grid, block, 0, s, a);
+    STS_LAUNCH((attn_split_kernel<D, NQ, false, false, FAR>), grid, block, 0, s, a);
   return sts_take_launch_status();
 }
 
 template <int D, int NQ>
 hipError_t launch_split_dn(const AttnArgs &a, bool sparse, hipStream_t s) {
-  return a.block_table ? launch_split_dnp<D, NQ, true>(a, sparse, s)
-                       : launch_split_dnp<D, NQ, false>(a, sparse, s);
+  // 32-bit row offsets while a head's rows span less than 4 GB (the last row's bytes included)
+  const bool far = a.block_table || (sparse && (uint64_t)a.N * (uint64_t)a.stride_n * 2 > 0xffffff00ull);
+  return far ? launch_split_dnp<D, NQ, true>(a, sparse, s) : launch_split_dnp<D, NQ, false>(a, sparse, s);
 }
 
 template <int D>

@@ -60,6 +60,8 @@ constexpr int STS_MAX_HEADS = 256;   // Hq, Hd upper bound (tables travel as ker
 constexpr int STS_MAX_GROUP = 16;    // query heads per KV head
 constexpr int STS_TILE_KEYS = 32;    // keys per wave tile
 constexpr int STS_WG_WAVES = 4;      // waves per attention workgroup
+constexpr int STS_XCDS = 8;          // accelerator dies, each with an L2 of its own; workgroups go round them in turn
+constexpr int STS_GRID_Z = 32768;    // batch elements in the last dimension of a grid at most
 
 // A work unit of the attention kernels: the query heads of one KV group that share one index
 // row (sparse) or all heads of the group (dense). Packed: bits 0-7 KV head, 8-23 mask of the
@@ -76,6 +78,7 @@ struct AttnArgs {
   int64_t idx_stride_b, cnt_stride_b;     // elements between batches of indices / counts
   int32_t B, Tq, Hq, Hkv, G, N, kmax;
   int32_t num_units, num_splits;
+  int32_t z_rounds;                       // batch elements / STS_GRID_Z, rounded up
   int32_t page, page_shift;               // tokens per index entry / page (power of two <= 32)
   const int32_t *block_table;             // [B, table_stride] logical block -> physical page, or NULL
   int32_t table_stride, num_pages;
