@@ -301,6 +301,8 @@ int sts_version(void);
  * stream is being captured into a graph (the stamped launch is not a capturable node).
  */
 typedef enum {
+  /* (rows of one bf16 score per token that a workgroup's registers hold are counted under SMALL, FUSED, BAND or ROWPASS,
+   * by their length and number) */
   STS_K_SELECT_CLEAR = 0,  /* zero histograms, or the words that the parts of a row exchange */
   STS_K_SELECT_AGG = 1,    /* aggregation + first-digit histogram */
   STS_K_SELECT_HIST = 2,   /* refinement histograms */
@@ -344,7 +346,8 @@ sts_status sts_prof_read(int kernel_kind, int32_t *launches, double *total_ms);
  *    of 32768 tokens (the rule stops at 8 in calls of fewer than 4M tokens), 4 one workgroup per row in several passes wherever the shape
  *    allows it (Tq = 1, probabilities, token granularity, no agg_out, N a multiple of 4, or of 8
  *    for bf16), 5 the sampled selection with one workgroup per row wherever the shape allows it (token
- *    granularity, N a multiple of 4 up to 524288). It changes sts_select_workspace_bytes, never
+ *    granularity, N a multiple of 4 up to 524288), 6 rows of one bf16 score per token held in one workgroup's registers
+ *    wherever the shape allows it (Tq = 1, probabilities, token granularity, no agg_out, 8 to 131072 tokens). It changes sts_select_workspace_bytes, never
  *    the results.
  *  - STS_KNOB_SELECT_ROW_THREADS (env STS_SELECT_ROW_THREADS): 256 or 1024, the workgroup size of
  *    the several-pass one-workgroup-per-row selection (the rule: 256 from 4 rows per compute

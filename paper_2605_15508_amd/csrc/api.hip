@@ -317,6 +317,8 @@ struct SelectPlan {
   bool pool;           // shape allows chunk-local top-k + one ranking workgroup per row
   bool fused;          // long rows: the sampled selection, one launch (plus the clearing of the exchanged words)
   bool band;           // the same for a row for every second CU or more: can do without a workspace
+  bool row16;          // one bf16 score per token: one workgroup per row, which its registers hold, no workspace
+  int row16_kind;
   bool rowpass;        // many long rows of ready-made scores: one workgroup per row, no workspace
   int rowpass_threads;
   int nchunks, page, srcN, pool_pitch, pool_chunk, pool_nchunks;
@@ -330,7 +332,7 @@ struct SelectPlan {
   // a pool-shaped call falls back to the pipeline when its pointers are not 16-byte aligned,
   // so the workspace covers both
   size_t total() const {
-    if (rowpass) return 0;
+    if (rowpass || row16) return 0;
     if (fused || band) return fused_total();
     return pipeline_total() > pool_total() ? pipeline_total() : pool_total();
   }
@@ -398,6 +400,8 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
   pl.pool_key_bytes = 0;
   pl.fused = false;
   pl.rowpass = false;
+  pl.row16 = false;
+  pl.row16_kind = 0;
   pl.band = false;
   pl.rowpass_threads = 0;
   pl.smp_tokens = pl.smp_parts = 0;
@@ -429,6 +433,24 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
     const bool take_rowpass = path == 4 ? rowpass_ok
                                         : path == 0 && rowpass_ok && long_rows && p->scores_bf16 && (int64_t)rows >= 4 * cus;
     const bool take_band = path == 5 ? band_ok && p->N % 4 == 0 && aligned : path == 0 && !take_rowpass && has_edge && long_rows && 2 * (int64_t)rows >= cus;
+    // One bf16 score per token: rows of 4096 to 131072 of them are held packed in one workgroup's registers
+    // (select_row16_kernel), whatever their number. us, with the paths that such calls would take otherwise: 16 rows of
+    // 131072 43.5 -> 24.8, 64 of 65536 42.1 -> 15.5, 512 of 65536 85.3 -> 25.4, 4096 of 65536 239 -> 155, 8192 of 131072
+    // 970 -> 870, 4096 of 32768 268 -> 75, 512 of 4096 11.7 -> 8.8. Shorter rows keep select_row_kernel (512 rows of 2048: 11.8, 10.7;
+    // 4096: 28.6, 39.7).
+    const bool row16_ok = pl.page == 1 && p->Tq == 1 && p->kind == STS_SCORES_PROBS && p->scores_bf16 && !p->agg_out &&
+                          p->N >= 8 && p->N <= SEL_ROW16_N;
+    const bool take_row16 = path == 6 ? row16_ok : path == 0 && row16_ok && p->N >= 4096;
+    if (take_row16) {
+      // (counted by the timing aid as the class of call that its rows put it in)
+      pl.row16 = true;
+      pl.row16_kind = pl.small ? STS_K_SELECT_SMALL : take_rowpass ? STS_K_SELECT_ROWPASS : take_band ? STS_K_SELECT_BAND : STS_K_SELECT_FUSED;
+      pl.small = false;
+      pl.nchunks = 0;
+      pl.pool_chunk = pl.pool_nchunks = 0;
+      pl.agg_bytes = pl.blk_bytes = pl.hist_bytes = pl.state_bytes = pl.chunk_bytes = 0;
+      return STS_OK;
+    }
     if (take_rowpass || take_band) {
       pl.small = false;
       pl.band = take_band;
@@ -637,6 +659,14 @@ static sts_status enqueue_select(const sts_select_params *p, void *stream) {
     a.smp_tokens = pl.smp_tokens;
     a.smp_parts = pl.smp_parts;
     rc = run_kernel(STS_K_SELECT_BAND, s, [&] { return launch_select_band(a, s); });
+    return rc == hipSuccess ? STS_OK : STS_EHIP;
+  }
+  if (pl.row16) {
+    a.agg = nullptr;
+    a.src = nullptr;
+    a.hist = a.state = a.chunk_cnt = nullptr;
+    a.row16 = 1;
+    rc = run_kernel(pl.row16_kind, s, [&] { return launch_select_small(a, s); });
     return rc == hipSuccess ? STS_OK : STS_EHIP;
   }
   if (pl.rowpass) {

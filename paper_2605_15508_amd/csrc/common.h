@@ -116,6 +116,7 @@ constexpr int SEL_BINS = 2048;          // bins of the widest digit
 constexpr int SEL_CHUNK = 8192;         // tokens per workgroup in the scan kernels
 constexpr int SEL_THREADS = 256;
 constexpr int SEL_SMALL_N = 32768;      // LDS capacity of the one-workgroup-per-row selection (tokens)
+constexpr int SEL_ROW16_N = 131072;     // tokens of one bf16 score each that a workgroup's registers hold
 constexpr int SEL_FLAG_PITCH = 32;      // words between the published counts of two chunks: one 128-byte line each
 constexpr int SEL_FUSED_N = 8192;
 constexpr int SEL_FUSED_MAX_PARTS = 8;   // units of 32768 tokens up to which small calls take the sampled selection
@@ -175,6 +176,7 @@ struct SelectArgs {
                               // exchange (top bit: written), zero before the launch
   int32_t smp_tokens, smp_parts;   // tokens per workgroup (a multiple of 256), workgroups per row
   int32_t fused_spin_limit;   // polls of another part's words before the row is ranked by plain passes instead
+  int32_t row16;              // one bf16 score per token, rows in registers (select_row16_kernel)
   int32_t rowpass_threads;    // one workgroup per row (select_rowpass_kernel): 256 or 1024 threads
   int32_t agg_is_input;       // `agg` is the caller's score tensor itself (one fp32 probability row per head): never stored to
   int32_t B, Hd, Tq, N, Hq, k, kind, reduce, nchunks;   // k: row pitch of indices = largest budget

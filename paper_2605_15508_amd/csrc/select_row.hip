@@ -390,7 +390,359 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
   }
 }
 
+// ------------------------------------------------- rows of one bf16 score per token, packed in registers
+// Calls with a mask per query row (prefill) rank thousands of rows of bf16 scores. 64K of them are 128 KB, 64 registers of
+// 512 threads: a CU holds two such rows, each is read once, and one row's ranking hides behind the loads of the other.
+// Keys are 16 bits, two to a register, and nearly everything is done to both at once (packed 16-bit subtraction with
+// saturation, minimum, maximum): a sample of one key in eight gives a window of keys around the threshold; one pass counts
+// the window's keys one by one in LDS and those above it; the threshold is one of them. Each token's two bits (above,
+// equal) go to LDS and are read in order for the list.
+//
+// What bounds it: memory and vector instructions alike. 4096 rows of 65536 tokens, 10% kept: 155 us, 537 MB read and
+// 107 MB written, 12 vector instructions per token; the several-pass kernel that served it read them twice, 17 per token: 236.
+// Other calls beside the rule in the host code. Measured on the way: masks of lanes and ballots instead of a slot per lane for
+// the keys outside the window 229 us; 256 threads with 128 registers of keys, three rows per CU, 153-157, but 256 rows of
+// 65536 20.5 against 17.0; 131072 tokens in 512 threads 1053 us for 8192 rows, in 1024 threads 870.
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+// nothing is moved across: a pass over keys in registers needs few others then
+__device__ __forceinline__ void fence_schedule() {
+#if defined(__AMDGCN__)
+  __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+
+// Scores with their order as signed numbers (positive ones as they are): -0 is +0, and the lowest value stays free for
+// "no token" (a NaN shares the key of its neighbour).
+__device__ __forceinline__ uint32_t signed16(uint32_t w) {
+  const u16x2 x = __builtin_bit_cast(u16x2, w);
+  const u16x2 sign = __builtin_bit_cast(u16x2, __builtin_bit_cast(uint32_t, x >> (u16x2)15) * 0x7fffu);
+  u16x2 k = x ^ sign ^ (u16x2)0x8000;                                     // -0: 0x7fff, +0: 0x8000
+  k += (u16x2)1 - __builtin_elementwise_min(k ^ (u16x2)0x7fff, (u16x2)1);
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(k, (u16x2)1)) ^ 0x80008000u;
+}
+
+// T threads, IT 16-byte words per thread: rows of up to 8 * T * IT tokens, at least 8.
+template <int T, int IT>
+__global__ void __launch_bounds__(T, 4) select_row16_kernel(const SelectArgs A) {
+  constexpr int TOK = 8 * T * IT;
+  constexpr int CODES = TOK / 16;                                  // words of two bits per token
+  constexpr int STAGE = 8192;
+  typedef typename std::conditional<(TOK <= 65536), uint16_t, uint32_t>::type stage_t;
+  __shared__ uint32_t codes[CODES + CODES / 16];                   // a word of padding after every 16
+  constexpr int SLOTS = SEL_BINS + 2 * 64;                         // a window's bins, and 64 for the keys on either side of it
+  __shared__ uint32_t h[SLOTS];
+  __shared__ __attribute__((aligned(16))) stage_t staged[STAGE];
+  __shared__ uint32_t tot[2][T / 64];
+  __shared__ uint32_t res[8];
+  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int bt = row / A.Hd, j = row % A.Hd;
+  const int nb = __builtin_amdgcn_readfirstlane(row_len(A, bt));
+  const uint32_t c = (uint32_t)min(A.kh[j], nb);
+  const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
+  write_tail<T>(A, bt, j, c);
+  if (c == 0 || t0 == t1) return;
+  const uint16_t *src = static_cast<const uint16_t *>(A.scores) + (size_t)row * A.N;
+
+  // ---- the row: thread tid holds the words tid, tid + T, ... as unsigned keys, 0 where there is no token
+  u16x2 k[IT][4];
+  {
+    u32x4 raw[IT];
+#pragma clang loop unroll(full)
+    for (int i = 0; i < IT; ++i) {
+      const bool inside = 8 * (i + 1) * T <= A.N;                  // (a slab past the valid length reads where it can, and is not used)
+      const unsigned char *at = reinterpret_cast<const unsigned char *>(src) + (inside ? (size_t)i * T * 16 : 0);
+      const uint32_t off = inside ? tid * 16 : 2 * min(8 * (i * T + tid), A.N - 8);
+      raw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any *>(at + off));
+    }
+    for (int i = tid; i < SLOTS; i += T) h[i] = 0u;
+    uint32_t any = 0;
+#pragma clang loop unroll(full)
+    for (int i = 0; i < IT; ++i) any |= raw[i][0] | raw[i][1] | raw[i][2] | raw[i][3];
+    if (ballot64((any & 0x80008000u) != 0u)) {                     // negative scores in this wave
+#pragma clang loop unroll(full)
+      for (int i = 0; i < IT; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) raw[i][e] = signed16(raw[i][e]);
+    }
+#pragma clang loop unroll(full)
+    for (int i = 0; i < IT; ++i)
+      if (8 * (i + 1) * T > nb) {                                  // the row's end
+        const int n = 8 * (i * T + tid), d = n - min(n, A.N - 8);  // tokens that the word was read before its place
+        if (d & 4) { raw[i][0] = raw[i][2]; raw[i][1] = raw[i][3]; }
+        if (d & 2) { raw[i][0] = raw[i][1]; raw[i][1] = raw[i][2]; raw[i][2] = raw[i][3]; }
+        if (d & 1) {
+#pragma unroll
+          for (int e = 0; e < 3; ++e) raw[i][e] = raw[i][e] >> 16 | raw[i][e + 1] << 16;
+          raw[i][3] >>= 16;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (n + 2 * e >= nb) raw[i][e] = (raw[i][e] & 0xffff0000u) | 0x8000u;
+          if (n + 2 * e + 1 >= nb) raw[i][e] = (raw[i][e] & 0xffffu) | 0x80000000u;
+        }
+      }
+#pragma clang loop unroll(full)
+    for (int i = 0; i < IT; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) k[i][e] = __builtin_bit_cast(u16x2, raw[i][e] ^ 0x80008000u);
+  }
+
+  // Exclusive sums over the workgroup of two values per thread; the totals too.
+  auto scan2 = [&](uint32_t a, uint32_t b, uint32_t &a0, uint32_t &b0, uint32_t &at, uint32_t &bs) {
+    const uint32_t ai = wave_incl_scan(a), bi = wave_incl_scan(b);
+    if (lane == 63) {
+      tot[0][wave] = ai;
+      tot[1][wave] = bi;
+    }
+    __syncthreads();
+    a0 = ai - a;
+    b0 = bi - b;
+    at = bs = 0;
+#pragma unroll
+    for (int w = 0; w < T / 64; ++w) {
+      const uint32_t x = tot[0][w], y = tot[1][w];
+      if (w < wave) {
+        a0 += x;
+        b0 += y;
+      }
+      at += x;
+      bs += y;
+    }
+  };
+  constexpr int PER = SEL_BINS / T;
+  // Counts of this thread's bins (of n, from slot `at` on), returned: keys in the bins above them, in all bins, and in the
+  // 64 slots after the bins.
+  auto bins_above = [&](uint32_t at, uint32_t n, uint32_t (&loc)[PER], uint32_t &inside, uint32_t &beyond) -> uint32_t {
+    uint32_t sum = 0, before, unused;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const uint32_t x = (uint32_t)(tid * PER + i);
+      loc[i] = x < n ? h[at + x] : 0u;
+      sum += loc[i];
+    }
+    scan2(sum, tid < 64 ? h[at + n + tid] : 0u, before, unused, inside, beyond);
+    return inside - before - sum;
+  };
+  auto clear = [&] {
+    __syncthreads();                                               // every thread has read what it needs
+    for (int i = tid; i < SLOTS; i += T) h[i] = 0u;
+    __syncthreads();
+  };
+
+  // ---- a window of keys lo .. lo + last around the threshold, from a sample
+  uint32_t lo = 1, last = 0xfffe, heavy = 0;
+  __syncthreads();
+  if (nb >= 1024) {                                                // one key of eight
+#pragma clang loop unroll(full)
+    for (int i = 0; i < IT; ++i) {
+      const uint32_t s = k[i][i & 3][0];
+      if (s) atomicAdd(&h[s >> 5], 1u);
+    }
+    __syncthreads();
+    uint32_t loc[PER], ns, unused;
+    uint32_t above = bins_above(0u, SEL_BINS, loc, ns, unused);
+    // 5 standard deviations of the sample's count; a window that misses the threshold is found out by the counts
+    const uint32_t cs = max(1u, min(ns, (uint32_t)((uint64_t)c * ns / (uint32_t)nb)));
+    const uint32_t margin = (uint32_t)(5.f * sqrtf((float)cs)) + 4u;
+    const uint32_t deep = cs + margin, top = cs > margin ? cs - margin : 0u;
+    if (tid == 0) {
+      res[0] = 0u;
+      res[1] = SEL_BINS - 1;
+      res[5] = 0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = PER - 1; i >= 0; --i) {
+      if (above < deep && above + loc[i] >= deep) {
+        res[0] = (uint32_t)(tid * PER + i);
+        res[5] = loc[i];
+      }
+      if (above < top && above + loc[i] >= top) res[1] = (uint32_t)(tid * PER + i);
+      above += loc[i];
+    }
+    clear();
+    const uint32_t lo_bin = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[0]), hi_bin = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[1]);
+    lo = max(1u, lo_bin << 5);
+    last = (hi_bin << 5) + 31u - lo;
+    // A value that repeats at the window's lower end (zeros, below a gap) would meet itself in one slot: the window begins
+    // above it, where there is room as far up as its slots for keys below reach, and that value is looked at by itself if
+    // the threshold is not in the window.
+    const uint32_t end = (hi_bin << 5) + 31u, next = (lo_bin + 1u) << 5;
+    if (hi_bin > lo_bin + 1u && 8u * (uint32_t)__builtin_amdgcn_readfirstlane((int)res[5]) > ns) {
+      heavy = lo;
+      const uint32_t room = next + (64u << max(0, 21 - __builtin_clz(end - next)));
+      lo = room < (hi_bin << 5) ? room : next;
+      last = end - lo;
+    }
+  }
+
+  // ---- the threshold: count the window's keys (in bins, if there are more than 2048) until a bin is one key
+  uint32_t krem = c;
+  bool first = true;
+#pragma unroll 1
+  for (;;) {
+    const uint32_t shift = (uint32_t)max(0, 32 - __builtin_clz(last | 1u) - 11), n = (last >> shift) + 1u;
+    // Every token adds to some slot: the window's n bins from slot `at` on, the slots before them for keys below and the
+    // slots after them for keys above, there each lane to its own (no comparison, no mask of lanes, no conflict). Few bins
+    // have 2^rs copies each, by lane: keys that repeat do not wait for each other.
+    const uint32_t rs = min(6u, (uint32_t)__builtin_clz(max(n, 2u) - 1u) - 21u);                 // n << rs <= 2048
+    const uint32_t at = min(64u >> rs, lo >> shift), base = lo - (at << shift);
+    auto pair = [](uint32_t x) { return (u16x2)(unsigned short)x; };
+    const u16x2 base2 = pair(base), shift2 = pair(shift), copies = pair(1u << rs), copy = pair((uint32_t)lane & ((1u << rs) - 1u));
+    const u16x2 least = pair(at ? min((uint32_t)lane >> rs, at - 1u) : 0u), most = pair(at + n + ((uint32_t)lane >> rs));
+#pragma clang loop unroll(full)
+    for (int i = 0; i < IT; ++i) {
+      if (8 * i * T < nb) {
+        u16x2 x[4];                                                // (four at a time: a packed result cannot be used at once)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = __builtin_elementwise_sub_sat(k[i][e], base2);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = x[e] >> shift2;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = __builtin_elementwise_max(x[e], least);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = __builtin_elementwise_min(x[e], most);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = x[e] * copies + copy;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          atomicAdd(&h[x[e][0]], 1u);
+          atomicAdd(&h[x[e][1]], 1u);
+        }
+      }
+      fence_schedule();
+    }
+    __syncthreads();
+    uint32_t loc[PER], inside, beyond;
+    uint32_t above = bins_above(at << rs, n << rs, loc, inside, beyond);
+    if (first) krem = c - min(beyond, c);
+    if (krem < 1u || krem > inside) {                              // not in the window: below it, or the sample misled
+      lo = heavy && krem > inside ? heavy : 1u;
+      last = lo == heavy ? 31u - (lo & 31u) : 0xfffeu;
+      heavy = 0;
+      clear();
+      continue;
+    }
+    uint32_t top = above;
+#pragma unroll
+    for (int i = PER - 1; i >= 0; --i) {
+      if (top < krem && top + loc[i] >= krem) res[2] = (uint32_t)(tid * PER + i) >> rs;
+      top += loc[i];
+    }
+    __syncthreads();
+    const uint32_t bin = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[2]);
+#pragma unroll
+    for (int i = PER - 1; i >= 0; --i) {
+      const uint32_t x = (uint32_t)(tid * PER + i);
+      if (x >> rs == bin && (x + 1u) >> rs != bin) res[3] = krem - above;        // (the bin's last copy)
+      above += loc[i];
+    }
+    __syncthreads();
+    first = false;
+    krem = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[3]);
+    lo += bin << shift;
+    last = (1u << shift) - 1u;
+    if (shift == 0) break;
+    clear();
+  }
+  const uint32_t r = krem;                                         // of the tokens with key lo, the first r are kept
+
+  // ---- two bits per token: 0 below, 1 equal, 2 above the threshold
+  const u16x2 below = (u16x2)(unsigned short)(lo - 1u);
+  uint16_t *const codes16 = reinterpret_cast<uint16_t *>(codes);
+#pragma clang loop unroll(full)
+  for (int i = 0; i < IT; ++i) {
+    uint32_t m = 0;
+    u16x2 x[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = __builtin_elementwise_sub_sat(k[i][e], below);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = __builtin_elementwise_min(x[e], (u16x2)2);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m |= __builtin_bit_cast(uint32_t, x[e]) << (4 * e);
+    const int w = i * T + tid;
+    codes16[w + 2 * (w >> 5)] = (uint16_t)(m | m >> 14);
+    fence_schedule();
+  }
+  __syncthreads();
+  constexpr int CW = CODES / T;                                    // words per thread, consecutive
+  static_assert(CW % 2 == 0, "two words make one");
+  uint32_t w[CW], gt = 0, eq = 0;
+#pragma unroll
+  for (int x = 0; x < CW; ++x) {
+    const int at = tid * CW + x;
+    w[x] = codes[at + (at >> 4)];
+    gt += (uint32_t)__builtin_popcount(w[x] & 0xaaaaaaaau);
+    eq += (uint32_t)__builtin_popcount(w[x] & 0x55555555u);
+  }
+  uint32_t gt0, eq0, gts, eqs;
+  scan2(gt, eq, gt0, eq0, gts, eqs);
+  const uint32_t pos = gt0 + min(eq0, r);                          // this thread's first place in the list
+  // its kept tokens, a bit each
+  uint32_t mine = 0;
+#pragma unroll
+  for (int x = 0; x < CW; ++x) {
+    const uint32_t e = w[x] & 0x55555555u, n = (uint32_t)__builtin_popcount(e);
+    uint32_t keep = eq0 + n <= r ? e : 0u;
+    if (n && eq0 < r && eq0 + n > r) {
+      uint32_t rest = e;
+      for (uint32_t q = eq0; q < r; ++q) {
+        keep |= rest & (0u - rest);
+        rest &= rest - 1u;
+      }
+    }
+    eq0 += n;
+    uint32_t y = ((w[x] >> 1) & 0x55555555u) | keep;
+    mine += (uint32_t)__builtin_popcount(y);
+    y = (y | y >> 1) & 0x33333333u;                                // the even bits next to each other
+    y = (y | y >> 2) & 0x0f0f0f0fu;
+    y = (y | y >> 4) & 0x00ff00ffu;
+    y = (y | y >> 8) & 0x0000ffffu;
+    if (x & 1) w[x >> 1] |= y << 16;
+    else w[x >> 1] = y;
+  }
+#pragma unroll 1
+  for (uint32_t base = 0; base < c; base += STAGE) {
+    uint32_t p = pos;
+    if (p < base + STAGE && p + mine > base) {
+#pragma unroll
+      for (int x = 0; x < CW / 2; ++x)
+        for (uint32_t rest = w[x]; rest; rest &= rest - 1u, ++p)
+          if (p - base < (uint32_t)STAGE) staged[p - base] = (stage_t)(32 * (tid * (CW / 2) + x) + __builtin_ctz(rest));
+    }
+    __syncthreads();
+    const uint32_t cnt = min(c - base, (uint32_t)STAGE);
+    for (int ti = t0; ti < t1; ++ti) {
+      int32_t *dst = A.indices + ((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + base;
+      const uint32_t quads = cnt / 4;
+      for (uint32_t i = tid; i < quads; i += T) {
+        typedef stage_t stage4 __attribute__((ext_vector_type(4)));
+        typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+        const stage4 x = *reinterpret_cast<const stage4 *>(&staged[4 * i]);
+        *reinterpret_cast<i32x4_any *>(dst + 4 * i) = i32x4_any{(int32_t)x[0], (int32_t)x[1], (int32_t)x[2], (int32_t)x[3]};
+      }
+      if (tid < (int)(cnt & 3u)) dst[4 * quads + tid] = (int32_t)staged[4 * quads + tid];
+    }
+    __syncthreads();
+  }
+}
+
 }  // namespace
+
+// Rows of 8 to 131072 tokens of one bf16 score each.
+static hipError_t launch_select_row16(const SelectArgs &a, hipStream_t s) {
+  const int64_t rows = (int64_t)a.B * a.Hd;
+  if (rows == 0) return hipSuccess;
+  if (a.N < 8 || a.N > SEL_ROW16_N) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)rows);
+  if (a.N <= 8192) STS_LAUNCH((select_row16_kernel<256, 4>), grid, dim3(256), 0, s, a);
+  else if (a.N <= 16384) STS_LAUNCH((select_row16_kernel<256, 8>), grid, dim3(256), 0, s, a);
+  else if (a.N <= 32768) STS_LAUNCH((select_row16_kernel<256, 16>), grid, dim3(256), 0, s, a);
+  else if (a.N <= 65536) STS_LAUNCH((select_row16_kernel<512, 16>), grid, dim3(512), 0, s, a);
+  else STS_LAUNCH((select_row16_kernel<1024, 16>), grid, dim3(1024), 0, s, a);
+  return sts_take_launch_status();
+}
 
 // Rows of 4 to 32768 tokens. Calls of up to 512 rows get 1024 threads per row (latency: 256 rows of 16384 tokens 25 us
 // with 256 threads per row), others as few as hold the row in 64 registers per thread (several workgroups per CU: 4096
@@ -398,6 +750,7 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
 hipError_t launch_select_row(const SelectArgs &a, hipStream_t s) {
   const int64_t rows = (int64_t)a.B * a.Hd;
   if (rows == 0) return hipSuccess;
+  if (a.row16) return launch_select_row16(a, s);
   if (a.N < 4 || a.N > SEL_SMALL_N) return hipErrorInvalidValue;
   const dim3 grid((unsigned)rows);
   if (rows <= 512) {

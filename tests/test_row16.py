@@ -1,0 +1,91 @@
+"""Rows of one bf16 score per token, ranked in one workgroup's registers (select_row16_kernel in
+csrc/select_row.hip), against the CPU oracle bit for bit: at the edges of the kernel's forms, at odd
+addresses and lengths, and on scores that its sample and its windows of keys do not expect. On the GPU,
+and compiled for the CPU (tests/emulated), where the waves run in random order."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_15508_amd as sts
+from test_select_emulated import check, lib  # noqa: F401  (lib: the emulated library, a fixture)
+
+PATH_KNOB = 3
+
+
+def scores_of(what, N, k, seed):
+    g = torch.Generator().manual_seed(seed)
+    r = torch.randn(N, generator=g)
+    p = torch.softmax(r * 2, dim=-1)
+    some = torch.rand(N, generator=g)
+    if what == "softmax":
+        return p
+    if what == "zeros":                               # about as many scores as are kept, zeros otherwise
+        return p * (some < k / N)
+    if what == "zeros then a stretch":                # exactly as many: the lowest score lies alone above the gap
+        p[:N - k] = 0
+        return p
+    if what == "constant":
+        return torch.full((N,), -0.25)
+    if what == "signed":                              # zeros of both signs in the middle
+        r[some < 0.3] = 0.0
+        r[some < 0.1] = -0.0
+        return r
+    if what == "infinite":                            # saturated scores above, masked ones below
+        r[some < k / N / 2] = float("inf")
+        r[some > 0.9] = float("-inf")
+        return r
+    if what == "heavy tail":                          # keys all over the range
+        return torch.exp(r * 30)
+    if what == "sorted":
+        return p.sort().values
+    p[N // 3:N // 3 + N // 8] *= 1e5                  # "stretch"
+    return p
+
+
+# lengths around the forms' limits (8192, 16384, 32768, 65536, 131072 tokens), below the sampled ones (1024), a
+# list longer than what is staged at once, a budget of one, of all but one and of all
+CASES = [
+    ("softmax", 8, 3), ("signed", 1023, 100), ("softmax", 1024, 102), ("infinite", 4096, 400), ("constant", 8191, 4000),
+    ("softmax", 8193, 8192), ("zeros", 16384, 1638), ("zeros then a stretch", 16385, 1638), ("signed", 32768, 20000),
+    ("stretch", 32769, 3277), ("heavy tail", 65535, 6553), ("sorted", 65536, 1), ("zeros then a stretch", 65537, 6553),
+    ("softmax", 100001, 10000), ("signed", 131071, 131071), ("zeros", 131072, 13107), ("constant", 131072, 9000),
+]
+
+
+@pytest.mark.parametrize("what,N,k", CASES)
+def test_emulated(lib, what, N, k):  # noqa: F811
+    lib.emu_schedule(N, -1, -1)
+    lib.sts_set_knob(PATH_KNOB, 6.0)
+    try:
+        s = scores_of(what, N, k, N + k).to(torch.bfloat16)
+        flat = torch.zeros(2 * N + 3, dtype=torch.bfloat16)
+        at = flat[3:].view(2, 1, 1, N)                # an odd element
+        at[0, 0, 0], at[1, 0, 0] = s, s.flip(0)
+        check(lib, at, [0, 0], k, lens=[N, max(1, N - 9)])
+    finally:
+        lib.sts_set_knob(PATH_KNOB, float("nan"))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("what,N,k", CASES)
+def test_on_the_gpu(what, N, k):
+    B, Hd = 5, 3
+    s = torch.stack([torch.stack([scores_of(what, N, k, N + k + 7 * b + j) for j in range(Hd)]) for b in range(B)]).to(torch.bfloat16)
+    flat = torch.zeros(s.numel() + 3, dtype=torch.bfloat16, device="cuda:0")
+    sd = flat[3:].view(B, Hd, 1, N)
+    sd.copy_(s[:, :, None])
+    hm = [0, 0, 2]                                    # draft head 1 is read by none
+    kh = [k, 1, max(1, k - k // 3)]
+    lens = torch.tensor([N, max(1, N - 9), N // 2 + 1, 0, min(N, 20)], dtype=torch.int32)
+    sts.set_knob("select_path", 6)
+    try:
+        idx, cnt, _ = sts.sts_select(sd, hm, k, k_head=kh, seq_lens=lens.to("cuda:0"))
+    finally:
+        sts.set_knob("select_path", None)
+    o_idx, o_cnt, _ = oracle.select_indices(s[:, :, None].float().numpy(), np.asarray(hm, np.int32), k, k_head=kh, seq_lens=lens.numpy())
+    np.testing.assert_array_equal(cnt.cpu().numpy(), o_cnt)
+    np.testing.assert_array_equal(idx.cpu().numpy(), o_idx)
+    if N >= 4096:                                     # the library's own rule
+        idx2, cnt2, _ = sts.sts_select(sd, hm, k, k_head=kh, seq_lens=lens.to("cuda:0"))
+        assert torch.equal(idx, idx2) and torch.equal(cnt, cnt2)
