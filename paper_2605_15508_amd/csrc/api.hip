@@ -665,7 +665,7 @@ static sts_status enqueue_select(const sts_select_params *p, void *stream) {
     a.agg = nullptr;
     a.src = nullptr;
     a.hist = a.state = a.chunk_cnt = nullptr;
-    a.row16 = 1;
+    a.rowpass_threads = SEL_ROW16;
     rc = run_kernel(pl.row16_kind, s, [&] { return launch_select_small(a, s); });
     return rc == hipSuccess ? STS_OK : STS_EHIP;
   }

@@ -116,6 +116,7 @@ constexpr int SEL_BINS = 2048;          // bins of the widest digit
 constexpr int SEL_CHUNK = 8192;         // tokens per workgroup in the scan kernels
 constexpr int SEL_THREADS = 256;
 constexpr int SEL_SMALL_N = 32768;      // LDS capacity of the one-workgroup-per-row selection (tokens)
+constexpr int SEL_ROW16 = 16;
 constexpr int SEL_ROW16_N = 131072;     // tokens of one bf16 score each that a workgroup's registers hold
 constexpr int SEL_FLAG_PITCH = 32;      // words between the published counts of two chunks: one 128-byte line each
 constexpr int SEL_FUSED_N = 8192;
@@ -159,7 +160,7 @@ struct SelectArgs {
   float *blk;                 // [B,Hd,NB] per-block sums (page > 1), else unused
   const float *src;           // what is ranked: agg (page == 1) or blk
   int32_t srcN;               // row length of src: N or NB
-  int32_t page;               // tokens per block (>= 1)
+  int32_t page;               // tokens per block (>= 1); rows of block sums that are ranked as scores have their lengths in tokens
   uint32_t *hist;             // [rows][3][SEL_BINS]
   uint32_t *state;            // [rows][8]: digits 0/1 and remaining k after each, [6] budget
   uint32_t *chunk_cnt;        // [rows][nchunks][SEL_FLAG_PITCH], word 0: published flag | equal count << 14 | greater count
@@ -176,8 +177,8 @@ struct SelectArgs {
                               // exchange (top bit: written), zero before the launch
   int32_t smp_tokens, smp_parts;   // tokens per workgroup (a multiple of 256), workgroups per row
   int32_t fused_spin_limit;   // polls of another part's words before the row is ranked by plain passes instead
-  int32_t row16;              // one bf16 score per token, rows in registers (select_row16_kernel)
-  int32_t rowpass_threads;    // one workgroup per row (select_rowpass_kernel): 256 or 1024 threads
+  int32_t rowpass_threads;    // one workgroup per row (select_rowpass_kernel): 256 or 1024 threads; SEL_ROW16: rows of one
+                              // bf16 score per token in registers (select_row16_kernel)
   int32_t agg_is_input;       // `agg` is the caller's score tensor itself (one fp32 probability row per head): never stored to
   int32_t B, Hd, Tq, N, Hq, k, kind, reduce, nchunks;   // k: row pitch of indices = largest budget
   SelectTargets targets;

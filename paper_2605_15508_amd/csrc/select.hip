@@ -1100,6 +1100,19 @@ hipError_t launch_select_small(const SelectArgs &a, hipStream_t s) {
 // ranks the rows of a.src (up to SEL_SMALL_N entries each) out of LDS
 hipError_t launch_select_rank(const SelectArgs &a, hipStream_t s) {
   if ((size_t)a.B * a.Hd == 0) return hipSuccess;
+  // 64 rows of 8192 or 16384 blocks: 39.3 -> 37.1, 46.5 -> 41.8 us with the block sums; 128 rows of 1024: 22.6, 23.8
+  if (a.srcN > 2048) {
+    SelectArgs b = a;                                  // one fp32 score per block
+    b.scores = a.src;
+    b.scores_bf16 = 0;
+    b.lse = nullptr;
+    b.kind = STS_SCORES_PROBS;
+    b.reduce = STS_REDUCE_SUM;
+    b.agg = nullptr;
+    b.Tq = 1;
+    b.N = a.srcN;
+    return launch_select_row(b, s);
+  }
   STS_LAUNCH(select_small_kernel<true>, dim3(a.B * a.Hd), dim3(SMALL_THREADS), 0, s, a);
   return sts_take_launch_status();
 }

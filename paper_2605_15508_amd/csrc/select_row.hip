@@ -1,67 +1,79 @@
 // Short rows (gfx950): a row that one workgroup's registers hold, ranked in one launch. Every thread
 // loads and aggregates the row's quads that are its own (same fp32 order as everywhere) and keeps the
-// keys; nothing is read twice. The threshold is found among keys counted into 2048 bins that divide
-// the range in question: first the row's own key range, then, if the bin of the threshold still holds more
-// than a few keys, that bin. Long rows count only a sixteenth of their keys at first, which gives a band
-// around the threshold that is listed and counted (and if that fails, all keys, as for short rows).
+// keys; nothing is read twice. Three kernels:
+//   short_select_row_kernel  a few keys per thread: all of them counted, in 2048 bins that divide the row's key range and,
+//                            if the bin of the threshold still holds more than a few keys, that bin;
+//   select_row_kernel        more keys per thread: a sample gives a window of keys around the threshold, whose keys are counted
+//                            in up to 2048 bins;
+//   select_row16_kernel      rows of one bf16 score per token, two keys to a register.
 // The kept tokens are bits in LDS; the list is the bits read in order.
 //
-// What bounds it: for thousands of rows (head mapping: 6144 rows of 16K tokens, 403 MB) memory and vector
-// instructions alike; several small workgroups per CU hide each other's latencies. For few rows latency.
+// What bounds it: for thousands of rows memory and vector instructions alike; several small workgroups per CU hide each
+// other's latencies. For few rows latency. Counting used to be a comparison per key and mask of lanes; where every key adds
+// to some slot, each lane to its own outside the window, 4096 rows of 16384 tokens take 98 us (131), 2048 of 30001 99 (136),
+// 4096 of 20000 156 (234), 256 rows of 16384 with five scores per token 21.9 (24.2), and rows of zeros with the budget at
+// their edge 130 (625).
 #include "select_util.h"
 
 namespace {
 
 constexpr int ROW_CAND = 64;              // keys of the threshold's bin that are ranked against each other
 
+// nothing is moved across: a pass over keys in registers needs few others then
+__device__ __forceinline__ void fence_schedule() {
+#if defined(__AMDGCN__)
+  __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+
+// the same value, which the compiler does not know: what is computed from it is not kept from earlier
+__device__ __forceinline__ int again(int x) {
+#if defined(__AMDGCN__)
+  asm("" : "+v"(x));
+#endif
+  return x;
+}
+
+// Exclusive sums over the workgroup of two values per thread (tot: 2 * T / 64 words), and the totals.
 template <int T>
-__device__ __forceinline__ void row_min_max(uint32_t &lo, uint32_t &hi, uint32_t *red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    lo = min(lo, (uint32_t)__shfl_xor((int)lo, off, 64));
-    hi = max(hi, (uint32_t)__shfl_xor((int)hi, off, 64));
-  }
-  if ((threadIdx.x & 63) == 0) {
-    red[2 * (threadIdx.x >> 6)] = lo;
-    red[2 * (threadIdx.x >> 6) + 1] = hi;
+__device__ __forceinline__ void scan2(uint32_t a, uint32_t b, uint32_t *tot, int lane, int wave, uint32_t &a0, uint32_t &b0,
+                                      uint32_t &as, uint32_t &bs) {
+  const uint32_t ai = wave_incl_scan(a), bi = wave_incl_scan(b);
+  if (lane == 63) {
+    tot[2 * wave] = ai;
+    tot[2 * wave + 1] = bi;
   }
   __syncthreads();
+  a0 = ai - a;
+  b0 = bi - b;
+  as = bs = 0;
 #pragma unroll
   for (int w = 0; w < T / 64; ++w) {
-    lo = min(lo, red[2 * w]);
-    hi = max(hi, red[2 * w + 1]);
+    const uint32_t x = tot[2 * w], y = tot[2 * w + 1];
+    if (w < wave) {
+      a0 += x;
+      b0 += y;
+    }
+    as += x;
+    bs += y;
   }
 }
 
-// T threads, IT quads per thread: rows of up to 4 * T * IT tokens. SAMPLE: IT is a multiple of 4.
-template <int T, int IT, bool SAMPLE>
-__global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const SelectArgs A) {
-  constexpr int TOK = 4 * T * IT;
-  constexpr int LIST = SAMPLE ? TOK * 3 / 16 : ROW_CAND;           // band tokens
-  constexpr int STAGE = TOK / 8 > 1024 ? TOK / 8 : 1024;           // list entries staged per round
-  __shared__ uint32_t bits[TOK / 32];
-  __shared__ uint32_t h[SEL_BINS];
-  __shared__ __attribute__((aligned(8))) uint32_t store[2 * LIST > STAGE ? 2 * LIST : STAGE];
-  __shared__ uint32_t tmp[T / 64 + 2];
-  __shared__ uint32_t red[2 * T / 64];
-  __shared__ uint32_t ctr[4];
-  u32x2 *const list = reinterpret_cast<u32x2 *>(store);            // key, token
-  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-  const int bt = row / A.Hd, j = row % A.Hd;
-  const int nb = __builtin_amdgcn_readfirstlane(row_len(A, bt));
-  const uint32_t c = (uint32_t)min(A.kh[j], nb);
-  const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
-  write_tail<T>(A, bt, j, c);
-  float *out = A.agg ? A.agg + (size_t)row * A.N : nullptr;
-  const bool ranked = c > 0 && t0 != t1;
-  if (!ranked && !out) return;
-  const AggRow R = agg_row(A, row);
-  for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
-  if (tid < 4) ctr[tid] = 0u;
+// Valid length of a row. Block sums are ranked as rows of scores whose lengths are given in tokens.
+__device__ __forceinline__ int ranked_len(const SelectArgs &A, int bt) {
+  int n = A.N;
+  if (A.seq_lens) {
+    n = max(A.seq_lens[bt], 0);
+    if (A.page > 1) n = (int)(((uint32_t)n + (uint32_t)A.page - 1u) / (uint32_t)A.page);
+  }
+  return min(n, A.N);
+}
 
-  // ---- the row: thread tid owns the quads tid, tid + T, ... A position past the row's valid length holds INT_MIN,
-  // which no token does.
-  int v[IT][4];
+// The row's scores, aggregated, as signed numbers of their order: thread tid gets the quads tid, tid + T, ... A position past
+// the row's valid length holds INT_MIN, which no token does. out: the aggregate, stored on request.
+template <int T, int IT>
+__device__ __forceinline__ void load_row(const AggRow &R, float *out, int nb, int tid, int (&v)[IT][4]) {
   int any = 0;
   auto take = [&](int i, f32x4 acc) {
     const int n = 4 * (i * T + tid);
@@ -137,38 +149,73 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
       take(i, acc[i]);
     }
   }
-  if (!ranked) return;
   if (ballot64(any < 0)) {                             // negative scores in this wave
 #pragma clang loop unroll(full)
     for (int i = 0; i < IT; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[i][e] = max(ordered(v[i][e]), (int)0x80000001);
   }
-  if (nb < TOK) {
+  if (nb < 4 * T * IT) {
 #pragma clang loop unroll(full)
     for (int i = 0; i < IT; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[i][e] = 4 * (i * T + tid) + e < nb ? v[i][e] : (int)0x80000000;
   }
+}
 
-  // the part of the row's keys that is counted: all, or (sampled) one of sixteen, from every fourth quad of a thread
-  auto each = [&](bool sampled, auto f) {
-    if (SAMPLE && sampled) {
-#pragma clang loop unroll(full)
-      for (int i = 0; i < IT; ++i)
-        if ((i & 3) == (tid & 3)) {
-          const int e = (tid >> 2) & 3;
-          int s = 0;                                   // (masks: a choice among array elements would put the array in memory)
+// ----------------------------------------------------------- rows of at most eight quads per four waves
+template <int T>
+__device__ __forceinline__ void row_min_max(uint32_t &lo, uint32_t &hi, uint32_t *red) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) s |= v[i][q] & (e == q ? -1 : 0);
-          f(s, 4 * (i * T + tid) + e);
-        }
-    } else {
-#pragma clang loop unroll(full)
-      for (int i = 0; i < IT; ++i)
+  for (int off = 32; off > 0; off >>= 1) {
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, off, 64));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, off, 64));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[2 * (threadIdx.x >> 6)] = lo;
+    red[2 * (threadIdx.x >> 6) + 1] = hi;
+  }
+  __syncthreads();
 #pragma unroll
-        for (int e = 0; e < 4; ++e) f(v[i][e], 4 * (i * T + tid) + e);
-    }
+  for (int w = 0; w < T / 64; ++w) {
+    lo = min(lo, red[2 * w]);
+    hi = max(hi, red[2 * w + 1]);
+  }
+}
+
+// T threads, IT quads per thread: rows of up to 4 * T * IT tokens. All keys are counted, in bins that divide their range.
+template <int T, int IT>
+__global__ void __launch_bounds__(T) short_select_row_kernel(const SelectArgs A) {
+  constexpr int TOK = 4 * T * IT;
+  constexpr int STAGE = TOK / 8 > 1024 ? TOK / 8 : 1024;           // list entries staged per round
+  __shared__ uint32_t bits[TOK / 32];
+  __shared__ uint32_t h[SEL_BINS];
+  __shared__ uint32_t store[STAGE];                                // bits of the equal tokens, then list entries
+  __shared__ uint32_t tmp[T / 64 + 2];
+  __shared__ uint32_t red[2 * T / 64];
+  __shared__ uint32_t ctr[4];
+  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int bt = row / A.Hd, j = row % A.Hd;
+  const int nb = __builtin_amdgcn_readfirstlane(ranked_len(A, bt));
+  const uint32_t c = (uint32_t)min(A.kh[j], nb);
+  const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
+  write_tail<T>(A, bt, j, c);
+  float *out = A.agg ? A.agg + (size_t)row * A.N : nullptr;
+  const bool ranked = c > 0 && t0 != t1;
+  if (!ranked && !out) return;
+  const AggRow R = agg_row(A, row);
+  for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
+  if (tid < 4) ctr[tid] = 0u;
+
+  int v[IT][4];
+  load_row<T, IT>(R, out, nb, tid, v);
+  if (!ranked) return;
+
+  auto each = [&](auto f) {
+#pragma clang loop unroll(full)
+    for (int i = 0; i < IT; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f(v[i][e], 4 * (i * T + tid) + e);
   };
   // the bin of the rank-th largest of the keys counted in h, and what is left of the rank in it
   auto find = [&](uint32_t rank, uint32_t &bin, uint32_t &left) {
@@ -177,11 +224,9 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
     left = (uint32_t)__builtin_amdgcn_readfirstlane((int)left);
   };
 
-  // ---- keys in question: lo .. lo + last; G keys lie above them, `listed` of them (if any) are in the list
-  // (sampled only if the band that the sample is expected to give fits the list with room to spare)
-  const bool sampled = SAMPLE && nb > TOK / 4 && 32.f * (5.f * sqrtf((float)c * 0.0625f) + 4.f) <= 0.75f * LIST;
+  // ---- keys in question: lo .. lo + last
   uint32_t kmin = 0xffffffffu, kmax = 0u;
-  each(sampled, [&](int s, int) {
+  each([&](int s, int) {
     if (s != (int)0x80000000) {
       kmin = min(kmin, key_of_ordered(s));
       kmax = max(kmax, key_of_ordered(s));
@@ -189,104 +234,15 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
   });
   row_min_max<T>(kmin, kmax, red);
   uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)kmin), last = (uint32_t)__builtin_amdgcn_readfirstlane((int)(kmax - kmin));
-  uint32_t krem = c, listed = 0;
-  bool from_list = false;
-  if (SAMPLE && sampled) {
-    const int shift = max(0, 32 - __clz((int)last) - 11);
-    each(true, [&](int s, int) {
-      if (s != (int)0x80000000) {
-        atomicAdd(&h[(key_of_ordered(s) - lo) >> shift], 1u);
-      }
-    });
-    __syncthreads();
-    uint32_t ns;
-    {
-      constexpr int PER = SEL_BINS / T;
-      uint32_t sum = 0;
-#pragma unroll
-      for (int i = 0; i < PER; ++i) sum += h[tid * PER + i];
-      (void)block_excl_scan<T, true>(sum, tmp, ns);
-      ns = (uint32_t)__builtin_amdgcn_readfirstlane((int)ns);
-    }
-    // 5 standard deviations of the sample count, as if the tokens were independent: a stretch of heavy tokens longer
-    // than 16 is sampled more exactly than that
-    const uint32_t cs = max(1u, min(ns, (uint32_t)((uint64_t)c * ns / (uint32_t)nb)));
-    const uint32_t margin = (uint32_t)(5.f * sqrtf((float)cs)) + 4u;
-    uint32_t lo_bin = 0, hi_bin = SEL_BINS - 1, unused;
-    const bool haveL = cs + margin <= ns, haveU = cs > margin;
-    if (haveL) find(cs + margin, lo_bin, unused);
-    if (haveU) find(cs - margin, hi_bin, unused);
-    const uint64_t u = (uint64_t)lo + ((uint64_t)(hi_bin + 1u) << shift);
-    const uint32_t L = haveL ? lo + (lo_bin << shift) : 1u;            // (key 0 is no token's)
-    const uint32_t U1 = haveU && u <= 0xffffffffull ? (uint32_t)u - 1u : 0xffffffffu;   // last key of the band
-    // the band is listed, what lies above it counted
-    const int sL = ordered_of_key(L), sU1 = ordered_of_key(U1);
-    uint32_t G = 0;                                    // wave-uniform
-#pragma clang loop unroll(full)
-    for (int i = 0; i < IT; ++i) {
-      uint64_t bd[4];
-      bool in[4];
-      uint32_t held = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bool sure = v[i][e] > sU1;
-        in[e] = !sure && v[i][e] >= sL;
-        G += (uint32_t)__builtin_popcountll(ballot64(sure));
-        bd[e] = ballot64(in[e]);
-        held += (uint32_t)__builtin_popcountll(bd[e]);
-      }
-      uint32_t at = 0;
-      if (lane == 0) at = atomicAdd(&ctr[0], held);
-      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-      if (at + held <= (uint32_t)LIST) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (in[e]) list[lanes_before(bd[e], at)] = u32x2{key_of_ordered(v[i][e]), (uint32_t)(4 * (i * T + tid) + e)};
-          at += (uint32_t)__builtin_popcountll(bd[e]);
-        }
-      }
-    }
-    if (lane == 0) atomicAdd(&ctr[1], G);
-    for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
-    __syncthreads();
-    const uint32_t M = (uint32_t)__builtin_amdgcn_readfirstlane((int)ctr[0]);
-    G = (uint32_t)__builtin_amdgcn_readfirstlane((int)ctr[1]);
-    if (G < c && G + M >= c && M <= (uint32_t)LIST) {
-      from_list = true;
-      listed = M;
-      krem = c - G;
-      lo = L;
-      last = U1 - L;
-    } else {                                           // the sample misled: all keys are counted
-      kmin = 0xffffffffu;
-      kmax = 0u;
-      each(false, [&](int s, int) {
-        if (s != (int)0x80000000) {
-          kmin = min(kmin, key_of_ordered(s));
-          kmax = max(kmax, key_of_ordered(s));
-        }
-      });
-      __syncthreads();
-      row_min_max<T>(kmin, kmax, red);
-      lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)kmin);
-      last = (uint32_t)__builtin_amdgcn_readfirstlane((int)(kmax - kmin));
-    }
-  }
+  uint32_t krem = c;
   int shift = max(0, 32 - __clz((int)last) - 11);
   uint32_t in_bin;
 #pragma unroll 1
   for (;;) {
-    if (SAMPLE && from_list) {
-      for (uint32_t i = tid; i < listed; i += T) {
-        const uint32_t k = list[i][0] - lo;
-        if (k <= last) atomicAdd(&h[k >> shift], 1u);
-      }
-    } else {
-      each(false, [&](int s, int) {
-        const uint32_t k = key_of_ordered(s) - lo;
-        if (k <= last && s != (int)0x80000000) atomicAdd(&h[k >> shift], 1u);
-      });
-    }
+    each([&](int s, int) {
+      const uint32_t k = key_of_ordered(s) - lo;
+      if (k <= last && s != (int)0x80000000) atomicAdd(&h[k >> shift], 1u);
+    });
     __syncthreads();
     uint32_t bin, left;
     find(krem, bin, left);
@@ -311,13 +267,9 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
         if (s < (uint32_t)ROW_CAND) h[s] = k;
       }
     };
-    if (SAMPLE && from_list) {
-      for (uint32_t i = tid; i < listed; i += T) add(list[i][0]);
-    } else {
-      each(false, [&](int s, int) {
-        if (s != (int)0x80000000) add(key_of_ordered(s));
-      });
-    }
+    each([&](int s, int) {
+      if (s != (int)0x80000000) add(key_of_ordered(s));
+    });
     __syncthreads();
     const uint32_t n = min(in_bin, (uint32_t)ROW_CAND);
     const uint32_t mine = h[min((uint32_t)lane, n - 1u)];
@@ -334,7 +286,7 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
   }
 
   // ---- bits of the kept tokens: all above T, and equal ones unless only some of them are kept, which then get bits
-  // of their own (the list's memory is free)
+  // of their own
   const int sT = ordered_of_key(Tk);
   const bool all_eq = r >= E;
   __syncthreads();
@@ -390,6 +342,305 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
   }
 }
 
+// ----------------------------------------------------------- longer rows: a window of keys from a sample
+// T threads, IT quads per thread: rows of up to 4 * T * IT tokens. (Up to eight keys per thread of 1024, or 16 of 256, are ranked
+// faster without a sample: 16 rows of 4096 tokens 8.3 against 9.5 us, 1024 of 4096 10.4, 10.8.)
+template <int T, int IT>
+__global__ void __launch_bounds__(T, 4) select_row_kernel(const SelectArgs A) {
+  constexpr int TOK = 4 * T * IT;
+  constexpr int STAGE = TOK / 8 > 1024 ? TOK / 8 : 1024;           // list entries staged per round
+  constexpr int SLOTS = SEL_BINS + 2 * 64;                         // a window's bins, and 64 for the keys on either side of it
+  __shared__ __attribute__((aligned(16))) uint32_t codes[TOK / 16];            // a byte per quad: bits of the tokens above, of the equal ones
+  __shared__ uint32_t h[SLOTS];
+  __shared__ uint32_t staged[STAGE];
+  __shared__ uint32_t cand_key[ROW_CAND], cand_tok[ROW_CAND];      // (not as pairs: the keys would be held in pairs of registers)
+  __shared__ uint32_t tot[2 * T / 64];
+  __shared__ uint32_t res[8];
+  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int bt = row / A.Hd, j = row % A.Hd;
+  const int nb = __builtin_amdgcn_readfirstlane(ranked_len(A, bt));
+  const uint32_t c = (uint32_t)min(A.kh[j], nb);
+  const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
+  write_tail<T>(A, bt, j, c);
+  float *out = A.agg ? A.agg + (size_t)row * A.N : nullptr;
+  const bool ranked = c > 0 && t0 != t1;
+  if (!ranked && !out) return;
+  const AggRow R = agg_row(A, row);
+  for (int i = tid; i < SLOTS; i += T) h[i] = 0u;
+
+  int v[IT][4];
+  load_row<T, IT>(R, out, nb, tid, v);
+  if (!ranked) return;
+  uint32_t k[IT][4];                                   // unsigned keys, 0 where there is no token
+#pragma clang loop unroll(full)
+  for (int i = 0; i < IT; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) k[i][e] = key_of_ordered(v[i][e]);
+
+  constexpr int PER = SEL_BINS / T;
+  // Counts of this thread's bins (of n, from slot `at` on), returned: keys in the bins above them, in all bins, and in the
+  // 64 slots after the bins.
+  auto bins_above = [&](uint32_t at, uint32_t n, uint32_t (&loc)[PER], uint32_t &inside, uint32_t &beyond) -> uint32_t {
+    uint32_t sum = 0, before, unused;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const uint32_t x = (uint32_t)(tid * PER + i);
+      loc[i] = x < n ? h[at + x] : 0u;
+      sum += loc[i];
+    }
+    scan2<T>(sum, tid < 64 ? h[at + n + tid] : 0u, tot, lane, wave, before, unused, inside, beyond);
+    return inside - before - sum;
+  };
+  auto clear = [&] {
+    __syncthreads();                                               // every thread has read what it needs
+    for (int i = tid; i < SLOTS; i += T) h[i] = 0u;
+    __syncthreads();
+  };
+  auto uniform = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
+
+  // ---- a window of keys lo .. lo + last around the threshold
+  uint32_t lo = 1, last = 0xfffffffeu, heavy = 0;
+  if (nb >= 1024) {
+    // From a sample of one key in four or eight, by its keys' upper 11 bits and, if that is one value, by the 11 bits below.
+    constexpr int STEP = IT >= 16 ? 2 : 1;
+    uint32_t from = 0, sh = 21;
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t deep = 0, top = 0;;) {
+#pragma clang loop unroll(full)
+      for (int i = 0; i < IT; i += STEP) {
+        const uint32_t s = k[i][(i / STEP) & 3], x = (s - from) >> sh;
+        if (s && x < (uint32_t)SEL_BINS) atomicAdd(&h[x], 1u);
+      }
+      __syncthreads();
+      uint32_t loc[PER], ns, unused;
+      uint32_t above = bins_above(0u, SEL_BINS, loc, ns, unused);
+      if (sh == 21) {
+        // 5 standard deviations of the sample's count; a window that misses the threshold is found out by the counts
+        const uint32_t cs = max(1u, min(ns, (uint32_t)((uint64_t)c * ns / (uint32_t)nb)));
+        const uint32_t margin = (uint32_t)(5.f * sqrtf((float)cs)) + 4u;
+        deep = cs + margin;
+        top = cs > margin ? cs - margin : 0u;
+      }
+      if (tid == 0) {
+        res[0] = 0u;
+        res[1] = SEL_BINS - 1;
+        res[2] = res[3] = 0u;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = PER - 1; i >= 0; --i) {
+        if (above < deep && above + loc[i] >= deep) {
+          res[0] = (uint32_t)(tid * PER + i);
+          res[2] = loc[i];
+          res[3] = above;
+        }
+        if (above < top && above + loc[i] >= top) res[1] = (uint32_t)(tid * PER + i);
+        above += loc[i];
+      }
+      clear();
+      const uint32_t lo_bin = uniform(res[0]), hi_bin = uniform(res[1]);
+      const uint32_t end = from + (hi_bin << sh) + ((1u << sh) - 1u), next = from + ((lo_bin + 1u) << sh);
+      const bool zero_bin = sh == 21 && lo_bin == (0x80000000u >> 21);
+      lo = max(1u, from + (lo_bin << sh));
+      if (hi_bin == lo_bin && !zero_bin && sh == 21) {
+        from = lo_bin << sh;
+        sh = 10;
+        deep -= uniform(res[3]);
+        top -= uniform(res[3]);
+        continue;
+      }
+      // Zeros at the window's lower end would meet in one slot: the window begins above them, as far up as its slots for
+      // keys below reach, and they are looked at by themselves if the threshold is not in the window.
+      if (zero_bin && hi_bin > lo_bin && 8u * uniform(res[2]) > ns) {
+        heavy = lo;
+        const uint32_t room = next + (64u << max(0, 21 - __builtin_clz(end - next)));
+        lo = room < (hi_bin << sh) ? room : next;
+      }
+      last = zero_bin && hi_bin == lo_bin ? 31u : end - lo;
+      break;
+    }
+  } else {
+    __syncthreads();
+  }
+
+  // ---- the threshold's bin: count the window's keys in up to 2048 bins, until a bin is one key or holds few
+  uint32_t krem = c, in_bin;
+  bool first = true;
+#pragma unroll 1
+  for (;;) {
+    const uint32_t shift = (uint32_t)max(0, 21 - __builtin_clz(last | 1u)), n = (last >> shift) + 1u;
+    // Every token adds to some slot: the window's n bins from slot `at` on, the slots before them for keys below and the
+    // slots after them for keys above, there each lane to its own (no comparison, no mask of lanes, no conflict). Few bins
+    // have 2^rs copies each, by lane: keys that repeat do not wait for each other.
+    const uint32_t rs = shift ? 0u : min(6u, (uint32_t)__builtin_clz(max(n, 2u) - 1u) - 21u);   // n << rs <= 2048
+    const uint32_t at = min(64u >> rs, lo >> shift), base = lo - (at << shift);
+    const uint32_t least = at ? min((uint32_t)lane >> rs, at - 1u) : 0u, most = at + n + ((uint32_t)lane >> rs);
+    const uint32_t copy = 4u * ((uint32_t)lane & ((1u << rs) - 1u));
+#pragma clang loop unroll(full)
+    for (int i = 0; i < IT; ++i) {
+      if (4 * i * T < nb) {
+        uint32_t x[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = __builtin_elementwise_sub_sat(k[i][e], base) >> shift;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = (min(max(x[e], least), most) << (rs + 2u)) | copy;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) atomicAdd(reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(h) + x[e]), 1u);
+      }
+      fence_schedule();
+    }
+    __syncthreads();
+    uint32_t loc[PER], inside, beyond;
+    uint32_t above = bins_above(at << rs, n << rs, loc, inside, beyond);
+    if (first) krem = c - min(beyond, c);
+    if (krem < 1u || krem > inside) {                              // not in the window: below it, or the sample misled
+      const bool zeros = heavy && krem > inside;
+      lo = zeros ? heavy : 1u;
+      last = zeros ? 31u : 0xfffffffeu;
+      heavy = 0;
+      clear();
+      continue;
+    }
+    if (tid == 0) res[6] = 0u;                                     // candidates, below
+    if (rs && tid == 0) res[5] = 0u;
+    uint32_t over = above;
+#pragma unroll
+    for (int i = PER - 1; i >= 0; --i) {
+      if (over < krem && over + loc[i] >= krem) {
+        res[3] = (uint32_t)(tid * PER + i) >> rs;
+        if (!rs) {
+          res[4] = krem - over;
+          res[5] = loc[i];
+        }
+      }
+      over += loc[i];
+    }
+    __syncthreads();
+    const uint32_t bin = uniform(res[3]);
+    if (rs) {                                                      // the counts of the bin's copies
+#pragma unroll
+      for (int i = PER - 1; i >= 0; --i) {
+        const uint32_t x = (uint32_t)(tid * PER + i);
+        if (x >> rs == bin) {
+          if ((x + 1u) >> rs != bin) res[4] = krem - above;        // (the bin's last copy)
+          if (loc[i]) atomicAdd(&res[5], loc[i]);
+        }
+        above += loc[i];
+      }
+      __syncthreads();
+    }
+    first = false;
+    krem = uniform(res[4]);
+    in_bin = uniform(res[5]);
+    lo += bin << shift;
+    last = (1u << shift) - 1u;
+    if (shift == 0 || in_bin <= (uint32_t)ROW_CAND) break;
+    clear();
+  }
+
+  // ---- a byte per quad. Few keys in the threshold's bin: they are listed, and those that are kept get their bits. Many
+  // equal ones: bits of their own, of which the first r in token order are kept.
+  unsigned char *const bytes = reinterpret_cast<unsigned char *>(codes);
+  const bool few = in_bin <= (uint32_t)ROW_CAND;
+  const uint32_t r = few ? 0u : krem, hi = lo + last;
+  const int own = again(tid);
+  if (few) {
+#pragma clang loop unroll(full)
+    for (int i = 0; i < IT; ++i) {
+      uint32_t m = 0, x[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        m |= k[i][e] > hi ? 1u << e : 0u;
+        x[e] = k[i][e] - lo;
+      }
+      if (min(min(x[0], x[1]), min(x[2], x[3])) <= last) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (x[e] <= last) {
+            const uint32_t at = atomicAdd(&res[6], 1u);
+            if (at < (uint32_t)ROW_CAND) {
+              cand_key[at] = k[i][e];
+              cand_tok[at] = (uint32_t)(4 * (i * T + own) + e);
+            }
+          }
+      }
+      bytes[i * T + own] = (unsigned char)m;
+      fence_schedule();
+    }
+    __syncthreads();
+    if (wave == 0) {
+      const uint32_t n = min(in_bin, (uint32_t)ROW_CAND);
+      const uint32_t key = cand_key[min((uint32_t)lane, n - 1u)], tok = cand_tok[min((uint32_t)lane, n - 1u)];
+      uint32_t ahead = 0;
+      for (uint32_t q = 0; q < n; ++q) {
+        const uint32_t x = cand_key[q];
+        ahead += x > key || (x == key && cand_tok[q] < tok) ? 1u : 0u;
+      }
+      if ((uint32_t)lane < n && ahead < krem) atomicOr(&codes[tok >> 4], 1u << (8 * (tok >> 2 & 3u) + (tok & 3u)));
+    }
+  } else {
+#pragma clang loop unroll(full)
+    for (int i = 0; i < IT; ++i) {
+      uint32_t m = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m |= k[i][e] > lo ? 1u << e : k[i][e] == lo ? 16u << e : 0u;
+      bytes[i * T + own] = (unsigned char)m;
+      fence_schedule();
+    }
+  }
+  __syncthreads();
+  constexpr int CW = IT >= 4 ? IT / 4 : 1;             // words of 16 tokens per thread, consecutive
+  uint32_t w[CW], gt = 0, eq = 0;
+#pragma unroll
+  for (int x = 0; x < CW; ++x) {
+    w[x] = tid * CW + x < TOK / 16 ? codes[tid * CW + x] : 0u;
+    gt += (uint32_t)__builtin_popcount(w[x] & 0x0f0f0f0fu);
+    eq += (uint32_t)__builtin_popcount(w[x] & 0xf0f0f0f0u);
+  }
+  uint32_t gt0, eq0, gts, eqs;
+  scan2<T>(gt, eq, tot, lane, wave, gt0, eq0, gts, eqs);
+  const uint32_t pos = gt0 + min(eq0, r);              // this thread's first place in the list
+  uint32_t mine = 0;
+#pragma unroll
+  for (int x = 0; x < CW; ++x) {
+    const uint32_t e = (w[x] >> 4) & 0x0f0f0f0fu, n = (uint32_t)__builtin_popcount(e);
+    uint32_t keep = eq0 + n <= r ? e : 0u;
+    if (n && eq0 < r && eq0 + n > r) {
+      uint32_t rest = e;
+      for (uint32_t q = eq0; q < r; ++q) {
+        keep |= rest & (0u - rest);
+        rest &= rest - 1u;
+      }
+    }
+    eq0 += n;
+    uint32_t y = (w[x] & 0x0f0f0f0fu) | keep;
+    mine += (uint32_t)__builtin_popcount(y);
+    y = (y | y >> 4) & 0x00ff00ffu;                    // the nibbles next to each other
+    y = (y | y >> 8) & 0x0000ffffu;
+    if (x & 1) w[x >> 1] |= y << 16;
+    else w[x >> 1] = y;
+  }
+  constexpr int LW = (CW + 1) / 2, LT = CW >= 2 ? 32 : 16;         // words of LT tokens
+#pragma unroll 1
+  for (uint32_t base = 0; base < c; base += STAGE) {
+    uint32_t p = pos;
+    if (p < base + STAGE && p + mine > base) {
+#pragma unroll
+      for (int x = 0; x < LW; ++x)
+        for (uint32_t rest = w[x]; rest; rest &= rest - 1u, ++p)
+          if (p - base < (uint32_t)STAGE) staged[p - base] = (uint32_t)(LT * (tid * LW + x) + __builtin_ctz(rest));
+    }
+    __syncthreads();
+    const uint32_t cnt = min(c - base, (uint32_t)STAGE);
+    for (int ti = t0; ti < t1; ++ti) {
+      int32_t *dst = A.indices + ((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + base;
+      for (uint32_t i = tid; i < cnt; i += T) dst[i] = (int32_t)staged[i];
+    }
+    __syncthreads();
+  }
+}
+
 // ------------------------------------------------- rows of one bf16 score per token, packed in registers
 // Calls with a mask per query row (prefill) rank thousands of rows of bf16 scores. 64K of them are 128 KB, 64 registers of
 // 512 threads: a CU holds two such rows, each is read once, and one row's ranking hides behind the loads of the other.
@@ -404,14 +655,6 @@ __global__ void __launch_bounds__(T, SAMPLE ? 4 : 1) select_row_kernel(const Sel
 // the keys outside the window 229 us; 256 threads with 128 registers of keys, three rows per CU, 153-157, but 256 rows of
 // 65536 20.5 against 17.0; 131072 tokens in 512 threads 1053 us for 8192 rows, in 1024 threads 870.
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-// nothing is moved across: a pass over keys in registers needs few others then
-__device__ __forceinline__ void fence_schedule() {
-#if defined(__AMDGCN__)
-  __builtin_amdgcn_sched_barrier(0);
-#endif
-}
-typedef u32x4 u32x4_any __attribute__((aligned(2)));
-
 // Scores with their order as signed numbers (positive ones as they are): -0 is +0, and the lowest value stays free for
 // "no token" (a NaN shares the key of its neighbour).
 __device__ __forceinline__ uint32_t signed16(uint32_t w) {
@@ -433,7 +676,7 @@ __global__ void __launch_bounds__(T, 4) select_row16_kernel(const SelectArgs A) 
   constexpr int SLOTS = SEL_BINS + 2 * 64;                         // a window's bins, and 64 for the keys on either side of it
   __shared__ uint32_t h[SLOTS];
   __shared__ __attribute__((aligned(16))) stage_t staged[STAGE];
-  __shared__ uint32_t tot[2][T / 64];
+  __shared__ uint32_t tot[2 * T / 64];
   __shared__ uint32_t res[8];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int bt = row / A.Hd, j = row % A.Hd;
@@ -488,28 +731,6 @@ __global__ void __launch_bounds__(T, 4) select_row16_kernel(const SelectArgs A) 
       for (int e = 0; e < 4; ++e) k[i][e] = __builtin_bit_cast(u16x2, raw[i][e] ^ 0x80008000u);
   }
 
-  // Exclusive sums over the workgroup of two values per thread; the totals too.
-  auto scan2 = [&](uint32_t a, uint32_t b, uint32_t &a0, uint32_t &b0, uint32_t &at, uint32_t &bs) {
-    const uint32_t ai = wave_incl_scan(a), bi = wave_incl_scan(b);
-    if (lane == 63) {
-      tot[0][wave] = ai;
-      tot[1][wave] = bi;
-    }
-    __syncthreads();
-    a0 = ai - a;
-    b0 = bi - b;
-    at = bs = 0;
-#pragma unroll
-    for (int w = 0; w < T / 64; ++w) {
-      const uint32_t x = tot[0][w], y = tot[1][w];
-      if (w < wave) {
-        a0 += x;
-        b0 += y;
-      }
-      at += x;
-      bs += y;
-    }
-  };
   constexpr int PER = SEL_BINS / T;
   // Counts of this thread's bins (of n, from slot `at` on), returned: keys in the bins above them, in all bins, and in the
   // 64 slots after the bins.
@@ -521,7 +742,7 @@ __global__ void __launch_bounds__(T, 4) select_row16_kernel(const SelectArgs A) 
       loc[i] = x < n ? h[at + x] : 0u;
       sum += loc[i];
     }
-    scan2(sum, tid < 64 ? h[at + n + tid] : 0u, before, unused, inside, beyond);
+    scan2<T>(sum, tid < 64 ? h[at + n + tid] : 0u, tot, lane, wave, before, unused, inside, beyond);
     return inside - before - sum;
   };
   auto clear = [&] {
@@ -677,7 +898,7 @@ __global__ void __launch_bounds__(T, 4) select_row16_kernel(const SelectArgs A) 
     eq += (uint32_t)__builtin_popcount(w[x] & 0x55555555u);
   }
   uint32_t gt0, eq0, gts, eqs;
-  scan2(gt, eq, gt0, eq0, gts, eqs);
+  scan2<T>(gt, eq, tot, lane, wave, gt0, eq0, gts, eqs);
   const uint32_t pos = gt0 + min(eq0, r);                          // this thread's first place in the list
   // its kept tokens, a bit each
   uint32_t mine = 0;
@@ -750,23 +971,24 @@ static hipError_t launch_select_row16(const SelectArgs &a, hipStream_t s) {
 hipError_t launch_select_row(const SelectArgs &a, hipStream_t s) {
   const int64_t rows = (int64_t)a.B * a.Hd;
   if (rows == 0) return hipSuccess;
-  if (a.row16) return launch_select_row16(a, s);
-  if (a.N < 4 || a.N > SEL_SMALL_N) return hipErrorInvalidValue;
+  if (a.rowpass_threads == SEL_ROW16) return launch_select_row16(a, s);
+  const int N = a.N;
+  if (N < 4 || N > SEL_SMALL_N) return hipErrorInvalidValue;
   const dim3 grid((unsigned)rows);
   if (rows <= 512) {
     const dim3 block(1024);
-    if (a.N <= 4096) STS_LAUNCH((select_row_kernel<1024, 1, false>), grid, block, 0, s, a);
-    else if (a.N <= 8192) STS_LAUNCH((select_row_kernel<1024, 2, false>), grid, block, 0, s, a);
-    else if (a.N <= 16384) STS_LAUNCH((select_row_kernel<1024, 4, true>), grid, block, 0, s, a);
-    else STS_LAUNCH((select_row_kernel<1024, 8, true>), grid, block, 0, s, a);
-  } else if (a.N <= 4096) {
-    STS_LAUNCH((select_row_kernel<256, 4, false>), grid, dim3(256), 0, s, a);
-  } else if (a.N <= 8192) {
-    STS_LAUNCH((select_row_kernel<256, 8, true>), grid, dim3(256), 0, s, a);
-  } else if (a.N <= 16384) {
-    STS_LAUNCH((select_row_kernel<256, 16, true>), grid, dim3(256), 0, s, a);
+    if (N <= 4096) STS_LAUNCH((short_select_row_kernel<1024, 1>), grid, block, 0, s, a);
+    else if (N <= 8192) STS_LAUNCH((short_select_row_kernel<1024, 2>), grid, block, 0, s, a);
+    else if (N <= 16384) STS_LAUNCH((select_row_kernel<1024, 4>), grid, block, 0, s, a);
+    else STS_LAUNCH((select_row_kernel<1024, 8>), grid, block, 0, s, a);
+  } else if (N <= 4096) {
+    STS_LAUNCH((short_select_row_kernel<256, 4>), grid, dim3(256), 0, s, a);
+  } else if (N <= 8192) {
+    STS_LAUNCH((select_row_kernel<256, 8>), grid, dim3(256), 0, s, a);
+  } else if (N <= 16384) {
+    STS_LAUNCH((select_row_kernel<256, 16>), grid, dim3(256), 0, s, a);
   } else {
-    STS_LAUNCH((select_row_kernel<512, 16, true>), grid, dim3(512), 0, s, a);
+    STS_LAUNCH((select_row_kernel<512, 16>), grid, dim3(512), 0, s, a);
   }
   return sts_take_launch_status();
 }

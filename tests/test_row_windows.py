@@ -1,0 +1,88 @@
+"""Rows ranked in one workgroup's registers by a window of keys from a sample (select_row_kernel in
+csrc/select_row.hip), and rows of block sums ranked by the same kernels, against the CPU oracle bit for
+bit: scores that the sample, the windows and the slots beside them do not expect, at the edges of the
+kernel's forms."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_15508_amd as sts
+from test_select_emulated import check, lib  # noqa: F401  (lib: the emulated library, a fixture)
+
+DEV = "cuda:0"
+
+
+def scores_of(what, rows, Tq, N, k, seed):
+    g = torch.Generator().manual_seed(seed)
+    r = torch.randn(rows, 1, Tq, N, generator=g)
+    p = torch.softmax(r * 2, dim=-1)
+    some = torch.rand(rows, 1, 1, N, generator=g).expand(rows, 1, Tq, N)
+    if what == "softmax":
+        return p
+    if what == "zeros":                               # about as many scores as are kept, zeros otherwise
+        return p * (some < k / N)
+    if what == "zeros then scores":                   # exactly as many: the lowest one lies alone above the gap
+        p[..., :N - k] = 0
+        return p
+    if what == "zeros then denormals":                # ... below where the window begins
+        p[..., :N - k] = 0
+        return p * 1e-41
+    if what == "one value":
+        return torch.full((rows, 1, Tq, N), 0.375)
+    if what == "close together":                      # all keys share their upper 11 bits, some the next 11
+        return 1 + r * 1e-6
+    if what == "signed":
+        r[some < 0.4] = 0.0
+        r[some < 0.2] = -0.0
+        return r
+    if what == "levels":
+        return torch.round(r * 2) / 8
+    return torch.exp(r * 30)                          # "all over the range"
+
+
+# (rows, scores per token, N, k): 1024 threads with four and eight quads each; 256 threads with eight and sixteen; 512
+FORMS = [(256, 1, 8193, 800), (257, 2, 16384, 1638), (256, 1, 32767, 300), (513, 1, 4097, 409), (520, 1, 8192, 8000), (513, 1, 16383, 512),
+         (513, 1, 32768, 3277)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("what", ["softmax", "zeros", "zeros then scores", "zeros then denormals", "one value", "close together", "signed",
+                                  "levels", "all over the range"])
+@pytest.mark.parametrize("rows,Tq,N,k", FORMS)
+def test_windows(rows, Tq, N, k, what):
+    live = 6                                          # the other rows are empty
+    s = scores_of(what, live, Tq, N, k, N + k)
+    sd = torch.zeros(rows, 1, Tq, N, device=DEV)
+    sd[:live] = s.to(DEV)
+    lens = torch.zeros(rows, dtype=torch.int32)
+    lens[:live] = torch.tensor([N, N - 3, N // 2, 1023, 1024, 5])
+    idx, cnt, _ = sts.sts_select(sd, [0, 0], k, seq_lens=lens.to(DEV))
+    assert (cnt[live:] == 0).all() and (idx[live:] == -1).all()
+    o_idx, o_cnt, _ = oracle.select_indices(s.numpy(), np.zeros(2, np.int32), k, seq_lens=lens[:live].numpy())
+    np.testing.assert_array_equal(cnt[:live].cpu().numpy(), o_cnt)
+    np.testing.assert_array_equal(idx[:live].cpu().numpy(), o_idx)
+
+
+@pytest.mark.parametrize("what", ["zeros", "zeros then denormals", "close together", "signed"])
+@pytest.mark.parametrize("rows,Tq,N,k", [FORMS[0], FORMS[3], FORMS[5]])
+def test_windows_emulated(lib, rows, Tq, N, k, what):  # noqa: F811
+    lib.emu_schedule(N + k, -1, -1)
+    s = torch.zeros(rows, 1, Tq, N)
+    s[:2] = scores_of(what, 2, Tq, N, k, N + k)
+    check(lib, s, [0], k, lens=[N, N - 3] + [0] * (rows - 2))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,page,k", [(32784, 16, 300), (131072, 16, 820), (131072, 8, 16384), (65544, 8, 1), (66000, 16, 900)])
+def test_rows_of_block_sums(N, page, k):
+    B, Hd, Tq = 3, 2, 3
+    g = torch.Generator().manual_seed(N + k)
+    s = torch.softmax(torch.randn(B, Hd, Tq, N, generator=g) * 2, dim=-1)
+    s[0, 1] = 0.0
+    lens = torch.tensor([N, N - page - 3, 70], dtype=torch.int32)
+    hm = [0, 1, 1]
+    idx, cnt, _ = sts.sts_select(s.to(DEV), hm, k, seq_lens=lens.to(DEV), page_size=page)
+    o_idx, o_cnt, _ = oracle.select_indices(s.numpy(), np.asarray(hm, np.int32), k, seq_lens=lens.numpy(), page=page)
+    np.testing.assert_array_equal(cnt.cpu().numpy(), o_cnt)
+    np.testing.assert_array_equal(idx.cpu().numpy(), o_idx)
