@@ -315,6 +315,7 @@ sts_status run_attn(const sts_attn_params *p, int sparse, hipStream_t s, void *w
 struct SelectPlan {
   bool small;          // one workgroup per row, keys in LDS, a single launch
   bool pool;           // shape allows chunk-local top-k + one ranking workgroup per row
+  bool one_row;        // of those, the calls that one workgroup per row serves (the workspace is not touched)
   bool fused;          // long rows: the sampled selection, one launch (plus the clearing of the exchanged words)
   bool band;           // the same for a row for every second CU or more: can do without a workspace
   bool row16;          // one bf16 score per token: one workgroup per row, which its registers hold, no workspace
@@ -391,9 +392,8 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
   pl.srcN = (p->N + pl.page - 1) / pl.page;
   pl.nchunks = (pl.srcN + SEL_CHUNK - 1) / SEL_CHUNK;
   const size_t rows = (size_t)p->B * p->Hd;
-  // One workgroup ranks a whole row out of LDS at one CU's pace: a clear win for short rows
-  // (one launch instead of six), and for rows up to the LDS limit when there are enough rows
-  // to fill the chip anyway; longer or fewer rows keep the many-workgroup pipeline.
+  // One workgroup ranks a whole row in its registers (up to 32768 tokens in calls that fill the chip with such rows; see
+  // also `one_row` below).
   pl.small = pl.page == 1 && (p->N <= SEL_FUSED_N || (p->N <= SEL_SMALL_N && rows >= 256));
   pl.pool = false;
   pl.pool_pitch = 0;
@@ -411,6 +411,16 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
   // several passes wherever its shape limits allow, 5 the sampled selection with one workgroup per row likewise
   const double path_knob = knob(STS_KNOB_SELECT_PATH);
   const int path = path_knob == path_knob ? (int)path_knob : 0;
+  // Rows of up to 32768 tokens in calls of fewer rows: one workgroup per row, too, unless few workgroups would have much to
+  // read each (one CU reads some 60 GB/s; the sampled selection's parts are more CUs, but exchange what they counted and need
+  // a launch that clears). us, against the sampled selection, five fp32 scores per token: 16 rows of 12000 13.8, 25.1; of
+  // 32768 18.7, 27.8; 128 rows of 32768 26.3, 35.6; nine: 16 rows of 20001 24.3, 29.5; of 32768 31.6, 31.1; one: 16 rows of
+  // 32768 14.1, 26.0. Calls of fewer than eight rows, fewer than any model's draft heads, keep the route that they had (and
+  // calls of few rows the workspace that they had to bring).
+  const bool one_row = path == 0 && pl.page == 1 && !pl.small && p->N > SEL_FUSED_N && p->N <= SEL_SMALL_N && rows >= 8 &&
+                       (int64_t)p->N * p->Tq * (p->scores_bf16 ? 2 : 4) <= 1 << 20;
+  pl.one_row = false;
+  if (one_row && 2 * (int64_t)rows >= cu_count()) pl.small = true;
   // Enough rows to give at least every second CU one, and rows that do not fit one workgroup's
   // LDS: the sampled selection, which here can do without a workspace, in one workgroup per row (with one it
   // may take more, see plan_sampled). Budgets next to the row's length, and rows of more than 512K tokens, go by the
@@ -510,6 +520,7 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
     const bool large = (int64_t)rows * p->N >= (int64_t)1 << 22 && !pl.pool;
     if (((int64_t)p->N + 32767) / 32768 <= (path == 3 || large ? 256 : SEL_FUSED_MAX_PARTS)) {
       pl.fused = true;
+      pl.one_row = one_row;
       pl.pool = false;
       plan_sampled(p, rows, pl);
     }
@@ -684,6 +695,10 @@ static sts_status enqueue_select(const sts_select_params *p, void *stream) {
     a.agg = p->agg_out;   // optional output only: the keys never leave LDS
     a.src = nullptr;
     a.hist = a.state = a.chunk_cnt = nullptr;   // the pipeline's scratch does not exist on this path
+    if (pl.one_row) {
+      rc = run_kernel(STS_K_SELECT_SMALL, s, [&] { return launch_select_small(a, s); });
+      return rc == hipSuccess ? STS_OK : STS_EHIP;
+    }
     if (pl.smp_parts > 1) {
       rc = run_kernel(STS_K_SELECT_CLEAR, s, [&] { return launch_select_clear_pub(a, s); });
       if (rc != hipSuccess) return STS_EHIP;

@@ -89,26 +89,81 @@ __device__ __forceinline__ void load_row(const AggRow &R, float *out, int nb, in
       any |= v[i][e];
     }
   };
-  if constexpr (T == 1024) {
-    // Few quads: their score rows are in flight together. Up to four by code for each number of rows (256 rows of 16384
-    // tokens 16.9 us, 18.7 with branches between the rows), eight with branches: that kernel was 305 KB (256 rows of 30000
-    // tokens, 5 scores: 39.8 us, 48.7 with the caches flushed; now 40.5 and 44.6).
-    auto quads = [&](auto bf16) {
+  if constexpr (T == 1024 && IT <= 4) {
+    // Few quads: their score rows are in flight together, by code for each number of rows (256 rows of 16384
+    // tokens 16.9 us, 18.7 with branches between the rows).
 #pragma clang loop unroll(full)
-      for (int i = 0; i < IT; ++i) {
-        const int n = 4 * (i * T + tid);
-        const bool inside = 4 * (i + 1) * T <= R.N;
-        if constexpr (IT == 8) {
-          take(i, agg_quad_any<decltype(bf16)::value>(R, n, inside));
+    for (int i = 0; i < IT; ++i) {
+      const int n = 4 * (i * T + tid);
+      const bool inside = 4 * (i + 1) * T <= R.N;
+      const int at = min(n, R.N - 4);
+      const f32x4 y = agg_quad(R, at);
+      take(i, inside ? y : shifted_quad(y, n - at));
+    }
+  } else if constexpr (T == 1024) {
+    // Four quads at a time, a score row of them in flight while the one before is added (a quad at a time with all its score
+    // rows: the same for five and nine, but 16 rows of 32768 tokens with one score per token 18.0 us, now 14.1; eight quads at
+    // a time spill). Larger rows in this way: 16 of 33001, five scores, 28.7 us, sampled 27.3.
+    auto blocks = [&](auto bf16) {
+      typedef ScoreLoad<f32x4, decltype(bf16)::value> SL;
+      constexpr int QB = 4;
+      const size_t pitch = (size_t)R.N * (decltype(bf16)::value ? 2 : 4);
+#pragma clang loop unroll(full)
+      for (int b = 0; b < IT; b += QB) {
+        f32x4 acc[QB];
+        if (4 * b * T < (out ? R.N : nb)) {
+          typename SL::raw x[QB], y[QB];
+          auto load = [&](typename SL::raw (&r)[QB], int q) {
+            const unsigned char *at = static_cast<const unsigned char *>(R.P) + q * pitch;
+#pragma unroll
+            for (int i = 0; i < QB; ++i) {
+              uint32_t off = (uint32_t)min(4 * ((b + i) * T + tid), R.N - 4) * (decltype(bf16)::value ? 2u : 4u);
+              r[i] = SL::load_at(at + off);
+            }
+          };
+          auto add = [&](const typename SL::raw (&r)[QB], int q) {
+            const float l = R.logits ? R.L[q] : 0.f;
+#pragma unroll
+            for (int i = 0; i < QB; ++i) {
+              f32x4 p = SL::widen(r[i]);
+              if (R.logits) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) p[e] = prob_of(p[e], l);
+              }
+              if (q == 0) {
+                acc[i] = p;
+              } else if (R.use_max) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[i][e] = fmaxf(acc[i][e], p[e]);
+              } else {
+                acc[i] = acc[i] + p;
+              }
+            }
+          };
+          load(x, 0);
+#pragma unroll 1
+          for (int q = 0; q < R.Tq; q += 2) {
+            if (q + 1 < R.Tq) load(y, q + 1);
+            fence_schedule();
+            add(x, q);
+            if (q + 1 >= R.Tq) break;
+            if (q + 2 < R.Tq) load(x, q + 2);
+            fence_schedule();
+            add(y, q + 1);
+          }
         } else {
-          const int at = min(n, R.N - 4);
-          const f32x4 y = agg_quad(R, at);
-          take(i, inside ? y : shifted_quad(y, n - at));
+#pragma unroll
+          for (int i = 0; i < QB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int i = 0; i < QB; ++i) {
+          const int n = 4 * ((b + i) * T + tid);
+          take(b + i, 4 * (b + i + 1) * T <= R.N ? acc[i] : shifted_quad(acc[i], n - min(n, R.N - 4)));
         }
       }
     };
-    if (IT < 8 || R.bf16) quads(std::true_type{});     // (the type matters for the form with branches only)
-    else quads(std::false_type{});
+    if (R.bf16) blocks(std::true_type{});
+    else blocks(std::false_type{});
   } else {
     // many quads: one score row at a time, all quads of it in flight together (same order of additions per token)
     f32x4 acc[IT];
