@@ -318,7 +318,7 @@ struct SelectPlan {
   bool one_row;        // of those, the calls that one workgroup per row serves (the workspace is not touched)
   bool fused;          // long rows: the sampled selection, one launch (plus the clearing of the exchanged words)
   bool band;           // the same for a row for every second CU or more: can do without a workspace
-  bool row16;          // one bf16 score per token: one workgroup per row, which its registers hold, no workspace
+  bool row16;          // one bf16 score per token: one workgroup per row, which its registers hold (the workspace is not touched)
   int row16_kind;
   bool rowpass;        // many long rows of ready-made scores: one workgroup per row, no workspace
   int rowpass_threads;
@@ -333,7 +333,7 @@ struct SelectPlan {
   // a pool-shaped call falls back to the pipeline when its pointers are not 16-byte aligned,
   // so the workspace covers both
   size_t total() const {
-    if (rowpass || row16) return 0;
+    if (rowpass) return 0;
     if (fused || band) return fused_total();
     return pipeline_total() > pool_total() ? pipeline_total() : pool_total();
   }
@@ -408,17 +408,24 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
   pl.pub_bytes = 0;
   // test / tuning knob: 0 the library's rule, 1 histogram pipeline only, 2 pipeline or pool,
   // 3 the sampled selection wherever its shape limits allow, 4 one workgroup per row in
-  // several passes wherever its shape limits allow, 5 the sampled selection with one workgroup per row likewise
+  // several passes wherever its shape limits allow, 5 the sampled selection with one workgroup per row likewise,
+  // 6 rows of one bf16 score per token in registers wherever they fit
   const double path_knob = knob(STS_KNOB_SELECT_PATH);
   const int path = path_knob == path_knob ? (int)path_knob : 0;
   // Rows of up to 32768 tokens in calls of fewer rows: one workgroup per row, too, unless few workgroups would have much to
   // read each (one CU reads some 60 GB/s; the sampled selection's parts are more CUs, but exchange what they counted and need
-  // a launch that clears). us, against the sampled selection, five fp32 scores per token: 16 rows of 12000 13.8, 25.1; of
-  // 32768 18.7, 27.8; 128 rows of 32768 26.3, 35.6; nine: 16 rows of 20001 24.3, 29.5; of 32768 31.6, 31.1; one: 16 rows of
-  // 32768 14.1, 26.0. Calls of fewer than eight rows, fewer than any model's draft heads, keep the route that they had (and
-  // calls of few rows the workspace that they had to bring).
-  const bool one_row = path == 0 && pl.page == 1 && !pl.small && p->N > SEL_FUSED_N && p->N <= SEL_SMALL_N && rows >= 8 &&
-                       (int64_t)p->N * p->Tq * (p->scores_bf16 ? 2 : 4) <= 1 << 20;
+  // a launch that clears). us on other scores in every call, against the sampled selection, fp32 unless said otherwise: 16
+  // rows of 12000 with five scores per token 17.8, 25.1; of 16384 with ten 25.6, 31.2; 64 of 16384 with sixteen 34.6, 42.3.
+  // Beyond 16384 tokens a thread has eight quads, and every further score per token costs a pass over them whatever N is:
+  // 16 rows of 32768 with five 27.8, 28.6, but with six 30.1, 29.1 and of 20000 with eight 29.6, 27.3; 64 rows of 32768 with
+  // five 29.2, 32.9, but of 20000 with eight 30.8, 29.4; 128 of 17000 with eight 31.4, 35.6, of 32768 39.5, 49.3, but 96 of
+  // 20000 with twelve 41.3, 38.0; bf16, 16 rows of 32768 with ten 33.3, 33.4, of 26000 with twelve 35.5, 33.1. Calls of fewer
+  // than eight rows, fewer than any model's draft heads, keep the route that they had (and calls of few rows the workspace
+  // that they had to bring).
+  const int64_t token_bytes = (int64_t)p->Tq * (p->scores_bf16 ? 2 : 4);
+  const bool reads_little = p->N <= 16384 ? p->N * token_bytes <= (4 * (int64_t)rows >= cu_count() ? 1024 : 640) << 10
+                                          : token_bytes <= (2 * (int64_t)rows >= cu_count() ? 32 : 20);
+  const bool one_row = path == 0 && pl.page == 1 && !pl.small && p->N > SEL_FUSED_N && p->N <= SEL_SMALL_N && rows >= 8 && reads_little;
   pl.one_row = false;
   if (one_row && 2 * (int64_t)rows >= cu_count()) pl.small = true;
   // Enough rows to give at least every second CU one, and rows that do not fit one workgroup's
@@ -428,9 +435,9 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
   // Measured, 128K-token rows, 10%: 128 rows of one fp32 score per token 45 us (two workgroups per
   // row; one workgroup per row took 57), 128 rows of eight bf16 scaled logits of 50000 tokens 52
   // (70 with one workgroup per row).
-  // One bf16 score per token and many rows per CU (a mask per query row of prefill) is the one
-  // shape that plain passes by small workgroups serve better (select_rowpass_kernel; 4096 rows of
-  // 128K: 754 against 962 us; one workgroup per row out of parts that exchange: 2.1 ms).
+  // One bf16 score per token and many rows per CU (a mask per query row of prefill): rows of up to 131072 tokens fit
+  // registers (below); longer ones are the one shape that plain passes by small workgroups serve better
+  // (select_rowpass_kernel; 4096 rows of 128K, which the registers take now: 754 against 962 us with the sampled selection).
   {
     const bool aligned = reinterpret_cast<uintptr_t>(p->scores) % 16 == 0;
     const bool band_ok = pl.page == 1 && p->N >= 4 && p->N <= SMP_MAX_TOKENS;
@@ -452,14 +459,10 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
                           p->N >= 8 && p->N <= SEL_ROW16_N;
     const bool take_row16 = path == 6 ? row16_ok : path == 0 && row16_ok && p->N >= 4096;
     if (take_row16) {
-      // (counted by the timing aid as the class of call that its rows put it in)
+      // The rest of the plan stays: such a call has to bring the workspace that its rows asked for before (nothing in it
+      // is touched), and the timing aid counts it as the class of call that they put it in.
       pl.row16 = true;
       pl.row16_kind = pl.small ? STS_K_SELECT_SMALL : take_rowpass ? STS_K_SELECT_ROWPASS : take_band ? STS_K_SELECT_BAND : STS_K_SELECT_FUSED;
-      pl.small = false;
-      pl.nchunks = 0;
-      pl.pool_chunk = pl.pool_nchunks = 0;
-      pl.agg_bytes = pl.blk_bytes = pl.hist_bytes = pl.state_bytes = pl.chunk_bytes = 0;
-      return STS_OK;
     }
     if (take_rowpass || take_band) {
       pl.small = false;
@@ -662,6 +665,14 @@ static sts_status enqueue_select(const sts_select_params *p, void *stream) {
   }
 
   hipError_t rc;
+  if (pl.row16) {
+    a.agg = nullptr;
+    a.src = nullptr;
+    a.hist = a.state = a.chunk_cnt = nullptr;
+    a.rowpass_threads = SEL_ROW16;
+    rc = run_kernel(pl.row16_kind, s, [&] { return launch_select_small(a, s); });
+    return rc == hipSuccess ? STS_OK : STS_EHIP;
+  }
   if (pl.band) {
     a.agg = p->agg_out;   // optional output only
     a.src = nullptr;
@@ -670,14 +681,6 @@ static sts_status enqueue_select(const sts_select_params *p, void *stream) {
     a.smp_tokens = pl.smp_tokens;
     a.smp_parts = pl.smp_parts;
     rc = run_kernel(STS_K_SELECT_BAND, s, [&] { return launch_select_band(a, s); });
-    return rc == hipSuccess ? STS_OK : STS_EHIP;
-  }
-  if (pl.row16) {
-    a.agg = nullptr;
-    a.src = nullptr;
-    a.hist = a.state = a.chunk_cnt = nullptr;
-    a.rowpass_threads = SEL_ROW16;
-    rc = run_kernel(pl.row16_kind, s, [&] { return launch_select_small(a, s); });
     return rc == hipSuccess ? STS_OK : STS_EHIP;
   }
   if (pl.rowpass) {
@@ -916,7 +919,7 @@ const char *sts_strerror(int status) {   // an int on purpose: any value a calle
   return "unknown status";
 }
 
-int sts_version(void) { return 206; }
+int sts_version(void) { return 207; }
 
 void sts_set_knob(int which, double value) {
   if (which < 0 || which >= STS_KNOB_COUNT_) return;

@@ -2,8 +2,9 @@
 // index sets, remapped to the target heads (paper Section 4.2; Section 4.3: one mask per
 // speculative batch).
 //
-// Ways through, chosen on the host from the shape; one row = one (batch, draft head). Most rows longer
-// than 8192 tokens take the sampled selection of select_sampled.hip; here are:
+// Ways through, chosen on the host from the shape; one row = one (batch, draft head). Rows of up to 8192 tokens, many of up
+// to 32768 and rows of one bf16 score per token are ranked in registers (select_row.hip), most longer ones by the sampled
+// selection of select_sampled.hip; here are:
 //  * few very long rows, block scores -- every kernel on a (chunk, row) grid of 8192-token chunks:
 //      clear  zero the three digit histograms and the chunk flags of every row
 //      agg    A[n] = ((P[0,n] + P[1,n]) + ...) in fp32, stored; histogram of the top 11 key bits
@@ -21,8 +22,8 @@
 //             chunk's own top-k (same tie rule) goes to a pool, in token order. Every token of
 //             the row's top-k is in the top-k of its chunk.
 //      pool   one workgroup per row ranks the pooled candidates out of LDS and writes the list.
-//  * short lists of block scores -- one workgroup per row ranks them out of LDS (select_small_kernel);
-//    short rows of scores are ranked in registers (select_row.hip).
+//  * short lists of block scores (up to 2048) -- one workgroup per row ranks them out of LDS (select_small_kernel);
+//    longer ones and short rows of scores are ranked in registers (select_row.hip).
 // Keys are the usual order-preserving map of fp32 to uint32 (with -0 folded onto +0), so the
 // whole selection is integer arithmetic: the index sets are exact, ties go to the lower token.
 // Histograms use LDS atomics per workgroup and integer global atomics to merge (order-free).
@@ -636,7 +637,8 @@ __global__ void __launch_bounds__(SMALL_THREADS) select_small_kernel(const Selec
 
 // --------------------------------- many long rows of ready-made scores: one workgroup per row
 // A call with one score per token (Tq = 1: the per-query-row masks of prefill rank every row of a
-// block's scores on its own; a draft layer's summed weights) and far more rows than CUs. Cutting
+// block's scores on its own; a draft layer's summed weights), far more rows than CUs and rows of more than 128K tokens
+// (shorter ones fit a workgroup's registers, select_row16_kernel). Cutting
 // such rows into parts that wait for each other leaves every CU idle during the exchanges; here a
 // row belongs to ONE workgroup, which keeps nothing but a digit histogram in LDS and reads the
 // row once per digit level and once more to compact it. The re-reads come out of the caches (a
