@@ -86,3 +86,27 @@ def test_rows_of_block_sums(N, page, k):
     o_idx, o_cnt, _ = oracle.select_indices(s.numpy(), np.asarray(hm, np.int32), k, seq_lens=lens.numpy(), page=page)
     np.testing.assert_array_equal(cnt.cpu().numpy(), o_cnt)
     np.testing.assert_array_equal(idx.cpu().numpy(), o_idx)
+
+
+# both sides of the line between one workgroup per row and parts of a row: rows, scores per token, N, k, bf16 scores
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,Tq,N,k,bf16", [(8, 5, 8193, 819, False), (8, 10, 16384, 1, False), (8, 11, 16384, 1638, False), (9, 5, 16385, 16000, False),
+                                              (16, 5, 32768, 3277, False), (16, 6, 32767, 3276, False), (16, 10, 32765, 3276, True), (64, 16, 16383, 512, False),
+                                              (128, 8, 16391, 1639, False), (128, 9, 16391, 1639, False), (255, 2, 20003, 2000, True)])
+def test_few_rows(rows, Tq, N, k, bf16):
+    live = 6                                          # the other rows are empty
+    s = scores_of("softmax", live, Tq, N, k, N + k)
+    s[1:3] = scores_of("zeros then scores", 2, Tq, N, k, N + k)
+    s = s.to(torch.bfloat16) if bf16 else s
+    sd = torch.zeros(rows, 1, Tq, N, device=DEV, dtype=s.dtype)
+    sd[:live] = s.to(DEV)
+    lens = torch.zeros(rows, dtype=torch.int32)
+    lens[:live] = torch.tensor([N, N, N - 3, N // 2, 1023, 5])
+    idx, cnt, _ = sts.sts_select(sd, [0, 0], k, seq_lens=lens.to(DEV))
+    a_idx, a_cnt, agg = sts.sts_select(sd, [0, 0], k, seq_lens=lens.to(DEV), want_agg=True)
+    assert torch.equal(idx, a_idx) and torch.equal(cnt, a_cnt)
+    assert (cnt[live:] == 0).all() and (idx[live:] == -1).all()
+    o_idx, o_cnt, o_agg = oracle.select_indices(s.float().numpy(), np.zeros(2, np.int32), k, seq_lens=lens[:live].numpy())
+    np.testing.assert_array_equal(cnt[:live].cpu().numpy(), o_cnt)
+    np.testing.assert_array_equal(idx[:live].cpu().numpy(), o_idx)
+    np.testing.assert_array_equal(agg[0].cpu().numpy(), o_agg[0])
