@@ -427,7 +427,6 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
                                           : token_bytes <= (2 * (int64_t)rows >= cu_count() ? 32 : 20);
   const bool one_row = path == 0 && pl.page == 1 && !pl.small && p->N > SEL_FUSED_N && p->N <= SEL_SMALL_N && rows >= 8 && reads_little;
   pl.one_row = false;
-  if (one_row && 2 * (int64_t)rows >= cu_count()) pl.small = true;
   // Enough rows to give at least every second CU one, and rows that do not fit one workgroup's
   // LDS: the sampled selection, which here can do without a workspace, in one workgroup per row (with one it
   // may take more, see plan_sampled). Budgets next to the row's length, and rows of more than 512K tokens, go by the
@@ -446,6 +445,7 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
     const bool rowpass_ok = pl.page == 1 && p->Tq == 1 && p->kind == STS_SCORES_PROBS && !p->agg_out && p->N > 0 &&
                             (p->N % (p->scores_bf16 ? 8 : 4)) == 0 && aligned;
     const int64_t cus = cu_count();
+    if (one_row && has_edge && 2 * (int64_t)rows >= cus) pl.small = true;      // (such calls did without a workspace before, too)
     const bool long_rows = !pl.small && p->N > SEL_FUSED_N;
     const bool take_rowpass = path == 4 ? rowpass_ok
                                         : path == 0 && rowpass_ok && long_rows && p->scores_bf16 && (int64_t)rows >= 4 * cus;
