@@ -589,7 +589,7 @@ __global__ void __launch_bounds__(T, 4) select_row_kernel(const SelectArgs A) {
     krem = uniform(res[4]);
     in_bin = uniform(res[5]);
     lo += bin << shift;
-    last = (1u << shift) - 1u;
+    last = min((1u << shift) - 1u, ~lo);                           // (the window's last bin may run past the highest key)
     if (shift == 0 || in_bin <= (uint32_t)ROW_CAND) break;
     clear();
   }

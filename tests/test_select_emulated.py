@@ -244,3 +244,43 @@ def test_bands_that_lie_in_one_part(lib, levels, one_part):
         lib.sts_set_knob(3, float("nan"))
     read = lib.emu_loaded() / (4 * N * min(B, 2))
     assert read < (2.5 if one_part else 2.2) + 3.0 * (levels > 0), read
+
+
+def by_keys(scores, n, k):
+    """The kept tokens of one row of scores of any bits: ascending, the largest of the order-preserving keys, ties to the lower token."""
+    if scores.dtype == torch.bfloat16:
+        u = scores.view(torch.int16).numpy().astype(np.int64) << 16 & 0xffffffff
+    else:
+        u = scores.view(torch.int32).numpy().astype(np.int64) & 0xffffffff
+    key = np.where(u == 0x80000000, 0x80000000, np.where(u >> 31, u ^ 0xffffffff, u | 0x80000000))[:n]
+    return np.sort(np.argsort(-key, kind="stable")[:k])
+
+
+def check_keys(lib, live, rows, k, lens):
+    """live [R,N] in a call of that many rows, the others empty."""
+    s = torch.zeros(rows, 1, 1, live.shape[1], dtype=live.dtype)
+    s[:len(live), 0, 0] = live
+    idx, cnt = select(lib, s, [0], k, lens=lens + [0] * (rows - len(live)))
+    for b, n in enumerate(lens):
+        assert cnt[b, 0] == min(k, n)
+        np.testing.assert_array_equal(idx[b, 0, :cnt[b, 0]], by_keys(live[b], n, k), err_msg=f"row {b}, length {n}")
+
+
+# 1024 threads with one quad, two, four and eight; 256 threads with four, eight and sixteen; 512
+ROW_FORMS = [(16, 4001), (16, 8190), (256, 9000), (256, 20001), (513, 4090), (513, 8190), (513, 9001), (513, 20001)]
+
+
+@pytest.mark.parametrize("rows,N", ROW_FORMS)
+@pytest.mark.parametrize("n", [1000, 2051])
+def test_highest_keys_of_all(lib, rows, N, n):
+    """The threshold next to the highest key there is, 0xffffffff: the keys of its bin do not run past it. Rows below 1024
+    tokens are not sampled, their window is every key."""
+    lib.emu_schedule(1, -1, -1)
+    s = torch.rand(3, N, generator=torch.Generator().manual_seed(n))
+    bits = s.view(torch.int32)
+    bits[0, 500] = 0x7fffffff
+    bits[1, 500:503] = 0x7fffffff
+    bits[2, 100:800:100] = torch.tensor([0x7fffffff, 0x7fff0000, 0x7ffffffe, 0x7f800000, 0x7fffffff, 0x7fe00000, 0x7fefffff], dtype=torch.int32)
+    bits[2, 5:900:200] = torch.tensor([-1, -2, -0x200000, -3, -0x100000], dtype=torch.int32)       # ... and the lowest
+    for k in (1, 3, 6, 990):
+        check_keys(lib, s, rows, k, [n, n, n])
