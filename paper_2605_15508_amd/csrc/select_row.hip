@@ -546,6 +546,9 @@ __global__ void __launch_bounds__(T, 4) select_row_kernel(const SelectArgs A) {
       fence_schedule();
     }
     __syncthreads();
+    // Without slots below, the positions after the row's end are in bin 0: there only tokens count. (Its copies are one, and
+    // thread 0 is the one that reads it.)
+    if (at == 0u && tid == 0) h[0] -= (uint32_t)((nb + 4 * T - 1) / (4 * T) * (4 * T) - nb);
     uint32_t loc[PER], inside, beyond;
     uint32_t above = bins_above(at << rs, n << rs, loc, inside, beyond);
     if (first) krem = c - min(beyond, c);

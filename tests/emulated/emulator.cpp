@@ -1,5 +1,6 @@
 // The fibers and the schedule of the CPU stand-in (hip/hip_runtime.h), and stand-ins for the launchers of the
 // sources that are not compiled for the CPU. Test infrastructure, not part of libsts.so.
+#include <link.h>
 #include <sched.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -20,6 +21,7 @@ constexpr size_t STACK = 64 * 1024;
 int g_slow_wave = -1, g_slow_part = -1, g_cus = 256;
 unsigned g_seed = 1;
 uint64_t g_loaded = 0;
+uint32_t g_lds = 0;
 
 enum State { READY, IN_WAVE_OP, AT_BARRIER, SLEEPING, ENDED };
 struct Fiber : Lane {
@@ -104,7 +106,24 @@ void fiber_main() {
   abort();
 }
 
+// LDS holds anything when a workgroup begins: every thread-local word of this library gets the value that was asked for
+int fill_lds(struct dl_phdr_info *info, size_t, void *) {
+  const ElfW(Addr) here = reinterpret_cast<ElfW(Addr)>(&g_lds) - info->dlpi_addr;
+  bool mine = false;
+  for (int i = 0; i < info->dlpi_phnum; ++i) {
+    const ElfW(Phdr) &h = info->dlpi_phdr[i];
+    mine |= h.p_type == PT_LOAD && here >= h.p_vaddr && here < h.p_vaddr + h.p_memsz;
+  }
+  for (int i = 0; mine && i < info->dlpi_phnum; ++i)
+    if (info->dlpi_phdr[i].p_type == PT_TLS)
+      for (size_t w = 0; w < info->dlpi_phdr[i].p_memsz / 4; ++w) static_cast<uint32_t *>(info->dlpi_tls_data)[w] = g_lds;
+  return mine;
+}
+
 void run_group(Group *g, dim3 block, dim3 where) {
+  loaded = 0;                                          // (this module's thread-local memory exists from here on)
+  if (g_lds) dl_iterate_phdr(fill_lds, nullptr);
+  loaded = 0;
   g_group = g;
   const int n = (int)block.x, nw = n / 64;
   g->fibers.assign(n, Fiber());
@@ -222,6 +241,9 @@ extern "C" void emu_schedule(int seed, int slow_part, int slow_wave) {
   emu::g_slow_part = slow_part;
   emu::g_slow_wave = slow_wave;
 }
+
+// what every word of a workgroup's LDS holds when it begins
+extern "C" void emu_lds(uint32_t word) { emu::g_lds = word; }
 
 // bytes of scores loaded since the last call
 extern "C" uint64_t emu_loaded() { return __atomic_exchange_n(&emu::g_loaded, 0, __ATOMIC_SEQ_CST); }

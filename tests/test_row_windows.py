@@ -8,7 +8,7 @@ import torch
 
 import oracle
 import paper_2605_15508_amd as sts
-from test_select_emulated import check, lib  # noqa: F401  (lib: the emulated library, a fixture)
+from test_select_emulated import by_keys, check, lib  # noqa: F401  (lib: the emulated library, a fixture)
 
 DEV = "cuda:0"
 
@@ -71,6 +71,30 @@ def test_windows_emulated(lib, rows, Tq, N, k, what):  # noqa: F811
     s = torch.zeros(rows, 1, Tq, N)
     s[:2] = scores_of(what, 2, Tq, N, k, N + k)
     check(lib, s, [0], k, lens=[N, N - 3] + [0] * (rows - 2))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,N", [(16, 4001), (16, 8190), (256, 9000), (256, 20001), (513, 4090), (513, 8190), (513, 9001), (513, 20001)])
+def test_both_ends_of_the_key_range(rows, N):
+    """NaNs of the highest and the lowest keys (their order is that of the bits), in rows whose end leaves a few places of a
+    slab without a token."""
+    for n in (1000, 1021, 2047, 4081, 8129, N - 3):
+        if n > N:
+            continue
+        s = torch.rand(2, N, generator=torch.Generator().manual_seed(n))
+        bits = s.view(torch.int32)
+        bits[0, 100:800:100] = torch.tensor([0x7fffffff, 0x7fff0000, 0x7ffffffe, 0x7f800000, 0x7fffffff, 0x7fe00000, 0x7fefffff], dtype=torch.int32)
+        bits[0, 700:705] = torch.tensor([-2, -0x200000, -9, -0x100, -3], dtype=torch.int32)
+        bits[1, 5:990:98] = -9
+        sd = torch.zeros(rows, 1, 1, N, device=DEV)
+        sd[:2, 0, 0] = s.to(DEV)
+        lens = torch.zeros(rows, dtype=torch.int32, device=DEV)
+        lens[:2] = n
+        for k in (1, 3, n - 9, n - 3, n - 1):
+            idx, cnt, _ = sts.sts_select(sd, [0], k, seq_lens=lens)
+            assert cnt[:2, 0].tolist() == [k, k]
+            for b in range(2):
+                np.testing.assert_array_equal(idx[b, 0].cpu().numpy(), by_keys(s[b], n, k), err_msg=f"row {b}, length {n}, k {k}")
 
 
 @pytest.mark.gpu

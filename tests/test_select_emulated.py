@@ -284,3 +284,24 @@ def test_highest_keys_of_all(lib, rows, N, n):
     bits[2, 5:900:200] = torch.tensor([-1, -2, -0x200000, -3, -0x100000], dtype=torch.int32)       # ... and the lowest
     for k in (1, 3, 6, 990):
         check_keys(lib, s, rows, k, [n, n, n])
+
+
+@pytest.mark.parametrize("rows,N", ROW_FORMS)
+def test_lowest_keys_of_all(lib, rows, N):
+    """The threshold next to the lowest key there is, 1: a bin that begins there does not count the positions after the
+    row's end, which hold key 0 and are not listed, whatever the list's memory holds."""
+    lib.emu_schedule(1, -1, -1)
+    lib.emu_lds(0x101)
+    try:
+        for n in (1000, 1021, 2047, 4081, 8129, N - 3):
+            if n > N:
+                continue
+            s = torch.rand(3, N, generator=torch.Generator().manual_seed(n))
+            bits = s.view(torch.int32)
+            bits[0, 700:705] = torch.tensor([-2, -0x200000, -9, -0x100, -3], dtype=torch.int32)
+            bits[1, 5:990:98] = -9
+            bits[2, 0:900:2] = -0x7f0000 - torch.arange(450, dtype=torch.int32)            # many below all other scores
+            for k in (n - 1, n - 3, n - 9, n - 400):
+                check_keys(lib, s, rows, k, [n, n, n])
+    finally:
+        lib.emu_lds(0)
