@@ -70,8 +70,9 @@ __device__ __forceinline__ int ranked_len(const SelectArgs &A, int bt) {
   return min(n, A.N);
 }
 
-// The row's scores, aggregated, as signed numbers of their order: thread tid gets the quads tid, tid + T, ... A position past
-// the row's valid length holds INT_MIN, which no token does. out: the aggregate, stored on request.
+// The row's scores, aggregated, as signed numbers of their order (positive ones as they are, the others their magnitude's
+// negative, so that -0 is +0): thread tid gets the quads tid, tid + T, ... A position past the row's valid length holds INT_MIN,
+// which no token does. out: the aggregate, stored on request.
 template <int T, int IT>
 __device__ __forceinline__ void load_row(const AggRow &R, float *out, int nb, int tid, int (&v)[IT][4]) {
   int any = 0;
@@ -208,7 +209,7 @@ __device__ __forceinline__ void load_row(const AggRow &R, float *out, int nb, in
 #pragma clang loop unroll(full)
     for (int i = 0; i < IT; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[i][e] = max(ordered(v[i][e]), (int)0x80000001);
+      for (int e = 0; e < 4; ++e) v[i][e] = v[i][e] < 0 ? (int)(0x80000000u - (uint32_t)v[i][e]) : v[i][e];
   }
   if (nb < 4 * T * IT) {
 #pragma clang loop unroll(full)
@@ -713,14 +714,12 @@ __global__ void __launch_bounds__(T, 4) select_row_kernel(const SelectArgs A) {
 // the keys outside the window 229 us; 256 threads with 128 registers of keys, three rows per CU, 153-157, but 256 rows of
 // 65536 20.5 against 17.0; 131072 tokens in 512 threads 1053 us for 8192 rows, in 1024 threads 870.
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-// Scores with their order as signed numbers (positive ones as they are): -0 is +0, and the lowest value stays free for
-// "no token" (a NaN shares the key of its neighbour).
+// Scores with their order as signed numbers: positive ones as they are, the others their magnitude's negative, so that -0 is
+// +0 and the lowest number stays free for "no token".
 __device__ __forceinline__ uint32_t signed16(uint32_t w) {
-  const u16x2 x = __builtin_bit_cast(u16x2, w);
-  const u16x2 sign = __builtin_bit_cast(u16x2, __builtin_bit_cast(uint32_t, x >> (u16x2)15) * 0x7fffu);
-  u16x2 k = x ^ sign ^ (u16x2)0x8000;                                     // -0: 0x7fff, +0: 0x8000
-  k += (u16x2)1 - __builtin_elementwise_min(k ^ (u16x2)0x7fff, (u16x2)1);
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(k, (u16x2)1)) ^ 0x80008000u;
+  const u16x2 x = __builtin_bit_cast(u16x2, w), sign = x >> (u16x2)15;
+  const u16x2 flip = __builtin_bit_cast(u16x2, __builtin_bit_cast(uint32_t, sign) * 0x7fffu);
+  return __builtin_bit_cast(uint32_t, (x ^ flip) + sign);
 }
 
 // T threads, IT 16-byte words per thread: rows of up to 8 * T * IT tokens, at least 8.

@@ -8,7 +8,7 @@ import torch
 
 import oracle
 import paper_2605_15508_amd as sts
-from test_select_emulated import check, lib  # noqa: F401  (lib: the emulated library, a fixture)
+from test_select_emulated import by_keys, check, check_keys, lib  # noqa: F401  (lib: the emulated library, a fixture)
 
 PATH_KNOB = 3
 
@@ -89,3 +89,43 @@ def test_on_the_gpu(what, N, k):
     if N >= 4096:                                     # the library's own rule
         idx2, cnt2, _ = sts.sts_select(sd, hm, k, k_head=kh, seq_lens=lens.to("cuda:0"))
         assert torch.equal(idx, idx2) and torch.equal(cnt, cnt2)
+
+
+def lowest_nans(N):
+    """Every negative NaN of bf16 there is at the end of a row, the lowest ones last but one and before."""
+    s = torch.rand(N, generator=torch.Generator().manual_seed(N)).to(torch.bfloat16)
+    s.view(torch.int16)[-127:] = torch.arange(-1, -128, -1, dtype=torch.int16)
+    s.view(torch.int16)[5] = -2
+    return s
+
+
+@pytest.mark.parametrize("N", [300, 4096, 16385])
+def test_lowest_nans_emulated(lib, N):  # noqa: F811
+    """The two lowest keys are told apart, as every path does that compares widened scores."""
+    lib.emu_schedule(1, -1, -1)
+    lib.sts_set_knob(PATH_KNOB, 6.0)
+    try:
+        for k in (N - 1, N - 2, N - 3, N - 100):
+            check_keys(lib, torch.stack([lowest_nans(N), lowest_nans(N).flip(0)]), 2, k, [N, N])
+    finally:
+        lib.sts_set_knob(PATH_KNOB, float("nan"))
+
+
+@pytest.mark.parametrize("rows,N", [(16, 4096), (256, 9000), (513, 8190)])
+def test_lowest_nans_of_rows_in_fp32_emulated(lib, rows, N):  # noqa: F811
+    lib.emu_schedule(1, -1, -1)
+    s = torch.rand(N, generator=torch.Generator().manual_seed(N))
+    s.view(torch.int32)[-9:] = torch.arange(-1, -10, -1, dtype=torch.int32)
+    s.view(torch.int32)[5] = -2
+    for k in (N - 1, N - 2, N - 3, N - 7):
+        check_keys(lib, torch.stack([s, s.flip(0)]), rows, k, [N, N])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N", [4096, 16384, 32768, 65536, 131072])
+def test_lowest_nans_on_the_gpu(N):
+    s = torch.stack([lowest_nans(N), lowest_nans(N).flip(0)])
+    for k in (N - 1, N - 2, N - 100):
+        idx, _, _ = sts.sts_select(s[:, None, None].to("cuda:0").contiguous(), [0], k)
+        for b in range(2):
+            np.testing.assert_array_equal(idx[b, 0].cpu().numpy(), by_keys(s[b], N, k))
