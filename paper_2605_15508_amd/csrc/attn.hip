@@ -162,7 +162,7 @@ attn_split_kernel(const AttnArgs A) {
   const int t_begin = split * tps;
   // (an empty list's entries are read from Q and never used)
   const bool some = len_max > 0;
-  const int last = max(len_max, 1) - 1;
+  int last = max(len_max, 1) - 1;
   const size_t list = some ? (size_t)bt * A.idx_stride_b + (size_t)head0 * A.kmax : 0;
   const int32_t *idx_row = SPARSE ? (some ? A.indices : reinterpret_cast<const int32_t *>(A.q)) + list : nullptr;
   const uint16_t *mask_row = ROWMASK ? (some ? A.row_mask : A.q) + list : nullptr;
@@ -268,9 +268,10 @@ attn_split_kernel(const AttnArgs A) {
   // byte offset of the row, and its row bits (cleared where the slot holds no key); lanes 32 apart write the same words
   auto place = [&](int x, int bits, uint32_t tile_mask, int v) {
     if (!GATHER) return;
-    if (FAR && paged)
-      lds_off[wave][lane & 31] = (row_off)((int64_t)min(max(x, 0), A.num_pages - 1) * page_bytes + (int64_t)(lane & pmask) * row_bytes);
-    else
+    if (FAR && paged) {
+      const int in_page = ((tile_mask >> (lane & 31)) & 1u) ? lane & pmask : 0;       // (a page's first row is always filled)
+      lds_off[wave][lane & 31] = (row_off)((int64_t)min(max(x, 0), A.num_pages - 1) * page_bytes + (int64_t)in_page * row_bytes);
+    } else
       lds_off[wave][lane & 31] = (row_off)x * (row_off)row_bytes;
     if (ROWMASK) lds_bits[wave][v & 3][lane & 31] = (uint16_t)(((tile_mask >> (lane & 31)) & 1u) ? bits : 0);
   };
@@ -521,6 +522,17 @@ attn_split_kernel(const AttnArgs A) {
     const int n_max = SPARSE ? A.kmax : A.N;
     c = __builtin_amdgcn_readfirstlane(len_src ? min(max(n_read, 0), n_max) : n_max) << (SPARSE ? psh : 0);
     t_end = min(t_begin + tps, (c + STS_TILE_KEYS - 1) / STS_TILE_KEYS);
+    // A slot past the end reads a row that is attended to: its weight is 0, but what lies past a list or a sequence may be
+    // NaN, and 0 times NaN is not 0. Entries are fetched up to the end from here on; of those that have been, a slot past it
+    // takes the tile's first.
+    if (GATHER) last = max(c, 1) - 1;
+    auto within = [&](int raw, int t) -> int {
+      if (!GATHER) return raw;
+      const int first = __builtin_amdgcn_readfirstlane(raw);
+      return t * STS_TILE_KEYS + (lane & 31) < c ? raw : first;
+    };
+    raw_a = within(raw_a, tile_of(0));
+    raw_b = within(raw_b, tile_of(1));
     // Tiles of this wave. The loop below has one exit, after a pair of tiles, and the odd last tile has code of its own:
     // with an exit between the two halves the compiler cannot tell at the loop's head which loads are in flight and
     // waits for all of them in every second tile.
@@ -548,7 +560,7 @@ attn_split_kernel(const AttnArgs A) {
       take_q();
       int x = resolve(raw_b, tile_of(1), m1);
       place(x, bits_b, m1, 1);
-      raw_a = raw_c;
+      raw_a = within(raw_c, tile_of(2));
       bits_a = bits_c;
       pin();
       for (; v < nv; ++v) {
@@ -579,7 +591,7 @@ attn_split_kernel(const AttnArgs A) {
       take_q();
       int x_b = resolve(raw_b, tile_of(1), m_next);
       place(x_b, bits_b, m_next, 1);
-      raw_a = raw_c;
+      raw_a = within(raw_c, tile_of(2));
       bits_a = bits_c;
       pin();
       for (; v + 2 <= nv; v += 2) {
