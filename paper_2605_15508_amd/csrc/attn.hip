@@ -358,9 +358,10 @@ attn_split_kernel(const AttnArgs A) {
   auto consume = [&](int t, int v, const chunk_t (&Vr)[8], const uint32_t tile_mask, const bool second) {
     const int pos0 = t * STS_TILE_KEYS;
     uint64_t key_bits[2];           // ROWMASK: the row bits of this lane's 8 keys, 16 each
+    typedef uint64_t four_bits __attribute__((may_alias));       // (stored one by one, with no barrier in between)
     if constexpr (ROWMASK) {
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) key_bits[ks] = *reinterpret_cast<const uint64_t *>(&lds_bits[wave][v & 3][16 * ks + 4 * a]);
+      for (int ks = 0; ks < 2; ++ks) key_bits[ks] = *reinterpret_cast<const four_bits *>(&lds_bits[wave][v & 3][16 * ks + 4 * a]);
     }
     // ---- S^T = K Q^T
     f32x4 St[NQ][2];

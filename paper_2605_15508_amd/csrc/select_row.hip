@@ -928,7 +928,8 @@ __global__ void __launch_bounds__(T, 4) select_row16_kernel(const SelectArgs A) 
 
   // ---- two bits per token: 0 below, 1 equal, 2 above the threshold
   const u16x2 below = (u16x2)(unsigned short)(lo - 1u);
-  uint16_t *const codes16 = reinterpret_cast<uint16_t *>(codes);
+  typedef uint16_t half_word __attribute__((may_alias));
+  half_word *const codes16 = reinterpret_cast<half_word *>(codes);
 #pragma clang loop unroll(full)
   for (int i = 0; i < IT; ++i) {
     uint32_t m = 0;
@@ -940,7 +941,7 @@ __global__ void __launch_bounds__(T, 4) select_row16_kernel(const SelectArgs A) 
 #pragma unroll
     for (int e = 0; e < 4; ++e) m |= __builtin_bit_cast(uint32_t, x[e]) << (4 * e);
     const int w = i * T + tid;
-    codes16[w + 2 * (w >> 5)] = (uint16_t)(m | m >> 14);
+    codes16[w + 2 * (w >> 5)] = (half_word)(m | m >> 14);
     fence_schedule();
   }
   __syncthreads();

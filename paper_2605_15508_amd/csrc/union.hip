@@ -139,7 +139,8 @@ __global__ void __launch_bounds__(UN_THREADS) union_rows_kernel(const UnionArgs 
     // from the owning threads were the slowest part of this kernel.
     const uint32_t rel0 = before + incl - kept;       // this thread's first place within the chunk
     int32_t *stg_idx = reinterpret_cast<int32_t *>(bits);
-    uint16_t *stg_mask = reinterpret_cast<uint16_t *>(bits + UN_STAGE);
+    typedef uint16_t staged_mask __attribute__((may_alias));
+    staged_mask *stg_mask = reinterpret_cast<staged_mask *>(bits + UN_STAGE);
     for (uint32_t r0 = 0; r0 < total; r0 += UN_STAGE) {
       uint32_t rel = rel0;
       if (rel < r0 + UN_STAGE && rel + kept > r0) {
@@ -151,7 +152,7 @@ __global__ void __launch_bounds__(UN_THREADS) union_rows_kernel(const UnionArgs 
             if (m) {
               if (rel >= r0 && rel - r0 < (uint32_t)UN_STAGE) {
                 stg_idx[rel - r0] = base + tid * 32 + 2 * x + hlf;
-                stg_mask[rel - r0] = (uint16_t)m;
+                stg_mask[rel - r0] = (staged_mask)m;
               }
               ++rel;
             }
