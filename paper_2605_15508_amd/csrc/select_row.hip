@@ -72,10 +72,12 @@ __device__ __forceinline__ int ranked_len(const SelectArgs &A, int bt) {
 
 // The row's scores, aggregated, as signed numbers of their order (positive ones as they are, the others their magnitude's
 // negative, so that -0 is +0): thread tid gets the quads tid, tid + T, ... A position past the row's valid length holds INT_MIN,
-// which no token does. out: the aggregate, stored on request.
+// which no token does, and its scores are not read: past the last quad with a token that quad is asked for again, which costs
+// no memory (rows of a tensor that is allocated for the longest sequence). out: the aggregate, stored on request.
 template <int T, int IT>
 __device__ __forceinline__ void load_row(const AggRow &R, float *out, int nb, int tid, int (&v)[IT][4]) {
   int any = 0;
+  const int last = max(min(R.N - 4, (nb - 1) & ~3), 0);
   auto take = [&](int i, f32x4 acc) {
     const int n = 4 * (i * T + tid);
     if (out && n < R.N) {
@@ -97,7 +99,7 @@ __device__ __forceinline__ void load_row(const AggRow &R, float *out, int nb, in
     for (int i = 0; i < IT; ++i) {
       const int n = 4 * (i * T + tid);
       const bool inside = 4 * (i + 1) * T <= R.N;
-      const int at = min(n, R.N - 4);
+      const int at = min(n, last);
       const f32x4 y = agg_quad(R, at);
       take(i, inside ? y : shifted_quad(y, n - at));
     }
@@ -112,13 +114,13 @@ __device__ __forceinline__ void load_row(const AggRow &R, float *out, int nb, in
 #pragma clang loop unroll(full)
       for (int b = 0; b < IT; b += QB) {
         f32x4 acc[QB];
-        if (4 * b * T < (out ? R.N : nb)) {
+        if (4 * b * T < nb) {
           typename SL::raw x[QB], y[QB];
           auto load = [&](typename SL::raw (&r)[QB], int q) {
             const unsigned char *at = static_cast<const unsigned char *>(R.P) + q * pitch;
 #pragma unroll
             for (int i = 0; i < QB; ++i) {
-              uint32_t off = (uint32_t)min(4 * ((b + i) * T + tid), R.N - 4) * (decltype(bf16)::value ? 2u : 4u);
+              uint32_t off = (uint32_t)min(4 * ((b + i) * T + tid), last) * (decltype(bf16)::value ? 2u : 4u);
               r[i] = SL::load_at(at + off);
             }
           };
@@ -175,7 +177,7 @@ __device__ __forceinline__ void load_row(const AggRow &R, float *out, int nb, in
         const float l = R.logits ? R.L[q] : 0.f;
 #pragma clang loop unroll(full)
         for (int i = 0; i < IT; ++i) {
-          f32x4 p = SL::widen(SL::load(R, q, min(4 * (i * T + tid), R.N - 4)));
+          f32x4 p = SL::widen(SL::load(R, q, min(4 * (i * T + tid), last)));
           if (R.logits) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) p[e] = prob_of(p[e], l);
@@ -722,38 +724,28 @@ __device__ __forceinline__ uint32_t signed16(uint32_t w) {
   return __builtin_bit_cast(uint32_t, (x ^ flip) + sign);
 }
 
-// T threads, IT 16-byte words per thread: rows of up to 8 * T * IT tokens, at least 8.
-template <int T, int IT>
-__global__ void __launch_bounds__(T, 4) select_row16_kernel(const SelectArgs A) {
-  constexpr int TOK = 8 * T * IT;
-  constexpr int CODES = TOK / 16;                                  // words of two bits per token
-  constexpr int STAGE = 8192;
-  typedef typename std::conditional<(TOK <= 65536), uint16_t, uint32_t>::type stage_t;
-  __shared__ uint32_t codes[CODES + CODES / 16];                   // a word of padding after every 16
-  constexpr int SLOTS = SEL_BINS + 2 * 64;                         // a window's bins, and 64 for the keys on either side of it
-  __shared__ uint32_t h[SLOTS];
-  __shared__ __attribute__((aligned(16))) stage_t staged[STAGE];
-  __shared__ uint32_t tot[2 * T / 64];
-  __shared__ uint32_t res[8];
-  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int bt = row / A.Hd, j = row % A.Hd;
-  const int nb = __builtin_amdgcn_readfirstlane(row_len(A, bt));
-  const uint32_t c = (uint32_t)min(A.kh[j], nb);
-  const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
-  write_tail<T>(A, bt, j, c);
-  if (c == 0 || t0 == t1) return;
+constexpr int ROW16_SLOTS = SEL_BINS + 2 * 64;                     // a window's bins, and 64 for the keys on either side of it
+constexpr int ROW16_STAGE = 8192;                                  // list entries staged per round
+
+// The ranking of one row of nb valid tokens, c of them kept, by T threads with IT 16-byte words each. codes, h, staged, tot, res: LDS.
+template <int T, int IT, class stage_t>
+__device__ __forceinline__ void rank_row16(const SelectArgs &A, int row, int nb, uint32_t c, uint32_t *codes, uint32_t *h, stage_t *staged,
+                                           uint32_t *tot, uint32_t *res) {
+  constexpr int CODES = 8 * T * IT / 16;                           // words of two bits per token
+  constexpr int STAGE = ROW16_STAGE, SLOTS = ROW16_SLOTS;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int bt = row / A.Hd, j = row % A.Hd, t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
   const uint16_t *src = static_cast<const uint16_t *>(A.scores) + (size_t)row * A.N;
 
   // ---- the row: thread tid holds the words tid, tid + T, ... as unsigned keys, 0 where there is no token
   u16x2 k[IT][4];
   {
     u32x4 raw[IT];
+    // (past the last word with a token that word is asked for again, which costs no memory)
+    const uint32_t cap = 2u * (uint32_t)min(A.N - 8, (nb - 1) & ~7);
 #pragma clang loop unroll(full)
     for (int i = 0; i < IT; ++i) {
-      const bool inside = 8 * (i + 1) * T <= A.N;                  // (a slab past the valid length reads where it can, and is not used)
-      const unsigned char *at = reinterpret_cast<const unsigned char *>(src) + (inside ? (size_t)i * T * 16 : 0);
-      const uint32_t off = inside ? tid * 16 : 2 * min(8 * (i * T + tid), A.N - 8);
-      raw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any *>(at + off));
+      raw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any *>(reinterpret_cast<const unsigned char *>(src) + min(16u * (uint32_t)(i * T + tid), cap)));
     }
     for (int i = tid; i < SLOTS; i += T) h[i] = 0u;
     uint32_t any = 0;
@@ -871,7 +863,7 @@ __global__ void __launch_bounds__(T, 4) select_row16_kernel(const SelectArgs A) 
     const u16x2 least = pair(at ? min((uint32_t)lane >> rs, at - 1u) : 0u), most = pair(at + n + ((uint32_t)lane >> rs));
 #pragma clang loop unroll(full)
     for (int i = 0; i < IT; ++i) {
-      if (8 * i * T < nb) {
+      if (8 * (i * T + 64 * wave) < nb) {                          // (a wave past the row's end has nothing to count)
         u16x2 x[4];                                                // (four at a time: a packed result cannot be used at once)
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[e] = __builtin_elementwise_sub_sat(k[i][e], base2);
@@ -1005,6 +997,34 @@ __global__ void __launch_bounds__(T, 4) select_row16_kernel(const SelectArgs A) 
     }
     __syncthreads();
   }
+}
+
+// T threads, IT 16-byte words per thread: rows of up to 8 * T * IT tokens, at least 8. Rows that a quarter of the words hold (of a
+// tensor that is allocated for the longest sequence) are ranked by code for so many.
+template <int T, int IT>
+__global__ void __launch_bounds__(T, 4) select_row16_kernel(const SelectArgs A) {
+  constexpr int TOK = 8 * T * IT, CODES = TOK / 16;
+  typedef typename std::conditional<(TOK <= 65536), uint16_t, uint32_t>::type stage_t;
+  __shared__ uint32_t codes[CODES + CODES / 16];                   // a word of padding after every 16
+  __shared__ uint32_t h[ROW16_SLOTS];
+  __shared__ __attribute__((aligned(16))) stage_t staged[ROW16_STAGE];
+  __shared__ uint32_t tot[2 * T / 64];
+  __shared__ uint32_t res[8];
+  const int row = blockIdx.x;
+  const int bt = row / A.Hd, j = row % A.Hd;
+  const int nb = __builtin_amdgcn_readfirstlane(row_len(A, bt));
+  const uint32_t c = (uint32_t)min(A.kh[j], nb);
+  write_tail<T>(A, bt, j, c);
+  if (c == 0 || A.targets.off[j] == A.targets.off[j + 1]) return;
+  if (c == (uint32_t)nb) {                                         // every token is kept
+    for (int ti = A.targets.off[j]; ti < A.targets.off[j + 1]; ++ti)
+      for (int i = threadIdx.x; i < nb; i += T) A.indices[((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + i] = i;
+    return;
+  }
+  if constexpr (IT >= 16) {
+    if (nb <= TOK / 4) return rank_row16<T, IT / 4>(A, row, nb, c, codes, h, staged, tot, res);
+  }
+  rank_row16<T, IT>(A, row, nb, c, codes, h, staged, tot, res);
 }
 
 }  // namespace

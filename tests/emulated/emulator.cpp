@@ -15,6 +15,7 @@ namespace emu {
 
 thread_local Lane *lane = nullptr;
 thread_local uint64_t loaded = 0;
+thread_local const void *recent[128];
 
 namespace {
 constexpr size_t STACK = 64 * 1024;

@@ -91,6 +91,39 @@ def test_on_the_gpu(what, N, k):
         assert torch.equal(idx, idx2) and torch.equal(cnt, cnt2)
 
 
+# lengths on both sides of a quarter of what the workgroup's registers hold, and next to them; budgets below and beyond the length
+SHORT = [(20001, 8192), (20000, 8193), (20001, 8185), (65536, 16384), (65535, 16385), (131072, 32768), (131071, 32769), (131072, 1025), (65536, 700)]
+
+
+def short_row(N, n, seed):
+    s = torch.full((2, N), float("inf"))              # (above all others, were they looked at)
+    for b, what in enumerate(("softmax", "signed")):
+        s[b, :n] = scores_of(what, n, max(1, n // 3), seed + b)
+    return s.to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("N,n", SHORT)
+def test_rows_that_are_mostly_empty_emulated(lib, N, n):  # noqa: F811
+    lib.emu_schedule(n, -1, -1)
+    for k in (n // 3, n - 1, n, min(N, n + 9)):
+        check(lib, short_row(N, n, N)[:, None, None].contiguous(), [0, 0], k, lens=[n, n])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,n", SHORT)
+def test_rows_that_are_mostly_empty_on_the_gpu(N, n):
+    s = short_row(N, n, N)[:, None, None].contiguous()
+    flat = torch.zeros(s.numel() + 1, dtype=torch.bfloat16, device="cuda:0")
+    sd = flat[1:].view(s.shape)                       # an odd element
+    sd.copy_(s)
+    lens = torch.full((2,), n, dtype=torch.int32)
+    for k in (1, n // 3, n - 1, n, min(N, n + 9)):
+        idx, cnt, _ = sts.sts_select(sd, [0, 0], k, seq_lens=lens.to("cuda:0"))
+        o_idx, o_cnt, _ = oracle.select_indices(s.float().numpy(), np.zeros(2, np.int32), k, seq_lens=lens.numpy())
+        np.testing.assert_array_equal(cnt.cpu().numpy(), o_cnt)
+        np.testing.assert_array_equal(idx.cpu().numpy(), o_idx)
+
+
 def lowest_nans(N):
     """Every negative NaN of bf16 there is at the end of a row, the lowest ones last but one and before."""
     s = torch.rand(N, generator=torch.Generator().manual_seed(N)).to(torch.bfloat16)

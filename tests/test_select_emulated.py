@@ -305,3 +305,20 @@ def test_lowest_keys_of_all(lib, rows, N):
                 check_keys(lib, s, rows, k, [n, n, n])
     finally:
         lib.emu_lds(0)
+
+
+@pytest.mark.parametrize("rows,Tq,N,bf16", [
+    (16, 5, 4001, False), (16, 3, 8190, True), (256, 2, 9000, False), (256, 9, 20001, False), (256, 2, 32768, True),
+    (513, 1, 4090, False), (513, 2, 8190, False), (513, 1, 9001, False), (513, 3, 20001, True),
+    (3, 1, 4099, True), (3, 1, 16384, True), (3, 1, 32765, True), (3, 1, 65536, True), (3, 1, 131071, True),       # packed in registers
+])
+def test_scores_past_the_valid_length_are_not_read(lib, rows, Tq, N, bf16):
+    """A row that is an eighth full, in a tensor that is allocated for the longest sequence."""
+    lib.emu_schedule(1, -1, -1)
+    n = N // 8 - 3
+    s = torch.zeros(rows, 1, Tq, N)
+    s[:2] = softmax(2, 1, Tq, N, N)
+    s = s.to(torch.bfloat16) if bf16 else s
+    lib.emu_loaded()
+    check(lib, s, [0], N // 20, lens=[n, n] + [0] * (rows - 2))
+    assert lib.emu_loaded() <= 0.6 * 2 * Tq * N * s.element_size()
