@@ -435,8 +435,8 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
   // row; one workgroup per row took 57), 128 rows of eight bf16 scaled logits of 50000 tokens 52
   // (70 with one workgroup per row).
   // One bf16 score per token and many rows per CU (a mask per query row of prefill): rows of up to 131072 tokens fit
-  // registers (below); longer ones are the one shape that plain passes by small workgroups serve better
-  // (select_rowpass_kernel; 4096 rows of 128K, which the registers take now: 754 against 962 us with the sampled selection).
+  // registers (below), and those that do so badly or not at all are the shape that plain passes by small workgroups serve
+  // better (select_rowpass_kernel; 4096 rows of 128K: 754 against 962 us with the sampled selection).
   {
     const bool aligned = reinterpret_cast<uintptr_t>(p->scores) % 16 == 0;
     const bool band_ok = pl.page == 1 && p->N >= 4 && p->N <= SMP_MAX_TOKENS;
@@ -451,13 +451,16 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
                                         : path == 0 && rowpass_ok && long_rows && p->scores_bf16 && (int64_t)rows >= 4 * cus;
     const bool take_band = path == 5 ? band_ok && p->N % 4 == 0 && aligned : path == 0 && !take_rowpass && has_edge && long_rows && 2 * (int64_t)rows >= cus;
     // One bf16 score per token: rows of 4096 to 131072 of them are held packed in one workgroup's registers
-    // (select_row16_kernel), whatever their number. us, with the paths that such calls would take otherwise: 16 rows of
-    // 131072 43.5 -> 24.8, 64 of 65536 42.1 -> 15.5, 512 of 65536 85.3 -> 25.4, 4096 of 65536 239 -> 155, 8192 of 131072
-    // 970 -> 870, 4096 of 32768 268 -> 75, 512 of 4096 11.7 -> 8.8. Shorter rows keep select_row_kernel (512 rows of 2048: 11.8, 10.7;
-    // 4096: 28.6, 39.7).
+    // (select_row16_kernel). us, with the paths that such calls would take otherwise: 16 rows of
+    // 131072 43.5 -> 24.8, 64 of 65536 42.1 -> 15.5, 512 of 65536 85.3 -> 25.4, 4096 of 65536 239 -> 155, 4096 of 32768
+    // 268 -> 75, 512 of 4096 11.7 -> 8.8. Shorter rows keep select_row_kernel (512 rows of 2048: 11.8, 10.7;
+    // 4096: 28.6, 39.7). Rows of more than 65536 tokens take a CU's whole register file, whatever they fill of it: where there
+    // are many, the plain passes of select_rowpass_kernel, several rows per CU, are faster up to 112K tokens. 1024 rows, 10%:
+    // of 65544 tokens 75, 88; of 98304 104, 112; of 114688 123, 120; of 131072 140, 129; 4096 rows of 65544 245, 329; of 106496
+    // 380, 424; of 131072 501, 464. (Rows that are not a multiple of 8 long cannot take those: 1024 of 66001 157, in registers 92.)
     const bool row16_ok = pl.page == 1 && p->Tq == 1 && p->kind == STS_SCORES_PROBS && p->scores_bf16 && !p->agg_out &&
                           p->N >= 8 && p->N <= SEL_ROW16_N;
-    const bool take_row16 = path == 6 ? row16_ok : path == 0 && row16_ok && p->N >= 4096;
+    const bool take_row16 = path == 6 ? row16_ok : path == 0 && row16_ok && p->N >= 4096 && !(take_rowpass && p->N > 65536 && p->N < 114688);
     if (take_row16) {
       // The rest of the plan stays: such a call has to bring the workspace that its rows asked for before (nothing in it
       // is touched), and the timing aid counts it as the class of call that they put it in.

@@ -637,8 +637,8 @@ __global__ void __launch_bounds__(SMALL_THREADS) select_small_kernel(const Selec
 
 // --------------------------------- many long rows of ready-made scores: one workgroup per row
 // A call with one score per token (Tq = 1: the per-query-row masks of prefill rank every row of a
-// block's scores on its own; a draft layer's summed weights), far more rows than CUs and rows of more than 128K tokens
-// (shorter ones fit a workgroup's registers, select_row16_kernel). Cutting
+// block's scores on its own; a draft layer's summed weights), far more rows than CUs and rows that do not fit a workgroup's
+// registers, or take a CU's for each (select_row16_kernel and the rule in the host code). Cutting
 // such rows into parts that wait for each other leaves every CU idle during the exchanges; here a
 // row belongs to ONE workgroup, which keeps nothing but a digit histogram in LDS and reads the
 // row once per digit level and once more to compact it. The re-reads come out of the caches (a

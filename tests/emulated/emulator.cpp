@@ -6,6 +6,7 @@
 #include <stdlib.h>
 #include <sys/mman.h>
 
+#include <string>
 #include <thread>
 #include <vector>
 
@@ -23,6 +24,8 @@ int g_slow_wave = -1, g_slow_part = -1, g_cus = 256;
 unsigned g_seed = 1;
 uint64_t g_loaded = 0;
 uint32_t g_lds = 0;
+bool g_only_names = false;
+std::string g_names;
 
 enum State { READY, IN_WAVE_OP, AT_BARRIER, SLEEPING, ENDED };
 struct Fiber : Lane {
@@ -211,6 +214,13 @@ void barrier() {
 }
 void sleep() { leave(SLEEPING); }
 
+bool noted(const char *kernel) {
+  std::string name = kernel;
+  if (name[0] == '(') name = name.substr(1, name.size() - 2);
+  if (g_only_names) g_names += (g_names.empty() ? "" : " ") + name;
+  return g_only_names;
+}
+
 // Workgroups start in the order of their ids, a few at a time, each on a thread of its own: the parts of a row
 // run side by side, and every workgroup's LDS (thread-local statics) is its own.
 void launch(void (*body)(void *), void *arg, dim3 grid, dim3 block) {
@@ -245,6 +255,13 @@ extern "C" void emu_schedule(int seed, int slow_part, int slow_wave) {
 
 // what every word of a workgroup's LDS holds when it begins
 extern "C" void emu_lds(uint32_t word) { emu::g_lds = word; }
+
+// launches are noted down by name from here on (1), or run (0)
+extern "C" void emu_only_names(int on) {
+  emu::g_only_names = on != 0;
+  emu::g_names.clear();
+}
+extern "C" const char *emu_names() { return emu::g_names.c_str(); }
 
 // bytes of scores loaded since the last call
 extern "C" uint64_t emu_loaded() { return __atomic_exchange_n(&emu::g_loaded, 0, __ATOMIC_SEQ_CST); }

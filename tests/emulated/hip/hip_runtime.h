@@ -44,6 +44,7 @@ uint64_t live();                                      // lanes of the wave that 
 void barrier();
 void sleep();
 void launch(void (*body)(void *), void *arg, dim3 grid, dim3 block);
+bool noted(const char *kernel);                       // true: the launch is noted down and not run
 
 inline int lane_id() { return (int)(lane->thread.x & 63u); }
 inline int readlane(int v, int l) { return (int)exchange((uint32_t)v)[l & 63]; }

@@ -8,7 +8,7 @@ import torch
 
 import oracle
 import paper_2605_15508_amd as sts
-from test_select_emulated import by_keys, check, check_keys, lib  # noqa: F401  (lib: the emulated library, a fixture)
+from test_select_emulated import by_keys, check, check_keys, lib, route  # noqa: F401  (lib: the emulated library, a fixture)
 
 PATH_KNOB = 3
 
@@ -122,6 +122,16 @@ def test_rows_that_are_mostly_empty_on_the_gpu(N, n):
         o_idx, o_cnt, _ = oracle.select_indices(s.float().numpy(), np.zeros(2, np.int32), k, seq_lens=lens.numpy())
         np.testing.assert_array_equal(cnt.cpu().numpy(), o_cnt)
         np.testing.assert_array_equal(idx.cpu().numpy(), o_idx)
+
+
+@pytest.mark.parametrize("rows,N,kernel", [
+    (1024, 65536, "select_row16_kernel<512, 16>"), (1024, 65544, "select_rowpass_kernel<256, true>"), (1024, 114680, "select_rowpass_kernel<256, true>"),
+    (1024, 114688, "select_row16_kernel<1024, 16>"), (1023, 65544, "select_row16_kernel<1024, 16>"), (1024, 65545, "select_row16_kernel<1024, 16>"),
+    (1024, 131080, "select_rowpass_kernel<256, true>"),
+])
+def test_many_rows_that_take_a_compute_unit_each(lib, rows, N, kernel):  # noqa: F811
+    """Many rows of more than half of what fits registers go by plain passes over them."""
+    assert route(lib, rows, 1, 1, N, 2, N // 10, bf16=True, lens=True) == kernel
 
 
 def lowest_nans(N):

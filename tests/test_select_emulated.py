@@ -40,6 +40,7 @@ def lib(tmp_path_factory):
     lib.sts_select_workspace_bytes.restype = ctypes.c_size_t
     lib.sts_headmap_workspace_bytes.restype = ctypes.c_size_t
     lib.emu_loaded.restype = ctypes.c_uint64
+    lib.emu_names.restype = ctypes.c_char_p
     lib.sts_set_knob.argtypes = [ctypes.c_int, ctypes.c_double]
     return lib
 
@@ -59,6 +60,22 @@ def select(lib, scores, hm, k, k_head=None, lens=None, ws_offset=0, ws_bytes=Non
     p.workspace_bytes = need if ws_bytes is None else ws_bytes
     assert lib.sts_select(ctypes.byref(p), None) == status
     return idx, cnt
+
+
+def route(lib, B, Hd, Tq, N, Hq, k, bf16=False, page=1, lens=False, agg=False, logits=False, unaligned=False, status=0):
+    """The kernels that a call launches, without running them: their names, in order."""
+    hm = np.arange(Hq, dtype=np.int32) * Hd // Hq
+    p = binding.SelectParams(B=B, Hd=Hd, Tq=Tq, N=N, Hq=Hq, k=k, page_size=page, kind=int(logits), scores=(1 << 20) + 2 * unaligned, head_map=hm.ctypes.data,
+                             seq_lens=1 << 20 if lens else None, lse=1 << 20 if logits else None, agg_out=1 << 20 if agg else None, indices=1 << 20,
+                             counts=1 << 20, scores_bf16=int(bf16))
+    p.workspace_bytes = lib.sts_select_workspace_bytes(ctypes.byref(p))
+    p.workspace = 1 << 20
+    lib.emu_only_names(1)
+    try:
+        assert lib.sts_select(ctypes.byref(p), None) == status
+        return lib.emu_names().decode()
+    finally:
+        lib.emu_only_names(0)
 
 
 def check(lib, scores, hm, k, **kw):
