@@ -4,6 +4,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -422,10 +423,19 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
   // 20000 with twelve 41.3, 38.0; bf16, 16 rows of 32768 with ten 33.3, 33.4, of 26000 with twelve 35.5, 33.1. Calls of fewer
   // than eight rows, fewer than any model's draft heads, keep the route that they had (and calls of few rows the workspace
   // that they had to bring).
+  //
+  // What one workgroup writes counts, too: an entry of a list costs it as much as 13 stores to make, and a store per list that
+  // takes it, where the parts of the sampled selection share this (list_work: the stores that they would take off it). us, in
+  // one workgroup per row and sampled, half of the tokens kept: 8 rows of 16384, 32 lists for each 52.6, 43.4, 8 lists 26 or less,
+  // 32; of 32768 one score per token, two lists 22.6, 27.8, 8 lists 31.5, 31.1; five scores, one list 30.7, 29.8, but 10% kept,
+  // 32 lists faster; of 9000, 32 lists 41.5, 39.0.
+  const int64_t parts = std::max<int64_t>(std::min<int64_t>({cu_count() / std::max<int64_t>((int64_t)rows, 1), ((int64_t)p->N + 8191) / 8192, 32}), 1);
+  const int64_t list_work = (int64_t)std::min(largest_budget(p), p->N) * (13 + (p->Hq + p->Hd - 1) / p->Hd) * (parts - 1) / parts;
   const int64_t token_bytes = (int64_t)p->Tq * (p->scores_bf16 ? 2 : 4);
+  const bool writes_little = list_work <= (p->N <= 16384 ? 96000 : 240000 - 6000 * std::min<int64_t>(token_bytes, 32));
   const bool reads_little = p->N <= 16384 ? p->N * token_bytes <= (4 * (int64_t)rows >= cu_count() ? 1024 : 640) << 10
                                           : token_bytes <= (2 * (int64_t)rows >= cu_count() ? 32 : 20);
-  const bool one_row = path == 0 && pl.page == 1 && !pl.small && p->N > SEL_FUSED_N && p->N <= SEL_SMALL_N && rows >= 8 && reads_little;
+  const bool one_row = path == 0 && pl.page == 1 && !pl.small && p->N > SEL_FUSED_N && p->N <= SEL_SMALL_N && rows >= 8 && reads_little && writes_little;
   pl.one_row = false;
   // Enough rows to give at least every second CU one, and rows that do not fit one workgroup's
   // LDS: the sampled selection, which here can do without a workspace, in one workgroup per row (with one it
@@ -458,9 +468,12 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
     // are many, the plain passes of select_rowpass_kernel, several rows per CU, are faster up to 112K tokens. 1024 rows, 10%:
     // of 65544 tokens 75, 88; of 98304 104, 112; of 114688 123, 120; of 131072 140, 129; 4096 rows of 65544 245, 329; of 106496
     // 380, 424; of 131072 501, 464. (Rows that are not a multiple of 8 long cannot take those: 1024 of 66001 157, in registers 92.)
+    // Few rows whose lists are long or many stay with the sampled selection, see list_work: 1 row of 131072, half kept, one list
+    // 65, sampled 42, 32 lists 159, 56; 10% kept, 32 lists 49, 45; of 65536, half kept, two lists 38.4, 38.2, 8 lists 50, 41.
     const bool row16_ok = pl.page == 1 && p->Tq == 1 && p->kind == STS_SCORES_PROBS && p->scores_bf16 && !p->agg_out &&
                           p->N >= 8 && p->N <= SEL_ROW16_N;
-    const bool take_row16 = path == 6 ? row16_ok : path == 0 && row16_ok && p->N >= 4096 && !(take_rowpass && p->N > 65536 && p->N < 114688);
+    const bool take_row16 = path == 6 ? row16_ok : path == 0 && row16_ok && p->N >= 4096 && (p->N <= SEL_FUSED_N || list_work <= 440000) &&
+                                                   !(take_rowpass && p->N > 65536 && p->N < 114688);
     if (take_row16) {
       // The rest of the plan stays: such a call has to bring the workspace that its rows asked for before (nothing in it
       // is touched), and the timing aid counts it as the class of call that they put it in.

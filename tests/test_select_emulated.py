@@ -339,3 +339,18 @@ def test_scores_past_the_valid_length_are_not_read(lib, rows, Tq, N, bf16):
     lib.emu_loaded()
     check(lib, s, [0], N // 20, lens=[n, n] + [0] * (rows - 2))
     assert lib.emu_loaded() <= 0.6 * 2 * Tq * N * s.element_size()
+
+
+@pytest.mark.parametrize("rows,Hq,Tq,N,k,bf16,one", [
+    (1, 1, 1, 131072, 13107, True, True), (1, 1, 1, 131072, 65536, True, False), (1, 64, 1, 131072, 60000, True, False), (1, 32, 1, 131072, 13107, True, False),
+    (1, 2, 1, 65536, 32768, True, True), (1, 8, 1, 65536, 32768, True, False), (120, 256, 1, 131072, 13107, True, True), (4096, 64, 1, 65536, 32768, True, True),
+    (1, 256, 1, 8192, 8192, True, True),
+    (8, 8 * 2, 5, 32768, 3277, False, True), (8, 8 * 8, 5, 32768, 16384, False, False), (8, 8 * 2, 1, 32768, 16384, False, True),
+    (8, 8 * 32, 1, 32768, 16384, False, False), (8, 8 * 32, 5, 32768, 3277, False, True), (8, 8 * 32, 1, 16384, 8192, False, False),
+    (8, 8 * 8, 1, 16384, 8192, False, True), (8, 8 * 32, 1, 9000, 4500, False, False), (255, 2, 1, 20000, 10000, False, True),
+])
+def test_rows_whose_lists_one_workgroup_would_write_for_long(lib, rows, Hq, Tq, N, k, bf16, one):
+    """Few rows with long lists, or a list for each of many target heads, are cut into parts that share the writing."""
+    Hd = 8 if rows % 8 == 0 and Hq > 2 else 1
+    got = route(lib, rows // Hd, Hd, Tq, N, max(Hq, Hd), k, bf16=bf16)
+    assert got.startswith("select_row" if one else "select_clear16_kernel select_sampled_kernel"), got
