@@ -60,14 +60,14 @@ __device__ __forceinline__ void scan2(uint32_t a, uint32_t b, uint32_t *tot, int
   }
 }
 
-// Valid length of a row. Block sums are ranked as rows of scores whose lengths are given in tokens.
+// Valid length of a row; of a row of block sums, which is ranked as a row of scores, from its length in tokens. (Kernels of
+// their own: the page's size, asked for after the length, is another latency in front of every row's first load. 16 rows of 4096
+// tokens with lengths: 8.3 us, 8.55 with one kernel for both.)
+template <bool BLOCKS>
 __device__ __forceinline__ int ranked_len(const SelectArgs &A, int bt) {
-  int n = A.N;
-  if (A.seq_lens) {
-    n = max(A.seq_lens[bt], 0);
-    if (A.page > 1) n = (int)(((uint32_t)n + (uint32_t)A.page - 1u) / (uint32_t)A.page);
-  }
-  return min(n, A.N);
+  if (!BLOCKS) return row_len(A, bt);
+  if (!A.seq_lens) return A.N;
+  return min((int)(((uint32_t)max(A.seq_lens[bt], 0) + (uint32_t)A.page - 1u) / (uint32_t)A.page), A.N);
 }
 
 // The row's scores, aggregated, as signed numbers of their order (positive ones as they are, the others their magnitude's
@@ -242,8 +242,8 @@ __device__ __forceinline__ void row_min_max(uint32_t &lo, uint32_t &hi, uint32_t
 }
 
 // T threads, IT quads per thread: rows of up to 4 * T * IT tokens. All keys are counted, in bins that divide their range.
-template <int T, int IT>
-__global__ void __launch_bounds__(T) short_select_row_kernel(const SelectArgs A) {
+template <int T, int IT, bool BLOCKS>
+__device__ __forceinline__ void rank_short_row(const SelectArgs &A) {
   constexpr int TOK = 4 * T * IT;
   constexpr int STAGE = TOK / 8 > 1024 ? TOK / 8 : 1024;           // list entries staged per round
   __shared__ uint32_t bits[TOK / 32];
@@ -254,7 +254,7 @@ __global__ void __launch_bounds__(T) short_select_row_kernel(const SelectArgs A)
   __shared__ uint32_t ctr[4];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int bt = row / A.Hd, j = row % A.Hd;
-  const int nb = __builtin_amdgcn_readfirstlane(ranked_len(A, bt));
+  const int nb = __builtin_amdgcn_readfirstlane(ranked_len<BLOCKS>(A, bt));
   const uint32_t c = (uint32_t)min(A.kh[j], nb);
   const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
   write_tail<T>(A, bt, j, c);
@@ -400,11 +400,16 @@ __global__ void __launch_bounds__(T) short_select_row_kernel(const SelectArgs A)
   }
 }
 
+template <int T, int IT>
+__global__ void __launch_bounds__(T) short_select_row_kernel(const SelectArgs A) { rank_short_row<T, IT, false>(A); }
+template <int T, int IT>
+__global__ void __launch_bounds__(T) short_select_blocks_kernel(const SelectArgs A) { rank_short_row<T, IT, true>(A); }
+
 // ----------------------------------------------------------- longer rows: a window of keys from a sample
 // T threads, IT quads per thread: rows of up to 4 * T * IT tokens. (Up to eight keys per thread of 1024, or 16 of 256, are ranked
 // faster without a sample: 16 rows of 4096 tokens 8.3 against 9.5 us, 1024 of 4096 10.4, 10.8.)
-template <int T, int IT>
-__global__ void __launch_bounds__(T, 4) select_row_kernel(const SelectArgs A) {
+template <int T, int IT, bool BLOCKS>
+__device__ __forceinline__ void rank_row(const SelectArgs &A) {
   constexpr int TOK = 4 * T * IT;
   constexpr int STAGE = TOK / 8 > 1024 ? TOK / 8 : 1024;           // list entries staged per round
   constexpr int SLOTS = SEL_BINS + 2 * 64;                         // a window's bins, and 64 for the keys on either side of it
@@ -416,7 +421,7 @@ __global__ void __launch_bounds__(T, 4) select_row_kernel(const SelectArgs A) {
   __shared__ uint32_t res[8];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int bt = row / A.Hd, j = row % A.Hd;
-  const int nb = __builtin_amdgcn_readfirstlane(ranked_len(A, bt));
+  const int nb = __builtin_amdgcn_readfirstlane(ranked_len<BLOCKS>(A, bt));
   const uint32_t c = (uint32_t)min(A.kh[j], nb);
   const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
   write_tail<T>(A, bt, j, c);
@@ -701,6 +706,11 @@ __global__ void __launch_bounds__(T, 4) select_row_kernel(const SelectArgs A) {
     __syncthreads();
   }
 }
+
+template <int T, int IT>
+__global__ void __launch_bounds__(T, 4) select_row_kernel(const SelectArgs A) { rank_row<T, IT, false>(A); }
+template <int T, int IT>
+__global__ void __launch_bounds__(T, 4) select_blocks_kernel(const SelectArgs A) { rank_row<T, IT, true>(A); }
 
 // ------------------------------------------------- rows of one bf16 score per token, packed in registers
 // Calls with a mask per query row (prefill) rank thousands of rows of bf16 scores. 64K of them are 128 KB, 64 registers of
@@ -1046,6 +1056,7 @@ static hipError_t launch_select_row16(const SelectArgs &a, hipStream_t s) {
 // Rows of 4 to 32768 tokens. Calls of up to 512 rows get 1024 threads per row (latency: 256 rows of 16384 tokens 25 us
 // with 256 threads per row), others as few as hold the row in 64 registers per thread (several workgroups per CU: 4096
 // such rows 128 us; one workgroup per CU took 290).
+// (Rows of block sums where a page holds several tokens: kernels that turn lengths in tokens into blocks, see ranked_len.)
 hipError_t launch_select_row(const SelectArgs &a, hipStream_t s) {
   const int64_t rows = (int64_t)a.B * a.Hd;
   if (rows == 0) return hipSuccess;
@@ -1053,20 +1064,25 @@ hipError_t launch_select_row(const SelectArgs &a, hipStream_t s) {
   const int N = a.N;
   if (N < 4 || N > SEL_SMALL_N) return hipErrorInvalidValue;
   const dim3 grid((unsigned)rows);
+#define STS_ROW(kind, T, IT) \
+  do { \
+    if (a.page > 1) STS_LAUNCH((kind##_blocks_kernel<T, IT>), grid, dim3(T), 0, s, a); \
+    else STS_LAUNCH((kind##_row_kernel<T, IT>), grid, dim3(T), 0, s, a); \
+  } while (0)
   if (rows <= 512) {
-    const dim3 block(1024);
-    if (N <= 4096) STS_LAUNCH((short_select_row_kernel<1024, 1>), grid, block, 0, s, a);
-    else if (N <= 8192) STS_LAUNCH((short_select_row_kernel<1024, 2>), grid, block, 0, s, a);
-    else if (N <= 16384) STS_LAUNCH((select_row_kernel<1024, 4>), grid, block, 0, s, a);
-    else STS_LAUNCH((select_row_kernel<1024, 8>), grid, block, 0, s, a);
+    if (N <= 4096) STS_ROW(short_select, 1024, 1);
+    else if (N <= 8192) STS_ROW(short_select, 1024, 2);
+    else if (N <= 16384) STS_ROW(select, 1024, 4);
+    else STS_ROW(select, 1024, 8);
   } else if (N <= 4096) {
-    STS_LAUNCH((short_select_row_kernel<256, 4>), grid, dim3(256), 0, s, a);
+    STS_ROW(short_select, 256, 4);
   } else if (N <= 8192) {
-    STS_LAUNCH((select_row_kernel<256, 8>), grid, dim3(256), 0, s, a);
+    STS_ROW(select, 256, 8);
   } else if (N <= 16384) {
-    STS_LAUNCH((select_row_kernel<256, 16>), grid, dim3(256), 0, s, a);
+    STS_ROW(select, 256, 16);
   } else {
-    STS_LAUNCH((select_row_kernel<512, 16>), grid, dim3(512), 0, s, a);
+    STS_ROW(select, 512, 16);
   }
+#undef STS_ROW
   return sts_take_launch_status();
 }

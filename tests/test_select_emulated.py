@@ -354,3 +354,15 @@ def test_rows_whose_lists_one_workgroup_would_write_for_long(lib, rows, Hq, Tq, 
     Hd = 8 if rows % 8 == 0 and Hq > 2 else 1
     got = route(lib, rows // Hd, Hd, Tq, N, max(Hq, Hd), k, bf16=bf16)
     assert got.startswith("select_row" if one else "select_clear16_kernel select_sampled_kernel"), got
+
+
+@pytest.mark.parametrize("rows,blocks,kernel", [
+    (6, 2048, "select_small_kernel<true>"), (6, 2049, "short_select_blocks_kernel<1024, 1>"), (6, 8192, "short_select_blocks_kernel<1024, 2>"),
+    (6, 16384, "select_blocks_kernel<1024, 4>"), (513, 2049, "short_select_blocks_kernel<256, 4>"), (513, 8192, "select_blocks_kernel<256, 8>"),
+    (513, 16384, "select_blocks_kernel<256, 16>"),
+])
+def test_kernels_that_rank_block_sums(lib, rows, blocks, kernel):
+    """Rows of scores do not look at the page's size: their kernels are others."""
+    assert route(lib, rows, 1, 1, 8 * blocks, 2, 100, page=8, lens=True).endswith(" " + kernel)
+    if blocks <= 8192:
+        assert route(lib, rows, 1, 1, blocks, 2, 100, lens=True).startswith(("short_select_row_kernel", "select_row_kernel"))
