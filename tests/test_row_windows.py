@@ -112,6 +112,25 @@ def test_rows_of_block_sums(N, page, k):
     np.testing.assert_array_equal(idx.cpu().numpy(), o_idx)
 
 
+# blocks a row: 256 threads with four, eight and sixteen quads, 512 threads (more than 512 rows), and 1024 threads
+@pytest.mark.gpu
+@pytest.mark.parametrize("what", ["softmax", "zeros", "levels"])
+@pytest.mark.parametrize("rows,blocks,page,k", [(520, 2049, 8, 205), (513, 4096, 4, 4000), (600, 4097, 4, 400), (513, 8192, 2, 1), (520, 8193, 2, 819),
+                                                (513, 16384, 2, 1638), (70, 2050, 12, 300)])
+def test_many_rows_of_block_sums(rows, blocks, page, k, what):
+    live, N = 6, blocks * page - 1                    # the other rows are empty; the last block is cut
+    s = scores_of(what, live, 1, N, k * page, blocks + k)
+    sd = torch.zeros(rows, 1, 1, N, device=DEV)
+    sd[:live] = s.to(DEV)
+    lens = torch.zeros(rows, dtype=torch.int32)
+    lens[:live] = torch.tensor([N, N - page - 1, N // 2 + 1, 1024 * page - 1, 3 * page + 1, 1])
+    idx, cnt, _ = sts.sts_select(sd, [0, 0], k, seq_lens=lens.to(DEV), page_size=page)
+    assert (cnt[live:] == 0).all() and (idx[live:] == -1).all()
+    o_idx, o_cnt, _ = oracle.select_indices(s.numpy(), np.zeros(2, np.int32), k, seq_lens=lens[:live].numpy(), page=page)
+    np.testing.assert_array_equal(cnt[:live].cpu().numpy(), o_cnt)
+    np.testing.assert_array_equal(idx[:live].cpu().numpy(), o_idx)
+
+
 # both sides of the line between one workgroup per row and parts of a row: rows, scores per token, N, k, bf16 scores
 @pytest.mark.gpu
 @pytest.mark.parametrize("rows,Tq,N,k,bf16", [(8, 5, 8193, 819, False), (8, 10, 16384, 1, False), (8, 11, 16384, 1638, False), (9, 5, 16385, 16000, False),
