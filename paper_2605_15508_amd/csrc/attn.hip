@@ -957,9 +957,7 @@ template <int D, int NQ, bool FAR>
 hipError_t launch_split_dnp(const AttnArgs &a, bool sparse, hipStream_t s) {
   const unsigned z = a.B < STS_GRID_Z ? a.B : STS_GRID_Z;
   const dim3 grid((unsigned)(a.num_splits * a.z_rounds), a.num_units, z), block(64 * STS_WG_WAVES);
-  // Batch elements that share one cache (stride 0): 16 blocks of 16 rows over 64K, 6554 kept per row: 375 -> 214 us;
-  // 8 blocks over 32K, 3277 kept: 55 -> 25. Where each has its own, rows are used once and streamed.
-  const bool shared = !FAR && a.stride_b == 0 && a.B > 1 && a.B <= STS_GRID_Z;
+  const bool shared = !FAR && attn_shares_cache(a, D, one_buffer(D, NQ, true));
   if (sparse && shared) {
     if constexpr (!FAR) {
       const dim3 wide(64 * wg_waves(D, NQ, true));

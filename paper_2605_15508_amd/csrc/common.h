@@ -201,6 +201,23 @@ hipError_t launch_union_rows(const UnionArgs &a, hipStream_t s);
 sts_status sts_static_scratch(void **out);
 
 // launches (defined in the .hip files); each returns the status of its own launch call
+// Do the workgroups of a sparse call gather from one cache closely enough to be placed by die and to keep what they load in
+// the caches (attn.hip)? Batch elements that share one (stride 0), and either some rows asked for several times, or little
+// asked for in all. us there and streamed, each workgroup where it falls: 16 blocks of 16 rows, 6554 kept of 65536 214, 375; 16 of
+// five rows, 13107 of 131072 129, 185; 2 blocks, 9830 of 32768 26, 29. With rows
+// asked for 0.4 times on average and more than a cache holds: 2 blocks, 100000 of 1M 271, 249, 50000 of 500000 136, 129, but 26214 of
+// 262144 (0.4 times, 429 MB) 67.5, 68.5; 4 blocks, 20000 of 1M (0.16 times, 655 MB) 114, 106; at 0.6 times 187 to 191 either way, at 0.64 161, 181.
+// Where this means eight waves instead of four (two query tiles at head size 128), a workgroup needs more than eight tiles
+// to make up for the merging of twice the waves, and rows asked for 0.25 times: lists of 128 9.7, 7.6, of 600 in three
+// parts 14.3, 13.0; ten tiles of 32 keys are even, 19 17.9, 20.2; 16 blocks, 600 of 131072 18.2, 17.3, 1200 27.2, 28.7.
+inline bool attn_shares_cache(const AttnArgs &a, int d, bool eight_waves) {
+  if (a.stride_b != 0 || a.B <= 1 || a.B > STS_GRID_Z) return false;
+  const int64_t tokens = (int64_t)a.kmax << a.page_shift, tiles = (tokens + STS_TILE_KEYS - 1) / STS_TILE_KEYS;
+  const int64_t asked = (int64_t)a.B * a.num_units * tokens, rows = (int64_t)a.N * a.Hkv;
+  if (5 * asked <= 3 * rows && asked > (400ll << 20) / (4 * d)) return false;
+  return !eight_waves || ((tiles + a.num_splits - 1) / a.num_splits > 8 && 4 * asked >= rows);
+}
+
 hipError_t launch_attn_split(const AttnArgs &a, int d, int nq, bool sparse, hipStream_t s);
 hipError_t launch_attn_combine(const AttnArgs &a, int d, int nq, hipStream_t s);
 hipError_t launch_attn_probsum(const AttnArgs &a, int d, int nq, hipStream_t s);

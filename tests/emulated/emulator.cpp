@@ -267,7 +267,12 @@ extern "C" const char *emu_names() { return emu::g_names.c_str(); }
 extern "C" uint64_t emu_loaded() { return __atomic_exchange_n(&emu::g_loaded, 0, __ATOMIC_SEQ_CST); }
 
 sts_status sts_static_scratch(void **) { return STS_EUNSUPPORTED; }
-hipError_t launch_attn_split(const AttnArgs &, int, int, bool, hipStream_t) { return hipErrorInvalidValue; }
-hipError_t launch_attn_combine(const AttnArgs &, int, int, hipStream_t) { return hipErrorInvalidValue; }
+hipError_t launch_attn_split(const AttnArgs &a, int d, int nq, bool sparse, hipStream_t) {
+  const bool shared = sparse && attn_shares_cache(a, d, d == 128 && nq == 2);
+  return emu::noted(shared ? "attn_split shared" : "attn_split") ? hipSuccess : hipErrorInvalidValue;
+}
+hipError_t launch_attn_combine(const AttnArgs &, int, int, hipStream_t) {
+  return emu::noted("attn_combine") ? hipSuccess : hipErrorInvalidValue;
+}
 hipError_t launch_attn_probsum(const AttnArgs &, int, int, hipStream_t) { return hipErrorInvalidValue; }
 int attn_probsum_wgs_per_cu(int, int) { return 1; }

@@ -27,6 +27,7 @@ SHAPES = [
     (5, 8, 2, 128, 3000, 700, 2),         # one query tile; several tiles per wave, split
     (3, 4, 2, 128, 2000, 257, 2),         # ... and not split
     (16, 8, 2, 128, 3000, 1500, 2),       # two query tiles
+    (16, 8, 2, 128, 3000, 450, 2),        # ... which eight waves share
     (16, 8, 2, 128, 3000, 900, 4),        # four
     (8, 8, 2, 64, 3000, 900, 4),
 ]

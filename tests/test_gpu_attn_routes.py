@@ -60,6 +60,17 @@ def test_blocks_over_one_shared_cache(B, Tq, Hq, Hkv, d, N, kk, shared, row_bits
     check_attn(out, lse, ref, what="shared cache, row bits")
 
 
+# eight waves: two query tiles at head size 128, more than eight key tiles a workgroup
+@pytest.mark.parametrize("B,Tq,Hq,Hkv,N,kk,shared", [
+    (3, 16, 4, 2, 3000, 289, 2),          # ten key tiles, the last one a single key
+    (2, 16, 8, 2, 1500, 500, 2),          # sixteen
+    (32, 13, 8, 4, 2500, 1033, 2),        # lists in two parts; padding rows
+])
+@pytest.mark.parametrize("row_bits", [False, True])
+def test_blocks_over_one_shared_cache_by_eight_waves(B, Tq, Hq, Hkv, N, kk, shared, row_bits):
+    test_blocks_over_one_shared_cache(B, Tq, Hq, Hkv, 128, N, kk, shared, row_bits)
+
+
 @pytest.mark.parametrize("scale", [-0.11, 0.0, 0.3])
 @pytest.mark.parametrize("Tq,d", [(3, 128), (5, 64), (16, 128)])
 def test_scales_of_any_sign(scale, Tq, d):
