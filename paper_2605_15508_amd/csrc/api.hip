@@ -315,7 +315,7 @@ sts_status run_attn(const sts_attn_params *p, int sparse, hipStream_t s, void *w
 
 // --------------------------------------------------------------------------- select plan
 struct SelectPlan {
-  bool small;          // one workgroup per row, keys in LDS, a single launch
+  bool small;          // one workgroup per row, keys in registers, a single launch
   bool pool;           // shape allows chunk-local top-k + one ranking workgroup per row
   bool one_row;        // of those, the calls that one workgroup per row serves (the workspace is not touched)
   bool fused;          // long rows: the sampled selection, one launch (plus the clearing of the exchanged words)
@@ -747,8 +747,9 @@ static sts_status enqueue_select(const sts_select_params *p, void *stream) {
   }
   // Block granularity: aggregation and block sums in one pass when the shape allows (the
   // per-token aggregate is then stored only on request), and up to 16384 blocks per row are
-  // ranked by one workgroup per row out of LDS: two launches, nothing to clear (18 us for 8192
-  // blocks, 28 us for 16384, against about 30 us for the four kernels it replaces).
+  // ranked by one workgroup per row, out of LDS or in registers: two launches, nothing to clear (64 rows
+  // of 8192 blocks 24 us with the block sums, of 16384 26.3, 27.5 and 33 out of LDS; the four kernels that the ranking replaces
+  // take about 30 without them).
   SelectArgs f = a;
   f.agg = p->agg_out;
   const bool fused_blocks = pl.page > 1 && select_aggblock_ok(f);

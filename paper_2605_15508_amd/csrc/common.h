@@ -115,7 +115,8 @@ constexpr int SEL_BITS0 = 11, SEL_BITS1 = 11, SEL_BITS2 = 10;
 constexpr int SEL_BINS = 2048;          // bins of the widest digit
 constexpr int SEL_CHUNK = 8192;         // tokens per workgroup in the scan kernels
 constexpr int SEL_THREADS = 256;
-constexpr int SEL_SMALL_N = 32768;      // LDS capacity of the one-workgroup-per-row selection (tokens)
+constexpr int SEL_SMALL_N = 32768;      // scores of a row that the one-workgroup-per-row selection holds in registers at most
+constexpr int SEL_RANK_N = 2048;        // block sums of a row up to which they are ranked out of LDS
 constexpr int SEL_ROW16 = 16;
 constexpr int SEL_ROW16_N = 131072;     // tokens of one bf16 score each that a workgroup's registers hold
 constexpr int SEL_FLAG_PITCH = 32;      // words between the published counts of two chunks: one 128-byte line each

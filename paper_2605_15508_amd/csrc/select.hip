@@ -587,12 +587,13 @@ __device__ __forceinline__ void lds_compact(const uint32_t *keys, int m, uint32_
 
 // ------------------------------------------------- keys of a row in LDS, ranked by one workgroup
 // FROM_SRC: the scores to rank are already there (A.src, row pitch A.srcN: the block sums of
-// block-granular selection) and are loaded, up to SEL_SMALL_N of them (128 KB of the 160 KB of LDS), then
-// three digit histograms over the LDS-resident keys, ordered compaction and the copies to the target
-// heads in a single launch. Otherwise: rows of fewer than four tokens, which are aggregated here.
+// block-granular selection) and are loaded, up to SEL_RANK_N of them (17 KB of LDS with the histogram: two workgroups per CU;
+// with room for 32768 keys one: 1024 rows of 1024 blocks 48.1 -> 41.0 us, 2048 62.7 -> 47.6, 512 27.6 -> 24.3), then three digit
+// histograms over the LDS-resident keys, ordered compaction and the copies to the target heads in a single launch. Otherwise:
+// rows of fewer than four tokens, which are aggregated here.
 template <bool FROM_SRC>
 __global__ void __launch_bounds__(SMALL_THREADS) select_small_kernel(const SelectArgs A) {
-  __shared__ uint32_t keys[SEL_SMALL_N + SEL_SMALL_N / 32];
+  __shared__ uint32_t keys[SEL_RANK_N + SEL_RANK_N / 32];
   __shared__ uint32_t h[SEL_BINS];
   __shared__ uint32_t tmp[SMALL_THREADS / 64 + 2];
   const int row = blockIdx.x;
@@ -630,7 +631,7 @@ __global__ void __launch_bounds__(SMALL_THREADS) select_small_kernel(const Selec
 
   uint32_t T, r;
   lds_threshold<SMALL_THREADS>(keys, nb, h, tmp, c, T, r);
-  lds_compact<SMALL_THREADS, SEL_SMALL_N / SMALL_THREADS>(keys, nb, T, r, c, tmp, [&](uint32_t pos, int n) {
+  lds_compact<SMALL_THREADS, SEL_RANK_N / SMALL_THREADS>(keys, nb, T, r, c, tmp, [&](uint32_t pos, int n) {
     for (int ti = t0; ti < t1; ++ti) A.indices[((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + pos] = n;
   });
 }
@@ -1099,11 +1100,11 @@ hipError_t launch_select_small(const SelectArgs &a, hipStream_t s) {
   return sts_take_launch_status();
 }
 
-// ranks the rows of a.src (up to SEL_SMALL_N entries each) out of LDS
+// ranks the rows of a.src, up to SEL_SMALL_N entries each: out of LDS, or in registers from SEL_RANK_N entries on
 hipError_t launch_select_rank(const SelectArgs &a, hipStream_t s) {
   if ((size_t)a.B * a.Hd == 0) return hipSuccess;
   // 64 rows of 8192 or 16384 blocks: 39.3 -> 37.1, 46.5 -> 41.8 us with the block sums; 128 rows of 1024: 22.6, 23.8
-  if (a.srcN > 2048) {
+  if (a.srcN > SEL_RANK_N) {
     SelectArgs b = a;                                  // one fp32 score per block
     b.scores = a.src;
     b.scores_bf16 = 0;

@@ -55,3 +55,12 @@ def test_the_sampled_and_the_row_selection_fit_their_registers(resources):
         assert v["ScratchSize"] <= (8 if "ILi512ELi16E" in k else 0), demangle(k)
     for v in sampled.values():
         assert v["LDS Size"] <= 160 * 1024
+
+
+def test_the_ranking_of_block_sums_leaves_room_for_others(resources):
+    small = {k: v for k, v in resources.items() if "select_small_kernel" in k}
+    blocks = {k: v for k, v in resources.items() if "select_blocks_kernel" in k}
+    assert len(small) == 2 and len(blocks) == 8
+    for k, v in {**small, **blocks}.items():
+        assert v["LDS Size"] <= 40 * 1024, demangle(k)                                # several workgroups per CU
+        assert v["VGPRs"] <= 128 and v["ScratchSize"] <= (8 if "ILi512ELi16E" in k else 0), demangle(k)
