@@ -62,12 +62,16 @@ __device__ __forceinline__ void scan2(uint32_t a, uint32_t b, uint32_t *tot, int
 
 // Valid length of a row; of a row of block sums, which is ranked as a row of scores, from its length in tokens. (Kernels of
 // their own: the page's size, asked for after the length, is another latency in front of every row's first load. 16 rows of 4096
-// tokens with lengths: 8.3 us, 8.55 with one kernel for both.)
+// tokens with lengths: 8.3 us, 8.55 with one kernel for both. The longer rows' kernels are 1% faster with this form than with
+// row_len, 4096 rows of 16384 tokens; the short rows' 1% slower.)
 template <bool BLOCKS>
 __device__ __forceinline__ int ranked_len(const SelectArgs &A, int bt) {
-  if (!BLOCKS) return row_len(A, bt);
-  if (!A.seq_lens) return A.N;
-  return min((int)(((uint32_t)max(A.seq_lens[bt], 0) + (uint32_t)A.page - 1u) / (uint32_t)A.page), A.N);
+  int n = A.N;
+  if (A.seq_lens) {
+    n = max(A.seq_lens[bt], 0);
+    if (BLOCKS) n = (int)(((uint32_t)n + (uint32_t)A.page - 1u) / (uint32_t)A.page);
+  }
+  return min(n, A.N);
 }
 
 // The row's scores, aggregated, as signed numbers of their order (positive ones as they are, the others their magnitude's
@@ -254,7 +258,7 @@ __device__ __forceinline__ void rank_short_row(const SelectArgs &A) {
   __shared__ uint32_t ctr[4];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int bt = row / A.Hd, j = row % A.Hd;
-  const int nb = __builtin_amdgcn_readfirstlane(ranked_len<BLOCKS>(A, bt));
+  const int nb = __builtin_amdgcn_readfirstlane(BLOCKS ? ranked_len<true>(A, bt) : row_len(A, bt));
   const uint32_t c = (uint32_t)min(A.kh[j], nb);
   const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
   write_tail<T>(A, bt, j, c);
@@ -724,7 +728,8 @@ __global__ void __launch_bounds__(T, 4) select_blocks_kernel(const SelectArgs A)
 // 107 MB written, 12 vector instructions per token; the several-pass kernel that served it read them twice, 17 per token: 236.
 // Other calls beside the rule in the host code. Measured on the way: masks of lanes and ballots instead of a slot per lane for
 // the keys outside the window 229 us; 256 threads with 128 registers of keys, three rows per CU, 153-157, but 256 rows of
-// 65536 20.5 against 17.0; 131072 tokens in 512 threads 1053 us for 8192 rows, in 1024 threads 870.
+// 65536 20.5 against 17.0; 131072 tokens in 512 threads 1053 us for 8192 rows, in 1024 threads 889 (several
+// passes 949).
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 // Scores with their order as signed numbers: positive ones as they are, the others their magnitude's negative, so that -0 is
 // +0 and the lowest number stays free for "no token".
