@@ -464,8 +464,8 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
     // One bf16 score per token: rows of 4096 to 131072 of them are held packed in one workgroup's registers
     // (select_row16_kernel). us, with the paths that such calls would take otherwise: 16 rows of
     // 131072 43.5 -> 24.8, 64 of 65536 42.1 -> 15.5, 512 of 65536 85.3 -> 25.4, 4096 of 65536 239 -> 155, 4096 of 32768
-    // 268 -> 75, 512 of 4096 11.7 -> 8.8. Shorter rows keep select_row_kernel (512 rows of 2048: 11.8, 10.7;
-    // 4096: 28.6, 39.7). Rows of more than 65536 tokens take a CU's whole register file, whatever they fill of it: where there
+    // 268 -> 75, 512 of 4096 11.7 -> 8.8. Shorter rows keep short_select_row_kernel (512 rows of 2048 there
+    // 11.6, packed 10.3; 4096 rows 31.9, 38.6). Rows of more than 65536 tokens take a CU's whole register file, whatever they fill of it: where there
     // are many, the plain passes of select_rowpass_kernel, several rows per CU, are faster up to 112K tokens. 1024 rows, 10%:
     // of 65544 tokens 75, 88; of 98304 104, 112; of 114688 123, 120; of 131072 140, 129; 4096 rows of 65544 245, 329; of 106496
     // 380, 424; of 131072 501, 464. (Rows that are not a multiple of 8 long cannot take those: 1024 of 66001 157, in registers 92.)
@@ -937,7 +937,7 @@ const char *sts_strerror(int status) {   // an int on purpose: any value a calle
   return "unknown status";
 }
 
-int sts_version(void) { return 207; }
+int sts_version(void) { return 208; }
 
 void sts_set_knob(int which, double value) {
   if (which < 0 || which >= STS_KNOB_COUNT_) return;

@@ -468,7 +468,7 @@ attn_split_kernel(const AttnArgs A) {
       }
       // Most tiles of a long list raise no row's maximum and rescale nothing. (A maximum that may lag by a factor of 256
       // skips nearly all, but was no faster, and the largest weight is then no longer 1, which bf16 holds exactly: the
-      // outputs were 2% further from 64 bits.)
+      // outputs were 2.7% further from 64 bits.)
       if (__builtin_amdgcn_ballot_w64(grown)) {
 #pragma unroll
         for (int nq = q0; nq < q0 + NQH; ++nq) {
