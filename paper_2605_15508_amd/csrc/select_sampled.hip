@@ -298,7 +298,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   constexpr bool TWO_MAPS = 2 * MAP < CAP;
   static_assert(MAP <= CAP, "the bits of a heavy key share the list's memory");
   uint32_t *const store = reinterpret_cast<uint32_t *>(list);
-  uint32_t *const mapL = store + 2 * (CAP - MAP), *const mapU = TWO_MAPS ? mapL - 2 * MAP : mapL;
+  uint32_t *const mapL = store + 2 * (CAP - MAP);
   __shared__ uint32_t h[SEL_BINS];
   __shared__ uint32_t hb[SMP_HIST];                    // the earlier parts' share of an exchanged histogram; first the band
                                                        // tokens that the list has no room for, by bins
@@ -379,6 +379,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   else __syncthreads();
   const bool heavyL = band.heavyL, heavyU = band.heavyU && (TWO_MAPS || !heavyL);
   const uint32_t cap = (uint32_t)(CAP - (heavyL ? MAP : 0) - (heavyU ? MAP : 0));
+  uint32_t *const mapU = TWO_MAPS && heavyL ? mapL - 2 * MAP : mapL;   // (the bitmaps there are lie at the list's end)
 
   // ---- the pass
   // INT_MIN marks what is no token of the row: it stays below every edge

@@ -120,3 +120,23 @@ def test_equal_scores_above_all_that_the_sample_saw(N, k, path):
             np.testing.assert_array_equal(cnt.cpu().numpy(), o_cnt)
     finally:
         sts.set_knob("select_path", None)
+
+
+@pytest.mark.parametrize("N,n,step", [(131907, 34394, 4), (131072, 131072, 8), (400003, 390000, 8), (262144, 200001, 16)])
+def test_scores_of_a_few_levels(N, n, step):
+    """Rows of a few levels of very different weight, one part per row: one level or two at the edges of the band that much
+    of the row shares, others between them."""
+    B = 128
+    s = torch.zeros(B, 1, 1, N, device=DEV)
+    lens = torch.zeros(B, dtype=torch.int32)
+    live = [0, 5]
+    for b in live:
+        s[b, 0, 0, :n] = torch.round(torch.randn(n, generator=torch.Generator().manual_seed(7 + b)) * step / 2).to(DEV) / step
+        lens[b] = n
+    for share in (0.03, 0.2, 0.4, 0.6, 0.75, 0.835, 0.9, 0.97):
+        k = int(n * share)
+        idx, cnt, _ = sts.sts_select(s, [0], max(k, int(0.4 * N)), k_head=[k], seq_lens=lens.to(DEV))
+        for b in live:
+            assert cnt[b, 0] == k
+            want = torch.sort(s[b, 0, 0, :n] + 0.0, descending=True, stable=True).indices[:k].sort().values
+            assert torch.equal(idx[b, 0, :k].long(), want), (b, share)

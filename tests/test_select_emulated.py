@@ -366,3 +366,14 @@ def test_kernels_that_rank_block_sums(lib, rows, blocks, kernel):
     assert route(lib, rows, 1, 1, 8 * blocks, 2, 100, page=8, lens=True).endswith(" " + kernel)
     if blocks <= 8192:
         assert route(lib, rows, 1, 1, blocks, 2, 100, lens=True).startswith(("short_select_row_kernel", "select_row_kernel"))
+
+
+@pytest.mark.parametrize("budget", [28712, 28000, 30000, 26000])
+def test_one_heavy_value_at_the_bands_upper_edge(lib, budget):
+    """A value that much of the row shares at the upper edge of the band, none at the lower one, and many tokens in
+    between: the list does not run into the bits of the heavy value's tokens."""
+    N, n, rows = 131907, 34394, 130
+    s = torch.zeros(rows, 1, 1, N)
+    s[0, 0, 0, :n] = torch.round(torch.randn(n, generator=torch.Generator().manual_seed(7)) * 2) / 4
+    lib.emu_schedule(1, -1, -1)
+    check(lib, s, [0], 53920, k_head=[budget], lens=[n] + [0] * (rows - 1))
