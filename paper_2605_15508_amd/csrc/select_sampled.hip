@@ -693,6 +693,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
       pre_gt += wave_sum(gt);
       lo += bin << shift;
       last = bin == (uint32_t)SMP_HIST - 1u ? last - (bin << shift) : (1u << shift) - 1u;   // the last bin has no upper end
+      last = min(last, last_key - lo);                   // (a bin may run past the band, whose upper keys are kept already)
       // one key or few are left at the latest after round SMP_ROUNDS - 1
       if (fits && (last == 0u || in_bin <= (uint32_t)SMP_CAND)) break;
       shift = max(0, 32 - __clz((int)last) - 9);

@@ -140,3 +140,19 @@ def test_scores_of_a_few_levels(N, n, step):
             assert cnt[b, 0] == k
             want = torch.sort(s[b, 0, 0, :n] + 0.0, descending=True, stable=True).indices[:k].sort().values
             assert torch.equal(idx[b, 0, :k].long(), want), (b, share)
+
+
+@pytest.mark.parametrize("budget", [36294, 35931])
+def test_bins_that_run_past_the_band(budget):
+    """A band that begins at the lowest key, overflows the list and ends inside the threshold's bin."""
+    N, rows = 36294, 130
+    g = torch.Generator().manual_seed(35)
+    base = float(0.5 + torch.rand(1, generator=g) * 0.4)
+    row = base * torch.exp(torch.softmax(2 * torch.randn(N, generator=g), -1).to(torch.bfloat16).float())
+    s = torch.zeros(rows, 1, 1, N, device=DEV)
+    s[0, 0, 0] = row.to(DEV)
+    lens = torch.zeros(rows, dtype=torch.int32, device=DEV)
+    lens[0] = N
+    idx, cnt, _ = sts.sts_select(s, [0], N, k_head=[budget], seq_lens=lens)
+    want = torch.sort(row, descending=True, stable=True).indices[:budget].sort().values
+    assert cnt[0, 0] == budget and torch.equal(idx[0, 0, :budget].cpu().long(), want)

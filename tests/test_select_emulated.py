@@ -377,3 +377,16 @@ def test_one_heavy_value_at_the_bands_upper_edge(lib, budget):
     s[0, 0, 0, :n] = torch.round(torch.randn(n, generator=torch.Generator().manual_seed(7)) * 2) / 4
     lib.emu_schedule(1, -1, -1)
     check(lib, s, [0], 53920, k_head=[budget], lens=[n] + [0] * (rows - 1))
+
+
+@pytest.mark.parametrize("budget", [36294, 35931])
+def test_bins_that_run_past_the_band(lib, budget):
+    """A band that begins at the lowest key and overflows the list: the bin of the threshold reaches beyond its upper edge,
+    and the tokens above that, which are kept already, are not counted again when the part's tokens are."""
+    N, rows = 36294, 130
+    g = torch.Generator().manual_seed(35)
+    base = float(0.5 + torch.rand(1, generator=g) * 0.4)
+    s = torch.zeros(rows, 1, 1, N)
+    s[0, 0, 0] = base * torch.exp(torch.softmax(2 * torch.randn(N, generator=g), -1).to(torch.bfloat16).float())
+    lib.emu_schedule(1, -1, -1)
+    check(lib, s, [0], N, k_head=[budget], lens=[N] + [0] * (rows - 1))
