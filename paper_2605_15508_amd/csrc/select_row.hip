@@ -10,9 +10,9 @@
 //
 // What bounds it: for thousands of rows memory and vector instructions alike; several small workgroups per CU hide each
 // other's latencies. For few rows latency. Counting used to be a comparison per key and mask of lanes; where every key adds
-// to some slot, each lane to its own outside the window, 4096 rows of 16384 tokens take 98 us (131), 2048 of 30001 99 (136),
+// to some slot, each lane to its own outside the window, 4096 rows of 16384 tokens took 98 us (131), 2048 of 30001 99 (136),
 // 4096 of 20000 156 (234), 256 rows of 16384 with five scores per token 21.9 (24.2), and rows of zeros with the budget at
-// their edge 130 (625).
+// their edge 130 (625); with a row's loads in flight together 4096 rows of 16384 take 69, 2048 of 30001 73, 4096 of 20000 123.
 #include "select_util.h"
 
 namespace {
@@ -78,7 +78,7 @@ __device__ __forceinline__ int ranked_len(const SelectArgs &A, int bt) {
 // negative, so that -0 is +0): thread tid gets the quads tid, tid + T, ... A position past the row's valid length holds INT_MIN,
 // which no token does, and its scores are not read: past the last quad with a token that quad is asked for again, which costs
 // no memory (rows of a tensor that is allocated for the longest sequence). out: the aggregate, stored on request.
-template <int T, int IT>
+template <int T, int IT, bool ONE>
 __device__ __forceinline__ void load_row(const AggRow &R, float *out, int nb, int tid, int (&v)[IT][4]) {
   int any = 0;
   const int last = max(min(R.N - 4, (nb - 1) & ~3), 0);
@@ -96,7 +96,7 @@ __device__ __forceinline__ void load_row(const AggRow &R, float *out, int nb, in
       any |= v[i][e];
     }
   };
-  if constexpr (T == 1024 && IT <= 4) {
+  if constexpr (T == 1024 && IT <= 4 && !ONE) {
     // Few quads: their score rows are in flight together, by code for each number of rows (256 rows of 16384
     // tokens 16.9 us, 18.7 with branches between the rows).
 #pragma clang loop unroll(full)
@@ -107,10 +107,11 @@ __device__ __forceinline__ void load_row(const AggRow &R, float *out, int nb, in
       const f32x4 y = agg_quad(R, at);
       take(i, inside ? y : shifted_quad(y, n - at));
     }
-  } else if constexpr (T == 1024) {
+  } else if constexpr (!ONE) {
     // Four quads at a time, a score row of them in flight while the one before is added (a quad at a time with all its score
-    // rows: the same for five and nine, but 16 rows of 32768 tokens with one score per token 18.0 us, now 14.1; eight quads at
-    // a time spill). Larger rows in this way: 16 of 33001, five scores, 28.7 us, sampled 27.3.
+    // rows: the same for five and nine; eight quads at a time spill). Larger rows in this way: 16 of 33001, five scores, 28.7 us,
+    // sampled 27.3. All quads of a score row in a loop, each waited for by itself: 1024 rows of 30000 with five scores
+    // 139 us, now 122; of 24000 with two 67, 50; of 8192 with five 38.5, 34.3.
     auto blocks = [&](auto bf16) {
       typedef ScoreLoad<f32x4, decltype(bf16)::value> SL;
       constexpr int QB = 4;
@@ -122,9 +123,10 @@ __device__ __forceinline__ void load_row(const AggRow &R, float *out, int nb, in
           typename SL::raw x[QB], y[QB];
           auto load = [&](typename SL::raw (&r)[QB], int q) {
             const unsigned char *at = static_cast<const unsigned char *>(R.P) + q * pitch;
+            const int own = IT > 8 ? again(tid) : tid;
 #pragma unroll
             for (int i = 0; i < QB; ++i) {
-              uint32_t off = (uint32_t)min(4 * ((b + i) * T + tid), last) * (decltype(bf16)::value ? 2u : 4u);
+              const uint32_t off = (uint32_t)min(4 * ((b + i) * T + own), last) * (decltype(bf16)::value ? 2u : 4u);
               r[i] = SL::load_at(at + off);
             }
           };
@@ -172,44 +174,25 @@ __device__ __forceinline__ void load_row(const AggRow &R, float *out, int nb, in
     if (R.bf16) blocks(std::true_type{});
     else blocks(std::false_type{});
   } else {
-    // many quads: one score row at a time, all quads of it in flight together (same order of additions per token)
-    f32x4 acc[IT];
+    // One probability per token: all quads in flight together. (A load next to its use in a loop over the quads is waited for
+    // at once, one memory latency after the other, which is how rows of many quads were loaded: 4096 rows of 16384 tokens 95 us, now 69;
+    // 4096 of 20000 159, 123; 2048 of 30001 98, 73; 4096 of 8192 51, 41.)
     auto rows = [&](auto bf16) {
       typedef ScoreLoad<f32x4, decltype(bf16)::value> SL;
-#pragma unroll 1
-      for (int q = 0; q < R.Tq; ++q) {
-        const float l = R.logits ? R.L[q] : 0.f;
+      typename SL::raw x[IT];
 #pragma clang loop unroll(full)
-        for (int i = 0; i < IT; ++i) {
-          f32x4 p = SL::widen(SL::load(R, q, min(4 * (i * T + tid), last)));
-          if (R.logits) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) p[e] = prob_of(p[e], l);
-          }
-          if (q == 0) {
-            acc[i] = p;
-          } else if (R.use_max) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[i][e] = fmaxf(acc[i][e], p[e]);
-          } else {
-            acc[i] = acc[i] + p;
-          }
-        }
+      for (int i = 0; i < IT; ++i)
+        x[i] = SL::load_at(static_cast<const unsigned char *>(R.P) + (uint32_t)min(4 * (i * T + tid), last) * (decltype(bf16)::value ? 2u : 4u));
+      fence_schedule();
+#pragma clang loop unroll(full)
+      for (int i = 0; i < IT; ++i) {
+        const int n = 4 * (i * T + tid);
+        const f32x4 y = SL::widen(x[i]);
+        take(i, 4 * (i + 1) * T <= R.N ? y : shifted_quad(y, n - min(n, R.N - 4)));      // the row's end: read where it still fits
       }
     };
     if (R.bf16) rows(std::true_type{});
     else rows(std::false_type{});
-#pragma clang loop unroll(full)
-    for (int i = 0; i < IT; ++i) {
-      if (4 * (i + 1) * T > R.N) {                     // the row's end: the quad was read where it still fits
-        const int n = 4 * (i * T + tid), d = n - min(n, R.N - 4);
-        const f32x4 y = acc[i];
-        acc[i][0] = d == 0 ? y[0] : d == 1 ? y[1] : d == 2 ? y[2] : y[3];
-        acc[i][1] = d == 0 ? y[1] : d == 1 ? y[2] : y[3];
-        acc[i][2] = d == 0 ? y[2] : y[3];
-      }
-      take(i, acc[i]);
-    }
   }
   if (ballot64(any < 0)) {                             // negative scores in this wave
 #pragma clang loop unroll(full)
@@ -246,7 +229,7 @@ __device__ __forceinline__ void row_min_max(uint32_t &lo, uint32_t &hi, uint32_t
 }
 
 // T threads, IT quads per thread: rows of up to 4 * T * IT tokens. All keys are counted, in bins that divide their range.
-template <int T, int IT, bool BLOCKS>
+template <int T, int IT, bool BLOCKS, bool ONE>
 __device__ __forceinline__ void rank_short_row(const SelectArgs &A) {
   constexpr int TOK = 4 * T * IT;
   constexpr int STAGE = TOK / 8 > 1024 ? TOK / 8 : 1024;           // list entries staged per round
@@ -270,7 +253,7 @@ __device__ __forceinline__ void rank_short_row(const SelectArgs &A) {
   if (tid < 4) ctr[tid] = 0u;
 
   int v[IT][4];
-  load_row<T, IT>(R, out, nb, tid, v);
+  load_row<T, IT, ONE>(R, out, nb, tid, v);
   if (!ranked) return;
 
   auto each = [&](auto f) {
@@ -404,15 +387,15 @@ __device__ __forceinline__ void rank_short_row(const SelectArgs &A) {
   }
 }
 
+template <int T, int IT, bool ONE>
+__global__ void __launch_bounds__(T) short_select_row_kernel(const SelectArgs A) { rank_short_row<T, IT, false, ONE>(A); }
 template <int T, int IT>
-__global__ void __launch_bounds__(T) short_select_row_kernel(const SelectArgs A) { rank_short_row<T, IT, false>(A); }
-template <int T, int IT>
-__global__ void __launch_bounds__(T) short_select_blocks_kernel(const SelectArgs A) { rank_short_row<T, IT, true>(A); }
+__global__ void __launch_bounds__(T) short_select_blocks_kernel(const SelectArgs A) { rank_short_row<T, IT, true, true>(A); }
 
 // ----------------------------------------------------------- longer rows: a window of keys from a sample
 // T threads, IT quads per thread: rows of up to 4 * T * IT tokens. (Up to eight keys per thread of 1024, or 16 of 256, are ranked
 // faster without a sample: 16 rows of 4096 tokens 8.3 against 9.5 us, 1024 of 4096 10.4, 10.8.)
-template <int T, int IT, bool BLOCKS>
+template <int T, int IT, bool BLOCKS, bool ONE>
 __device__ __forceinline__ void rank_row(const SelectArgs &A) {
   constexpr int TOK = 4 * T * IT;
   constexpr int STAGE = TOK / 8 > 1024 ? TOK / 8 : 1024;           // list entries staged per round
@@ -436,7 +419,7 @@ __device__ __forceinline__ void rank_row(const SelectArgs &A) {
   for (int i = tid; i < SLOTS; i += T) h[i] = 0u;
 
   int v[IT][4];
-  load_row<T, IT>(R, out, nb, tid, v);
+  load_row<T, IT, ONE>(R, out, nb, tid, v);
   if (!ranked) return;
   uint32_t k[IT][4];                                   // unsigned keys, 0 where there is no token
 #pragma clang loop unroll(full)
@@ -711,10 +694,10 @@ __device__ __forceinline__ void rank_row(const SelectArgs &A) {
   }
 }
 
+template <int T, int IT, bool ONE>
+__global__ void __launch_bounds__(T, 4) select_row_kernel(const SelectArgs A) { rank_row<T, IT, false, ONE>(A); }
 template <int T, int IT>
-__global__ void __launch_bounds__(T, 4) select_row_kernel(const SelectArgs A) { rank_row<T, IT, false>(A); }
-template <int T, int IT>
-__global__ void __launch_bounds__(T, 4) select_blocks_kernel(const SelectArgs A) { rank_row<T, IT, true>(A); }
+__global__ void __launch_bounds__(T, 4) select_blocks_kernel(const SelectArgs A) { rank_row<T, IT, true, true>(A); }
 
 // ------------------------------------------------- rows of one bf16 score per token, packed in registers
 // Calls with a mask per query row (prefill) rank thousands of rows of bf16 scores. 64K of them are 128 KB, 64 registers of
@@ -1060,7 +1043,8 @@ static hipError_t launch_select_row16(const SelectArgs &a, hipStream_t s) {
 
 // Rows of 4 to 32768 tokens. Calls of up to 512 rows get 1024 threads per row (latency: 256 rows of 16384 tokens 25 us
 // with 256 threads per row), others as few as hold the row in 64 registers per thread (several workgroups per CU: 4096
-// such rows 128 us; one workgroup per CU took 290).
+// such rows 128 us; one workgroup per CU took 290), in 32 where the scores of up to 16384 tokens are added up (1024 rows of 16384
+// with five scores 64.2 us, 68.6).
 // (Rows of block sums where a page holds several tokens: kernels that turn lengths in tokens into blocks, see ranked_len.)
 hipError_t launch_select_row(const SelectArgs &a, hipStream_t s) {
   const int64_t rows = (int64_t)a.B * a.Hd;
@@ -1069,25 +1053,35 @@ hipError_t launch_select_row(const SelectArgs &a, hipStream_t s) {
   const int N = a.N;
   if (N < 4 || N > SEL_SMALL_N) return hipErrorInvalidValue;
   const dim3 grid((unsigned)rows);
-#define STS_ROW(kind, T, IT) \
+  // one probability per token: nothing is added up, and all of a thread's quads are in flight together
+  const bool one = a.Tq == 1 && a.kind == STS_SCORES_PROBS;
+#define STS_SHORT(T, IT) \
   do { \
-    if (a.page > 1) STS_LAUNCH((kind##_blocks_kernel<T, IT>), grid, dim3(T), 0, s, a); \
-    else STS_LAUNCH((kind##_row_kernel<T, IT>), grid, dim3(T), 0, s, a); \
+    if (a.page > 1) STS_LAUNCH((short_select_blocks_kernel<T, IT>), grid, dim3(T), 0, s, a); \
+    else if (one) STS_LAUNCH((short_select_row_kernel<T, IT, true>), grid, dim3(T), 0, s, a); \
+    else STS_LAUNCH((short_select_row_kernel<T, IT, false>), grid, dim3(T), 0, s, a); \
+  } while (0)
+#define STS_ROW(T, IT, T5, IT5) \
+  do { \
+    if (a.page > 1) STS_LAUNCH((select_blocks_kernel<T, IT>), grid, dim3(T), 0, s, a); \
+    else if (one) STS_LAUNCH((select_row_kernel<T, IT, true>), grid, dim3(T), 0, s, a); \
+    else STS_LAUNCH((select_row_kernel<T5, IT5, false>), grid, dim3(T5), 0, s, a); \
   } while (0)
   if (rows <= 512) {
-    if (N <= 4096) STS_ROW(short_select, 1024, 1);
-    else if (N <= 8192) STS_ROW(short_select, 1024, 2);
-    else if (N <= 16384) STS_ROW(select, 1024, 4);
-    else STS_ROW(select, 1024, 8);
+    if (N <= 4096) STS_SHORT(1024, 1);
+    else if (N <= 8192) STS_SHORT(1024, 2);
+    else if (N <= 16384) STS_ROW(1024, 4, 1024, 4);
+    else STS_ROW(1024, 8, 1024, 8);
   } else if (N <= 4096) {
-    STS_ROW(short_select, 256, 4);
+    STS_SHORT(256, 4);
   } else if (N <= 8192) {
-    STS_ROW(select, 256, 8);
+    STS_ROW(256, 8, 256, 8);
   } else if (N <= 16384) {
-    STS_ROW(select, 256, 16);
+    STS_ROW(256, 16, 512, 8);
   } else {
-    STS_ROW(select, 512, 16);
+    STS_ROW(512, 16, 512, 16);
   }
+#undef STS_SHORT
 #undef STS_ROW
   return sts_take_launch_status();
 }

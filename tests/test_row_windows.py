@@ -153,3 +153,48 @@ def test_few_rows(rows, Tq, N, k, bf16):
     np.testing.assert_array_equal(cnt[:live].cpu().numpy(), o_cnt)
     np.testing.assert_array_equal(idx[:live].cpu().numpy(), o_idx)
     np.testing.assert_array_equal(agg[0].cpu().numpy(), o_agg[0])
+
+
+# many rows with several scores per token (or one scaled logit): 256 threads with four and eight quads, 512 with eight and sixteen
+@pytest.mark.gpu
+@pytest.mark.parametrize("how", ["sum", "max", "bf16", "logits"])
+@pytest.mark.parametrize("Tq,N,k", [(3, 4095, 400), (1, 4100, 410), (2, 8189, 8000), (9, 8193, 800), (4, 16384, 1638), (1, 16387, 300), (5, 32767, 3276)])
+def test_many_rows_of_several_scores(Tq, N, k, how):
+    rows, live = 513, 5                               # the other rows are empty
+    s = scores_of("softmax", live, Tq, N, k, N + k)
+    s[1] = scores_of("signed", 1, Tq, N, k, N + k)[0]
+    lse = None
+    kw = {}
+    if how == "bf16":
+        s = s.to(torch.bfloat16)
+    if how == "max":
+        kw["reduce"] = sts.STS_REDUCE_MAX
+    if how == "logits":
+        s = torch.log(s.abs().clamp_min(1e-30))
+        lse = torch.zeros(rows, 1, Tq, device=DEV) + torch.arange(Tq, device=DEV) / 16
+        kw.update(kind=sts.STS_SCORES_LOGITS_LSE, lse=lse)
+    sd = torch.zeros(rows, 1, Tq, N, device=DEV, dtype=s.dtype)
+    sd[:live] = s.to(DEV)
+    lens = torch.zeros(rows, dtype=torch.int32)
+    lens[:live] = torch.tensor([N, N - 1, N // 2, 1023, 6])
+    idx, cnt, agg = sts.sts_select(sd, [0, 0], k, seq_lens=lens.to(DEV), want_agg=True, **kw)
+    idx2, _, _ = sts.sts_select(sd, [0, 0], k, seq_lens=lens.to(DEV), **kw)
+    assert torch.equal(idx, idx2) and (idx[live:] == -1).all()
+    a = agg[:live].cpu()
+    if how == "logits":
+        want = torch.exp(s - lse[:live].cpu()[..., None]).sum(dim=2)
+    else:
+        want = s[:, :, 0].float()
+        for i in range(1, Tq):
+            want = torch.maximum(want, s[:, :, i].float()) if how == "max" else want + s[:, :, i].float()
+    for b in range(live):
+        n = int(lens[b])
+        if how == "logits":
+            # the device's exponential is good to 1e-5 relative (see prob_of)
+            torch.testing.assert_close(a[b, 0, :n], want[b, 0, :n], rtol=1e-5, atol=0.0)
+        else:
+            assert torch.equal(a[b, 0, :n], want[b, 0, :n])
+        assert (a[b, 0, n:] == 0).all()
+    o_idx, o_cnt, _ = oracle.select_indices(a[:, :, None].numpy(), np.zeros(2, np.int32), k, seq_lens=lens[:live].numpy())
+    np.testing.assert_array_equal(cnt[:live].cpu().numpy(), o_cnt)
+    np.testing.assert_array_equal(idx[:live].cpu().numpy(), o_idx)
