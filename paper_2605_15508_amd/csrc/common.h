@@ -146,9 +146,9 @@ inline int64_t smp_expected_band(int64_t nb, int64_t c, int part_tokens) {
 }
 
 struct SelectTargets {
-  // targets of draft head j: tgt[off[j] .. off[j+1])
-  uint16_t off[STS_MAX_HEADS + 1];
-  uint8_t tgt[STS_MAX_HEADS];
+  // targets of draft head j: tgt[off[j] .. off[j+1]); the kernels read both by words (target_off, target_head)
+  alignas(4) uint16_t off[STS_MAX_HEADS + 1];
+  alignas(4) uint8_t tgt[STS_MAX_HEADS];
 };
 
 struct SelectArgs {

@@ -52,7 +52,7 @@ template <bool VEC4>
 __global__ void __launch_bounds__(SEL_THREADS) select_agg_kernel(const SelectArgs A) {
   __shared__ uint32_t h[SEL_BINS];
   const int row = blockIdx.y, chunk = blockIdx.x;
-  const int bt = row / A.Hd;
+  const int bt = __builtin_amdgcn_readfirstlane(row / A.Hd);
   const int nb = row_len(A, bt);
   for (int i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS) h[i] = 0u;
   __syncthreads();
@@ -108,7 +108,7 @@ __global__ void __launch_bounds__(SEL_THREADS) select_agg_kernel(const SelectArg
 __global__ void __launch_bounds__(SEL_THREADS) select_block_kernel(const SelectArgs A) {
   __shared__ uint32_t h[SEL_BINS];
   const int row = blockIdx.y;
-  const int bt = row / A.Hd;
+  const int bt = __builtin_amdgcn_readfirstlane(row / A.Hd);
   const int nb = row_len(A, bt);
   const int nblk = (nb + A.page - 1) / A.page;
   for (int i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS) h[i] = 0u;
@@ -135,7 +135,7 @@ __global__ void __launch_bounds__(SEL_THREADS) select_block_kernel(const SelectA
 __global__ void __launch_bounds__(SEL_THREADS) select_block_vec_kernel(const SelectArgs A) {
   __shared__ uint32_t h[SEL_BINS];
   const int row = blockIdx.y;
-  const int bt = row / A.Hd;
+  const int bt = __builtin_amdgcn_readfirstlane(row / A.Hd);
   const int nb = row_len(A, bt);
   const int nblk = (nb + A.page - 1) / A.page;
   for (int i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS) h[i] = 0u;
@@ -188,7 +188,7 @@ __global__ void __launch_bounds__(SEL_THREADS) select_block_vec_kernel(const Sel
 __global__ void __launch_bounds__(SEL_THREADS) select_aggblock_kernel(const SelectArgs A) {
   __shared__ uint32_t h[SEL_BINS];
   const int row = blockIdx.y;
-  const int bt = row / A.Hd;
+  const int bt = __builtin_amdgcn_readfirstlane(row / A.Hd);
   const int nb = row_len(A, bt);
   const int nblk = (nb + A.page - 1) / A.page;
   const bool want_hist = A.hist != nullptr;
@@ -252,9 +252,9 @@ __global__ void __launch_bounds__(SEL_THREADS) select_hist_kernel(const SelectAr
   __shared__ uint32_t tmp[16];
   const int row = blockIdx.y;
   const int chunk0 = blockIdx.x * A.hist_cpw;      // this workgroup takes hist_cpw consecutive chunks
-  const int bt = row / A.Hd;
+  const int bt = __builtin_amdgcn_readfirstlane(row / A.Hd);
   const int nb = src_len(A, bt);
-  const uint32_t c = (uint32_t)min(A.kh[row % A.Hd], nb);
+  const uint32_t c = (uint32_t)min(A.kh[__builtin_amdgcn_readfirstlane(row % A.Hd)], nb);
   if (c == 0) return;
   uint32_t *st = A.state + (size_t)row * 8;
   const uint32_t *gh = A.hist + (size_t)row * 3 * SEL_BINS;
@@ -337,14 +337,15 @@ __global__ void __launch_bounds__(SEL_THREADS, 4) select_write_kernel(const Sele
   __shared__ uint32_t tmp[16];
   __shared__ uint32_t buf[SEL_THREADS * PITCH];  // keys first, then the staged token ids
   const int row = blockIdx.y, chunk = blockIdx.x;
-  const int bt = row / A.Hd, j = row % A.Hd;
+  int bt, j;
+  row_of(A, row, bt, j);
   const int nb = src_len(A, bt);
   const uint32_t c = (uint32_t)min(A.kh[j], nb);
-  const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
+  const int t0 = target_off(A, j), t1 = target_off(A, j + 1);
   if (chunk == 0) {
     // tail padding and counts for every target head of this draft head
     for (int ti = t0; ti < t1; ++ti) {
-      const int tgt = A.targets.tgt[ti];
+      const int tgt = target_head(A, ti);
       int32_t *dst = A.indices + ((size_t)bt * A.Hq + tgt) * A.k;
       for (uint32_t p = c + threadIdx.x; p < (uint32_t)A.k; p += SEL_THREADS) dst[p] = -1;
       if (A.counts && threadIdx.x == 0) A.counts[(size_t)bt * A.Hq + tgt] = (int32_t)c;
@@ -500,7 +501,7 @@ __global__ void __launch_bounds__(SEL_THREADS, 4) select_write_kernel(const Sele
   if (last > first) {
     const uint32_t cnt = min(last - first, (uint32_t)SEL_CHUNK);
     for (int ti = t0; ti < t1; ++ti) {
-      int32_t *dst = A.indices + ((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + first;
+      int32_t *dst = A.indices + ((size_t)bt * A.Hq + target_head(A, ti)) * A.k + first;
       for (uint32_t p = threadIdx.x; p < cnt; p += SEL_THREADS) dst[p] = staged[p];
     }
   }
@@ -597,10 +598,11 @@ __global__ void __launch_bounds__(SMALL_THREADS) select_small_kernel(const Selec
   __shared__ uint32_t h[SEL_BINS];
   __shared__ uint32_t tmp[SMALL_THREADS / 64 + 2];
   const int row = blockIdx.x;
-  const int bt = row / A.Hd, j = row % A.Hd;
+  int bt, j;
+  row_of(A, row, bt, j);
   const int nb = FROM_SRC ? src_len(A, bt) : row_len(A, bt);
   const uint32_t c = (uint32_t)min(A.kh[j], nb);
-  const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
+  const int t0 = target_off(A, j), t1 = target_off(A, j + 1);
   const int tid = threadIdx.x;
   write_tail<SMALL_THREADS>(A, bt, j, c);
   const bool want_agg = !FROM_SRC && A.agg != nullptr;
@@ -632,7 +634,7 @@ __global__ void __launch_bounds__(SMALL_THREADS) select_small_kernel(const Selec
   uint32_t T, r;
   lds_threshold<SMALL_THREADS>(keys, nb, h, tmp, c, T, r);
   lds_compact<SMALL_THREADS, SEL_RANK_N / SMALL_THREADS>(keys, nb, T, r, c, tmp, [&](uint32_t pos, int n) {
-    for (int ti = t0; ti < t1; ++ti) A.indices[((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + pos] = n;
+    for (int ti = t0; ti < t1; ++ti) A.indices[((size_t)bt * A.Hq + target_head(A, ti)) * A.k + pos] = n;
   });
 }
 
@@ -666,10 +668,11 @@ __global__ void __launch_bounds__(THREADS) select_rowpass_kernel(const SelectArg
   __shared__ uint32_t h[SEL_BINS];
   __shared__ uint32_t tmp[THREADS / 64 + 2];
   const int row = blockIdx.x, tid = threadIdx.x;
-  const int bt = row / A.Hd, j = row % A.Hd;
+  int bt, j;
+  row_of(A, row, bt, j);
   const int nb = row_len(A, bt);
   const uint32_t c = (uint32_t)min(A.kh[j], nb);
-  const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
+  const int t0 = target_off(A, j), t1 = target_off(A, j + 1);
   write_tail<THREADS>(A, bt, j, c);
   if (c == 0 || t0 == t1) return;
   // N % VPT == 0 and a 16-byte aligned base (the host's condition for this path): whole words
@@ -860,7 +863,7 @@ __global__ void __launch_bounds__(THREADS) select_rowpass_kernel(const SelectArg
       __syncthreads();
       const uint32_t cnt = min(last - base, (uint32_t)STAGE);
       for (int ti = t0; ti < t1; ++ti) {
-        int32_t *dst = A.indices + ((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + base;
+        int32_t *dst = A.indices + ((size_t)bt * A.Hq + target_head(A, ti)) * A.k + base;
         for (uint32_t p = tid; p < cnt; p += THREADS) dst[p] = staged[p];
       }
       __syncthreads();
@@ -892,13 +895,14 @@ __global__ void __launch_bounds__(THREADS) select_local_kernel(const SelectArgs 
   __shared__ uint32_t h[SEL_BINS];
   __shared__ uint32_t tmp[THREADS / 64 + 2];
   const int row = blockIdx.y, chunk = blockIdx.x;
-  const int bt = row / A.Hd, j = row % A.Hd;
+  int bt, j;
+  row_of(A, row, bt, j);
   const int nb = row_len(A, bt);
   const int n0 = chunk * CHUNK;
   const int nvalid = max(0, min(n0 + CHUNK, nb) - n0);     // ranked tokens of this chunk
   uint32_t c = (uint32_t)min(A.kh[j], nvalid);
   const bool want_agg = A.agg != nullptr;
-  if (A.targets.off[j] == A.targets.off[j + 1]) c = 0;        // no target head reads this draft head
+  if (target_off(A, j) == target_off(A, j + 1)) c = 0;        // no target head reads this draft head
   if (c == 0 && !want_agg) return;
   for (int i = threadIdx.x; i < SEL_BINS; i += THREADS) h[i] = 0u;
   __syncthreads();
@@ -1005,10 +1009,11 @@ __global__ void __launch_bounds__(SMALL_THREADS) select_pool_kernel(const Select
   __shared__ uint32_t red[2 * SMALL_THREADS / 64];
   __shared__ uint32_t tmp[SMALL_THREADS / 64 + 2];
   const int row = blockIdx.x;
-  const int bt = row / A.Hd, j = row % A.Hd;
+  int bt, j;
+  row_of(A, row, bt, j);
   const int nb = row_len(A, bt);
   const uint32_t c = (uint32_t)min(A.kh[j], nb);
-  const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
+  const int t0 = target_off(A, j), t1 = target_off(A, j + 1);
   const int tid = threadIdx.x;
   write_tail<SMALL_THREADS>(A, bt, j, c);
   if (c == 0 || t0 == t1) return;
@@ -1078,7 +1083,7 @@ __global__ void __launch_bounds__(SMALL_THREADS) select_pool_kernel(const Select
   }
   lds_compact<SMALL_THREADS, POOL_MAX / SMALL_THREADS>(keys, (int)m, T, r, c, tmp, [&](uint32_t pos, int n) {
     const int32_t tok = toks[small_slot(n)];
-    for (int ti = t0; ti < t1; ++ti) A.indices[((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + pos] = tok;
+    for (int ti = t0; ti < t1; ++ti) A.indices[((size_t)bt * A.Hq + target_head(A, ti)) * A.k + pos] = tok;
   });
 }
 

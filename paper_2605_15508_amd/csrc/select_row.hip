@@ -211,11 +211,7 @@ __device__ __forceinline__ void load_row(const AggRow &R, float *out, int nb, in
 // ----------------------------------------------------------- rows of at most eight quads per four waves
 template <int T>
 __device__ __forceinline__ void row_min_max(uint32_t &lo, uint32_t &hi, uint32_t *red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    lo = min(lo, (uint32_t)__shfl_xor((int)lo, off, 64));
-    hi = max(hi, (uint32_t)__shfl_xor((int)hi, off, 64));
-  }
+  wave_min_max(lo, hi);
   if ((threadIdx.x & 63) == 0) {
     red[2 * (threadIdx.x >> 6)] = lo;
     red[2 * (threadIdx.x >> 6) + 1] = hi;
@@ -239,11 +235,10 @@ __device__ __forceinline__ void rank_short_row(const SelectArgs &A) {
   __shared__ uint32_t tmp[T / 64 + 2];
   __shared__ uint32_t red[2 * T / 64];
   __shared__ uint32_t ctr[4];
-  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-  const int bt = row / A.Hd, j = row % A.Hd;
+  const int j = blockIdx.x, bt = blockIdx.y, row = bt * A.Hd + j, tid = threadIdx.x, lane = tid & 63;
   const int nb = __builtin_amdgcn_readfirstlane(BLOCKS ? ranked_len<true>(A, bt) : row_len(A, bt));
   const uint32_t c = (uint32_t)min(A.kh[j], nb);
-  const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
+  const int t0 = target_off(A, j), t1 = target_off(A, j + 1);
   write_tail<T>(A, bt, j, c);
   float *out = A.agg ? A.agg + (size_t)row * A.N : nullptr;
   const bool ranked = c > 0 && t0 != t1;
@@ -380,7 +375,7 @@ __device__ __forceinline__ void rank_short_row(const SelectArgs &A) {
     __syncthreads();
     const uint32_t cnt = min(total - base, (uint32_t)STAGE);
     for (int ti = t0; ti < t1; ++ti) {
-      int32_t *dst = A.indices + ((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + base;
+      int32_t *dst = A.indices + ((size_t)bt * A.Hq + target_head(A, ti)) * A.k + base;
       for (uint32_t i = tid; i < cnt; i += T) dst[i] = staged[i];
     }
     __syncthreads();
@@ -406,11 +401,11 @@ __device__ __forceinline__ void rank_row(const SelectArgs &A) {
   __shared__ uint32_t cand_key[ROW_CAND], cand_tok[ROW_CAND];      // (not as pairs: the keys would be held in pairs of registers)
   __shared__ uint32_t tot[2 * T / 64];
   __shared__ uint32_t res[8];
-  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int bt = row / A.Hd, j = row % A.Hd;
+  const int j = blockIdx.x, bt = blockIdx.y, row = bt * A.Hd + j;      // (no division in front of the first load)
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nb = __builtin_amdgcn_readfirstlane(ranked_len<BLOCKS>(A, bt));
   const uint32_t c = (uint32_t)min(A.kh[j], nb);
-  const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
+  const int t0 = target_off(A, j), t1 = target_off(A, j + 1);
   write_tail<T>(A, bt, j, c);
   float *out = A.agg ? A.agg + (size_t)row * A.N : nullptr;
   const bool ranked = c > 0 && t0 != t1;
@@ -467,7 +462,7 @@ __device__ __forceinline__ void rank_row(const SelectArgs &A) {
       uint32_t above = bins_above(0u, SEL_BINS, loc, ns, unused);
       if (sh == 21) {
         // 5 standard deviations of the sample's count; a window that misses the threshold is found out by the counts
-        const uint32_t cs = max(1u, min(ns, (uint32_t)((uint64_t)c * ns / (uint32_t)nb)));
+        const uint32_t cs = expected_rank(c, ns, nb);
         const uint32_t margin = (uint32_t)(5.f * sqrtf((float)cs)) + 4u;
         deep = cs + margin;
         top = cs > margin ? cs - margin : 0u;
@@ -687,7 +682,7 @@ __device__ __forceinline__ void rank_row(const SelectArgs &A) {
     __syncthreads();
     const uint32_t cnt = min(c - base, (uint32_t)STAGE);
     for (int ti = t0; ti < t1; ++ti) {
-      int32_t *dst = A.indices + ((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + base;
+      int32_t *dst = A.indices + ((size_t)bt * A.Hq + target_head(A, ti)) * A.k + base;
       for (uint32_t i = tid; i < cnt; i += T) dst[i] = (int32_t)staged[i];
     }
     __syncthreads();
@@ -732,7 +727,8 @@ __device__ __forceinline__ void rank_row16(const SelectArgs &A, int row, int nb,
   constexpr int CODES = 8 * T * IT / 16;                           // words of two bits per token
   constexpr int STAGE = ROW16_STAGE, SLOTS = ROW16_SLOTS;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int bt = row / A.Hd, j = row % A.Hd, t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
+  const int j = blockIdx.x, bt = blockIdx.y;
+  const int t0 = target_off(A, j), t1 = target_off(A, j + 1);
   const uint16_t *src = static_cast<const uint16_t *>(A.scores) + (size_t)row * A.N;
 
   // ---- the row: thread tid holds the words tid, tid + T, ... as unsigned keys, 0 where there is no token
@@ -811,7 +807,7 @@ __device__ __forceinline__ void rank_row16(const SelectArgs &A, int row, int nb,
     uint32_t loc[PER], ns, unused;
     uint32_t above = bins_above(0u, SEL_BINS, loc, ns, unused);
     // 5 standard deviations of the sample's count; a window that misses the threshold is found out by the counts
-    const uint32_t cs = max(1u, min(ns, (uint32_t)((uint64_t)c * ns / (uint32_t)nb)));
+    const uint32_t cs = expected_rank(c, ns, nb);
     const uint32_t margin = (uint32_t)(5.f * sqrtf((float)cs)) + 4u;
     const uint32_t deep = cs + margin, top = cs > margin ? cs - margin : 0u;
     if (tid == 0) {
@@ -983,7 +979,7 @@ __device__ __forceinline__ void rank_row16(const SelectArgs &A, int row, int nb,
     __syncthreads();
     const uint32_t cnt = min(c - base, (uint32_t)STAGE);
     for (int ti = t0; ti < t1; ++ti) {
-      int32_t *dst = A.indices + ((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + base;
+      int32_t *dst = A.indices + ((size_t)bt * A.Hq + target_head(A, ti)) * A.k + base;
       const uint32_t quads = cnt / 4;
       for (uint32_t i = tid; i < quads; i += T) {
         typedef stage_t stage4 __attribute__((ext_vector_type(4)));
@@ -1008,15 +1004,14 @@ __global__ void __launch_bounds__(T, 4) select_row16_kernel(const SelectArgs A) 
   __shared__ __attribute__((aligned(16))) stage_t staged[ROW16_STAGE];
   __shared__ uint32_t tot[2 * T / 64];
   __shared__ uint32_t res[8];
-  const int row = blockIdx.x;
-  const int bt = row / A.Hd, j = row % A.Hd;
+  const int j = blockIdx.x, bt = blockIdx.y, row = bt * A.Hd + j;
   const int nb = __builtin_amdgcn_readfirstlane(row_len(A, bt));
   const uint32_t c = (uint32_t)min(A.kh[j], nb);
   write_tail<T>(A, bt, j, c);
-  if (c == 0 || A.targets.off[j] == A.targets.off[j + 1]) return;
+  if (c == 0 || target_off(A, j) == target_off(A, j + 1)) return;
   if (c == (uint32_t)nb) {                                         // every token is kept
-    for (int ti = A.targets.off[j]; ti < A.targets.off[j + 1]; ++ti)
-      for (int i = threadIdx.x; i < nb; i += T) A.indices[((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + i] = i;
+    for (int ti = target_off(A, j); ti < target_off(A, j + 1); ++ti)
+      for (int i = threadIdx.x; i < nb; i += T) A.indices[((size_t)bt * A.Hq + target_head(A, ti)) * A.k + i] = i;
     return;
   }
   if constexpr (IT >= 16) {
@@ -1032,7 +1027,7 @@ static hipError_t launch_select_row16(const SelectArgs &a, hipStream_t s) {
   const int64_t rows = (int64_t)a.B * a.Hd;
   if (rows == 0) return hipSuccess;
   if (a.N < 8 || a.N > SEL_ROW16_N) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)rows);
+  const dim3 grid((unsigned)a.Hd, (unsigned)a.B);
   if (a.N <= 8192) STS_LAUNCH((select_row16_kernel<256, 4>), grid, dim3(256), 0, s, a);
   else if (a.N <= 16384) STS_LAUNCH((select_row16_kernel<256, 8>), grid, dim3(256), 0, s, a);
   else if (a.N <= 32768) STS_LAUNCH((select_row16_kernel<256, 16>), grid, dim3(256), 0, s, a);
@@ -1052,7 +1047,7 @@ hipError_t launch_select_row(const SelectArgs &a, hipStream_t s) {
   if (a.rowpass_threads == SEL_ROW16) return launch_select_row16(a, s);
   const int N = a.N;
   if (N < 4 || N > SEL_SMALL_N) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)rows);
+  const dim3 grid((unsigned)a.Hd, (unsigned)a.B);
   // one probability per token: nothing is added up, and all of a thread's quads are in flight together
   const bool one = a.Tq == 1 && a.kind == STS_SCORES_PROBS;
 #define STS_SHORT(T, IT) \

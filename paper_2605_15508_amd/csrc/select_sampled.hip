@@ -70,7 +70,7 @@ constexpr unsigned long long SMP_VALID = 1ull << 63;
 // part overflowed its list (256 rows of 128K tokens 277 us, with 8192 83). Smaller budgets have room enough and save the
 // larger sample's 2 to 4 us.
 struct SamplePlan {
-  int S, runs;
+  int S, runs;                                         // S: a power of two
   __device__ __forceinline__ int start(int i, int run) const {       // first token of sampled run i
     return (i * S + (int)((((uint32_t)i * 0x9e3779b1u) >> 16) & (uint32_t)(S - 1))) * run;
   }
@@ -78,9 +78,10 @@ struct SamplePlan {
 __device__ __forceinline__ SamplePlan sample_plan(int nb, int run, int target) {
   SamplePlan p;
   const int row_runs = (nb + run - 1) / run;
-  p.S = 1;
-  while (((row_runs + p.S - 1) / p.S) * run > target) p.S <<= 1;
-  p.runs = row_runs / p.S;                             // (at least one: S is at most half the runs here)
+  int sh = 0;
+  while (((row_runs + (1 << sh) - 1) >> sh) * run > target) ++sh;
+  p.S = 1 << sh;
+  p.runs = row_runs >> sh;                             // (at least one: S is at most half the runs here)
   return p;
 }
 
@@ -126,11 +127,7 @@ __device__ __forceinline__ Band sample_band(const SamplePlan &sp, int run, int n
           mn = min(mn, key[x][e]);
           mx = max(mx, key[x][e]);
         }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      mn = min(mn, (uint32_t)__shfl_xor((int)mn, off, 64));
-      mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
-    }
+    wave_min_max(mn, mx);
     if (lane == 0) {
       red[2 * wave] = mn;
       red[2 * wave + 1] = mx;
@@ -219,7 +216,7 @@ __device__ __forceinline__ Band sample_band(const SamplePlan &sp, int run, int n
     const uint32_t in_window = count(again, base, range, shift, over);
     if (ns == 0u) {                                    // the first window is the whole sample
       ns = in_window;
-      cs = max(1u, min(ns, (uint32_t)((uint64_t)c * ns / (uint32_t)nb)));    // expected rank of the threshold
+      cs = expected_rank(c, ns, nb);
     }
     margin = 0;                                        // (S == 1: the sample is the row)
     if (sp.S > 1) {
@@ -235,7 +232,11 @@ __device__ __forceinline__ Band sample_band(const SamplePlan &sp, int run, int n
         uint32_t n = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) n += (ok[x][e] && key[x][e] >= centre) ? 1u : 0u;
-        for (int off = 1; off < rq; off <<= 1) n += (uint32_t)__shfl_xor((int)n, off, 64);
+        // a run's quads are 8 or 16 lanes, whose sum its first lane gets
+        n += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)n, 0x101, 0xf, 0xf, true);      // row_shl:1
+        n += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)n, 0x102, 0xf, 0xf, true);      // row_shl:2
+        n += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)n, 0x104, 0xf, 0xf, true);      // row_shl:4
+        if (rq == 16) n += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)n, 0x108, 0xf, 0xf, true);
         const int d = (int)n - __shfl_down((int)n, rq, 64);
         sq += (lane & (rq - 1)) == 0 && lane + rq < 64 && tid + x * T + rq < nsq ? (uint32_t)(d * d) : 0u;
       }
@@ -308,12 +309,11 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   __shared__ uint32_t ticket;                          // next group of the pass
   __shared__ uint32_t ctr[12];                         // 0 list entries, 1 certain tokens, 9, 10 tokens of the heavy keys, 2.. see below
   __shared__ u32x2 cand[SMP_CAND];                     // key; 0 (own) or 1 << 31 | part
-  const int row = blockIdx.y, part = blockIdx.x;
+  const int part = blockIdx.x, j = blockIdx.y, bt = blockIdx.z, row = bt * A.Hd + j;     // (no division in front of the first load)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int bt = row / A.Hd, j = row % A.Hd;
   const int nb = __builtin_amdgcn_readfirstlane(row_len(A, bt));       // (a loaded value: said to be uniform, like others below)
   const uint32_t c = (uint32_t)min(A.kh[j], nb);
-  const int t0 = A.targets.off[j], t1 = A.targets.off[j + 1];
+  const int t0 = target_off(A, j), t1 = target_off(A, j + 1);
   if (part == 0) write_tail<T>(A, bt, j, c);
   float *out = A.agg ? A.agg + (size_t)row * A.N : nullptr;
   const bool ranked = c > 0 && t0 != t1;
@@ -828,7 +828,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
       __syncthreads();
       const uint32_t cnt = min(total - base, 2u * CAP);
       for (int ti = t0; ti < t1; ++ti) {
-        int32_t *dst = A.indices + ((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + pre + base;
+        int32_t *dst = A.indices + ((size_t)bt * A.Hq + target_head(A, ti)) * A.k + pre + base;
         for (uint32_t i = tid; i < cnt; i += T) dst[i] = staged[i];
       }
       __syncthreads();
@@ -854,7 +854,7 @@ static void clear_words(const SelectArgs &a, hipStream_t s) {
 static bool launch_sampled(const SelectArgs &a, hipStream_t s) {
   if (a.N < 4 || a.smp_tokens % SMP_GROUP != 0 || (int64_t)a.smp_tokens * a.smp_parts < a.N || a.smp_tokens > SMP_MAX_TOKENS)
     return false;
-  const dim3 grid(a.smp_parts, a.B * a.Hd), block(SMP_THREADS);
+  const dim3 grid(a.smp_parts, a.Hd, a.B), block(SMP_THREADS);
   auto form = [&](auto f) {
     constexpr int F = decltype(f)::value;
     if (a.scores_bf16) STS_LAUNCH((select_sampled_kernel<true, SMP_TOKENS[F], SMP_LIST[F]>), grid, block, 0, s, a);

@@ -26,6 +26,29 @@ __device__ __forceinline__ int row_len(const SelectArgs &A, int bt) {
   return min(max(nb, 0), A.N);
 }
 
+// What a workgroup needs of the tables in the kernel's arguments is read by scalar loads: the row's batch element and draft head
+// are told to be uniform (a division's result is not seen to be), and the 16- and 8-bit entries are taken out of words (there are
+// no narrower scalar loads). As vector loads they were two or three memory latencies in a row before a row's first score, and one
+// before its list: 16 rows of 16384 tokens, one score each, 12.5 -> 11.4 us, 256 rows 14.1 -> 12.8.
+__device__ __forceinline__ void row_of(const SelectArgs &A, int row, int &bt, int &j) {
+  bt = __builtin_amdgcn_readfirstlane(row / A.Hd);
+  j = __builtin_amdgcn_readfirstlane(row % A.Hd);
+}
+typedef uint32_t table_word __attribute__((may_alias));
+__device__ __forceinline__ int target_off(const SelectArgs &A, int j) {
+  return (int)(reinterpret_cast<const table_word *>(A.targets.off)[j >> 1] >> (16 * (j & 1)) & 0xffffu);
+}
+__device__ __forceinline__ int target_head(const SelectArgs &A, int ti) {
+  return (int)(reinterpret_cast<const table_word *>(A.targets.tgt)[ti >> 2] >> (8 * (ti & 3)) & 0xffu);
+}
+
+// c of nb tokens kept, out of ns sampled ones: where the threshold is expected among them (an estimate: fp32 does, a 64-bit
+// division is two hundred instructions in front of everything else; with it, the divisions by the sampling step and the permutes of
+// minima and sums gone 16 rows of 33001 tokens, five scores each, take 25.8 us instead of 27.4, 64 rows of 131072 48.0 instead of 50.4)
+__device__ __forceinline__ uint32_t expected_rank(uint32_t c, uint32_t ns, int nb) {
+  return max(1u, min(ns, (uint32_t)((float)c * ((float)ns / (float)nb))));
+}
+
 // number of ranked units (tokens, or blocks of `page` tokens) in the row of batch bt
 __device__ __forceinline__ int src_len(const SelectArgs &A, int bt) {
   return (row_len(A, bt) + A.page - 1) / A.page;
@@ -57,6 +80,23 @@ __device__ __forceinline__ int ordered_of_key(uint32_t k) { return (int)(k ^ 0x8
 __device__ __forceinline__ uint64_t ballot64(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 __device__ __forceinline__ uint32_t lanes_before(uint64_t mask, uint32_t base) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, base));
+}
+// lowest and highest over the wave, the same way as the sums (a lane without a source keeps its own value): seven register moves in a
+// row instead of six LDS permutes
+__device__ __forceinline__ void wave_min_max(uint32_t &lo, uint32_t &hi) {
+  auto step = [&](auto ctrl, auto rows) {
+    lo = min(lo, (uint32_t)__builtin_amdgcn_update_dpp((int)lo, (int)lo, decltype(ctrl)::value, decltype(rows)::value, 0xf, false));
+    hi = max(hi, (uint32_t)__builtin_amdgcn_update_dpp((int)hi, (int)hi, decltype(ctrl)::value, decltype(rows)::value, 0xf, false));
+  };
+  std::integral_constant<int, 0xf> all;
+  step(std::integral_constant<int, 0x111>{}, all);
+  step(std::integral_constant<int, 0x112>{}, all);
+  step(std::integral_constant<int, 0x114>{}, all);
+  step(std::integral_constant<int, 0x118>{}, all);
+  step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});
+  step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});
+  lo = (uint32_t)__builtin_amdgcn_readlane((int)lo, 63);
+  hi = (uint32_t)__builtin_amdgcn_readlane((int)hi, 63);
 }
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), 63); }
 
@@ -317,8 +357,8 @@ __device__ __forceinline__ float agg_one(const AggRow &R, int n) { return agg_at
 // tail padding (-1 from position c on) and counts for every target head of draft head j
 template <int THREADS>
 __device__ __forceinline__ void write_tail(const SelectArgs &A, int bt, int j, uint32_t c) {
-  for (int ti = A.targets.off[j]; ti < A.targets.off[j + 1]; ++ti) {
-    const int tgt = A.targets.tgt[ti];
+  for (int ti = target_off(A, j); ti < target_off(A, j + 1); ++ti) {
+    const int tgt = target_head(A, ti);
     int32_t *dst = A.indices + ((size_t)bt * A.Hq + tgt) * A.k;
     for (uint32_t p = c + threadIdx.x; p < (uint32_t)A.k; p += THREADS) dst[p] = -1;
     if (A.counts && threadIdx.x == 0) A.counts[(size_t)bt * A.Hq + tgt] = (int32_t)c;
@@ -335,8 +375,7 @@ __device__ __forceinline__ int fused_bin(uint32_t key, int level, uint32_t d0, u
 // sum over the block of one value per thread; red needs THREADS / 64 words
 template <int THREADS>
 __device__ __forceinline__ uint32_t block_sum1(uint32_t a, uint32_t *red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) a += (uint32_t)__shfl_xor((int)a, off, 64);
+  a = wave_sum(a);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
   __syncthreads();
   uint32_t s = 0;
@@ -402,7 +441,7 @@ __device__ __forceinline__ void rank_by_passes(const SelectArgs &A, const AggRow
         const uint32_t p = g + min(q, r);
         const int n = 4 * qlo + i;
         if (p < c && n >= from && n < to)
-          for (int ti = t0; ti < t1; ++ti) A.indices[((size_t)bt * A.Hq + A.targets.tgt[ti]) * A.k + p] = n;
+          for (int ti = t0; ti < t1; ++ti) A.indices[((size_t)bt * A.Hq + target_head(A, ti)) * A.k + p] = n;
       }
       g += is_gt ? 1u : 0u;
       q += is_gt ? 0u : 1u;
