@@ -65,14 +65,18 @@ __device__ __forceinline__ int nth_member(uint32_t mask, int n) {
   return pos;
 }
 
+// The larger of two numbers, one instruction: the median with +infinity (fmaxf first turns signalling NaNs into quiet ones, an
+// instruction per operand that the compiler cannot vouch for).
+__device__ __forceinline__ float larger(float x, float y) { return __builtin_amdgcn_fmed3f(x, y, INFINITY); }
+
 // maximum over the four lanes 16 apart (the row-of-16 swaps of this chip: no LDS round trip)
 __device__ __forceinline__ float max_over_groups(float x) {
   const uint32_t w = __builtin_bit_cast(uint32_t, x);
   const auto p = __builtin_amdgcn_permlane16_swap(w, w, false, false);       // rows 0, 0, 2, 2 and 1, 1, 3, 3
-  const float y = fmaxf(__builtin_bit_cast(float, (uint32_t)p[0]), __builtin_bit_cast(float, (uint32_t)p[1]));
+  const float y = larger(__builtin_bit_cast(float, (uint32_t)p[0]), __builtin_bit_cast(float, (uint32_t)p[1]));
   const uint32_t v = __builtin_bit_cast(uint32_t, y);
   const auto q = __builtin_amdgcn_permlane32_swap(v, v, false, false);       // the lower and the upper half
-  return fmaxf(__builtin_bit_cast(float, (uint32_t)q[0]), __builtin_bit_cast(float, (uint32_t)q[1]));
+  return larger(__builtin_bit_cast(float, (uint32_t)q[0]), __builtin_bit_cast(float, (uint32_t)q[1]));
 }
 
 // waves per workgroup, and whether a tile's K and V are loaded into one set of registers instead of two
@@ -106,6 +110,8 @@ attn_split_kernel(const AttnArgs A) {
   constexpr int MERGE_BYTES = W * 16 * OPITCH * 4;
   constexpr int LDS_MAIN = (W * KTILE_BYTES > MERGE_BYTES) ? W * KTILE_BYTES : MERGE_BYTES;
   __shared__ __attribute__((aligned(16))) unsigned char lds[LDS_MAIN];
+  // (ONE: every second K tile. An array of its own: reads of the one are not taken for reads of what is on its way to the other.)
+  __shared__ __attribute__((aligned(16))) unsigned char lds_odd[ONE ? W * KTILE_BYTES : 16];
   __shared__ float lds_ml[W][NQ * 16][2];
   // With two or more query tiles the Q operands (NQ*KK registers quads per lane) no longer fit
   // beside the accumulators and the load buffers: they live in LDS, already in MFMA B layout
@@ -175,10 +181,13 @@ attn_split_kernel(const AttnArgs A) {
   // bits of the same entry (ROWMASK only)
   auto fetch_rows = [&](int t) -> int {
     const int e = min(t * STS_TILE_KEYS + (lane & 31), last) >> psh;
+    if (ONE) return *reinterpret_cast<const int32_t *>(reinterpret_cast<const unsigned char *>(idx_row) + 4u * (uint32_t)e);   // (32 bits: a register less)
     return SPARSE ? idx_row[e] : e;
   };
   auto fetch_bits = [&](int t) -> int {
-    return ROWMASK ? (int)mask_row[min(t * STS_TILE_KEYS + (lane & 31), last) >> psh] : 0;
+    const int e = min(t * STS_TILE_KEYS + (lane & 31), last) >> psh;
+    if (ROWMASK && ONE) return *reinterpret_cast<const uint16_t *>(reinterpret_cast<const unsigned char *>(mask_row) + 2u * (uint32_t)e);
+    return ROWMASK ? (int)mask_row[e] : 0;
   };
   // The first three tiles' entries, the length and Q are asked for together; the length by a vector load, as scalar loads
   // return in any order and a wait for one is a wait for all.
@@ -281,7 +290,7 @@ attn_split_kernel(const AttnArgs A) {
   auto offsets = [&](int t, Offsets &o) {
     if (GATHER) {
 #pragma unroll
-      for (int m = 0; m < 8; ++m) o.o[m] = lds_off[GATHER ? wave : 0][slot_of(m)] + (row_off)(b * CHB);
+      for (int m = 0; m < 8; ++m) o.o[m] = lds_off[GATHER ? wave : 0][slot_of(m)] + (ONE ? (row_off)0 : (row_off)(b * CHB));
     }
   };
   // Rows are streamed past the caches where every one is used once per launch.
@@ -290,7 +299,7 @@ attn_split_kernel(const AttnArgs A) {
     for (int m = 0; m < 8; ++m) {
       const chunk_t *src;
       if (GATHER) {
-        row_off off = o.o[m];
+        row_off off = o.o[m] + (ONE ? (row_off)(b * CHB) : (row_off)0);
         asm("" : "+v"(off));      // (seen here as 32 bits, the offset is an operand of the load)
         src = reinterpret_cast<const chunk_t *>(base + off);
       } else {
@@ -300,6 +309,20 @@ attn_split_kernel(const AttnArgs A) {
       }
       if (CACHED) r[m] = *src;
       else r[m] = __builtin_nontemporal_load(src);
+    }
+  };
+  // ONE: K goes from memory to LDS without a register in between. Instruction m writes the 1 KB behind its address lane by lane, so
+  // LDS row 4 m + a holds slot slot_of(m), and which of the row's 16-byte chunks lies where is up to the chunk that a lane asks for.
+  auto load_k_lds = [&](const Offsets &o, int buf) {
+    typedef __attribute__((address_space(3))) unsigned char *lds_ptr;
+    // (buffer loads: the flat-encoded form of the same makes the compiler wait for all loads where one is waited for)
+    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(kuni), 0, 0xffffffff, 0x00027000);
+    int mine = 16 * (a ^ b);
+    asm("" : "+v"(mine));                              // (the four offsets that come of it are made anew, not kept)
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      uint32_t off = (uint32_t)(mine ^ (64 * (m & 3))) + (uint32_t)o.o[m];       // chunk b ^ (row & 15) of LDS row 4 m + a
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (lds_ptr)(buf ? lds_odd : lds) + wave * KTILE_BYTES + m * 1024, 16, (int)off, 0, 0, 0);
     }
   };
   float m_run[NQ], l_run[NQ];
@@ -367,6 +390,8 @@ attn_split_kernel(const AttnArgs A) {
     f32x4 St[NQ][2];
 #pragma unroll
     for (int nq = 0; nq < NQ; ++nq) St[nq][0] = St[nq][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int k_row = 4 * (b & 3) + (b >> 2), k_at = k_row * ROWB + (a ^ k_row) * 16;        // ONE: where slot b's row lies, and its chunk a
+    if constexpr (ONE) asm("" : "+v"(k_at));           // (as above)
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
       bf16x8 Ka[2];
@@ -374,7 +399,7 @@ attn_split_kernel(const AttnArgs A) {
       for (int ks = 0; ks < 2; ++ks) {
         const int row = 16 * ks + b;
         const int sl = (a + 4 * kk) ^ (row & (NSLOT - 1));
-        Ka[ks] = *reinterpret_cast<const bf16x8 *>(ldsK + row * ROWB + sl * 16);
+        Ka[ks] = *reinterpret_cast<const bf16x8 *>(ONE ? (second ? lds_odd : lds) + wave * KTILE_BYTES + (k_at ^ (64 * kk)) + 16 * ks * ROWB : ldsK + row * ROWB + sl * 16);
       }
 #pragma unroll
       for (int nq = 0; nq < NQ; ++nq) {
@@ -448,7 +473,6 @@ attn_split_kernel(const AttnArgs A) {
     for (int q0 = 0; q0 < NQ; q0 += NQH) {
       bf16x8 Pb[NQH];
       float mt[NQH];
-      bool grown = false;
 #pragma unroll
       for (int nq = q0; nq < q0 + NQH; ++nq) {
         float s[8];
@@ -462,17 +486,16 @@ attn_split_kernel(const AttnArgs A) {
             St[nq][i >> 2][i & 3] = s[i];
           }
         }
-        mt[nq - q0] = sl2 * max_over_groups(fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])),
-                                                  fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7]))));
-        grown |= mt[nq - q0] > m_run[nq];
+        mt[nq - q0] = sl2 * max_over_groups(larger(larger(larger(s[0], s[1]), larger(s[2], s[3])),
+                                                   larger(larger(s[4], s[5]), larger(s[6], s[7]))));
       }
       // Most tiles of a long list raise no row's maximum and rescale nothing. (A maximum that may lag by a factor of 256
       // skips nearly all, but was no faster, and the largest weight is then no longer 1, which bf16 holds exactly: the
       // outputs were 2.7% further from 64 bits.)
-      if (__builtin_amdgcn_ballot_w64(grown)) {
 #pragma unroll
-        for (int nq = q0; nq < q0 + NQH; ++nq) {
-          const float m_new = fmaxf(m_run[nq], mt[nq - q0]);   // finite: every consumed tile has a valid key ...
+      for (int nq = q0; nq < q0 + NQH; ++nq) {
+        if (__builtin_amdgcn_ballot_w64(mt[nq - q0] > m_run[nq])) {
+          const float m_new = larger(m_run[nq], mt[nq - q0]);  // finite: every consumed tile has a valid key ...
           // ... except with row bits: a row may keep none of a tile's keys, nor of any tile so far
           const float alpha = (ROWMASK && m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(m_run[nq] - m_new);
           l_run[nq] *= alpha;
@@ -551,12 +574,13 @@ attn_split_kernel(const AttnArgs A) {
     offsets(tile_of(0), o);
     pin();
     if constexpr (ONE) {
-      // One set of registers: K of the next tile is asked for when this one's has gone to LDS, V when this one's has been
-      // used; the second wave of the SIMD works meanwhile.
-      chunk_t K[8], V[8];
-      load_rows(kuni, tile_of(0), o, K);
+      // K of two tiles in LDS and V of two in registers: the next tile's rows are asked for before this one is worked on.
+      constexpr int BEHIND = 24 + (ROWMASK ? 2 : 1);   // loads that go out after a tile's K and before it is used: its V, list entries, the next tile's K and V
+      constexpr int K_HERE = (BEHIND & 15) | (BEHIND >> 4) << 14 | 0x0f70;     // (as the wait instruction has it: that many may be under way)
+      chunk_t V0[8], V1[8];
+      load_k_lds(o, 0);
       pin();
-      load_rows(vuni, tile_of(0), o, V);
+      load_rows(vuni, tile_of(0), o, V0);
       pin();
       take_q();
       int x = resolve(raw_b, tile_of(1), m1);
@@ -564,25 +588,29 @@ attn_split_kernel(const AttnArgs A) {
       raw_a = within(raw_c, tile_of(2));
       bits_a = bits_c;
       pin();
-      for (; v < nv; ++v) {
+      auto step = [&](int raw, int bits, int &raw_next, int &bits_next, const chunk_t (&V)[8], chunk_t (&Vn)[8], int v, bool odd) {
         offsets(tile_of(v + 1), o);
-        raw_b = fetch_rows(tile_of(v + 3));
-        bits_b = fetch_bits(tile_of(v + 3));
-        x = resolve(raw_a, tile_of(v + 2), m_new);
-        place(x, bits_a, m_new, v + 2);
-        store_k(K);
+        raw_next = fetch_rows(tile_of(v + 3));
+        bits_next = fetch_bits(tile_of(v + 3));
+        const int y = resolve(raw, tile_of(v + 2), m_new);
+        place(y, bits, m_new, v + 2);
         pin();
-        load_rows(kuni, tile_of(v + 1), o, K);
+        load_k_lds(o, odd ? 0 : 1);
         pin();
-        consume(tile_of(v), v, V, m0, false);
+        load_rows(vuni, tile_of(v + 1), o, Vn);
         pin();
-        load_rows(vuni, tile_of(v + 1), o, V);
+        __builtin_amdgcn_s_waitcnt(K_HERE);
+        consume(tile_of(v), v, V, m0, odd);
         pin();
         m0 = m1;
         m1 = m_new;
-        raw_a = raw_b;
-        bits_a = bits_b;
+      };
+      for (; v + 2 <= nv; v += 2) {
+        step(raw_a, bits_a, raw_b, bits_b, V0, V1, v, false);
+        step(raw_b, bits_b, raw_a, bits_a, V1, V0, v + 1, true);
       }
+      __builtin_amdgcn_s_waitcnt(0x0f70);              // all K that was asked for has come: the merge takes its place
+      if (v < nv) consume(tile_of(v), v, V0, m0, false);
     } else {
       chunk_t K0[8], V0[8], K1[8], V1[8];
       // prologue: tile v in flight, tile v+1 resolved, tile v+2 fetched

@@ -212,7 +212,7 @@ sts_status sts_static_scratch(void **out);
 // to make up for the merging of twice the waves, and rows asked for 0.25 times: lists of 128 9.7, 7.6, of 600 in three
 // parts 14.3, 13.0; ten tiles of 32 keys are even, 19 17.9, 20.2; 16 blocks, 600 of 131072 18.2, 17.3, 1200 27.2, 28.7.
 inline bool attn_shares_cache(const AttnArgs &a, int d, bool eight_waves) {
-  if (a.stride_b != 0 || a.B <= 1 || a.B > STS_GRID_Z) return false;
+  if (a.stride_b != 0 || a.B <= 1 || a.B > STS_GRID_Z || a.kmax >= 1 << 30) return false;       // (32-bit offsets into a list)
   const int64_t tokens = (int64_t)a.kmax << a.page_shift, tiles = (tokens + STS_TILE_KEYS - 1) / STS_TILE_KEYS;
   const int64_t asked = (int64_t)a.B * a.num_units * tokens, rows = (int64_t)a.N * a.Hkv;
   if (5 * asked <= 3 * rows && asked > (400ll << 20) / (4 * d)) return false;
