@@ -709,6 +709,7 @@ __global__ void __launch_bounds__(T, 4) select_blocks_kernel(const SelectArgs A)
 // 65536 20.5 against 17.0; 131072 tokens in 512 threads 1053 us for 8192 rows, in 1024 threads 889 (several
 // passes 949).
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+typedef short i16x2 __attribute__((ext_vector_type(2)));
 // Scores with their order as signed numbers: positive ones as they are, the others their magnitude's negative, so that -0 is
 // +0 and the lowest number stays free for "no token".
 __device__ __forceinline__ uint32_t signed16(uint32_t w) {
@@ -731,8 +732,9 @@ __device__ __forceinline__ void rank_row16(const SelectArgs &A, int row, int nb,
   const int t0 = target_off(A, j), t1 = target_off(A, j + 1);
   const uint16_t *src = static_cast<const uint16_t *>(A.scores) + (size_t)row * A.N;
 
-  // ---- the row: thread tid holds the words tid, tid + T, ... as unsigned keys, 0 where there is no token
-  u16x2 k[IT][4];
+  // ---- the row: thread tid holds the words tid, tid + T, ... as signed numbers of the scores' order, the lowest where there is no
+  // token (a score that is not negative is its own bit pattern). The key is that number's distance from the lowest.
+  i16x2 k[IT][4];
   {
     u32x4 raw[IT];
     // (past the last word with a token that word is asked for again, which costs no memory)
@@ -771,7 +773,10 @@ __device__ __forceinline__ void rank_row16(const SelectArgs &A, int row, int nb,
 #pragma clang loop unroll(full)
     for (int i = 0; i < IT; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) k[i][e] = __builtin_bit_cast(u16x2, raw[i][e] ^ 0x80008000u);
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t w = raw[i][e];                              // (a vector's element itself is not what would be converted)
+        k[i][e] = __builtin_bit_cast(i16x2, w);
+      }
   }
 
   constexpr int PER = SEL_BINS / T;
@@ -800,7 +805,7 @@ __device__ __forceinline__ void rank_row16(const SelectArgs &A, int row, int nb,
   if (nb >= 1024) {                                                // one key of eight
 #pragma clang loop unroll(full)
     for (int i = 0; i < IT; ++i) {
-      const uint32_t s = k[i][i & 3][0];
+      const uint32_t s = (uint32_t)(unsigned short)k[i][i & 3][0] ^ 0x8000u;
       if (s) atomicAdd(&h[s >> 5], 1u);
     }
     __syncthreads();
@@ -853,29 +858,45 @@ __device__ __forceinline__ void rank_row16(const SelectArgs &A, int row, int nb,
     const uint32_t rs = min(6u, (uint32_t)__builtin_clz(max(n, 2u) - 1u) - 21u);                 // n << rs <= 2048
     const uint32_t at = min(64u >> rs, lo >> shift), base = lo - (at << shift);
     auto pair = [](uint32_t x) { return (u16x2)(unsigned short)x; };
-    const u16x2 base2 = pair(base), shift2 = pair(shift), copies = pair(1u << rs), copy = pair((uint32_t)lane & ((1u << rs) - 1u));
-    const u16x2 least = pair(at ? min((uint32_t)lane >> rs, at - 1u) : 0u), most = pair(at + n + ((uint32_t)lane >> rs));
+    auto signed_pair = [](uint32_t x) { return (i16x2)(short)(unsigned short)x; };
+    const u16x2 copies = pair(1u << rs), copy = pair((uint32_t)lane & ((1u << rs) - 1u));
+    const uint32_t least = at ? min((uint32_t)lane >> rs, at - 1u) : 0u, most = at + n + ((uint32_t)lane >> rs);
+    auto add = [&](u16x2 x) {
+      x = x * copies + copy;
+      atomicAdd(&h[x[0]], 1u);
+      atomicAdd(&h[x[1]], 1u);
+    };
+    if (shift == 0u) {
+      // (nearly always: the differences that matter fit 15 bits, so the signed numbers do as they are)
+      const i16x2 base2 = signed_pair(base ^ 0x8000u), least2 = signed_pair(least), most2 = signed_pair(most);
 #pragma clang loop unroll(full)
-    for (int i = 0; i < IT; ++i) {
-      if (8 * (i * T + 64 * wave) < nb) {                          // (a wave past the row's end has nothing to count)
-        u16x2 x[4];                                                // (four at a time: a packed result cannot be used at once)
+      for (int i = 0; i < IT; ++i) {
+        if (8 * (i * T + 64 * wave) < nb) {                        // (a wave past the row's end has nothing to count)
+          i16x2 x[4];                                              // (four at a time: a packed result cannot be used at once)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = __builtin_elementwise_sub_sat(k[i][e], base2);
+          for (int e = 0; e < 4; ++e) x[e] = __builtin_elementwise_sub_sat(k[i][e], base2);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = x[e] >> shift2;
+          for (int e = 0; e < 4; ++e) x[e] = __builtin_elementwise_max(x[e], least2);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = __builtin_elementwise_max(x[e], least);
+          for (int e = 0; e < 4; ++e) x[e] = __builtin_elementwise_min(x[e], most2);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = __builtin_elementwise_min(x[e], most);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = x[e] * copies + copy;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          atomicAdd(&h[x[e][0]], 1u);
-          atomicAdd(&h[x[e][1]], 1u);
+          for (int e = 0; e < 4; ++e) add(__builtin_bit_cast(u16x2, x[e]));
         }
+        fence_schedule();
       }
-      fence_schedule();
+    } else {
+      const u16x2 base2 = pair(base), shift2 = pair(shift), least2 = pair(least), most2 = pair(most);
+#pragma clang loop unroll(full)
+      for (int i = 0; i < IT; ++i) {
+        if (8 * (i * T + 64 * wave) < nb) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const u16x2 x = __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, __builtin_bit_cast(uint32_t, k[i][e]) ^ 0x80008000u), base2) >> shift2;
+            add(__builtin_elementwise_min(__builtin_elementwise_max(x, least2), most2));
+          }
+        }
+        fence_schedule();
+      }
     }
     __syncthreads();
     uint32_t loc[PER], inside, beyond;
@@ -913,19 +934,29 @@ __device__ __forceinline__ void rank_row16(const SelectArgs &A, int row, int nb,
   const uint32_t r = krem;                                         // of the tokens with key lo, the first r are kept
 
   // ---- two bits per token: 0 below, 1 equal, 2 above the threshold
-  const u16x2 below = (u16x2)(unsigned short)(lo - 1u);
+  // Held between the two keys around the threshold's, a word's four numbers are added up as digits of 4 bits; what is too much is
+  // the lower key in every digit. (There is no key above the highest.)
+  const uint32_t under = lo - 1u, over = min(lo + 1u, 0xffffu);
+  const i16x2 under2 = (i16x2)(short)(unsigned short)(under ^ 0x8000u), over2 = (i16x2)(short)(unsigned short)(over ^ 0x8000u);
+  const u16x2 too_much = (u16x2)(unsigned short)((under ^ 0x8000u) * 0x1111u);
+  u16x2 digit[3] = {(u16x2)16, (u16x2)256, (u16x2)4096};
+#if defined(__AMDGCN__)
+#pragma unroll
+  for (int e = 0; e < 3; ++e) asm("" : "+s"(digit[e]));                // (a product and a sum are one instruction, a shift and a sum two)
+#endif
   typedef uint16_t half_word __attribute__((may_alias));
   half_word *const codes16 = reinterpret_cast<half_word *>(codes);
 #pragma clang loop unroll(full)
   for (int i = 0; i < IT; ++i) {
-    uint32_t m = 0;
     u16x2 x[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = __builtin_elementwise_sub_sat(k[i][e], below);
+    for (int e = 0; e < 4; ++e) x[e] = __builtin_bit_cast(u16x2, __builtin_elementwise_max(k[i][e], under2));
 #pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = __builtin_elementwise_min(x[e], (u16x2)2);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) m |= __builtin_bit_cast(uint32_t, x[e]) << (4 * e);
+    for (int e = 0; e < 4; ++e) x[e] = __builtin_bit_cast(u16x2, __builtin_elementwise_min(__builtin_bit_cast(i16x2, x[e]), over2));
+    u16x2 d = x[1] * digit[0] + x[0];
+    d = x[2] * digit[1] + d;
+    d = x[3] * digit[2] + d;
+    const uint32_t m = __builtin_bit_cast(uint32_t, d - too_much);
     const int w = i * T + tid;
     codes16[w + 2 * (w >> 5)] = (half_word)(m | m >> 14);
     fence_schedule();
@@ -970,7 +1001,11 @@ __device__ __forceinline__ void rank_row16(const SelectArgs &A, int row, int nb,
 #pragma unroll 1
   for (uint32_t base = 0; base < c; base += STAGE) {
     uint32_t p = pos;
-    if (p < base + STAGE && p + mine > base) {
+    if (c <= (uint32_t)STAGE) {                        // (all of it at once: no place is looked at)
+#pragma unroll
+      for (int x = 0; x < CW / 2; ++x)
+        for (uint32_t rest = w[x]; rest; rest &= rest - 1u, ++p) staged[p] = (stage_t)(32 * (tid * (CW / 2) + x) + __builtin_ctz(rest));
+    } else if (p < base + STAGE && p + mine > base) {
 #pragma unroll
       for (int x = 0; x < CW / 2; ++x)
         for (uint32_t rest = w[x]; rest; rest &= rest - 1u, ++p)
