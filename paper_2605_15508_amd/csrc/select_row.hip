@@ -447,7 +447,7 @@ __device__ __forceinline__ void rank_row(const SelectArgs &A) {
   uint32_t lo = 1, last = 0xfffffffeu, heavy = 0;
   if (nb >= 1024) {
     // From a sample of one key in four or eight, by its keys' upper 11 bits and, if that is one value, by the 11 bits below.
-    constexpr int STEP = IT >= 16 ? 2 : 1;
+    constexpr int STEP = T * IT > 2048 ? T * IT / 2048 : 1;
     uint32_t from = 0, sh = 21;
     __syncthreads();
 #pragma unroll 1
