@@ -7,11 +7,15 @@
 //
 // One 1024-thread workgroup per (draft head, batch); the union is the same for every target head
 // that reads the draft head and is written to each of them. The token range is walked in chunks
-// of 32768 tokens whose row bits sit in LDS (two tokens per word): every list entry that falls
+// of 32768 tokens whose row bits sit in LDS (16 bits per token): every list entry that falls
 // into the chunk ORs its row's bit into its token's half word (one entry of every row per thread
 // in flight: the lists come out of L2, and a thread that waited for each entry in turn spent
-// most of its time waiting); then every thread takes 32 consecutive tokens, one block scan gives the
-// kept tokens their places, and they are written in token order.
+// most of its time waiting); then every wave takes 2048 consecutive tokens, 64 at a time: a ballot says which of them are kept
+// and where they go, and they are stored from the registers, a run of neighbouring places per instruction. What bounds it:
+// the lists' reading and the latencies of the phases. 16 blocks x 16 draft heads of 16 x 6554 entries, 64K tokens: 57 us
+// (65 with 32 tokens per thread, whose entries went one by one to a stage in LDS and from there, coalesced, to each target head).
+// Rejected: no search, each chunk starting where the one before met its first entry past the end, and two steps of entries under way
+// (75 to 87 us: sixteen scalar addresses and limits per step cost more than the search).
 #include "common.h"
 
 namespace {
@@ -19,44 +23,33 @@ namespace {
 constexpr int UN_THREADS = 1024;
 constexpr int UN_CHUNK = 32768;            // tokens per LDS pass
 constexpr int UN_MAX_SEG = 64;             // chunks up to which the lists are read by segments (2M tokens)
-constexpr int UN_STAGE = 10240;            // entries staged at a time: 4 + 2 bytes each inside the 64 KB bit buffer
-
-__device__ __forceinline__ uint32_t un_wave_incl_scan(uint32_t v) {
-  int x = (int)v;
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
-  return (uint32_t)x;
-}
+constexpr int UN_STEPS = UN_CHUNK / UN_THREADS;      // tokens per lane
 
 __global__ void __launch_bounds__(UN_THREADS) union_rows_kernel(const UnionArgs A) {
-  __shared__ uint32_t bits[UN_CHUNK / 2];          // row bits of the chunk's tokens, two tokens per word
+  typedef uint16_t row_bits __attribute__((may_alias));
+  typedef u32x4 four_words __attribute__((may_alias));
+  __shared__ __attribute__((aligned(16))) uint32_t bits[UN_CHUNK / 2];   // row bits of the chunk's tokens, two tokens per word
   __shared__ uint32_t wave_tot[UN_THREADS / 64];
   __shared__ int tgt[STS_MAX_HEADS];               // target heads that read this draft head
   __shared__ int ntgt_s;
   const int j = blockIdx.x, bt = blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) {
-    int n = 0;
-    for (int t = 0; t < A.Hq; ++t)
-      if (A.map[t] == j) tgt[n++] = t;
-    ntgt_s = n;
-  }
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+  if (tid == 0) ntgt_s = 0;
+  for (int i = tid; i < UN_CHUNK / 8; i += UN_THREADS) reinterpret_cast<four_words *>(bits)[i] = u32x4{0u, 0u, 0u, 0u};
   __syncthreads();
-  const int ntgt = ntgt_s;
-  if (ntgt == 0) return;
+  if (tid < A.Hq && A.map[tid] == j) tgt[atomicAdd(&ntgt_s, 1)] = tid;      // (Hq <= 256; in any order)
   __shared__ int cnts[16];                         // entries of each row's list
   if (tid < 16) cnts[tid] = tid < A.Tq ? (A.row_cnt ? min(max(A.row_cnt[((size_t)bt * A.Hd + j) * A.Tq + tid], 0), A.k) : A.k) : 0;
   __syncthreads();
+  const int ntgt = uniform(ntgt_s);
+  if (ntgt == 0) return;
   const int32_t *lists = A.row_idx + ((size_t)bt * A.Hd + j) * A.Tq * (size_t)A.k;      // [Tq][k]
   const size_t out_row = (size_t)bt * A.Hq;        // outputs of target t: (out_row + t) * pitch
   // Lists as the selection writes them are ascending, so the entries of a chunk are one segment
   // of each list, and reading only that segment per chunk reads every list once instead of once
   // per chunk (at 128K tokens the re-reads were three quarters of this kernel's traffic). The
-  // segment ends come from a binary search per (row, chunk end), all at once. Nothing is taken on
+  // segment ends come from searches, a wave per list where there are few ends, else a thread per list and end. Nothing is taken on
   // trust: the segments cover every list completely, and an entry that names a token outside
   // the chunk of the segment it was read in (a list that is not ascending) sets a flag, after which
   // the whole union is built again the plain way, every chunk reading every entry.
@@ -66,7 +59,22 @@ __global__ void __launch_bounds__(UN_THREADS) union_rows_kernel(const UnionArgs 
   bool by_segments = nchunks > 1 && nchunks <= UN_MAX_SEG;
   if (by_segments) {
     if (tid == 0) out_of_place = 0;
-    for (int x = tid; x < 16 * (nchunks + 1); x += UN_THREADS) {
+    if (nchunks <= 4) {
+      // few ends: a wave per list, 64 probes a step (three memory latencies instead of thirteen)
+      const int32_t *row = lists + (size_t)min(wave, A.Tq - 1) * A.k;
+      const int n_row = uniform(cnts[wave]);
+      for (int c = 0; c <= nchunks; ++c) {
+        int lo = 0, len = c == 0 || c == nchunks ? 0 : n_row;
+        while (len > 0) {
+          const int step = (len + 63) / 64, p = lane * step;
+          const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(p < len && row[lo + min(p, len - 1)] < c * UN_CHUNK));
+          if (n == 0) break;                           // (probes 0 .. n - 1 lie below the end)
+          lo += (n - 1) * step + 1;
+          len = min(step - 1, len - (n - 1) * step - 1);
+        }
+        if (lane == 0) seg[wave][c] = c == nchunks ? n_row : lo;
+      }
+    } else for (int x = tid; x < 16 * (nchunks + 1); x += UN_THREADS) {
       const int i = x / (nchunks + 1), c = x % (nchunks + 1);
       int lo = 0, hi = cnts[i];                    // lower bound of c * UN_CHUNK in row i
       if (c == 0) hi = 0;
@@ -83,8 +91,6 @@ __global__ void __launch_bounds__(UN_THREADS) union_rows_kernel(const UnionArgs 
   }
   uint32_t written = 0;                            // union entries before the current chunk
   for (int base = 0; base < A.N; base += UN_CHUNK) {
-    for (int i = tid; i < UN_CHUNK / 2; i += UN_THREADS) bits[i] = 0u;
-    __syncthreads();
     const int ch = base / UN_CHUNK;
     // one entry of every row per thread and step: up to 16 loads in flight
     int span = A.k;                                // entries per row to look at: the longest segment
@@ -114,65 +120,49 @@ __global__ void __launch_bounds__(UN_THREADS) union_rows_kernel(const UnionArgs 
       by_segments = false;
       written = 0;
       base = -UN_CHUNK;
+      for (int i = tid; i < UN_CHUNK / 8; i += UN_THREADS) reinterpret_cast<four_words *>(bits)[i] = u32x4{0u, 0u, 0u, 0u};
+      __syncthreads();
       continue;
     }
-    // thread tid owns tokens base + 32 tid .. + 31 (16 words)
-    uint32_t w[16];
-    uint32_t kept = 0;
+    // the wave's 2048 tokens, lane by lane
+    const row_bits *const own = reinterpret_cast<const row_bits *>(bits) + wave * (64 * UN_STEPS) + lane;
+    uint32_t w[UN_STEPS], kept = 0;
 #pragma unroll
-    for (int x = 0; x < 16; ++x) {
-      w[x] = bits[tid * 16 + x];
-      kept += ((w[x] & 0xffffu) ? 1u : 0u) + ((w[x] >> 16) ? 1u : 0u);
-    }
-    const uint32_t incl = un_wave_incl_scan(kept);
-    if (lane == 63) wave_tot[wave] = incl;
+    for (int x = 0; x < UN_STEPS; ++x) w[x] = own[64 * x];
+#pragma unroll
+    for (int x = 0; x < UN_STEPS; ++x) kept += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(w[x] != 0u));
+    if (lane == 0) wave_tot[wave] = kept;
+    four_words *const mine = reinterpret_cast<four_words *>(bits) + wave * (8 * UN_STEPS) + lane;        // (nothing there for the next chunk)
+#pragma unroll
+    for (int x = 0; x < UN_STEPS / 8; ++x) mine[64 * x] = u32x4{0u, 0u, 0u, 0u};
     __syncthreads();
-    uint32_t before = 0, total = 0;
+    uint32_t at = written, total = 0;              // where the wave's entries go
 #pragma unroll
     for (int x = 0; x < UN_THREADS / 64; ++x) {
       const uint32_t v = wave_tot[x];
-      if (x < wave) before += v;
+      at += x < wave ? v : 0u;
       total += v;
     }
-    // The chunk's entries, in token order, are staged in the (now free) bit buffer, UN_STAGE at a
-    // time, and copied out coalesced to every target head: scattered 4- and 2-byte stores straight
-    // from the owning threads were the slowest part of this kernel.
-    const uint32_t rel0 = before + incl - kept;       // this thread's first place within the chunk
-    int32_t *stg_idx = reinterpret_cast<int32_t *>(bits);
-    typedef uint16_t staged_mask __attribute__((may_alias));
-    staged_mask *stg_mask = reinterpret_cast<staged_mask *>(bits + UN_STAGE);
-    for (uint32_t r0 = 0; r0 < total; r0 += UN_STAGE) {
-      uint32_t rel = rel0;
-      if (rel < r0 + UN_STAGE && rel + kept > r0) {
+    at = (uint32_t)uniform((int)at);
+    const uint32_t room = (uint32_t)A.pitch;       // a pitch below the union's size truncates the list
+    for (int ti = 0; ti < ntgt; ++ti) {
+      const size_t o = (out_row + uniform(tgt[ti])) * (size_t)A.pitch;
+      int32_t *const idx = A.indices + o;
+      uint16_t *const msk = A.row_mask + o;
+      uint32_t p = at;
 #pragma unroll
-        for (int x = 0; x < 16; ++x)
-#pragma unroll
-          for (int hlf = 0; hlf < 2; ++hlf) {
-            const uint32_t m = hlf ? (w[x] >> 16) : (w[x] & 0xffffu);
-            if (m) {
-              if (rel >= r0 && rel - r0 < (uint32_t)UN_STAGE) {
-                stg_idx[rel - r0] = base + tid * 32 + 2 * x + hlf;
-                stg_mask[rel - r0] = (staged_mask)m;
-              }
-              ++rel;
-            }
-          }
-      }
-      __syncthreads();
-      const uint32_t first = written + r0;             // place of the staged entries in the list
-      // a pitch below the union's size truncates the list
-      const uint32_t n = first < (uint32_t)A.pitch ? min(min(total - r0, (uint32_t)UN_STAGE), (uint32_t)A.pitch - first) : 0u;
-      for (int ti = 0; ti < ntgt; ++ti) {
-        const size_t o = (out_row + tgt[ti]) * (size_t)A.pitch + first;
-        for (uint32_t p = tid; p < n; p += UN_THREADS) {
-          A.indices[o + p] = stg_idx[p];
-          A.row_mask[o + p] = stg_mask[p];
+      for (int x = 0; x < UN_STEPS; ++x) {
+        const uint64_t b = __builtin_amdgcn_ballot_w64(w[x] != 0u);
+        const uint32_t place = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, p));
+        if (w[x] != 0u && place < room) {
+          idx[place] = base + wave * (64 * UN_STEPS) + 64 * x + lane;
+          msk[place] = (uint16_t)w[x];
         }
+        p += (uint32_t)__builtin_popcountll(b);
       }
-      __syncthreads();
     }
-    written += total;
-    __syncthreads();                                  // bits and wave_tot are rewritten next round
+    written += (uint32_t)uniform((int)total);
+    __syncthreads();                                  // wave_tot is rewritten next round
   }
   const uint32_t c = min(written, (uint32_t)A.pitch);
   for (int ti = 0; ti < ntgt; ++ti) {

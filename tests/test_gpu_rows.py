@@ -107,6 +107,36 @@ def test_union_over_several_chunks_does_not_depend_on_the_order_inside_a_list(sw
     np.testing.assert_array_equal(mask.cpu().numpy().view(np.uint16), o_mask)
 
 
+# two, four and five chunks (up to four a wave looks for a list's segments, beyond that a thread); lists that begin and end at the
+# chunks' edges, an empty one, one whose entries all lie in the last chunk; a pitch that cuts the union inside a wave's tokens
+@pytest.mark.parametrize("order", ["ascending", "falling"])
+@pytest.mark.parametrize("N,pitch", [(32769, 0), (65536, 1500), (131072, 0), (131073, 2047), (163841, 0)])
+def test_union_at_the_ends_of_chunks(N, pitch, order):
+    rng = np.random.default_rng(N)
+    B, Hd, Tq, k = 1, 2, 16, 700
+    sel = np.full((B, Hd, Tq, k), -1, np.int32)
+    cnt = np.zeros((B, Hd, Tq), np.int32)
+    edges = np.array([x for c in range(1, 6) for x in (32768 * c - 1, 32768 * c) if x < N] + [0, N - 1])
+    for j in range(Hd):
+        for i in range(Tq):
+            n = 0 if i == 3 else k if i < 8 else int(rng.integers(1, k))
+            low = N - 1 - k if i == 5 else 0
+            row = rng.choice(np.arange(low, N), size=n, replace=False)
+            if n > 40 and i != 5:
+                row = np.unique(np.concatenate([row[:n - 40], edges]))[:n]
+            row = np.sort(row)
+            sel[0, j, i, :len(row)] = row[::-1] if order == "falling" and i == 2 else row
+            cnt[0, j, i] = len(row)
+    hm = [0, 1, 0]
+    idx, mask, ucnt = sts.sts_union_rows(torch.from_numpy(sel).to(DEV), torch.from_numpy(cnt).to(DEV), hm, N, **({"pitch": pitch} if pitch else {}))
+    torch.cuda.synchronize()
+    o_idx, o_mask, o_cnt = oracle.union_rows(sel, cnt, hm, pitch=min(Tq * k, N))
+    p = idx.shape[2]
+    np.testing.assert_array_equal(ucnt.cpu().numpy(), np.minimum(o_cnt, p))
+    np.testing.assert_array_equal(idx.cpu().numpy(), o_idx[:, :, :p])
+    np.testing.assert_array_equal(mask.cpu().numpy().view(np.uint16), o_mask[:, :, :p])
+
+
 def make_qkv(seed, B, Tq, Hq, Hkv, d, N):
     g = torch.Generator().manual_seed(seed)
     q = torch.randn(B, Tq, Hq, d, generator=g).to(torch.bfloat16)
