@@ -329,9 +329,11 @@ struct SelectPlan {
   size_t agg_bytes, blk_bytes, hist_bytes, state_bytes, chunk_bytes;
   size_t pool_key_bytes;
   size_t pub_bytes;
+  bool sums;           // long rows of few: their sums first, which one workgroup per row then ranks (with a workspace for them)
+  size_t sums_bytes;
   size_t pipeline_total() const { return agg_bytes + blk_bytes + hist_bytes + state_bytes + chunk_bytes; }
   size_t pool_total() const { return pool ? 2 * pool_key_bytes : 0; }
-  size_t fused_total() const { return pub_bytes; }
+  size_t fused_total() const { return sums_bytes > pub_bytes ? sums_bytes : pub_bytes; }
   // a pool-shaped call falls back to the pipeline when its pointers are not 16-byte aligned,
   // so the workspace covers both
   size_t total() const {
@@ -408,6 +410,8 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
   pl.rowpass_threads = 0;
   pl.smp_tokens = pl.smp_parts = 0;
   pl.pub_bytes = 0;
+  pl.sums = false;
+  pl.sums_bytes = 0;
   // test / tuning knob: 0 the library's rule, 1 histogram pipeline only, 2 pipeline or pool,
   // 3 the sampled selection wherever its shape limits allow, 4 one workgroup per row in
   // several passes wherever its shape limits allow, 5 the sampled selection with one workgroup per row likewise,
@@ -543,6 +547,24 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
       pl.one_row = one_row;
       pl.pool = false;
       plan_sampled(p, rows, pl);
+      // Calls of 8 to 127 rows of up to 65536 tokens whose lists one workgroup per row writes as fast: the row is ranked in one
+      // workgroup's registers where it is one fp32 score per token (beyond 32768 tokens; below, `one_row` says the same), and
+      // several scores are summed first by as many workgroups as there are quads for. A launch more, but nothing to clear, to
+      // sample, to exchange, and the scores are read by the whole chip. us on other scores in every call, as it was (sampled, or
+      // added up by the workgroup that ranks them) and now: 16 rows of 33001 with one score 24.7, 19.2, with five 27.7, 23.4; of 65536 26.2,
+      // 21.5 and 29.9, 26.4; of 32768 with five 24.7, 17.8, with eight 30.7, 18.6; 32 of 65536 with two 28.0, 27.4, with five 33.5, 31.0; 64 of
+      // 33001 with five 32.3, 30.1, of 32768 with eight 37.2, 27.7, with five bf16 scores 21.8, 21.9. Not where the sums take longer than
+      // they save: 64 of 49000 with five 34.7, 35.6; of 65536 37.3, 39.8; of 24000 with two 17.5, 20.3; nor where two scores are added
+      // up in passing (16 of 24000 17.0, 17.1).
+      const bool ready = p->Tq == 1 && p->kind == STS_SCORES_PROBS && !p->scores_bf16;
+      const bool lists_fit = list_work <= 216000;        // (`writes_little` for one score per token)
+      if (path == 0 && !pl.row16 && !p->agg_out && p->N > 16384 && p->N <= SEL_ROW_N && rows >= 8 && lists_fit) {
+        if (ready) pl.one_row = true;
+        else if (p->N > SEL_SMALL_N ? (int64_t)rows * p->N <= 2250000 : p->Tq >= (rows <= 32 ? 3 : 5)) {
+          pl.sums = true;
+          pl.sums_bytes = align256(rows * (size_t)p->N * sizeof(float));
+        }
+      }
     }
   }
   pl.agg_bytes = p->agg_out ? 0 : align256(rows * (size_t)p->N * sizeof(float));
@@ -614,6 +636,11 @@ static sts_status enqueue_select(const sts_select_params *p, void *stream) {
   if (p->B == 0) return STS_OK;
   if (p->N > 0 && !p->scores) return STS_EINVAL;
   if (p->kind == STS_SCORES_LOGITS_LSE && !p->lse) return STS_EINVAL;
+  // (a workspace without room for the sums, as it was enough for such calls before they were summed first, still is)
+  if (pl.sums && p->workspace_bytes < pl.sums_bytes) {
+    pl.sums = false;
+    pl.sums_bytes = 0;
+  }
   size_t need = pl.total();
   const bool ws_usable = p->workspace && p->workspace_bytes >= need && reinterpret_cast<uintptr_t>(p->workspace) % 256 == 0;
   if (pl.band && need > 0 && !ws_usable) {
@@ -715,6 +742,20 @@ static sts_status enqueue_select(const sts_select_params *p, void *stream) {
     a.agg = p->agg_out;   // optional output only: the keys never leave LDS
     a.src = nullptr;
     a.hist = a.state = a.chunk_cnt = nullptr;   // the pipeline's scratch does not exist on this path
+    if (pl.sums) {
+      SelectArgs r = a;
+      a.agg = static_cast<float *>(p->workspace);
+      rc = run_kernel(STS_K_SELECT_AGG, s, [&] { return launch_select_agg(a, s); });
+      if (rc != hipSuccess) return STS_EHIP;
+      r.scores = p->workspace;
+      r.scores_bf16 = 0;
+      r.lse = nullptr;
+      r.kind = STS_SCORES_PROBS;
+      r.reduce = STS_REDUCE_SUM;
+      r.Tq = 1;
+      rc = run_kernel(STS_K_SELECT_SMALL, s, [&] { return launch_select_small(r, s); });
+      return rc == hipSuccess ? STS_OK : STS_EHIP;
+    }
     if (pl.one_row) {
       rc = run_kernel(STS_K_SELECT_SMALL, s, [&] { return launch_select_small(a, s); });
       return rc == hipSuccess ? STS_OK : STS_EHIP;

@@ -116,6 +116,7 @@ constexpr int SEL_BINS = 2048;          // bins of the widest digit
 constexpr int SEL_CHUNK = 8192;         // tokens per workgroup in the scan kernels
 constexpr int SEL_THREADS = 256;
 constexpr int SEL_SMALL_N = 32768;      // scores of a row that the one-workgroup-per-row selection holds in registers at most
+constexpr int SEL_ROW_N = 65536;        // the same for one fp32 score per token, in calls of up to 512 rows
 constexpr int SEL_RANK_N = 2048;        // block sums of a row up to which they are ranked out of LDS
 constexpr int SEL_ROW16 = 16;
 constexpr int SEL_ROW16_N = 131072;     // tokens of one bf16 score each that a workgroup's registers hold

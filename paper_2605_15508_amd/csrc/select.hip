@@ -48,6 +48,21 @@ __global__ void __launch_bounds__(SEL_THREADS) select_clear_kernel(uint32_t *p, 
 }
 
 // --------------------------------------------------------------------------- aggregation
+// The sums alone, a quad per thread, of the valid tokens: for rows that one workgroup then ranks. Bound by latency (16 rows of 33001 tokens,
+// five scores: some 4 us with its launch), by memory from 64 such rows on.
+template <bool BF16>
+__global__ void __launch_bounds__(SEL_THREADS) select_row_sums_kernel(const SelectArgs A) {
+  const int j = blockIdx.y, bt = blockIdx.z, row = bt * A.Hd + j;
+  const int n0 = (int)blockIdx.x * (4 * SEL_THREADS), n = n0 + 4 * (int)threadIdx.x;
+  const int nb = row_len(A, bt);
+  if (n >= nb) return;
+  const f32x4 x = agg_quad_any<BF16>(agg_row(A, row), n, n0 + 4 * SEL_THREADS <= A.N);
+  float *const out = A.agg + (size_t)row * A.N + n;
+  if (n + 4 <= A.N) *reinterpret_cast<f32x4_any *>(out) = x;
+  else
+    for (int e = 0; n + e < A.N; ++e) out[e] = x[e];
+}
+
 template <bool VEC4>
 __global__ void __launch_bounds__(SEL_THREADS) select_agg_kernel(const SelectArgs A) {
   __shared__ uint32_t h[SEL_BINS];
@@ -1200,6 +1215,13 @@ hipError_t launch_select_clear(const SelectArgs &a, hipStream_t s) {
 hipError_t launch_select_agg(const SelectArgs &a, hipStream_t s) {
   const int chunks = (a.N + SEL_CHUNK - 1) / SEL_CHUNK;
   if ((size_t)a.B * a.Hd == 0 || chunks == 0) return hipSuccess;
+  if (!a.hist) {                                       // no histogram: the sums alone
+    const dim3 sums((a.N + 4 * SEL_THREADS - 1) / (4 * SEL_THREADS), a.Hd, a.B);
+    if (a.N < 4) return hipErrorInvalidValue;
+    if (a.scores_bf16) STS_LAUNCH(select_row_sums_kernel<true>, sums, dim3(SEL_THREADS), 0, s, a);
+    else STS_LAUNCH(select_row_sums_kernel<false>, sums, dim3(SEL_THREADS), 0, s, a);
+    return sts_take_launch_status();
+  }
   const dim3 grid(chunks, a.B * a.Hd), block(SEL_THREADS);
   if (vec_ok(a))
     STS_LAUNCH(select_agg_kernel<true>, grid, block, 0, s, a);

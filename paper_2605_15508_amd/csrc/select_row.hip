@@ -1075,7 +1075,7 @@ static hipError_t launch_select_row16(const SelectArgs &a, hipStream_t s) {
   return sts_take_launch_status();
 }
 
-// Rows of 4 to 32768 tokens. Calls of up to 512 rows get 1024 threads per row (latency: 256 rows of 16384 tokens 25 us
+// Rows of 4 to 32768 tokens, of up to 65536 with one probability per token in calls of up to 512 rows. Calls of up to 512 rows get 1024 threads per row (latency: 256 rows of 16384 tokens 25 us
 // with 256 threads per row), others as few as hold the row in 64 registers per thread (several workgroups per CU: 4096
 // such rows 128 us; one workgroup per CU took 290), in 32 where the scores of up to 16384 tokens are added up (1024 rows of 16384
 // with five scores 64.2 us, 68.6).
@@ -1085,10 +1085,10 @@ hipError_t launch_select_row(const SelectArgs &a, hipStream_t s) {
   if (rows == 0) return hipSuccess;
   if (a.rowpass_threads == SEL_ROW16) return launch_select_row16(a, s);
   const int N = a.N;
-  if (N < 4 || N > SEL_SMALL_N) return hipErrorInvalidValue;
   const dim3 grid((unsigned)a.Hd, (unsigned)a.B);
   // one probability per token: nothing is added up, and all of a thread's quads are in flight together
   const bool one = a.Tq == 1 && a.kind == STS_SCORES_PROBS;
+  if (N < 4 || N > (one && a.page <= 1 && rows <= 512 ? SEL_ROW_N : SEL_SMALL_N)) return hipErrorInvalidValue;
 #define STS_SHORT(T, IT) \
   do { \
     if (a.page > 1) STS_LAUNCH((short_select_blocks_kernel<T, IT>), grid, dim3(T), 0, s, a); \
@@ -1105,7 +1105,8 @@ hipError_t launch_select_row(const SelectArgs &a, hipStream_t s) {
     if (N <= 4096) STS_SHORT(1024, 1);
     else if (N <= 8192) STS_SHORT(1024, 2);
     else if (N <= 16384) STS_ROW(1024, 4, 1024, 4);
-    else STS_ROW(1024, 8, 1024, 8);
+    else if (N <= 32768) STS_ROW(1024, 8, 1024, 8);
+    else STS_LAUNCH((select_row_kernel<1024, 16, true>), grid, dim3(1024), 0, s, a);
   } else if (N <= 4096) {
     STS_SHORT(256, 4);
   } else if (N <= 8192) {

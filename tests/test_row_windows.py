@@ -8,7 +8,7 @@ import torch
 
 import oracle
 import paper_2605_15508_amd as sts
-from test_select_emulated import by_keys, check, lib  # noqa: F401  (lib: the emulated library, a fixture)
+from test_select_emulated import by_keys, check, lib, route  # noqa: F401  (lib: the emulated library, a fixture)
 
 DEV = "cuda:0"
 
@@ -196,5 +196,54 @@ def test_many_rows_of_several_scores(Tq, N, k, how):
             assert torch.equal(a[b, 0, :n], want[b, 0, :n])
         assert (a[b, 0, n:] == 0).all()
     o_idx, o_cnt, _ = oracle.select_indices(a[:, :, None].numpy(), np.zeros(2, np.int32), k, seq_lens=lens[:live].numpy())
+    np.testing.assert_array_equal(cnt[:live].cpu().numpy(), o_cnt)
+    np.testing.assert_array_equal(idx[:live].cpu().numpy(), o_idx)
+
+
+# calls of few rows whose scores are summed first and then ranked by one workgroup per row, on both sides of the host's lines: rows, scores
+# per token, N, k, bf16 scores, the kernels' first name
+SUMMED = [(8, 3, 16385, 1638, False, "select_row_sums"), (32, 3, 32768, 300, True, "select_row_sums"), (33, 4, 20000, 2000, False, "select_row_kernel"),
+          (33, 5, 20000, 2000, False, "select_row_sums"), (16, 2, 32768, 3277, False, "select_row_kernel"), (16, 2, 32769, 3277, False, "select_row_sums"),
+          (34, 2, 65536, 6554, False, "select_row_sums"), (35, 2, 65536, 655, True, "select_clear16"), (8, 9, 65537, 655, False, "select_clear16"),
+          (16, 1, 32769, 3277, False, "select_row_kernel"), (127, 1, 65536, 6554, False, "select_row_kernel"), (16, 1, 65537, 6554, False, "select_clear16"),
+          (16, 5, 40003, 20000, False, "select_clear16"), (7, 5, 33001, 3301, False, "select_clear16")]
+
+
+@pytest.mark.parametrize("rows,Tq,N,k,bf16,first", SUMMED)
+def test_summed_rows_route(lib, rows, Tq, N, k, bf16, first):  # noqa: F811
+    assert route(lib, rows, 1, Tq, N, 2, k, bf16=bf16).startswith(first)
+    assert not route(lib, rows, 1, Tq, N, 2, k, bf16=bf16, agg=True).startswith("select_row_sums")
+
+
+def test_summed_rows_emulated(lib):  # noqa: F811
+    """With room for the sums, and with the workspace that such a call needed for the sampled selection."""
+    lib.emu_schedule(5, -1, -1)
+    s = torch.zeros(8, 1, 3, 16401)
+    s[:1] = scores_of("softmax", 1, 3, 16401, 1640, 3)
+    for ws in (None, 8 * 3 * 1352 * 8):
+        check(lib, s, [0, 0], 1640, lens=[16401] + [0] * 7, ws_bytes=ws)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("what", ["softmax", "zeros then scores", "one value", "signed", "logits"])
+@pytest.mark.parametrize("rows,Tq,N,k,bf16,first", [x for x in SUMMED if x[5].startswith("select_row")])
+def test_summed_rows(rows, Tq, N, k, bf16, first, what):
+    live = 5                                          # the other rows are empty
+    s = scores_of("softmax" if what == "logits" else what, live, Tq, N, k, N + k)
+    kw = {}
+    if what == "logits":
+        s = torch.log(s.clamp_min(1e-30))
+        kw = {"kind": sts.STS_SCORES_LOGITS_LSE, "lse": torch.zeros(rows, 1, Tq, device=DEV) + torch.arange(Tq, device=DEV) / 16}
+    s = s.to(torch.bfloat16) if bf16 else s
+    flat = torch.zeros(rows * Tq * N + 8, device=DEV, dtype=s.dtype)
+    sd = flat[N % 2:N % 2 + rows * Tq * N].view(rows, 1, Tq, N)      # an odd row length also starts at an odd element
+    sd[:live] = s.to(DEV)
+    lens = torch.zeros(rows, dtype=torch.int32)
+    lens[:live] = torch.tensor([N, N - 1, N // 2 + 3, 1023, 5])
+    idx, cnt, _ = sts.sts_select(sd, [0, 0], k, seq_lens=lens.to(DEV), **kw)
+    a_idx, a_cnt, agg = sts.sts_select(sd, [0, 0], k, seq_lens=lens.to(DEV), want_agg=True, **kw)      # (the sampled selection's way)
+    assert torch.equal(idx, a_idx) and torch.equal(cnt, a_cnt)
+    assert (cnt[live:] == 0).all() and (idx[live:] == -1).all()
+    o_idx, o_cnt, _ = oracle.select_indices(agg[:live, :, None].cpu().numpy(), np.zeros(2, np.int32), k, seq_lens=lens[:live].numpy())
     np.testing.assert_array_equal(cnt[:live].cpu().numpy(), o_cnt)
     np.testing.assert_array_equal(idx[:live].cpu().numpy(), o_idx)
