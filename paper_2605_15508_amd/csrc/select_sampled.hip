@@ -9,7 +9,7 @@
 //     of the counts of large keys over its runs, so rows whose heavy tokens sit next to each other
 //     get the wider band that they need. Every part of a row samples the same tokens and finds the
 //     same L and U. The part's first loads are on their way meanwhile.
-//  2. The pass over the part, eight loads in flight per thread all the time. A token whose key is >= U
+//  2. The pass over the part, four loads in flight per thread all the time. A token whose key is >= U
 //     is certainly kept: a bit in LDS. One in [L, U), a few per cent of the row, goes to the
 //     band list in LDS with its key. Nothing else is remembered.
 //  3. The threshold. The parts exchange a histogram of their bands (512 bins over [L, U)) and their
@@ -38,8 +38,8 @@
 //
 // What bounds it (64 rows of 128K tokens, 5 fp32 scores each, 4 parts per row, 168 MB): the sample and the pass
 // together 29 us (168 MB and 21 MB of samples, mostly from the last-level cache: the rate of the memory), then latency:
-// 5 us for the histogram exchange, 3.5 us for the keys, 3 us for bits and list; kernel 43-45 us on scores that the
-// last-level cache holds, 50 on new ones. Histograms of all keys at three digit levels, with the
+// 5 us for the histogram exchange, 3.5 us for the keys, 3 us for bits and list; kernel 42 us on scores that the
+// last-level cache holds, 44 on new ones. Histograms of all keys at three digit levels, with the
 // part's keys in LDS, took 54: the same 29 us, then 20 us for three levels and 5 us for the list. 16 rows of 1M
 // tokens (335 MB, 16 parts per row): 78 us against 122 for five kernels that stored the aggregate and read it
 // three times. Rows of one score per token are bound by vector instructions instead (about 60 per 256 tokens
@@ -57,6 +57,11 @@ constexpr int SMP_HIST = 512;             // bins of an exchanged histogram, two
 // upwards and hold any 32-bit range. With one less, more than 64 equal scores above all that the sample saw (saturated
 // scores, 16 rows of 33001 tokens, 256 kept) went by plain passes: 105 us instead of 52.
 constexpr int SMP_ROUNDS = 5;
+// Loads in flight per thread in the pass. Its code is there once for each (the ring's place has to be known where a load is waited for): with
+// eight the kernel was 74 KB, more than the instruction cache holds. us with 8, 6, 4, 3 and 2: 64 rows of 128K tokens, five scores 48.1,
+// 47.0, 46.8, 47.1, 47.2; 16 of 1M 77.3, 76.6, 76.0, 75.2, 78.2; 128 of 128K, one score, read anew 42.7, 41.0, 39.6, 39.3, 39.0; 128 of 50000,
+// eight bf16 scores (loads of half the size) 41.9, 42.2, 41.3, 45.0, 45.7. (10 and 12: 42.1 and 46.4 where 8 takes 40.5.)
+constexpr int SMP_FLIGHT = 4;
 constexpr int SMP_CAND = 64;              // keys of the threshold's bin that are exchanged one by one
 constexpr int SMP_G_WORD = SMP_ROUNDS * SMP_HIST / 2, SMP_CAND_WORD = SMP_G_WORD + 8;
 static_assert(SMP_CAND_WORD + SMP_CAND == SMP_WORDS, "layout of a part's exchange words");
@@ -330,7 +335,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
   if (tid == 0) ticket = 2 * W;
   const float lse_of = R.logits && lane < Tq ? R.L[lane] : 0.f;        // row i's normaliser in lane i (Tq <= 64)
   __syncthreads();
-  // ---- the sample's loads, then the first eight of the part's own
+  // ---- the sample's loads, then the first of the part's own
   constexpr int QT = 2;
   const int run = BF16 ? 64 : 32, rq = run >> 2;       // tokens and quads of a 128-byte run
   const SamplePlan sp = sample_plan(max(nb, 1), run, smp_sample(nb, c, A.smp_tokens));
@@ -343,11 +348,11 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
     pos[x] = sp.start(s / rq, run) + (s % rq) * 4;
   }
   // The part's loads: a group of 256 tokens at a time, whichever is next when the wave has room (a fixed
-  // share per wave left the oldest waves idle for the last third of the pass), and the Tq rows of it; eight in
+  // share per wave left the oldest waves idle for the last third of the pass), and the Tq rows of it; SMP_FLIGHT in
   // flight. The address is a scalar base and a 32-bit lane offset: no vector arithmetic but the clamp at the
   // row's end.
-  RawQuad<BF16> raw[8];
-  int grp[8];                                          // group of each slot (wave-uniform), >= ng: none
+  RawQuad<BF16> raw[SMP_FLIGHT];
+  int grp[SMP_FLIGHT];                                          // group of each slot (wave-uniform), >= ng: none
   int ld_g = wave, ld_i = 0;                           // next load: group and row (wave-uniform)
   uint32_t next_g = (uint32_t)(wave + W);              // in lane 0: the group after that, asked for one group ahead
   const int lane4 = 4 * lane;
@@ -373,7 +378,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
     }
   }
 #pragma unroll
-  for (int u = 0; u < 8; ++u) issue(raw[u], grp[u]);
+  for (int u = 0; u < SMP_FLIGHT; ++u) issue(raw[u], grp[u]);
   Band band = {0u, 0u, 0u, false, false, false};
   if (m > 0) band = sample_band<QT>(sp, run, nb, c, pos, sacc, h, tmp, red, found);   // (uniform; its barriers publish ctr)
   else __syncthreads();
@@ -486,7 +491,7 @@ __global__ void __launch_bounds__(SMP_THREADS) select_sampled_kernel(const Selec
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     while (grp[0] < ng) {                              // (groups come in order: behind a slot without one there is none)
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < SMP_FLIGHT; ++u) {
         f32x4 p = SL::widen(raw[u]);
         const int g = grp[u];
         issue(raw[u], grp[u]);
