@@ -239,16 +239,16 @@ __device__ __forceinline__ void rank_short_row(const SelectArgs &A) {
   const int nb = __builtin_amdgcn_readfirstlane(BLOCKS ? ranked_len<true>(A, bt) : row_len(A, bt));
   const uint32_t c = (uint32_t)min(A.kh[j], nb);
   const int t0 = target_off(A, j), t1 = target_off(A, j + 1);
-  write_tail<T>(A, bt, j, c);
   float *out = A.agg ? A.agg + (size_t)row * A.N : nullptr;
   const bool ranked = c > 0 && t0 != t1;
-  if (!ranked && !out) return;
+  if (!ranked && !out) return write_tail<T>(A, bt, j, c);
   const AggRow R = agg_row(A, row);
   for (int i = tid; i < SEL_BINS; i += T) h[i] = 0u;
   if (tid < 4) ctr[tid] = 0u;
 
   int v[IT][4];
   load_row<T, IT, ONE>(R, out, nb, tid, v);
+  write_tail<T>(A, bt, j, c);                          // (not in front of the loads)
   if (!ranked) return;
 
   auto each = [&](auto f) {
@@ -406,15 +406,15 @@ __device__ __forceinline__ void rank_row(const SelectArgs &A) {
   const int nb = __builtin_amdgcn_readfirstlane(ranked_len<BLOCKS>(A, bt));
   const uint32_t c = (uint32_t)min(A.kh[j], nb);
   const int t0 = target_off(A, j), t1 = target_off(A, j + 1);
-  write_tail<T>(A, bt, j, c);
   float *out = A.agg ? A.agg + (size_t)row * A.N : nullptr;
   const bool ranked = c > 0 && t0 != t1;
-  if (!ranked && !out) return;
+  if (!ranked && !out) return write_tail<T>(A, bt, j, c);
   const AggRow R = agg_row(A, row);
   for (int i = tid; i < SLOTS; i += T) h[i] = 0u;
 
   int v[IT][4];
   load_row<T, IT, ONE>(R, out, nb, tid, v);
+  write_tail<T>(A, bt, j, c);
   if (!ranked) return;
   uint32_t k[IT][4];                                   // unsigned keys, 0 where there is no token
 #pragma clang loop unroll(full)
