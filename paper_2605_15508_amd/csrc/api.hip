@@ -551,16 +551,16 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
       // workgroup's registers where it is one fp32 score per token (beyond 32768 tokens; below, `one_row` says the same), and
       // several scores are summed first by as many workgroups as there are quads for. A launch more, but nothing to clear, to
       // sample, to exchange, and the scores are read by the whole chip. us on other scores in every call, as it was (sampled, or
-      // added up by the workgroup that ranks them) and now: 16 rows of 33001 with one score 24.7, 19.2, with five 27.7, 23.4; of 65536 26.2,
-      // 21.5 and 29.9, 26.4; of 32768 with five 24.7, 17.8, with eight 30.7, 18.6; 32 of 65536 with two 28.0, 27.4, with five 33.5, 31.0; 64 of
-      // 33001 with five 32.3, 30.1, of 32768 with eight 37.2, 27.7, with five bf16 scores 21.8, 21.9. Not where the sums take longer than
-      // they save: 64 of 49000 with five 34.7, 35.6; of 65536 37.3, 39.8; of 24000 with two 17.5, 20.3; nor where two scores are added
-      // up in passing (16 of 24000 17.0, 17.1).
+      // added up by the workgroup that ranks them) and now: 16 rows of 33001 with one score 26.3, 16.9, with five 28.5, 20.8; of 65536 26.2,
+      // 21.1 and 29.9, 25.8; of 32768 with five 24.7, 18.5, with eight 30.7, 18.6; 32 of 65536 with two 28.0, 27.3, with five 33.5, 30.5; 64 of
+      // 33001 with five 33.3, 27.6, of 49152 with four 31.6, 29.6, with eight 40.4, 37.3; of 32768 with eight 37.2, 27.5, with five bf16 scores
+      // 21.8, 21.6. Not where the sums take longer than they save: 64 of 57000 with five 37.2, 37.2, of 65536 37.3, 39.8; of 24000 with two
+      // 17.5, 20.3; nor where two scores are added up in passing (16 of 24000 17.0, 17.1).
       const bool ready = p->Tq == 1 && p->kind == STS_SCORES_PROBS && !p->scores_bf16;
       const bool lists_fit = list_work <= 216000;        // (`writes_little` for one score per token)
       if (path == 0 && !pl.row16 && !p->agg_out && p->N > 16384 && p->N <= SEL_ROW_N && rows >= 8 && lists_fit) {
         if (ready) pl.one_row = true;
-        else if (p->N > SEL_SMALL_N ? (int64_t)rows * p->N <= 2250000 : p->Tq >= (rows <= 32 ? 3 : 5)) {
+        else if (p->N > SEL_SMALL_N ? (int64_t)rows * p->N <= (p->N <= 49152 && p->Tq >= 4 ? 3200000 : 2250000) : p->Tq >= (rows <= 32 ? 3 : 5)) {
           pl.sums = true;
           pl.sums_bytes = align256(rows * (size_t)p->N * sizeof(float));
         }

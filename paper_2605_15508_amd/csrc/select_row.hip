@@ -666,10 +666,11 @@ __device__ __forceinline__ void rank_row(const SelectArgs &A) {
     mine += (uint32_t)__builtin_popcount(y);
     y = (y | y >> 4) & 0x00ff00ffu;                    // the nibbles next to each other
     y = (y | y >> 8) & 0x0000ffffu;
-    if (x & 1) w[x >> 1] |= y << 16;
+    if (CW % 2) w[x] = y;
+    else if (x & 1) w[x >> 1] |= y << 16;
     else w[x >> 1] = y;
   }
-  constexpr int LW = (CW + 1) / 2, LT = CW >= 2 ? 32 : 16;         // words of LT tokens
+  constexpr int LW = CW % 2 ? CW : CW / 2, LT = CW % 2 ? 16 : 32;  // words of LT tokens
 #pragma unroll 1
   for (uint32_t base = 0; base < c; base += STAGE) {
     uint32_t p = pos;
@@ -1075,7 +1076,8 @@ static hipError_t launch_select_row16(const SelectArgs &a, hipStream_t s) {
   return sts_take_launch_status();
 }
 
-// Rows of 4 to 32768 tokens, of up to 65536 with one probability per token in calls of up to 512 rows. Calls of up to 512 rows get 1024 threads per row (latency: 256 rows of 16384 tokens 25 us
+// Rows of 4 to 32768 tokens, of up to 65536 with one probability per token in calls of up to 512 rows (16 rows of 33001 tokens 16.9 us with
+// twelve quads per thread, 18.6 with sixteen). Calls of up to 512 rows get 1024 threads per row (latency: 256 rows of 16384 tokens 25 us
 // with 256 threads per row), others as few as hold the row in 64 registers per thread (several workgroups per CU: 4096
 // such rows 128 us; one workgroup per CU took 290), in 32 where the scores of up to 16384 tokens are added up (1024 rows of 16384
 // with five scores 64.2 us, 68.6).
@@ -1106,6 +1108,7 @@ hipError_t launch_select_row(const SelectArgs &a, hipStream_t s) {
     else if (N <= 8192) STS_SHORT(1024, 2);
     else if (N <= 16384) STS_ROW(1024, 4, 1024, 4);
     else if (N <= 32768) STS_ROW(1024, 8, 1024, 8);
+    else if (N <= 49152) STS_LAUNCH((select_row_kernel<1024, 12, true>), grid, dim3(1024), 0, s, a);
     else STS_LAUNCH((select_row_kernel<1024, 16, true>), grid, dim3(1024), 0, s, a);
   } else if (N <= 4096) {
     STS_SHORT(256, 4);
