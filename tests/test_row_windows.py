@@ -248,3 +248,24 @@ def test_summed_rows(rows, Tq, N, k, bf16, first, what):
     o_idx, o_cnt, _ = oracle.select_indices(agg[:live, :, None].cpu().numpy(), np.zeros(2, np.int32), k, seq_lens=lens[:live].numpy())
     np.testing.assert_array_equal(cnt[:live].cpu().numpy(), o_cnt)
     np.testing.assert_array_equal(idx[:live].cpu().numpy(), o_idx)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("k", [1, 3, 30, 300])
+@pytest.mark.parametrize("rows,N,bf16", [(513, 16383, False), (513, 32768, False), (16, 17000, False), (16, 49000, False), (300, 65535, True), (300, 131071, True)])
+def test_few_kept(rows, N, bf16, k):
+    """Windows whose upper end is the sample's largest key; heavy tokens that the sample sees all of, or none."""
+    live = 6                                          # the other rows are empty
+    s = scores_of("softmax", live, 1, N, k, N + k)
+    s[1, ..., N // 2:N // 2 + max(k, 64)] += 0.5
+    for r in range(2, live):
+        s[r, ..., r - 2::4][..., ::max(1, N // (8 * k))] += 0.25
+    s = s.to(torch.bfloat16) if bf16 else s
+    sd = torch.zeros(rows, 1, 1, N, device=DEV, dtype=s.dtype)
+    sd[:live] = s.to(DEV)
+    lens = torch.zeros(rows, dtype=torch.int32)
+    lens[:live] = torch.tensor([N, N, N, N - 1, 1024, N // 3])
+    idx, cnt, _ = sts.sts_select(sd, [0, 0], k, seq_lens=lens.to(DEV))
+    o_idx, o_cnt, _ = oracle.select_indices(s.float().numpy(), np.zeros(2, np.int32), k, seq_lens=lens[:live].numpy())
+    np.testing.assert_array_equal(cnt[:live].cpu().numpy(), o_cnt)
+    np.testing.assert_array_equal(idx[:live].cpu().numpy(), o_idx)
