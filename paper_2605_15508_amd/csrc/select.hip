@@ -144,63 +144,17 @@ __global__ void __launch_bounds__(SEL_THREADS) select_block_kernel(const SelectA
   flush_hist<SEL_BINS>(gh, h);
 }
 
-// Coalesced variant for page % 4 == 0, page <= 256, N % 4 == 0: every lane loads 4 consecutive
-// tokens and the page/4 lanes of a block pass a running sum from left to right, so the
-// additions happen in exactly the order of the one-thread-per-block kernel above.
-__global__ void __launch_bounds__(SEL_THREADS) select_block_vec_kernel(const SelectArgs A) {
-  __shared__ uint32_t h[SEL_BINS];
-  const int row = blockIdx.y;
-  const int bt = __builtin_amdgcn_readfirstlane(row / A.Hd);
-  const int nb = row_len(A, bt);
-  const int nblk = (nb + A.page - 1) / A.page;
-  for (int i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS) h[i] = 0u;
-  __syncthreads();
-  const float *a = A.agg + (size_t)row * A.N;
-  float *out = A.blk + (size_t)row * A.srcN;
-  const int L = A.page >> 2;                       // lanes per block (1..64, power of two)
-  const int lane = threadIdx.x & 63;
-  const int pos_in_blk = lane & (L - 1);
-  // SEL_CHUNK tokens per workgroup, 1024 per sweep
-  for (int n = blockIdx.x * SEL_CHUNK + threadIdx.x * 4; n < min((blockIdx.x + 1) * SEL_CHUNK, A.N);
-       n += SEL_THREADS * 4) {
-    const f32x4 x = *reinterpret_cast<const f32x4 *>(a + n);
-    float run = 0.f;
-    bool have = false;                             // whether `run` holds at least one term
-    for (int s = 0; s < L; ++s) {
-      if (pos_in_blk == s) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (n + e < nb) {
-            run = have ? run + x[e] : x[e];
-            have = true;
-          }
-      }
-      if (s + 1 < L) {
-        const float up = __shfl_up(run, 1, 64);
-        const int hup = __shfl_up((int)have, 1, 64);
-        if (pos_in_blk == s + 1) {
-          run = up;
-          have = hup != 0;
-        }
-      }
-    }
-    if (pos_in_blk == L - 1) {
-      const int m = n / A.page;
-      out[m] = run;                                // blocks past the valid length hold 0
-      if (m < nblk) atomicAdd(&h[key_of(run) >> (32 - SEL_BITS0)], 1u);
-    }
-  }
-  __syncthreads();
-  uint32_t *gh = A.hist + (size_t)row * 3 * SEL_BINS;
-  flush_hist<SEL_BINS>(gh, h);
-}
-
-// Aggregation and block sums in one pass (page % 4 == 0, page <= 256, N % page == 0, 16-byte
-// aligned scores): every lane aggregates 4 consecutive tokens in registers and the page/4
-// lanes of a block pass the running sum from left to right, exactly as above; the per-token
+// Aggregation and block sums in one pass (a power of two from 4 to 256 tokens per block): every lane aggregates 4
+// consecutive tokens in registers and the page/4
+// lanes of a block pass the running sum from left to right, so the additions happen in exactly the order of the
+// one-thread-per-block kernel above; the per-token
 // aggregate is stored only when the caller asks for it. With A.hist == nullptr no histogram is
-// built (the blocks are ranked out of LDS afterwards).
-__global__ void __launch_bounds__(SEL_THREADS) select_aggblock_kernel(const SelectArgs A) {
+// built (the blocks are ranked out of LDS afterwards). ANY: rows of any length from 4 on and scores at any alignment
+// (the quad that would run past the row's end is read where it fits and shifted; the last block may be short). Such rows took six
+// launches, one of which read a chunk of 8192 tokens per workgroup and stored the sums per token: 32 rows of 13205 tokens, eight
+// scores each, pages of 16: 62 us, 12.7 with the ranking now.
+template <bool ANY>
+__global__ void __launch_bounds__(SEL_THREADS) select_aggblock_kernel(const SelectArgs A, int chunk) {
   __shared__ uint32_t h[SEL_BINS];
   const int row = blockIdx.y;
   const int bt = __builtin_amdgcn_readfirstlane(row / A.Hd);
@@ -217,15 +171,28 @@ __global__ void __launch_bounds__(SEL_THREADS) select_aggblock_kernel(const Sele
   const int L = A.page >> 2;                       // lanes per block (1..64, power of two)
   const int lane = threadIdx.x & 63;
   const int pos_in_blk = lane & (L - 1);
-  for (int n = blockIdx.x * SEL_CHUNK + threadIdx.x * 4; n < min((blockIdx.x + 1) * SEL_CHUNK, A.N);
-       n += SEL_THREADS * 4) {
-    const f32x4 x = agg_quad(R, n);
+  // `chunk` tokens per workgroup, a multiple of the 1024 of a sweep; the lanes of the last block are all here
+  const int end = (int)min((int64_t)(blockIdx.x + 1) * chunk, (int64_t)A.srcN * A.page);
+  for (int n = blockIdx.x * chunk + threadIdx.x * 4; n < end; n += SEL_THREADS * 4) {
+    f32x4 x;
+    if constexpr (ANY) {
+      const bool inside = __builtin_amdgcn_readfirstlane(n) + 256 <= A.N;      // (lane 0's quad is the wave's first)
+      x = R.bf16 ? agg_quad_any<true>(R, n, inside) : agg_quad_any<false>(R, n, inside);
+    } else {
+      x = agg_quad(R, n);
+    }
     if (tok_out) {
       f32x4 o = x;
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         if (n + e >= nb) o[e] = 0.f;
-      *reinterpret_cast<f32x4 *>(tok_out + n) = o;
+      if constexpr (ANY) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (n + e < A.N) tok_out[n + e] = o[e];
+      } else {
+        *reinterpret_cast<f32x4 *>(tok_out + n) = o;
+      }
     }
     float run = 0.f;
     bool have = false;                             // whether `run` holds at least one term
@@ -1141,16 +1108,21 @@ hipError_t launch_select_rank(const SelectArgs &a, hipStream_t s) {
 }
 
 bool select_aggblock_ok(const SelectArgs &a) {
-  const bool pow2 = (a.page & (a.page - 1)) == 0;
-  return pow2 && a.page >= 4 && a.page <= 256 && (a.N % a.page) == 0 &&
-         (reinterpret_cast<uintptr_t>(a.scores) % 16) == 0 &&
-         (a.agg == nullptr || (reinterpret_cast<uintptr_t>(a.agg) % 16) == 0);
+  // (calls that ask for the sums per token, too, of rows that end within a block keep the kernels that store those first)
+  return (a.page & (a.page - 1)) == 0 && a.page >= 4 && a.page <= 256 && a.N >= 4 && (a.agg == nullptr || a.N % a.page == 0);
 }
 
 hipError_t launch_select_aggblock(const SelectArgs &a, hipStream_t s) {
   if ((size_t)a.B * a.Hd == 0 || a.N == 0) return hipSuccess;
-  const dim3 grid((a.N + SEL_CHUNK - 1) / SEL_CHUNK, a.B * a.Hd), block(SEL_THREADS);
-  STS_LAUNCH(select_aggblock_kernel, grid, block, 0, s, a);
+  // One quad per thread where nothing is collected per workgroup. us with the ranking, 8192, 4096, 2048 and 1024 tokens per workgroup:
+  // 16 rows of 4096 tokens, five scores 14.9, 15.2, 12.3, 10.5; 32 of 13205, eight 24.4, 17.5, 14.0, 12.7; 64 of 131072, five
+  // 36.1, 37.3, 35.6, 35.6; 256 of 60000, eight 89.7, 86.4, 83.6, 82.6. (A histogram is worth a longer chunk: it is added to the row's.)
+  const int chunk = a.hist ? SEL_CHUNK : 4 * SEL_THREADS;
+  const dim3 grid((unsigned)(((int64_t)a.N + chunk - 1) / chunk), a.B * a.Hd), block(SEL_THREADS);
+  const bool quads = a.N % a.page == 0 && (reinterpret_cast<uintptr_t>(a.scores) % 16) == 0 &&
+                     (a.agg == nullptr || (reinterpret_cast<uintptr_t>(a.agg) % 16) == 0);
+  if (quads) STS_LAUNCH(select_aggblock_kernel<false>, grid, block, 0, s, a, chunk);
+  else STS_LAUNCH(select_aggblock_kernel<true>, grid, block, 0, s, a, chunk);
   return sts_take_launch_status();
 }
 
@@ -1192,15 +1164,8 @@ hipError_t launch_select_pool(const SelectArgs &a, hipStream_t s) {
 
 hipError_t launch_select_block(const SelectArgs &a, hipStream_t s) {
   if ((size_t)a.B * a.Hd == 0 || a.srcN == 0) return hipSuccess;
-  const bool pow2 = (a.page & (a.page - 1)) == 0;
-  if (pow2 && a.page >= 4 && a.page <= 256 && (a.N % a.page) == 0 &&
-      (reinterpret_cast<uintptr_t>(a.agg) % 16) == 0) {
-    const dim3 grid((a.N + SEL_CHUNK - 1) / SEL_CHUNK, a.B * a.Hd), block(SEL_THREADS);
-    STS_LAUNCH(select_block_vec_kernel, grid, block, 0, s, a);
-  } else {
-    const dim3 grid((a.srcN + SEL_THREADS - 1) / SEL_THREADS, a.B * a.Hd), block(SEL_THREADS);
-    STS_LAUNCH(select_block_kernel, grid, block, 0, s, a);
-  }
+  const dim3 grid((a.srcN + SEL_THREADS - 1) / SEL_THREADS, a.B * a.Hd), block(SEL_THREADS);
+  STS_LAUNCH(select_block_kernel, grid, block, 0, s, a);
   return sts_take_launch_status();
 }
 

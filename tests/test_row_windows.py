@@ -269,3 +269,44 @@ def test_few_kept(rows, N, bf16, k):
     o_idx, o_cnt, _ = oracle.select_indices(s.float().numpy(), np.zeros(2, np.int32), k, seq_lens=lens[:live].numpy())
     np.testing.assert_array_equal(cnt[:live].cpu().numpy(), o_cnt)
     np.testing.assert_array_equal(idx[:live].cpu().numpy(), o_idx)
+
+
+# scores per token, N, page: one token past a sweep's 1024 and short of it, rows within one page, the longest row that is
+# ranked by one workgroup and one past it
+BLOCKS = [(1, 4, 4), (3, 5, 256), (9, 1025, 16), (2, 8191, 8), (5, 4099, 64), (2, 65531, 4), (2, 65538, 4)]
+
+
+@pytest.mark.parametrize("Tq,N,page", BLOCKS)
+def test_blocks_of_any_length_route(lib, Tq, N, page):  # noqa: F811
+    for kw in ({}, {"bf16": True}, {"unaligned": True}):
+        assert "select_aggblock" in route(lib, 3, 2, Tq, N, 2, 1, page=page, **kw)
+    assert ("select_aggblock" in route(lib, 3, 2, Tq, N, 2, 1, page=page, agg=True, unaligned=True)) == (N % page == 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("how", ["fp32", "bf16", "logits", "max"])
+@pytest.mark.parametrize("Tq,N,page", BLOCKS)
+def test_blocks_of_any_length(Tq, N, page, how):
+    """The same lists as the kernels that store the sums per token make (asked for them), and as the oracle, bit for bit."""
+    B, Hd = 3, 2
+    g = torch.Generator().manual_seed(N + page)
+    s = torch.randn(B, Hd, Tq, N, generator=g)
+    s = s if how == "logits" else torch.softmax(s * 2, dim=-1)
+    s = s.to(torch.bfloat16) if how == "bf16" else s
+    lens = torch.tensor([N, max(N - page // 2 - 1, 1), N // 2 + 1], dtype=torch.int32)
+    kw = {"lse": torch.rand(B, Hd, Tq, generator=g).to(DEV), "kind": sts.STS_SCORES_LOGITS_LSE} if how == "logits" else {}
+    if how == "max":
+        kw = {"reduce": sts.STS_REDUCE_MAX}
+    nblk = (N + page - 1) // page
+    k = max(1, nblk // 5)
+    flat = torch.zeros(s.numel() + 8, dtype=s.dtype, device=DEV)
+    sd = flat[1:1 + s.numel()].view(s.shape)          # (an odd element to start at)
+    sd.copy_(s.to(DEV))
+    idx, cnt, agg = sts.sts_select(sd, [0, 1], k, seq_lens=lens.to(DEV), page_size=page, want_agg=True, **kw)
+    plain, pcnt, _ = sts.sts_select(sd, [0, 1], k, seq_lens=lens.to(DEV), page_size=page, **kw)
+    assert torch.equal(idx, plain) and torch.equal(cnt, pcnt)
+    t_idx, t_cnt, t_agg = sts.sts_select(sd, [0, 1], N, seq_lens=lens.to(DEV), want_agg=True, **kw)
+    assert torch.equal(agg, t_agg)                    # per token as without pages
+    o_idx, o_cnt, _ = oracle.select_indices(agg[:, :, None].cpu().numpy(), np.array([0, 1], np.int32), k, seq_lens=lens.numpy(), page=page)
+    np.testing.assert_array_equal(cnt.cpu().numpy(), o_cnt)
+    np.testing.assert_array_equal(idx.cpu().numpy(), o_idx)
