@@ -1,10 +1,13 @@
 // Short rows (gfx950): a row that one workgroup's registers hold, ranked in one launch. Every thread
 // loads and aggregates the row's quads that are its own (same fp32 order as everywhere) and keeps the
-// keys; nothing is read twice. Three kernels:
+// keys; nothing is read twice. The kernels:
 //   short_select_row_kernel  a few keys per thread: all of them counted, in 2048 bins that divide the row's key range and,
 //                            if the bin of the threshold still holds more than a few keys, that bin;
 //   select_row_kernel        more keys per thread: a sample gives a window of keys around the threshold, whose keys are counted
 //                            in up to 2048 bins;
+//   short_select_row_scores_kernel, select_row_scores_kernel  the same where several scores per token, or probabilities of
+//                            logits, are added up first;
+//   select_row_long_kernel   select_row_kernel for rows of 32769 to 65536 tokens, one score each;
 //   select_row16_kernel      rows of one bf16 score per token, two keys to a register.
 // The kept tokens are bits in LDS; the list is the bits read in order.
 //
@@ -382,8 +385,10 @@ __device__ __forceinline__ void rank_short_row(const SelectArgs &A) {
   }
 }
 
-template <int T, int IT, bool ONE>
-__global__ void __launch_bounds__(T) short_select_row_kernel(const SelectArgs A) { rank_short_row<T, IT, false, ONE>(A); }
+template <int T, int IT>
+__global__ void __launch_bounds__(T) short_select_row_kernel(const SelectArgs A) { rank_short_row<T, IT, false, true>(A); }
+template <int T, int IT>
+__global__ void __launch_bounds__(T) short_select_row_scores_kernel(const SelectArgs A) { rank_short_row<T, IT, false, false>(A); }
 template <int T, int IT>
 __global__ void __launch_bounds__(T) short_select_blocks_kernel(const SelectArgs A) { rank_short_row<T, IT, true, true>(A); }
 
@@ -697,8 +702,12 @@ __device__ __forceinline__ void rank_row(const SelectArgs &A) {
   }
 }
 
-template <int T, int IT, bool ONE>
-__global__ void __launch_bounds__(T, 4) select_row_kernel(const SelectArgs A) { rank_row<T, IT, false, ONE>(A); }
+template <int T, int IT>
+__global__ void __launch_bounds__(T, 4) select_row_kernel(const SelectArgs A) { rank_row<T, IT, false, true>(A); }
+template <int T, int IT>
+__global__ void __launch_bounds__(T, 4) select_row_scores_kernel(const SelectArgs A) { rank_row<T, IT, false, false>(A); }
+template <int T, int IT>
+__global__ void __launch_bounds__(T, 4) select_row_long_kernel(const SelectArgs A) { rank_row<T, IT, false, true>(A); }
 template <int T, int IT>
 __global__ void __launch_bounds__(T, 4) select_blocks_kernel(const SelectArgs A) { rank_row<T, IT, true, true>(A); }
 
@@ -1105,22 +1114,22 @@ hipError_t launch_select_row(const SelectArgs &a, hipStream_t s) {
 #define STS_SHORT(T, IT) \
   do { \
     if (a.page > 1) STS_LAUNCH((short_select_blocks_kernel<T, IT>), grid, dim3(T), 0, s, a); \
-    else if (one) STS_LAUNCH((short_select_row_kernel<T, IT, true>), grid, dim3(T), 0, s, a); \
-    else STS_LAUNCH((short_select_row_kernel<T, IT, false>), grid, dim3(T), 0, s, a); \
+    else if (one) STS_LAUNCH((short_select_row_kernel<T, IT>), grid, dim3(T), 0, s, a); \
+    else STS_LAUNCH((short_select_row_scores_kernel<T, IT>), grid, dim3(T), 0, s, a); \
   } while (0)
 #define STS_ROW(T, IT, T5, IT5) \
   do { \
     if (a.page > 1) STS_LAUNCH((select_blocks_kernel<T, IT>), grid, dim3(T), 0, s, a); \
-    else if (one) STS_LAUNCH((select_row_kernel<T, IT, true>), grid, dim3(T), 0, s, a); \
-    else STS_LAUNCH((select_row_kernel<T5, IT5, false>), grid, dim3(T5), 0, s, a); \
+    else if (one) STS_LAUNCH((select_row_kernel<T, IT>), grid, dim3(T), 0, s, a); \
+    else STS_LAUNCH((select_row_scores_kernel<T5, IT5>), grid, dim3(T5), 0, s, a); \
   } while (0)
   if (rows <= 512) {
     if (N <= 4096) STS_SHORT(1024, 1);
     else if (N <= 8192) STS_SHORT(1024, 2);
     else if (N <= 16384) STS_ROW(1024, 4, 1024, 4);
     else if (N <= 32768) STS_ROW(1024, 8, 1024, 8);
-    else if (N <= 49152) STS_LAUNCH((select_row_kernel<1024, 12, true>), grid, dim3(1024), 0, s, a);
-    else STS_LAUNCH((select_row_kernel<1024, 16, true>), grid, dim3(1024), 0, s, a);
+    else if (N <= 49152) STS_LAUNCH((select_row_long_kernel<1024, 12>), grid, dim3(1024), 0, s, a);
+    else STS_LAUNCH((select_row_long_kernel<1024, 16>), grid, dim3(1024), 0, s, a);
   } else if (N <= 4096) {
     STS_SHORT(256, 4);
   } else if (N <= 8192) {

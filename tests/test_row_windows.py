@@ -202,10 +202,10 @@ def test_many_rows_of_several_scores(Tq, N, k, how):
 
 # calls of few rows whose scores are summed first and then ranked by one workgroup per row, on both sides of the host's lines: rows, scores
 # per token, N, k, bf16 scores, the kernels' first name
-SUMMED = [(8, 3, 16385, 1638, False, "select_row_sums"), (32, 3, 32768, 300, True, "select_row_sums"), (33, 4, 20000, 2000, False, "select_row_kernel"),
-          (33, 5, 20000, 2000, False, "select_row_sums"), (16, 2, 32768, 3277, False, "select_row_kernel"), (16, 2, 32769, 3277, False, "select_row_sums"),
+SUMMED = [(8, 3, 16385, 1638, False, "select_row_sums"), (32, 3, 32768, 300, True, "select_row_sums"), (33, 4, 20000, 2000, False, "select_row_scores_kernel"),
+          (33, 5, 20000, 2000, False, "select_row_sums"), (16, 2, 32768, 3277, False, "select_row_scores_kernel"), (16, 2, 32769, 3277, False, "select_row_sums"),
           (34, 2, 65536, 6554, False, "select_row_sums"), (35, 2, 65536, 655, True, "select_clear16"), (8, 9, 65537, 655, False, "select_clear16"),
-          (16, 1, 32769, 3277, False, "select_row_kernel"), (127, 1, 65536, 6554, False, "select_row_kernel"), (16, 1, 65537, 6554, False, "select_clear16"),
+          (16, 1, 32769, 3277, False, "select_row_long_kernel"), (127, 1, 65536, 6554, False, "select_row_long_kernel"), (16, 1, 65537, 6554, False, "select_clear16"),
           (16, 5, 40003, 20000, False, "select_clear16"), (7, 5, 33001, 3301, False, "select_clear16"), (65, 4, 49152, 4915, False, "select_row_sums"),
           (9, 2, 49153, 4000, False, "select_row_sums"), (66, 5, 49152, 4915, True, "select_clear16"), (64, 3, 45000, 4500, False, "select_clear16")]
 
