@@ -14,6 +14,8 @@
 // and where they go, and they are stored from the registers, a run of neighbouring places per instruction. What bounds it:
 // the lists' reading and the latencies of the phases. 16 blocks x 16 draft heads of 16 x 6554 entries, 64K tokens: 57 us
 // (65 with 32 tokens per thread, whose entries went one by one to a stage in LDS and from there, coalesced, to each target head).
+// A chunk with fewer entries than a third of its tokens has them put together in LDS first, since a store instruction would be nearly
+// empty: 4 blocks of 16 x 6000 entries over 98304 tokens 63.7 us (69.0 from the registers), 24 of 16 x 6554 over 128K 239 (250).
 // Rejected: no search, each chunk starting where the one before met its first entry past the end, and two steps of entries under way
 // (75 to 87 us: sixteen scalar addresses and limits per step cost more than the search).
 #include "common.h"
@@ -24,6 +26,8 @@ constexpr int UN_THREADS = 1024;
 constexpr int UN_CHUNK = 32768;            // tokens per LDS pass
 constexpr int UN_MAX_SEG = 64;             // chunks up to which the lists are read by segments (2M tokens)
 constexpr int UN_STEPS = UN_CHUNK / UN_THREADS;      // tokens per lane
+constexpr int UN_STAGE = 10240;            // entries of a chunk up to which they are put together in LDS: 4 + 2 bytes each where the bits were
+static_assert(6 * UN_STAGE <= 2 * UN_CHUNK && UN_STAGE % 4 == 0, "room, and whole 16-byte pieces to clear");
 
 __global__ void __launch_bounds__(UN_THREADS) union_rows_kernel(const UnionArgs A) {
   typedef uint16_t row_bits __attribute__((may_alias));
@@ -145,7 +149,36 @@ __global__ void __launch_bounds__(UN_THREADS) union_rows_kernel(const UnionArgs 
     }
     at = (uint32_t)uniform((int)at);
     const uint32_t room = (uint32_t)A.pitch;       // a pitch below the union's size truncates the list
-    for (int ti = 0; ti < ntgt; ++ti) {
+    if (total <= (uint32_t)UN_STAGE) {
+      // few entries: put next to each other in LDS, from where every store instruction is full (the bits' place, cleared again)
+      int32_t *const stg_idx = reinterpret_cast<int32_t *>(bits);
+      row_bits *const stg_mask = reinterpret_cast<row_bits *>(bits + UN_STAGE);
+      uint32_t p = at - written;
+#pragma unroll
+      for (int x = 0; x < UN_STEPS; ++x) {
+        const uint64_t b = __builtin_amdgcn_ballot_w64(w[x] != 0u);
+        const uint32_t place = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, p));
+        if (w[x] != 0u) {
+          stg_idx[place] = base + wave * (64 * UN_STEPS) + 64 * x + lane;
+          stg_mask[place] = (uint16_t)w[x];
+        }
+        p += (uint32_t)__builtin_popcountll(b);
+      }
+      __syncthreads();
+      const uint32_t n = written < room ? min(total, room - written) : 0u;
+      for (int ti = 0; ti < ntgt; ++ti) {
+        const size_t o = (out_row + uniform(tgt[ti])) * (size_t)A.pitch + written;
+        for (uint32_t i = tid; i < n; i += UN_THREADS) {
+          A.indices[o + i] = stg_idx[i];
+          A.row_mask[o + i] = stg_mask[i];
+        }
+      }
+      __syncthreads();
+      if (base + UN_CHUNK < A.N) {
+        for (uint32_t i = tid; 4 * i < total; i += UN_THREADS) reinterpret_cast<four_words *>(bits)[i] = u32x4{0u, 0u, 0u, 0u};
+        for (uint32_t i = tid; 8 * i < total; i += UN_THREADS) reinterpret_cast<four_words *>(bits + UN_STAGE)[i] = u32x4{0u, 0u, 0u, 0u};
+      }
+    } else for (int ti = 0; ti < ntgt; ++ti) {
       const size_t o = (out_row + uniform(tgt[ti])) * (size_t)A.pitch;
       int32_t *const idx = A.indices + o;
       uint16_t *const msk = A.row_mask + o;

@@ -137,6 +137,29 @@ def test_union_at_the_ends_of_chunks(N, pitch, order):
     np.testing.assert_array_equal(mask.cpu().numpy().view(np.uint16), o_mask[:, :, :p])
 
 
+# a chunk's entries are put together in LDS up to 10240 of them; one more, and they are stored from the registers
+@pytest.mark.parametrize("first,second,pitch", [(10240, 10241, 0), (10241, 10240, 0), (10240, 10240, 15001), (32768, 1, 0), (1, 32768, 20000)])
+def test_union_of_full_and_sparse_chunks(first, second, pitch):
+    rng = np.random.default_rng(first)
+    N, Tq = 2 * 32768 + 5, 16
+    tokens = np.concatenate([np.sort(rng.choice(32768, first, replace=False)), 32768 + np.sort(rng.choice(32768, second, replace=False)), [65540]])
+    k = 2 * (len(tokens) // Tq + 1)
+    sel = np.full((1, 1, Tq, k), -1, np.int32)
+    cnt = np.zeros((1, 1, Tq), np.int32)
+    for i in range(Tq):                               # every token is kept by two rows next to each other
+        row = np.sort(np.concatenate([tokens[i::Tq], tokens[(i + 1) % Tq::Tq]]))
+        sel[0, 0, i, :len(row)] = row
+        cnt[0, 0, i] = len(row)
+    idx, mask, ucnt = sts.sts_union_rows(torch.from_numpy(sel).to(DEV), torch.from_numpy(cnt).to(DEV), [0, 0], N, **({"pitch": pitch} if pitch else {}))
+    torch.cuda.synchronize()
+    o_idx, o_mask, o_cnt = oracle.union_rows(sel, cnt, [0, 0], pitch=min(Tq * k, N))
+    p = idx.shape[2]
+    np.testing.assert_array_equal(o_cnt, len(tokens))
+    np.testing.assert_array_equal(ucnt.cpu().numpy(), np.minimum(o_cnt, p))
+    np.testing.assert_array_equal(idx.cpu().numpy(), o_idx[:, :, :p])
+    np.testing.assert_array_equal(mask.cpu().numpy().view(np.uint16), o_mask[:, :, :p])
+
+
 def make_qkv(seed, B, Tq, Hq, Hkv, d, N):
     g = torch.Generator().manual_seed(seed)
     q = torch.randn(B, Tq, Hq, d, generator=g).to(torch.bfloat16)
