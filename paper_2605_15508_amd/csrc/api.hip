@@ -547,7 +547,8 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
       pl.one_row = one_row;
       pl.pool = false;
       plan_sampled(p, rows, pl);
-      // Calls of 8 to 127 rows of up to 65536 tokens whose lists one workgroup per row writes as fast: the row is ranked in one
+      // Calls of 8 to 127 rows (less than one for every second CU: more come here, too, with budgets next to the row's length) of up
+      // to 65536 tokens whose lists one workgroup per row writes as fast: the row is ranked in one
       // workgroup's registers where it is one fp32 score per token (beyond 32768 tokens; below, `one_row` says the same), and
       // several scores are summed first by as many workgroups as there are quads for. A launch more, but nothing to clear, to
       // sample, to exchange, and the scores are read by the whole chip. us on other scores in every call, as it was (sampled, or
@@ -558,7 +559,8 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
       // 17.5, 20.3; nor where two scores are added up in passing (16 of 24000 17.0, 17.1).
       const bool ready = p->Tq == 1 && p->kind == STS_SCORES_PROBS && !p->scores_bf16;
       const bool lists_fit = list_work <= 216000;        // (`writes_little` for one score per token)
-      if (path == 0 && !pl.row16 && !p->agg_out && p->N > 16384 && p->N <= SEL_ROW_N && rows >= 8 && lists_fit) {
+      if (path == 0 && !pl.row16 && !p->agg_out && p->N > 16384 && p->N <= SEL_ROW_N && rows >= 8 && 2 * (int64_t)rows < cu_count() &&
+          lists_fit) {
         if (ready) pl.one_row = true;
         else if (p->N > SEL_SMALL_N ? (int64_t)rows * p->N <= (p->N <= 49152 && p->Tq >= 4 ? 3200000 : 2250000) : p->Tq >= (rows <= 32 ? 3 : 5)) {
           pl.sums = true;

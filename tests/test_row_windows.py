@@ -2,12 +2,15 @@
 csrc/select_row.hip), and rows of block sums ranked by the same kernels, against the CPU oracle bit for
 bit: scores that the sample, the windows and the slots beside them do not expect, at the edges of the
 kernel's forms."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
 import paper_2605_15508_amd as sts
+from paper_2605_15508_amd import binding
 from test_select_emulated import by_keys, check, lib, route  # noqa: F401  (lib: the emulated library, a fixture)
 
 DEV = "cuda:0"
@@ -214,6 +217,54 @@ SUMMED = [(8, 3, 16385, 1638, False, "select_row_sums"), (32, 3, 32768, 300, Tru
 def test_summed_rows_route(lib, rows, Tq, N, k, bf16, first):  # noqa: F811
     assert route(lib, rows, 1, Tq, N, 2, k, bf16=bf16).startswith(first)
     assert not route(lib, rows, 1, Tq, N, 2, k, bf16=bf16, agg=True).startswith("select_row_sums")
+
+
+# Budgets next to the row's length: the rule for calls of few rows does not take those of 128 rows and more, of which one
+# workgroup per row ranks up to 512 only where they are this long; and fewer rows have lists too long for it
+@pytest.mark.parametrize("rows", [127, 128, 129, 255, 512, 513, 4000])
+@pytest.mark.parametrize("N", [32769, 40000, 65536])
+def test_rows_that_keep_nearly_everything_route(lib, rows, N):  # noqa: F811
+    for k in (N * 92 // 100, N * 93 // 100, N - 1, N, N + 7):
+        for Tq in (1, 2, 5):
+            for lens in (False, True):
+                got = route(lib, rows, 1, Tq, N, 2, k, lens=lens)        # (and status 0)
+                assert "select_sampled_kernel" in got, (k, Tq, got)
+
+
+def test_rows_that_keep_nearly_everything_emulated(lib):  # noqa: F811
+    lib.emu_schedule(7, -1, -1)
+    for rows, N, k in ((513, 32769, 32700), (512, 40000, 39999), (128, 33001, 33001)):
+        s = torch.zeros(rows, 1, 1, N)
+        s[:2] = scores_of("zeros then scores", 2, 1, N, N // 3, N)
+        check(lib, s, [0], k, lens=[N, N - 9] + [0] * (rows - 2))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,N,k", [(513, 32769, 32700), (600, 40000, 40000), (528, 65536, 65535), (200, 40000, 39900)])
+def test_rows_that_keep_nearly_everything(rows, N, k):
+    live = 2                                          # the other rows are empty
+    s = scores_of("zeros then scores", live, 1, N, N // 3, N)
+    sd = torch.zeros(rows, 1, 1, N, device=DEV)
+    sd[:live] = s.to(DEV)
+    lens = torch.zeros(rows, dtype=torch.int32)
+    lens[:live] = torch.tensor([N, N - 9])
+    idx, cnt, _ = sts.sts_select(sd, [0], k, seq_lens=lens.to(DEV))
+    assert (cnt[live:] == 0).all() and (idx[live:] == -1).all()
+    o_idx, o_cnt, _ = oracle.select_indices(s.numpy(), np.zeros(1, np.int32), k, seq_lens=lens[:live].numpy())
+    np.testing.assert_array_equal(cnt[:live].cpu().numpy(), o_cnt)
+    np.testing.assert_array_equal(idx[:live].cpu().numpy(), o_idx)
+
+
+@pytest.mark.parametrize("S,R,Hd,Ht,N,k", [(1, 64, 16, 32, 40000, 38000), (1, 33, 16, 16, 65536, 65536), (1, 1, 40, 128, 33001, 32700)])
+def test_head_mapping_that_keeps_nearly_everything_route(lib, S, R, Hd, Ht, N, k):  # noqa: F811
+    p = binding.HeadmapParams(S=S, R=R, Hd=Hd, Ht=Ht, N=N, k=k, a_d=1 << 20, a_t=1 << 20, map=1 << 20)
+    p.workspace, p.workspace_bytes = 1 << 20, lib.sts_headmap_workspace_bytes(ctypes.byref(p))
+    lib.emu_only_names(1)
+    try:
+        assert lib.sts_head_map(ctypes.byref(p), None) == 0
+        assert "headmap_overlap" in lib.emu_names().decode()
+    finally:
+        lib.emu_only_names(0)
 
 
 def test_summed_rows_emulated(lib):  # noqa: F811
