@@ -451,22 +451,34 @@ __device__ __forceinline__ void rank_row(const SelectArgs &A) {
   // ---- a window of keys lo .. lo + last around the threshold
   uint32_t lo = 1, last = 0xfffffffeu, heavy = 0;
   if (nb >= 1024) {
-    // From a sample of one key in four, or 2048, by its keys' upper 11 bits and, if that is one value, by the 11 bits below. Every
-    // wave samples some of its registers, so that the sample is of all parts of the row.
+    // From a sample of one key in four, or 2048, by its keys' upper 11 bits and, if that is one value, by the 11 bits below. Of a row
+    // that fills the registers every thread takes one quad of STEP, its neighbours the others, so that each stretch of the row has
+    // its share of the sample; of one that is short enough for a key of every quad, all do. (Where the waves took a few
+    // registers each, 256 tokens next to each other were all in the sample or none, and rows shorter than the tensor were sampled by one or
+    // two waves: heavy tokens at the start misled the window. 16 rows of a tensor of 32768 tokens, 256 kept, such a start: 4096 valid
+    // 19.2 us, 12.9 now, 16384 valid 21.7, 13.3, all valid 22.5, 13.8; of 65536, 256 kept 32.3, 19.8. Rows without one as before.)
     constexpr int STEP = T * IT > 2048 ? T * IT / 2048 : 1;
+    static_assert(IT % STEP == 0, "a thread's quads are taken STEP at a time");
     uint32_t from = 0, sh = 21;
     __syncthreads();
 #pragma unroll 1
     for (uint32_t deep = 0, top = 0;;) {
+      auto count = [&](uint32_t s) {
+        const uint32_t x = (s - from) >> sh;
+        if (s && x < (uint32_t)SEL_BINS) atomicAdd(&h[x], 1u);
+      };
+      if (STEP > 1 && nb > TOK / STEP) {
 #pragma clang loop unroll(full)
-      for (int j = 0; j < STEP; ++j)
-        if (j == wave % STEP) {
+        for (int i = 0; i < IT; i += STEP) {
+          uint32_t s = k[i][(i / STEP) & 3];
 #pragma clang loop unroll(full)
-          for (int i = j; i < IT; i += STEP) {
-            const uint32_t s = k[i][(i / STEP) & 3], x = (s - from) >> sh;
-            if (s && x < (uint32_t)SEL_BINS) atomicAdd(&h[x], 1u);
-          }
+          for (int x = 1; x < STEP; ++x) s = tid % STEP == x ? k[i + x][(i / STEP + x) & 3] : s;
+          count(s);
         }
+      } else {
+#pragma clang loop unroll(full)
+        for (int i = 0; i < IT / STEP; ++i) count(k[i][i & 3]);
+      }
       __syncthreads();
       uint32_t loc[PER], ns, unused;
       uint32_t above = bins_above(0u, SEL_BINS, loc, ns, unused);
@@ -822,17 +834,26 @@ __device__ __forceinline__ void rank_row16(const SelectArgs &A, int row, int nb,
   if (nb >= 1024) {
     // One key of eight, or less where that would be more than 2048: bins of 32 keys are coarser than their error, and keys that share
     // a bin wait for each other. (4096 rows of 65536 tokens 150.6 us with one of eight, 141 with 4096 keys, 140 with 2048; 1024
-    // of 131072 128, 124, 122.)
+    // of 131072 128, 124, 122.) Taken as the longer fp32 rows are, see rank_row. (300 rows of 131072, 700 kept, heavy tokens at the start:
+    // 71.5 us with a few registers of every wave, 49.7 so.)
     constexpr int STEP = T * IT > 2048 ? T * IT / 2048 : 1;
+    static_assert(IT % STEP == 0, "a thread's words are taken STEP at a time");
+    auto count = [&](i16x2 w) {
+      const uint32_t s = (uint32_t)(unsigned short)w[0] ^ 0x8000u;
+      if (s) atomicAdd(&h[s >> 5], 1u);
+    };
+    if (STEP > 1 && nb > 8 * T * IT / STEP) {
 #pragma clang loop unroll(full)
-    for (int j = 0; j < STEP; ++j)
-      if (j == wave % STEP) {                                      // (some registers of every wave: of all parts of the row)
+      for (int i = 0; i < IT; i += STEP) {
+        i16x2 w = k[i][(i / STEP) & 3];
 #pragma clang loop unroll(full)
-        for (int i = j; i < IT; i += STEP) {
-          const uint32_t s = (uint32_t)(unsigned short)k[i][(i / STEP) & 3][0] ^ 0x8000u;
-          if (s) atomicAdd(&h[s >> 5], 1u);
-        }
+        for (int x = 1; x < STEP; ++x) w = tid % STEP == x ? k[i + x][(i / STEP + x) & 3] : w;
+        count(w);
       }
+    } else {
+#pragma clang loop unroll(full)
+      for (int i = 0; i < IT / STEP; ++i) count(k[i][i & 3]);
+    }
     __syncthreads();
     uint32_t loc[PER], ns, unused;
     uint32_t above = bins_above(0u, SEL_BINS, loc, ns, unused);

@@ -22,7 +22,7 @@ namespace {
 constexpr size_t STACK = 64 * 1024;
 int g_slow_wave = -1, g_slow_part = -1, g_cus = 256;
 unsigned g_seed = 1;
-uint64_t g_loaded = 0;
+uint64_t g_loaded = 0, g_barriers = 0;
 uint32_t g_lds = 0;
 bool g_only_names = false;
 std::string g_names;
@@ -206,6 +206,7 @@ const uint32_t *exchange(uint32_t v) {
 uint64_t live() { return wave_of(g_group).live; }
 void barrier() {
   Group *g = g_group;
+  if (g->cur->thread.x == 0) __atomic_fetch_add(&g_barriers, 1, __ATOMIC_SEQ_CST);
   wave_of(g).sleeps = 0;
   ++g->at_barrier;
   g->cur->state = AT_BARRIER;
@@ -265,6 +266,9 @@ extern "C" const char *emu_names() { return emu::g_names.c_str(); }
 
 // bytes of scores loaded since the last call
 extern "C" uint64_t emu_loaded() { return __atomic_exchange_n(&emu::g_loaded, 0, __ATOMIC_SEQ_CST); }
+
+// barriers that workgroups have passed since the last call
+extern "C" uint64_t emu_barriers() { return __atomic_exchange_n(&emu::g_barriers, 0, __ATOMIC_SEQ_CST); }
 
 sts_status sts_static_scratch(void **) { return STS_EUNSUPPORTED; }
 hipError_t launch_attn_split(const AttnArgs &a, int d, int nq, bool sparse, hipStream_t) {

@@ -219,6 +219,35 @@ def test_summed_rows_route(lib, rows, Tq, N, k, bf16, first):  # noqa: F811
     assert not route(lib, rows, 1, Tq, N, 2, k, bf16=bf16, agg=True).startswith("select_row_sums")
 
 
+def heavy_start(n, seed):
+    """A row's scores with most of the heavy ones among the first 256 tokens (sinks)."""
+    r = torch.randn(n, generator=torch.Generator().manual_seed(seed))
+    r[:256] += 3
+    return torch.softmax(r, dim=-1)
+
+
+# rows, tokens, those that are valid, kept, bf16: forms that sample one quad of 2, 4, 6 and 8, filled, partly filled and nearly empty
+CLUSTERED = [(256, 16384, 2048, 204, False), (513, 16384, 4096, 409, False), (16, 32768, 4096, 256, False), (16, 32768, 16384, 256, False), (16, 32768, 32768, 700, False),
+             (513, 32768, 2048, 204, False), (16, 33001, 33001, 256, False), (16, 65536, 1024, 102, False), (16, 65536, 4096, 409, False), (16, 65536, 65536, 256, False),
+             (64, 65536, 32773, 300, True), (300, 131072, 131072, 300, True),
+             (300, 131072, 65541, 500, True)]
+
+
+@pytest.mark.parametrize("rows,N,n,k,bf16", CLUSTERED)
+def test_the_sample_is_of_all_parts_of_the_row(lib, rows, N, n, k, bf16):  # noqa: F811
+    """Heavy tokens next to each other, or in the few registers that a short row fills, do not mislead the window: no more
+    counting (barriers) than the same scores need in another order."""
+    lib.emu_schedule(N + k, -1, -1)
+    passed = []
+    for order in (torch.arange(n), torch.randperm(n, generator=torch.Generator().manual_seed(n))):
+        s = torch.zeros(rows, 1, 1, N, dtype=torch.bfloat16 if bf16 else torch.float32)
+        s[0, 0, 0, :n] = heavy_start(n, N)[order].to(s.dtype)
+        lib.emu_barriers()
+        check(lib, s, [0], k, lens=[n] + [0] * (rows - 1))
+        passed.append(lib.emu_barriers())
+    assert passed[0] <= passed[1]
+
+
 # Budgets next to the row's length: the rule for calls of few rows does not take those of 128 rows and more, of which one
 # workgroup per row ranks up to 512 only where they are this long; and fewer rows have lists too long for it
 @pytest.mark.parametrize("rows", [127, 128, 129, 255, 512, 513, 4000])

@@ -40,6 +40,7 @@ def lib(tmp_path_factory):
     lib.sts_select_workspace_bytes.restype = ctypes.c_size_t
     lib.sts_headmap_workspace_bytes.restype = ctypes.c_size_t
     lib.emu_loaded.restype = ctypes.c_uint64
+    lib.emu_barriers.restype = ctypes.c_uint64
     lib.emu_names.restype = ctypes.c_char_p
     lib.sts_set_knob.argtypes = [ctypes.c_int, ctypes.c_double]
     return lib
