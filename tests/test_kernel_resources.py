@@ -57,6 +57,16 @@ def test_the_sampled_and_the_row_selection_fit_their_registers(resources):
         assert v["LDS Size"] <= 160 * 1024
 
 
+# the row kernels of other names, and how many forms each has: rows whose scores are added up first, the longest rows of one score, rows
+# of one bf16 score
+@pytest.mark.parametrize("name,forms", [("select_row_scores_kernel", 5), ("short_select_row_scores_kernel", 3), ("select_row_long_kernel", 2), ("select_row16_kernel", 5)])
+def test_every_form_of_the_row_selection_fits_its_registers(resources, name, forms):
+    row = {k: v for k, v in resources.items() if f"{len(name)}{name}I" in k}        # (as the symbol has it: the whole name)
+    assert len(row) == forms
+    for k, v in row.items():
+        assert v["VGPRs"] <= 128 and v["AGPRs"] == 0 and v["ScratchSize"] == 0, demangle(k)
+
+
 def test_the_ranking_of_block_sums_leaves_room_for_others(resources):
     small = {k: v for k, v in resources.items() if "select_small_kernel" in k}
     blocks = {k: v for k, v in resources.items() if "select_blocks_kernel" in k}
