@@ -106,6 +106,7 @@ attn_split_kernel(const AttnArgs A) {
   constexpr int ROWB = D * 2;        // bytes per K/V row
   constexpr int NSLOT = D / 8;       // 16-byte slots per LDS row
   constexpr int OPITCH = D + 4;      // floats per row of the merge buffer
+  constexpr int LOADS = 8;           // loads per lane of a tile's K, and of its V: one chunk of a row each
   constexpr int KTILE_BYTES = STS_TILE_KEYS * ROWB;
   constexpr int MERGE_BYTES = W * 16 * OPITCH * 4;
   constexpr int LDS_MAIN = (W * KTILE_BYTES > MERGE_BYTES) ? W * KTILE_BYTES : MERGE_BYTES;
@@ -294,9 +295,9 @@ attn_split_kernel(const AttnArgs A) {
     }
   };
   // Rows are streamed past the caches where every one is used once per launch.
-  auto load_rows = [&](const unsigned char *base, int t, const Offsets &o, chunk_t (&r)[8]) {
+  auto load_rows = [&](const unsigned char *base, int t, const Offsets &o, chunk_t (&r)[LOADS]) {
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
+    for (int m = 0; m < LOADS; ++m) {
       const chunk_t *src;
       if (GATHER) {
         row_off off = o.o[m] + (ONE ? (row_off)(b * CHB) : (row_off)0);
@@ -320,7 +321,7 @@ attn_split_kernel(const AttnArgs A) {
     int mine = 16 * (a ^ b);
     asm("" : "+v"(mine));                              // (the four offsets that come of it are made anew, not kept)
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
+    for (int m = 0; m < LOADS; ++m) {
       uint32_t off = (uint32_t)(mine ^ (64 * (m & 3))) + (uint32_t)o.o[m];       // chunk b ^ (row & 15) of LDS row 4 m + a
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (lds_ptr)(buf ? lds_odd : lds) + wave * KTILE_BYTES + m * 1024, 16, (int)off, 0, 0, 0);
     }
@@ -575,9 +576,14 @@ attn_split_kernel(const AttnArgs A) {
     pin();
     if constexpr (ONE) {
       // K of two tiles in LDS and V of two in registers: the next tile's rows are asked for before this one is worked on.
-      constexpr int BEHIND = 24 + (ROWMASK ? 2 : 1);   // loads that go out after a tile's K and before it is used: its V, list entries, the next tile's K and V
+      // Nothing but the wait below orders K's arrival in LDS before its reads. Loads return in order, so it is for all but those that
+      // go out after a tile's K: its V, list entries (and their row bits), the next tile's K and V, an instruction each. More of them
+      // would only wait longer; fewer (one that is merged, left out or moved) would read K too early: tests/test_attn_wait.py
+      // looks at the compiled loop.
+      static_assert(sizeof(chunk_t) == 16, "a row's chunk is one load");
+      constexpr int ENTRY_LOADS = ROWMASK ? 2 : 1, BEHIND = 3 * LOADS + ENTRY_LOADS;
       constexpr int K_HERE = (BEHIND & 15) | (BEHIND >> 4) << 14 | 0x0f70;     // (as the wait instruction has it: that many may be under way)
-      chunk_t V0[8], V1[8];
+      chunk_t V0[LOADS], V1[LOADS];
       load_k_lds(o, 0);
       pin();
       load_rows(vuni, tile_of(0), o, V0);
