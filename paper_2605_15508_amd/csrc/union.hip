@@ -16,6 +16,8 @@
 // (65 with 32 tokens per thread, whose entries went one by one to a stage in LDS and from there, coalesced, to each target head).
 // A chunk with fewer entries than a third of its tokens has them put together in LDS first, since a store instruction would be nearly
 // empty: 4 blocks of 16 x 6000 entries over 98304 tokens 63.7 us (69.0 from the registers), 24 of 16 x 6554 over 128K 239 (250).
+// The searches for the segments' ends go side by side (one after the other, and the bits cleared twice, the same 24 blocks took 239 us
+// instead of 232, 16 of 16 x 2622 65.5 instead of 62.3: more than the form before the stores by ballots, 236 and 65.0).
 // Rejected: no search, each chunk starting where the one before met its first entry past the end, and two steps of entries under way
 // (75 to 87 us: sixteen scalar addresses and limits per step cost more than the search).
 #include "common.h"
@@ -64,19 +66,34 @@ __global__ void __launch_bounds__(UN_THREADS) union_rows_kernel(const UnionArgs 
   if (by_segments) {
     if (tid == 0) out_of_place = 0;
     if (nchunks <= 4) {
-      // few ends: a wave per list, 64 probes a step (three memory latencies instead of thirteen)
+      // few ends: a wave per list, 64 probes a step for each of them (three memory latencies instead of thirteen)
       const int32_t *row = lists + (size_t)min(wave, A.Tq - 1) * A.k;
       const int n_row = uniform(cnts[wave]);
-      for (int c = 0; c <= nchunks; ++c) {
-        int lo = 0, len = c == 0 || c == nchunks ? 0 : n_row;
-        while (len > 0) {
-          const int step = (len + 63) / 64, p = lane * step;
-          const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(p < len && row[lo + min(p, len - 1)] < c * UN_CHUNK));
-          if (n == 0) break;                           // (probes 0 .. n - 1 lie below the end)
-          lo += (n - 1) * step + 1;
-          len = min(step - 1, len - (n - 1) * step - 1);
+      int lo[3], len[3];                               // of the ends 1 .. nchunks - 1
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        lo[c] = 0;
+        len[c] = c + 1 < nchunks ? n_row : 0;
+      }
+      while (len[0] | len[1] | len[2]) {
+        int probe[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) probe[c] = row[min(lo[c] + min(lane * ((len[c] + 63) / 64), max(len[c] - 1, 0)), n_row - 1)];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const int step = (len[c] + 63) / 64;
+          const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane * step < len[c] && probe[c] < (c + 1) * UN_CHUNK));
+          // (probes 0 .. n - 1 lie below the end)
+          lo[c] += n ? (n - 1) * step + 1 : 0;
+          len[c] = n ? min(step - 1, len[c] - (n - 1) * step - 1) : 0;
         }
-        if (lane == 0) seg[wave][c] = c == nchunks ? n_row : lo;
+      }
+      if (lane == 0) {
+        seg[wave][0] = 0;
+        seg[wave][nchunks] = n_row;
+#pragma unroll
+        for (int c = 1; c < 4; ++c)
+          if (c < nchunks) seg[wave][c] = lo[c - 1];
       }
     } else for (int x = tid; x < 16 * (nchunks + 1); x += UN_THREADS) {
       const int i = x / (nchunks + 1), c = x % (nchunks + 1);
@@ -136,9 +153,6 @@ __global__ void __launch_bounds__(UN_THREADS) union_rows_kernel(const UnionArgs 
 #pragma unroll
     for (int x = 0; x < UN_STEPS; ++x) kept += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(w[x] != 0u));
     if (lane == 0) wave_tot[wave] = kept;
-    four_words *const mine = reinterpret_cast<four_words *>(bits) + wave * (8 * UN_STEPS) + lane;        // (nothing there for the next chunk)
-#pragma unroll
-    for (int x = 0; x < UN_STEPS / 8; ++x) mine[64 * x] = u32x4{0u, 0u, 0u, 0u};
     __syncthreads();
     uint32_t at = written, total = 0;              // where the wave's entries go
 #pragma unroll
@@ -150,7 +164,7 @@ __global__ void __launch_bounds__(UN_THREADS) union_rows_kernel(const UnionArgs 
     at = (uint32_t)uniform((int)at);
     const uint32_t room = (uint32_t)A.pitch;       // a pitch below the union's size truncates the list
     if (total <= (uint32_t)UN_STAGE) {
-      // few entries: put next to each other in LDS, from where every store instruction is full (the bits' place, cleared again)
+      // few entries: put next to each other in LDS, from where every store instruction is full (the bits' place)
       int32_t *const stg_idx = reinterpret_cast<int32_t *>(bits);
       row_bits *const stg_mask = reinterpret_cast<row_bits *>(bits + UN_STAGE);
       uint32_t p = at - written;
@@ -174,10 +188,6 @@ __global__ void __launch_bounds__(UN_THREADS) union_rows_kernel(const UnionArgs 
         }
       }
       __syncthreads();
-      if (base + UN_CHUNK < A.N) {
-        for (uint32_t i = tid; 4 * i < total; i += UN_THREADS) reinterpret_cast<four_words *>(bits)[i] = u32x4{0u, 0u, 0u, 0u};
-        for (uint32_t i = tid; 8 * i < total; i += UN_THREADS) reinterpret_cast<four_words *>(bits + UN_STAGE)[i] = u32x4{0u, 0u, 0u, 0u};
-      }
     } else for (int ti = 0; ti < ntgt; ++ti) {
       const size_t o = (out_row + uniform(tgt[ti])) * (size_t)A.pitch;
       int32_t *const idx = A.indices + o;
@@ -195,6 +205,8 @@ __global__ void __launch_bounds__(UN_THREADS) union_rows_kernel(const UnionArgs 
       }
     }
     written += (uint32_t)uniform((int)total);
+    // nothing there for the next chunk (a stage is free, every wave has its words)
+    for (int i = tid; i < UN_CHUNK / 8; i += UN_THREADS) reinterpret_cast<four_words *>(bits)[i] = u32x4{0u, 0u, 0u, 0u};
     __syncthreads();                                  // wave_tot is rewritten next round
   }
   const uint32_t c = min(written, (uint32_t)A.pitch);

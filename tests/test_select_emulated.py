@@ -391,3 +391,28 @@ def test_bins_that_run_past_the_band(lib, budget):
     s[0, 0, 0] = base * torch.exp(torch.softmax(2 * torch.randn(N, generator=g), -1).to(torch.bfloat16).float())
     lib.emu_schedule(1, -1, -1)
     check(lib, s, [0], N, k_head=[budget], lens=[N] + [0] * (rows - 1))
+
+
+@pytest.mark.parametrize("order", ["ascending", "falling"])
+@pytest.mark.parametrize("N", [32768, 32769, 65537, 100000, 131072, 131073])
+def test_union_of_lists_of_every_length(lib, N, order):
+    """One to five chunks of 32768 tokens: the searches for the ends of each list's segments, side by side, in lists around the
+    64 entries of a probe, lists without one and lists that lie in one chunk alone."""
+    lib.emu_schedule(N, -1, -1)
+    rng = np.random.default_rng(N)
+    Tq, k, lengths = 16, 4500, [0, 1, 2, 63, 64, 65, 127, 128, 129, 700, 4095, 4096, 4097, 4500, 100, 90]
+    sel = np.full((1, 1, Tq, k), -1, np.int32)
+    for i, n in enumerate(lengths):
+        low, high = (N - 1 - n, N) if i == 14 else (0, n) if i == 15 else (0, N)
+        row = np.sort(rng.choice(np.arange(low, high), size=n, replace=False))
+        sel[0, 0, i, :n] = row[::-1] if order == "falling" and i == 9 else row
+    cnt = np.asarray(lengths, np.int32).reshape(1, 1, Tq)
+    hm, pitch = np.zeros(2, np.int32), 20000
+    idx, mask, ucnt = np.full((1, 2, pitch), -7, np.int32), np.full((1, 2, pitch), 7, np.uint16), np.full((1, 2), -7, np.int32)
+    p = binding.UnionParams(B=1, Hd=1, Hq=2, Tq=Tq, N=N, k=k, row_indices=sel.ctypes.data, row_counts=cnt.ctypes.data, head_map=hm.ctypes.data,
+                            pitch=pitch, indices=idx.ctypes.data, row_mask=mask.ctypes.data, counts=ucnt.ctypes.data)
+    assert lib.sts_union_rows(ctypes.byref(p), None) == 0
+    o_idx, o_mask, o_cnt = oracle.union_rows(sel, cnt, hm.tolist(), pitch=pitch)
+    np.testing.assert_array_equal(ucnt, o_cnt)
+    np.testing.assert_array_equal(idx, o_idx)
+    np.testing.assert_array_equal(mask, o_mask)
