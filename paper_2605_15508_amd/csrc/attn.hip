@@ -79,7 +79,7 @@ __device__ __forceinline__ float max_over_groups(float x) {
   return larger(__builtin_bit_cast(float, (uint32_t)q[0]), __builtin_bit_cast(float, (uint32_t)q[1]));
 }
 
-// waves per workgroup, and whether a tile's K and V are loaded into one set of registers instead of two
+// waves per workgroup, and whether they keep one tile's K and V on the way instead of two's
 constexpr bool one_buffer(int D, int NQ, bool cached) { return cached && D == 128 && NQ == 2; }
 constexpr int wg_waves(int D, int NQ, bool cached) { return one_buffer(D, NQ, cached) ? 2 * STS_WG_WAVES : STS_WG_WAVES; }
 
@@ -89,8 +89,12 @@ constexpr int wg_waves(int D, int NQ, bool cached) { return one_buffer(D, NQ, ca
 // ROWMASK: every index entry comes with a 16-bit word, bit i set iff query row i of the block keeps
 // the entry (prefill: an index set per query row, gathered once as their union).
 // CACHED: workgroups that gather from the same K and V (blocks of one prompt; the launcher's rule): see the mapping
-// below. Their loads stay in the caches. With two query tiles at head size 128 they run two waves per SIMD on one set of
-// load buffers: one wave per SIMD leaves it idle for half of the time (365 us against 214, the case above).
+// below. Their loads stay in the caches. With two query tiles at head size 128 (ONE) they run two waves per SIMD, each with a tile of
+// K, which goes straight to LDS, and one of V on the way: one wave per SIMD leaves it idle for half of the time (365 us against
+// 214, the case above). Short lists are bound by latency, code that is not in the instruction cache yet included, so
+// the loop's body is there once: two tiles of K in LDS and two of V ahead took three copies of it and 0.5 to 1.3 us more for
+// every workgroup (4 blocks, 2400 kept of 16384 23.6 us so, 22.3 now; 16 blocks, 2000 kept 33.3, 32.2), where 16 blocks of 24000
+// entries over 65536 take 205.5 us so and 207 now, 32 of 30600 over 131072 552 and 556.
 template <int D, int NQ, bool SPARSE, bool LOGITS, bool FAR, bool ROWMASK = false, bool CACHED = false>
 __global__ void __launch_bounds__(64 * wg_waves(D, NQ, CACHED),
                                   one_buffer(D, NQ, CACHED) ? 2 : (NQ == 4 || (D == 128 && (!SPARSE || NQ == 2))) ? 1 : 2)
@@ -106,13 +110,10 @@ attn_split_kernel(const AttnArgs A) {
   constexpr int ROWB = D * 2;        // bytes per K/V row
   constexpr int NSLOT = D / 8;       // 16-byte slots per LDS row
   constexpr int OPITCH = D + 4;      // floats per row of the merge buffer
-  constexpr int LOADS = 8;           // loads per lane of a tile's K, and of its V: one chunk of a row each
   constexpr int KTILE_BYTES = STS_TILE_KEYS * ROWB;
   constexpr int MERGE_BYTES = W * 16 * OPITCH * 4;
   constexpr int LDS_MAIN = (W * KTILE_BYTES > MERGE_BYTES) ? W * KTILE_BYTES : MERGE_BYTES;
   __shared__ __attribute__((aligned(16))) unsigned char lds[LDS_MAIN];
-  // (ONE: every second K tile. An array of its own: reads of the one are not taken for reads of what is on its way to the other.)
-  __shared__ __attribute__((aligned(16))) unsigned char lds_odd[ONE ? W * KTILE_BYTES : 16];
   __shared__ float lds_ml[W][NQ * 16][2];
   // With two or more query tiles the Q operands (NQ*KK registers quads per lane) no longer fit
   // beside the accumulators and the load buffers: they live in LDS, already in MFMA B layout
@@ -238,7 +239,9 @@ attn_split_kernel(const AttnArgs A) {
           Q[nq][kk] = __builtin_bit_cast(bf16x8, w);
         }
       }
-    if (QLDS) __syncthreads();
+    // (ONE: K is on its way to LDS, which the compiler's own barrier would wait for: 0.8 us)
+    if constexpr (ONE) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else if (QLDS) __syncthreads();
   };
   int c = 0, t_end = 0;              // the list's length, and the end of this workgroup's tiles
 
@@ -295,9 +298,9 @@ attn_split_kernel(const AttnArgs A) {
     }
   };
   // Rows are streamed past the caches where every one is used once per launch.
-  auto load_rows = [&](const unsigned char *base, int t, const Offsets &o, chunk_t (&r)[LOADS]) {
+  auto load_rows = [&](const unsigned char *base, int t, const Offsets &o, chunk_t (&r)[8]) {
 #pragma unroll
-    for (int m = 0; m < LOADS; ++m) {
+    for (int m = 0; m < 8; ++m) {
       const chunk_t *src;
       if (GATHER) {
         row_off off = o.o[m] + (ONE ? (row_off)(b * CHB) : (row_off)0);
@@ -314,16 +317,16 @@ attn_split_kernel(const AttnArgs A) {
   };
   // ONE: K goes from memory to LDS without a register in between. Instruction m writes the 1 KB behind its address lane by lane, so
   // LDS row 4 m + a holds slot slot_of(m), and which of the row's 16-byte chunks lies where is up to the chunk that a lane asks for.
-  auto load_k_lds = [&](const Offsets &o, int buf) {
+  auto load_k_lds = [&](const Offsets &o) {
     typedef __attribute__((address_space(3))) unsigned char *lds_ptr;
     // (buffer loads: the flat-encoded form of the same makes the compiler wait for all loads where one is waited for)
     const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(kuni), 0, 0xffffffff, 0x00027000);
     int mine = 16 * (a ^ b);
     asm("" : "+v"(mine));                              // (the four offsets that come of it are made anew, not kept)
 #pragma unroll
-    for (int m = 0; m < LOADS; ++m) {
+    for (int m = 0; m < 8; ++m) {
       uint32_t off = (uint32_t)(mine ^ (64 * (m & 3))) + (uint32_t)o.o[m];       // chunk b ^ (row & 15) of LDS row 4 m + a
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (lds_ptr)(buf ? lds_odd : lds) + wave * KTILE_BYTES + m * 1024, 16, (int)off, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (lds_ptr)lds + wave * KTILE_BYTES + m * 1024, 16, (int)off, 0, 0, 0);
     }
   };
   float m_run[NQ], l_run[NQ];
@@ -378,8 +381,8 @@ attn_split_kernel(const AttnArgs A) {
     }
   };
 
-  // tile t, v-th of this wave (K in LDS, V in registers)
-  auto consume = [&](int t, int v, const chunk_t (&Vr)[8], const uint32_t tile_mask, const bool second) {
+  // tile t, v-th of this wave (K in LDS, V in registers); after_qk: what follows the last read of K
+  auto consume = [&](int t, int v, const chunk_t (&Vr)[8], const uint32_t tile_mask, const bool second, auto after_qk) {
     const int pos0 = t * STS_TILE_KEYS;
     uint64_t key_bits[2];           // ROWMASK: the row bits of this lane's 8 keys, 16 each
     typedef uint64_t four_bits __attribute__((may_alias));       // (stored one by one, with no barrier in between)
@@ -400,7 +403,7 @@ attn_split_kernel(const AttnArgs A) {
       for (int ks = 0; ks < 2; ++ks) {
         const int row = 16 * ks + b;
         const int sl = (a + 4 * kk) ^ (row & (NSLOT - 1));
-        Ka[ks] = *reinterpret_cast<const bf16x8 *>(ONE ? (second ? lds_odd : lds) + wave * KTILE_BYTES + (k_at ^ (64 * kk)) + 16 * ks * ROWB : ldsK + row * ROWB + sl * 16);
+        Ka[ks] = *reinterpret_cast<const bf16x8 *>(ONE ? lds + wave * KTILE_BYTES + (k_at ^ (64 * kk)) + 16 * ks * ROWB : ldsK + row * ROWB + sl * 16);
       }
 #pragma unroll
       for (int nq = 0; nq < NQ; ++nq) {
@@ -410,6 +413,7 @@ attn_split_kernel(const AttnArgs A) {
           St[nq][ks] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ka[ks], Qb, St[nq][ks], 0, 0, 0);
       }
     }
+    after_qk();
     if constexpr (LOGITS) {
       if (A.logits_bf16) {
         u32x2 w[NQ][2];
@@ -575,18 +579,13 @@ attn_split_kernel(const AttnArgs A) {
     offsets(tile_of(0), o);
     pin();
     if constexpr (ONE) {
-      // K of two tiles in LDS and V of two in registers: the next tile's rows are asked for before this one is worked on.
-      // Nothing but the wait below orders K's arrival in LDS before its reads. Loads return in order, so it is for all but those that
-      // go out after a tile's K: its V, list entries (and their row bits), the next tile's K and V, an instruction each. More of them
-      // would only wait longer; fewer (one that is merged, left out or moved) would read K too early: tests/test_attn_wait.py
-      // looks at the compiled loop.
-      static_assert(sizeof(chunk_t) == 16, "a row's chunk is one load");
-      constexpr int ENTRY_LOADS = ROWMASK ? 2 : 1, BEHIND = 3 * LOADS + ENTRY_LOADS;
-      constexpr int K_HERE = (BEHIND & 15) | (BEHIND >> 4) << 14 | 0x0f70;     // (as the wait instruction has it: that many may be under way)
-      chunk_t V0[LOADS], V1[LOADS];
-      load_k_lds(o, 0);
+      // The next tile's K is asked for when this one's has been multiplied, V when this one's has been used; the second wave of the
+      // SIMD works meanwhile. K's reads are ordered after its loads by the compiler (a wait for all but the loads behind them, looked
+      // at by tests/test_attn_wait.py), and the loads after the reads of the tile before by the products that have taken these in.
+      chunk_t V[8];
+      load_k_lds(o);
       pin();
-      load_rows(vuni, tile_of(0), o, V0);
+      load_rows(vuni, tile_of(0), o, V);
       pin();
       take_q();
       int x = resolve(raw_b, tile_of(1), m1);
@@ -594,31 +593,30 @@ attn_split_kernel(const AttnArgs A) {
       raw_a = within(raw_c, tile_of(2));
       bits_a = bits_c;
       pin();
-      auto step = [&](int raw, int bits, int &raw_next, int &bits_next, const chunk_t (&V)[8], chunk_t (&Vn)[8], int v, bool odd) {
+      for (; v < nv; ++v) {
         offsets(tile_of(v + 1), o);
-        raw_next = fetch_rows(tile_of(v + 3));
-        bits_next = fetch_bits(tile_of(v + 3));
-        const int y = resolve(raw, tile_of(v + 2), m_new);
-        place(y, bits, m_new, v + 2);
+        raw_b = fetch_rows(tile_of(v + 3));
+        bits_b = fetch_bits(tile_of(v + 3));
+        x = resolve(raw_a, tile_of(v + 2), m_new);
+        place(x, bits_a, m_new, v + 2);
         pin();
-        load_k_lds(o, odd ? 0 : 1);
+        consume(tile_of(v), v, V, m0, false, [&] {
+          pin();
+          load_k_lds(o);
+          pin();
+        });
         pin();
-        load_rows(vuni, tile_of(v + 1), o, Vn);
-        pin();
-        __builtin_amdgcn_s_waitcnt(K_HERE);
-        consume(tile_of(v), v, V, m0, odd);
+        load_rows(vuni, tile_of(v + 1), o, V);
         pin();
         m0 = m1;
         m1 = m_new;
-      };
-      for (; v + 2 <= nv; v += 2) {
-        step(raw_a, bits_a, raw_b, bits_b, V0, V1, v, false);
-        step(raw_b, bits_b, raw_a, bits_a, V1, V0, v + 1, true);
+        raw_a = raw_b;
+        bits_a = bits_b;
       }
       __builtin_amdgcn_s_waitcnt(0x0f70);              // all K that was asked for has come: the merge takes its place
-      if (v < nv) consume(tile_of(v), v, V0, m0, false);
     } else {
       chunk_t K0[8], V0[8], K1[8], V1[8];
+      auto nothing = [] {};
       // prologue: tile v in flight, tile v+1 resolved, tile v+2 fetched
       load_rows(kuni, tile_of(0), o, K0);
       load_rows(vuni, tile_of(0), o, V0);
@@ -641,7 +639,7 @@ attn_split_kernel(const AttnArgs A) {
         m1 = m_next;
         pin();   // loads are in flight before the tile is consumed
         store_k(K0);
-        consume(tile_of(v), v, V0, m0, false);      // even step: first tile of a pair
+        consume(tile_of(v), v, V0, m0, false, nothing);      // even step: first tile of a pair
         if (FAR) place(x_a, bits_a, m_new, v + 2);  // (a page table entry has come by now)
         m_next = m_new;
         offsets(tile_of(v + 2), o);
@@ -655,13 +653,13 @@ attn_split_kernel(const AttnArgs A) {
         m0 = m_next;
         pin();
         store_k(K1);
-        consume(tile_of(v + 1), v + 1, V1, m1, true);       // odd step: second tile of the pair
+        consume(tile_of(v + 1), v + 1, V1, m1, true, nothing);       // odd step: second tile of the pair
         if (FAR) place(x_b, bits_b, m_new, v + 3);
         m_next = m_new;
       }
       if (v < nv) {
         store_k(K0);
-        consume(tile_of(v), v, V0, m0, false);
+        consume(tile_of(v), v, V0, m0, false, nothing);
       }
       if (LOGITS && stash_pos >= 0) store_bf16_tile(stash, stash_pos);   // a range that ends on a first tile
     }

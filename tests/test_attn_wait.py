@@ -1,6 +1,6 @@
 """The attention over a shared cache loads K straight to LDS (attn_split_kernel with two query tiles at head size 128 in
-csrc/attn.hip), where the compiler adds no wait: the kernel waits by the number of loads that it sends after a
-tile's K. Whether that is the number of loads in the compiled loop is looked at here, in the code of the last build."""
+csrc/attn.hip). Nothing in the source orders these loads before K's reads: the compiler puts in a wait for all but the loads that
+go out after them, if it sees that both are of one array. Whether it did is looked at here, in the code of the last build."""
 import os
 import re
 import shutil
@@ -11,7 +11,7 @@ import pytest
 from paper_2605_15508_amd import build
 
 OBJDUMP = shutil.which("llvm-objdump") or "/opt/rocm/llvm/bin/llvm-objdump"
-# with and without row bits
+# with and without row bits: a load of an entry and one of its bits, or the first alone
 KERNELS = {"attn_split_kernelILi128ELi2ELb1ELb0ELb0ELb1ELb1E": 2, "attn_split_kernelILi128ELi2ELb1ELb0ELb0ELb0ELb1E": 1}
 
 
@@ -37,12 +37,13 @@ def body(listing, kernel):
     return listing[at.end():at.end() + end.start()] if end else listing[at.end():]
 
 
-def loads_and_waits(text, behind):
-    """K: a load to LDS, V: a load of 16 bytes, E: of 4 or 2, O: any other access to memory, W: the wait that leaves `behind`
-    loads under way, in the order of the code."""
+def accesses(text):
+    """K: a load to LDS, V: a load of 16 bytes, E: of 4 or 2, O: any other access to memory, R: a read of 16 bytes from LDS, (n): a wait
+    that leaves n loads under way, P: a matrix product; in the order of the code."""
     seq = []
     for line in text.splitlines():
         op = line.split("//")[0].strip()
+        wait = re.match(r"s_waitcnt .*vmcnt\((\d+)\)", op)
         if op.startswith("buffer_load") and op.endswith(" lds"):
             seq.append("K")
         elif op.startswith("global_load_dwordx4"):
@@ -51,31 +52,37 @@ def loads_and_waits(text, behind):
             seq.append("E")
         elif re.match(r"(buffer|global|flat|scratch)_", op):
             seq.append("O")
-        elif re.match(rf"s_waitcnt vmcnt\({behind}\)", op):
-            seq.append("W")
+        elif op.startswith("ds_read_b128"):
+            seq.append("R")
+        elif op.startswith("v_mfma"):
+            seq.append("P")
+        elif wait:
+            seq.append(f"({wait.group(1)})")
     return "".join(seq)
 
 
 def is_ordered(seq, entries):
-    """The first tile's K and V, then twice in the loop: entries, the next tile's K and V, the wait."""
-    first, half = "K" * 8 + "V" * 8, "E" * entries + "K" * 8 + "V" * 8 + "W"
-    return seq.count("W") == 2 and first + 2 * half in seq
+    """From the loop's list entries on: the row offsets (two reads), a wait that leaves V's eight loads and the entries under way at most,
+    the reads of K and Q with their products, and, behind the last product, the loads of the next tile's K."""
+    if seq.count("K" * 8) != 2 or seq.count("K") != 16:
+        return False
+    body = seq[:seq.rindex("K" * 8)].rpartition("E" * entries)[2]
+    m = re.fullmatch(r"R{0,2}\((\d+)\)((?:R+P+)+)", body)
+    return bool(m) and int(m.group(1)) <= 8 + entries and m.group(2).count("P") == 16 and m.group(2).count("R") >= 8
 
 
 @pytest.mark.parametrize("kernel,entries", KERNELS.items())
-def test_the_wait_counts_the_loads_behind_k(listing, kernel, entries):
-    text = body(listing, kernel)
-    assert is_ordered(loads_and_waits(text, 24 + entries), entries)
-    # and the reads of a tile's K come after it: between a half's loads and its wait nothing is read from LDS in chunks of K
-    for half in re.findall(rf"buffer_load_dwordx4 [^\n]* lds.*?s_waitcnt vmcnt\({24 + entries}\)", text, re.S):
-        last = half[half.rindex(" lds"):]
-        assert "ds_read_b128" not in last and "ds_load_b128" not in last
+def test_k_is_waited_for(listing, kernel, entries):
+    assert is_ordered(accesses(body(listing, kernel)), entries)
 
 
-@pytest.mark.parametrize("seq", ["E" * 2 + "K" * 8 + "V" * 8 + "W" + "E" + "K" * 8 + "V" * 8 + "W",       # an entry's load less
-                                 2 * ("E" * 2 + "K" * 8 + "V" * 7 + "W"),                               # V in fewer loads
-                                 2 * ("K" * 8 + "E" * 2 + "V" * 8 + "W"),                               # entries after K
-                                 "E" * 2 + "K" * 8 + "V" * 8 + "W"])                                     # one half of the loop
-def test_fewer_or_other_loads_are_found(seq):
-    assert is_ordered("K" * 8 + "V" * 8 + 2 * ("E" * 2 + "K" * 8 + "V" * 8 + "W"), 2)
-    assert not is_ordered("K" * 8 + "V" * 8 + seq, 2)
+LOOP = "RR(10)" + 4 * "RRRRPPPP"
+
+
+@pytest.mark.parametrize("seq", [LOOP.replace("(10)", ""), LOOP.replace("(10)", "(11)"),       # no wait, or one that leaves a load of K under way
+                                 "RRR" + LOOP[2:],                                             # K read before it
+                                 LOOP[:-4] + "KKKKKKKK" + LOOP[-4:]])                          # the next K before the last products
+def test_reads_and_loads_out_of_order_are_found(seq):
+    start = "EEVVVVKKKKKKKKVVVVVVVVEE"
+    assert is_ordered(start + LOOP + "KKKKKKKK", 2)
+    assert not is_ordered(start + seq + "KKKKKKKK", 2)
