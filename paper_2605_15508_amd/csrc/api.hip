@@ -425,7 +425,9 @@ sts_status plan_select(const sts_select_params *p, SelectPlan &pl) {
   // Beyond 16384 tokens a thread has eight quads, and every further score per token costs a pass over them whatever N is:
   // 16 rows of 32768 with five 27.8, 28.6, but with six 30.1, 29.1 and of 20000 with eight 29.6, 27.3; 64 rows of 32768 with
   // five 29.2, 32.9, but of 20000 with eight 30.8, 29.4; 128 of 17000 with eight 31.4, 35.6, of 32768 39.5, 49.3, but 96 of
-  // 20000 with twelve 41.3, 38.0; bf16, 16 rows of 32768 with ten 33.3, 33.4, of 26000 with twelve 35.5, 33.1. Calls of fewer
+  // 20000 with twelve 41.3, 38.0; bf16, 16 rows of 32768 with ten 33.3, 33.4, of 26000 with twelve 35.5, 33.1. (Measured before calls of
+  // up to 127 such rows summed three to five scores and more in a launch of their own, which is faster than either, see `sums`
+  // below: there the line decides for fewer scores, for calls that ask for the sums and for those with a smaller workspace.) Calls of fewer
   // than eight rows, fewer than any model's draft heads, keep the route that they had (and calls of few rows the workspace
   // that they had to bring).
   //

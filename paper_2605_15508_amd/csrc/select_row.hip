@@ -731,8 +731,8 @@ __global__ void __launch_bounds__(T, 4) select_blocks_kernel(const SelectArgs A)
 // the window's keys one by one in LDS and those above it; the threshold is one of them. Each token's two bits (above,
 // equal) go to LDS and are read in order for the list.
 //
-// What bounds it: memory and vector instructions alike. 4096 rows of 65536 tokens, 10% kept: 155 us, 537 MB read and
-// 107 MB written, 12 vector instructions per token; the several-pass kernel that served it read them twice, 17 per token: 236.
+// What bounds it: memory and vector instructions alike. 4096 rows of 65536 tokens, 10% kept: 140 us (155 at first), 537 MB read
+// and 107 MB written, 12 vector instructions per token; the several-pass kernel that served it read them twice, 17 per token: 236.
 // Other calls beside the rule in the host code. Measured on the way: masks of lanes and ballots instead of a slot per lane for
 // the keys outside the window 229 us; 256 threads with 128 registers of keys, three rows per CU, 153-157, but 256 rows of
 // 65536 20.5 against 17.0; 131072 tokens in 512 threads 1053 us for 8192 rows, in 1024 threads 889 (several

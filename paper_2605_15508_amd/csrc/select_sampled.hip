@@ -38,8 +38,8 @@
 //
 // What bounds it (64 rows of 128K tokens, 5 fp32 scores each, 4 parts per row, 168 MB): the sample and the pass
 // together 29 us (168 MB and 21 MB of samples, mostly from the last-level cache: the rate of the memory), then latency:
-// 5 us for the histogram exchange, 3.5 us for the keys, 3 us for bits and list; kernel 42 us on scores that the
-// last-level cache holds, 44 on new ones. Histograms of all keys at three digit levels, with the
+// 5 us for the histogram exchange, 3.5 us for the keys, 3 us for bits and list; kernel 45 us on scores that the
+// last-level cache holds, 47 to 50 on new ones. Histograms of all keys at three digit levels, with the
 // part's keys in LDS, took 54: the same 29 us, then 20 us for three levels and 5 us for the list. 16 rows of 1M
 // tokens (335 MB, 16 parts per row): 78 us against 122 for five kernels that stored the aggregate and read it
 // three times. Rows of one score per token are bound by vector instructions instead (about 60 per 256 tokens
